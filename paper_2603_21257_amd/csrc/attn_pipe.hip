@@ -20,57 +20,97 @@ __global__ void __launch_bounds__(512, 2) __attribute__((amdgpu_num_vgpr(120))) 
 
 // Combines the pieces of split tiles: for every row and head, with m = max_c m_c,
 //     O = sum_c 2^(m_c - m) O_c  /  sum_c 2^(m_c - m) l_c
-// (the pieces' O_c, l_c are sums of weights 2^(x - m_c), x the exponent of a score).  One workgroup of
-// 256 threads per (split tile, head group, wave slot of the attention workgroup): thread = (row 0..31,
-// 16-float chunk 0..7).  A piece in which a row saw no key has l_c = 0 and m_c = -inf and drops out.
+// (the pieces' O_c, l_c are sums of weights 2^(x - m_c), x the exponent of a score).  A piece in which a
+// row saw no key has l_c = 0 and m_c = -inf and drops out.
+// What counts is how many loads are in flight and how often the chain of descriptor loads is paid: the
+// partials are a few MB to a few tens of MB that the caches still hold.  A wave merges ROWS rows: lane
+// (row, i) reads (m, l) of piece i of its row, the maximum and the denominator are reductions over the
+// row's lanes, and the O rows (64 lanes x 8 bytes) are fetched 16 at a time - 16 / ROWS pieces of ROWS
+// rows - with each piece's weight taken from its lane.
+// ROWS = 1 while a wave per row fits the chip's wave slots (896 rows x 18 pieces, a 28-token query over
+// 28K cached tokens: 5.8 us; four rows per wave 9.0; one thread per 16 floats walking the pieces one by
+// one 18.6), ROWS = 4 beyond (32000 rows x 4 pieces: 10.8 us, bandwidth; a wave per row 22.6 in four rounds).
+constexpr int kMergeLoads = 16;
+constexpr unsigned kMergeSingleRows = 8192;      // 256 CUs x 32 waves
+
+template <int ROWS>
 __global__ void __launch_bounds__(256) merge_splits_kernel(AttnParams p, const int32_t* split_tiles) {
   const int NW = p.waves_per_wg;
   const int HW = p.heads_per_wg, NHG = p.n_q_heads / HW, TPW = NW / HW;
-  const int wave_slot = blockIdx.x % NW;
-  const int hg = (blockIdx.x / NW) % NHG;
-  const int first = split_tiles[blockIdx.x / (NW * NHG)];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int kLanes = 64 / ROWS, kPieces = kMergeLoads / ROWS;
+  constexpr int kWgs = 8 / ROWS;                                 // workgroups per 32-row slot
+  const int row0 = ((blockIdx.x % kWgs) * 4 + wave) * ROWS;
+  const int slot_id = blockIdx.x / kWgs;
+  const int wave_slot = slot_id % NW;
+  const int hg = (slot_id / NW) % NHG;
+  const int first = split_tiles[slot_id / (NW * NHG)];
   const WorkItem wi = p.items[first];
   const ReqDesc rd = p.reqs[wi.req];
-  const int row = threadIdx.x >> 3, chunk = threadIdx.x & 7;
-  const int tokq = wi.q_tile * 32 * TPW + (wave_slot / HW) * 32 + row;
-  if (tokq >= rd.suffix_len) return;
+  const int tok0 = wi.q_tile * 32 * TPW + (wave_slot / HW) * 32 + row0;
+  const int n_rows = min(ROWS, rd.suffix_len - tok0);
+  if (n_rows <= 0) return;
   const int hq = hg * HW + wave_slot % HW;
+  const int n = wi.n_splits;
+  // row r of piece c: base + c * step + r
+  const int64_t base = (((int64_t)first * NHG + hg) * NW + wave_slot) * 32 + row0;
+  const int64_t step = (int64_t)NHG * NW * 32;
+  const int my_row = lane / kLanes, my_c = lane % kLanes;
+  const bool row_ok = my_row < n_rows;            // rows past the suffix were never written
+  const f32x2* ml = (const f32x2*)p.part_ml + base + my_row;
+  const f32x2* po = (const f32x2*)(p.part_o + base * kD) + lane;
+
   float m = -INFINITY;
-  for (int c = 0; c < wi.n_splits; c++) {
-    const int64_t slot = ((int64_t)(first + c) * NHG + hg) * NW + wave_slot;
-    m = fmaxf(m, p.part_ml[(slot * 32 + row) * 2]);
-  }
-  float acc[16], l = 0.f;
+  for (int c = my_c; c < n; c += kLanes)
+    if (row_ok) m = fmaxf(m, ml[c * step][0]);
 #pragma unroll
-  for (int i = 0; i < 16; i++) acc[i] = 0.f;
-  for (int c = 0; c < wi.n_splits; c++) {
-    const int64_t slot = ((int64_t)(first + c) * NHG + hg) * NW + wave_slot;
-    const float mc = p.part_ml[(slot * 32 + row) * 2], lc = p.part_ml[(slot * 32 + row) * 2 + 1];
-    if (!(lc > 0.f)) continue;
-    const float wgt = __builtin_amdgcn_exp2f(mc - m);
-    l += wgt * lc;
-    const f32x4* po = (const f32x4*)(p.part_o + (slot * 32 + row) * kD + 16 * chunk);
+  for (int o = kLanes / 2; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+  float l = 0.f;
+  f32x2 acc[ROWS];
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const f32x4 v = po[i];
-      acc[4 * i] += wgt * v[0]; acc[4 * i + 1] += wgt * v[1]; acc[4 * i + 2] += wgt * v[2]; acc[4 * i + 3] += wgt * v[3];
+  for (int r = 0; r < ROWS; r++) acc[r] = (f32x2){0.f, 0.f};
+  for (int c0 = 0; c0 < n; c0 += kLanes) {
+    float wgt = 0.f;
+    if (row_ok && c0 + my_c < n) {
+      const f32x2 v = ml[(c0 + my_c) * step];
+      if (v[1] > 0.f) {
+        wgt = __builtin_amdgcn_exp2f(v[0] - m);
+        l = __builtin_fmaf(wgt, v[1], l);
+      }
+    }
+    const int nc = min(kLanes, n - c0);
+    for (int c = 0; c < nc; c += kPieces) {
+      f32x2 v[kPieces][ROWS];
+#pragma unroll
+      for (int i = 0; i < kPieces; i++)
+#pragma unroll
+        for (int r = 0; r < ROWS; r++)                     // past the end: the last piece / row again, with weight 0 below
+          v[i][r] = po[((c0 + min(c + i, nc - 1)) * step + min(r, n_rows - 1)) * (kD / 2)];
+#pragma unroll
+      for (int i = 0; i < kPieces; i++)
+#pragma unroll
+        for (int r = 0; r < ROWS; r++) {
+          const float w = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wgt), r * kLanes + c + i));
+          if (w > 0.f) {                                         // also skips a dropped piece, whose O is not a number
+            acc[r][0] = __builtin_fmaf(w, v[i][r][0], acc[r][0]);
+            acc[r][1] = __builtin_fmaf(w, v[i][r][1], acc[r][1]);
+          }
+        }
     }
   }
-  const float inv = 1.f / l;
-  unsigned short* out = (unsigned short*)p.out + ((int64_t)(rd.q_off + tokq) * p.n_q_heads + hq) * kD + 16 * chunk;
-  u32x4 w0, w1;
 #pragma unroll
-  for (int i = 0; i < 4; i++) {
-    bf16x2 a, b;
-    a[0] = (__bf16)(acc[2 * i] * inv);
-    a[1] = (__bf16)(acc[2 * i + 1] * inv);
-    b[0] = (__bf16)(acc[8 + 2 * i] * inv);
-    b[1] = (__bf16)(acc[8 + 2 * i + 1] * inv);
-    w0[i] = __builtin_bit_cast(unsigned int, a);
-    w1[i] = __builtin_bit_cast(unsigned int, b);
+  for (int o = kLanes / 2; o > 0; o >>= 1) l += __shfl_xor(l, o);
+  unsigned short* out = (unsigned short*)p.out + ((int64_t)(rd.q_off + tok0) * p.n_q_heads + hq) * kD + 2 * lane;
+#pragma unroll
+  for (int r = 0; r < ROWS; r++) {
+    if (r >= n_rows) break;
+    const float inv = 1.f / __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, l), r * kLanes));
+    bf16x2 w;
+    w[0] = (__bf16)(acc[r][0] * inv);
+    w[1] = (__bf16)(acc[r][1] * inv);
+    *(unsigned int*)(out + (int64_t)r * p.n_q_heads * kD) = __builtin_bit_cast(unsigned int, w);
   }
-  *(u32x4*)out = w0;
-  *(u32x4*)(out + 8) = w1;
 }
 
 }  // namespace pipe
@@ -91,8 +131,11 @@ hipError_t launch_attn_pipe(const AttnParams& p, hipStream_t stream) {
 
 hipError_t launch_merge_splits(const AttnParams& p, const int32_t* split_tiles, int n_split_tiles, hipStream_t stream) {
   if (n_split_tiles <= 0) return hipSuccess;
-  const unsigned grid = (unsigned)n_split_tiles * (unsigned)(p.n_q_heads / p.heads_per_wg) * (unsigned)p.waves_per_wg;
-  hipLaunchKernelGGL(pipe::merge_splits_kernel, dim3(grid), dim3(256), 0, stream, p, split_tiles);
+  const unsigned slots = (unsigned)n_split_tiles * (unsigned)(p.n_q_heads / p.heads_per_wg) * (unsigned)p.waves_per_wg;
+  if (slots * 32u <= pipe::kMergeSingleRows)
+    hipLaunchKernelGGL(pipe::merge_splits_kernel<1>, dim3(slots * 8u), dim3(256), 0, stream, p, split_tiles);
+  else
+    hipLaunchKernelGGL(pipe::merge_splits_kernel<4>, dim3(slots * 2u), dim3(256), 0, stream, p, split_tiles);
   return hipGetLastError();
 }
 
