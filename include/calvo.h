@@ -519,8 +519,8 @@ int calvo_attn_plan_items(int32_t n_q_heads, int32_t n_kv_heads, int32_t n_cus, 
 
 /* Measurement helper: which attention kernel the most recent calvo_prefill_attn for `layer` chose
  * (*kernel: 3 = 8-wave workgroups with 64-token tiles, 4 = two 4-wave workgroups per CU with 32-token
- * tiles, 0-2 = comparison variants, -1 = the vector-ALU kernel for fp32 pools / other head dims) and
- * how many workgroups its work items made (*n_workgroups; 0 for the vector-ALU kernel).  Either
+ * tiles, 0-2 = comparison variants, -1 = the packed-rows kernel for fp32 pools / other head dims) and
+ * how many workgroups its work items made (*n_workgroups; 0 for the packed-rows kernel).  Either
  * output may be NULL.  CALVO_ENOTREADY if none was queued. */
 int calvo_attn_kernel_info(calvo_ctx* ctx, int layer, int* kernel, int* n_workgroups);
 

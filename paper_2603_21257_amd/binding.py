@@ -363,7 +363,7 @@ def calvo_sched_simulate(policy: int, model, jobs, load_s=None, comp_s=None, pip
     return start[:n], fin[:n]
 
 
-ATTN_KERNEL_NAMES = {3: "calvo::pipe::attn_pipe_kernel", 4: "calvo::duo::attn_duo_kernel", -1: "calvo::attn_simple_kernel"}
+ATTN_KERNEL_NAMES = {3: "calvo::pipe::attn_pipe_kernel", 4: "calvo::duo::attn_duo_kernel", -1: "calvo::rows::attn_rows_kernel"}
 
 
 def calvo_attn_plan(n_q_heads: int, n_kv_heads: int, n_cus: int, prefix_blocks, suffix_lens) -> dict:

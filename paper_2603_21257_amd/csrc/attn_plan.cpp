@@ -15,6 +15,14 @@
 
 namespace calvo {
 
+// Packed-rows kernel, in tenths of a microsecond: start and end of a workgroup (and a merge launch), and 32
+// keys for one wave's rows with both waves of its SIMD at work (measured per element type and padded head width).
+constexpr int kRowsFill = 60;
+static int rows_step_cost(bool f32, int head_dim) {
+  if (f32) return head_dim <= 64 ? 23 : head_dim <= 128 ? 53 : 64;
+  return head_dim <= 64 ? 7 : head_dim <= 128 ? 23 : 25;
+}
+
 int attn_pipe_tile_tokens(int heads_per_wg);
 int attn_duo_tile_tokens(int heads_per_wg);
 
@@ -60,11 +68,12 @@ std::vector<PlanTile> plan_tiles(const int32_t* prefix_blocks, const int32_t* su
 int plan_piece_len(int n_sub, int want, const PlanParams& p) {
   const int n = std::max(1, std::min(want, p.force_splits ? n_sub : n_sub / p.split_min));
   int len = (n_sub + n - 1) / n;
+  if (p.step_cost) return (len + 3) / 4 * 4;       // packed rows: the same number of wave steps on each of the four SIMDs
   if (n > 1 && !p.force_splits) len = (len + 5) / 8 * 8 + 2;
   return len;
 }
 
-int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p) {
+int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots) {
   if (p.force_splits) return p.force_splits;
   const int64_t wgs = (int64_t)tiles.size() * p.n_head_groups;
   if (wgs <= 0 || wgs > 16 * (int64_t)p.wg_slots) return 1;     // many rounds: the last one hardly matters
@@ -77,13 +86,15 @@ int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p) {
     heap.assign((size_t)p.wg_slots, 0);            // min-heap of the times at which workgroup slots become free
     auto cmp = std::greater<int64_t>();
     bool cut = false;
-    int64_t end = 0;
+    int64_t end = 0, slots = 0;
     for (const PlanTile& t : tiles) {
       const int len = plan_piece_len(t.n_sub, n, p);
       const int np = (t.n_sub + len - 1) / len;
       cut |= np > 1;
+      slots += (int64_t)np * p.n_head_groups;
       for (int k = 0; k < np; k++) {
-        const int64_t cost = std::min(t.n_sub, (k + 1) * len) - k * len + p.split_fill;
+        const int64_t subs = std::min(t.n_sub, (k + 1) * len) - k * len;
+        const int64_t cost = (p.step_cost ? (subs + 3) / 4 * p.step_cost : subs) + p.split_fill;
         for (int h = 0; h < p.n_head_groups; h++) {
           std::pop_heap(heap.begin(), heap.end(), cmp);
           heap.back() += cost;
@@ -92,6 +103,7 @@ int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p) {
         }
       }
     }
+    if (n > 1 && slots > max_slots) break;
     const double span = (double)end + (cut ? p.split_fill : 0);
     if (n == 1 || span < best * 0.98) {            // a cut has to win by 2 % over what is chosen so far
       best = span;
@@ -112,6 +124,27 @@ PlanItems plan_items(const std::vector<PlanTile>& tiles, int want, const PlanPar
     for (int k = 0; k < n; k++) out.items.push_back({t.req, t.tile, k * len, std::min(t.n_sub, (k + 1) * len), n, first, 0, 0});
   }
   return out;
+}
+
+RowsShape attn_rows_shape(bool f32, int head_dim) {
+  return {head_dim <= 128 ? 32 : 16, rows_step_cost(f32, head_dim)};
+}
+
+std::vector<PlanTile> plan_row_tiles(const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int group, int tile_rows) {
+  std::vector<PlanTile> tiles;
+  for (int r = 0; r < n_reqs; r++) {
+    const int64_t rows = (int64_t)suffix_lens[r] * group;
+    for (int64_t t = 0; t * tile_rows < rows; t++) {
+      const int64_t keys = (int64_t)prefix_blocks[r] * 16 + (std::min((t + 1) * tile_rows, rows) - 1) / group + 1;
+      tiles.push_back({r, (int32_t)t, (int32_t)((keys + 31) / 32)});
+    }
+  }
+  std::stable_sort(tiles.begin(), tiles.end(), [](const PlanTile& a, const PlanTile& b) { return a.n_sub > b.n_sub; });
+  return tiles;
+}
+
+PlanParams rows_plan_params(RowsShape shape, int n_kv_heads, int n_cus, int force_splits) {
+  return {n_kv_heads, n_cus, 1, kRowsFill, force_splits, shape.step_cost};
 }
 
 PlanItems plan_items_chunked(const std::vector<PlanTile>& tiles, const int32_t* prefix_blocks, int chunk_blocks, int n_chunks) {

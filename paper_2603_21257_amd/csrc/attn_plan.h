@@ -31,6 +31,7 @@ struct PlanParams {
   int split_min;      // shortest piece of a cut tile, in sub-tiles
   int split_fill;     // cost of a workgroup's pipeline fill and drain, in sub-tile steps
   int force_splits;   // > 0: cut every tile into this many pieces (test knob)
+  int step_cost = 0;  // packed-rows kernel: cost of a wave's 32-key step, in units of split_fill; else 0
 };
 
 // A work item is one workgroup's share of the attention of one request: a tile of suffix tokens
@@ -61,11 +62,23 @@ std::vector<PlanTile> plan_tiles(const int32_t* prefix_blocks, const int32_t* su
 // length of the pieces a tile of n_sub sub-tiles is cut into when `want` pieces are asked for
 int plan_piece_len(int n_sub, int want, const PlanParams& p);
 
-// pieces per tile to ask for (1 = no cut), from a replay of the launch
-int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p);
+// pieces per tile to ask for (1 = no cut), from a replay of the launch; packed rows: at most max_slots
+// (piece, head group) pairs (partial results there is room for)
+int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots = INT64_MAX);
 
 // work items of a whole-layer launch: every tile cut into pieces of plan_piece_len(n_sub, want)
 PlanItems plan_items(const std::vector<PlanTile>& tiles, int want, const PlanParams& p);
+
+// Tiling of the packed-rows kernel (attn_rows.hip): (token, head) rows of one KV head per work item, and what a
+// wave's step of 32 keys costs.
+struct RowsShape {
+  int tile_rows, step_cost;
+};
+RowsShape attn_rows_shape(bool f32, int head_dim);
+
+// the batch's tiles of tile_rows rows, heaviest first (group: query heads per KV head)
+std::vector<PlanTile> plan_row_tiles(const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int group, int tile_rows);
+PlanParams rows_plan_params(RowsShape shape, int n_kv_heads, int n_cus, int force_splits);
 
 // Work items of a layer that was loaded in n_chunks chunks of chunk_blocks block indices (even): piece
 // k of a tile covers the sub-tiles of chunk k that lie wholly inside the request's prefix and goes

@@ -1,0 +1,678 @@
+// Paged causal GQA prefill attention on packed query rows: any head_dim <= 256 (multiple of 8), fp32 or
+// bf16 storage, any group size.  This is the path for fp32 pools and for head widths the pipelined
+// kernels (attn_pipeline.h) do not cover.
+//
+// Rows.  The (token, query head) pairs of one KV head are numbered row = token * group + head of the
+// group; a workgroup owns NQB blocks of 16 consecutive rows, so that a one-token query with four heads per
+// group fills a quarter of a block instead of one row of four tiles, and any group size packs without gaps.
+//
+// Both contractions run on the matrix pipes with the transposed formulation of attn_pipeline.h: lane
+// (c = lane % 16, g = lane / 16) of a score tile holds query row c and keys 4g + r, r = 0..3, which is
+// the operand order of the second product, so weights never cross lanes.
+//   fp32: v_mfma_f32_16x16x4_f32 for both products (fp32 products and sums, as on the vector ALU).  The
+//         k-slots may be any permutation of d if K and Q use the same one: a lane reads 16 bytes of its
+//         key row (d = 16j + 4g ..) that feed four instructions.  For the second product a lane reads 16
+//         bytes of a V row (d = 64q + 4c ..); output row m of instruction e is then d = 64q + 4m + e.
+//   bf16: v_mfma_f32_16x16x32_bf16.  V rows are read 8 or 16 bytes per lane in the same way and the four
+//         keys of a lane are brought together with v_perm_b32.  The weights stay fp32: each is split into
+//         three bf16 terms (24 significant bits), three products with the exact bf16 V.
+//
+// No LDS on the way in: 16 keys are exactly one pool block, so a block's address is one scalar table
+// lookup and the lanes' offsets inside it are constants; K and V go straight to registers, K(next) is
+// requested as soon as the scores have consumed K and V(next) after the second product.  All waves of a
+// workgroup work on the same rows: they take alternate steps of the keys and are combined through LDS at
+// the end, which keeps short queries from being one long serial walk.  (Waves with rows of their own,
+// which read the same K and V through the L1, were measured: the same within 3 % where there are rows
+// enough to fill the chip, slower elsewhere.)  Contexts are cut into pieces across workgroups as well
+// (attn_plan.cpp) and merged by merge_rows_kernel.
+//
+// The suffix's K and V are read from the caller's arrays where the launch is given them, and stored
+// to the pool on the side; the append launch and its dependency go away.
+//
+// Softmax reference raised lazily as in attn_pipeline.h: weights are taken against the maximum of an
+// earlier step and the reference moves only when a score passes it by 2^16.
+//
+// What bounds it: fp32 the matrix pipes (a large fp32 product reaches 153 TFLOP/s on this part, a
+// sixteenth of bf16; 2.3 us per 32 keys of a wave's 32 rows at D = 64 against 1.8 us of MFMA), bf16 the
+// vector ALU (exponentials, weight split, V permutes; 0.7 us per step against 0.2 us of MFMA).
+// Measured against the kernel it replaces (one wave per token and head on the vector ALU), us a call:
+// fp32 8Q/2KV D = 64, 1024+128 tokens 194 -> 21; bf16 16Q/4KV D = 64, 4096+300 tokens 1170 -> 27.5.
+#include "attn_common.h"
+#include "../../include/calvo.h"
+
+namespace calvo {
+namespace rows {
+
+using namespace attn;
+
+typedef const __attribute__((address_space(4))) int32_t* const_i32p;
+
+// T_: storage.  DP: head_dim rounded up to 64, 128 or 256.  NQB: 16-row blocks of a tile.  KB: 16-key
+// blocks per step.  NW: waves per workgroup.  FULL: head_dim == DP, no lane of a K or Q operand is past the end.
+template <typename T_, int DP_, int NQB_, int KB_, int NW_, bool FULL_>
+struct RowsCfg {
+  typedef T_ T;
+  static constexpr int DP = DP_, NQB = NQB_, KB = KB_, NW = NW_;
+  static constexpr bool FULL = FULL_, F32 = sizeof(T_) == 4;
+  static constexpr int E = sizeof(T_);
+  static constexpr int KJ = F32 ? DP / 16 : DP / 32;         // 16-byte operand chunks of a K or Q row per lane
+  static constexpr int VW = F32 ? 4 : (DP % 128 == 0 ? 8 : 4);   // consecutive d a lane reads of a V row
+  static constexpr int VQ = DP / (16 * VW);                  // such reads per row
+  static constexpr int NACC = VQ * VW;                       // 16 x 16 output tiles per 16-row block
+  static constexpr int ROWS = 16 * NQB;                      // rows of a tile
+  static constexpr int UNITS = NQB * VQ * 4;                 // (row block, q, r): VW consecutive d of a lane's row
+  static constexpr int LDS_O = NW * UNITS * VW * 64 * 4;     // all waves' accumulators
+  static constexpr int LDS_BYTES = LDS_O + NW * ROWS * 8;
+};
+
+// by value: __builtin_bit_cast applied to an element of a vector reads element 0 with this compiler
+__device__ inline float as_float(unsigned x) { return __builtin_bit_cast(float, x); }
+__device__ inline unsigned bf16_rne(float x) {
+  return (unsigned)__builtin_bit_cast(unsigned short, (__bf16)x);
+}
+__device__ inline float bf16_widen(unsigned b) { return __builtin_bit_cast(float, b << 16); }
+
+template <class C>
+__global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
+  typedef typename C::T T;
+  constexpr int DP = C::DP, NQB = C::NQB, KB = C::KB, NW = C::NW, KJ = C::KJ, VW = C::VW, VQ = C::VQ, E = C::E;
+  constexpr bool F32 = C::F32;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = lane & 15, g = lane >> 4;
+  const int Hkv = p.n_kv_heads, Hq = p.n_q_heads, D = p.head_dim;
+  const unsigned G = p.group;
+  constexpr unsigned RT = C::ROWS;                             // rows of a work item
+
+  // ---- work item (wave-uniform); a KV head's workgroups stay on one XCD where the heads divide over the eight
+  int it, kv;
+  {
+    const int bid = blockIdx.x;
+    if ((Hkv & 7) == 0) {
+      const int per = Hkv >> 3, rest = bid >> 3;
+      kv = (bid & 7) * per + rest % per;
+      it = rest / per;
+    } else {
+      kv = bid % Hkv;
+      it = bid / Hkv;
+    }
+  }
+  int tile, sub_begin = 0, sub_end, n_splits = 1;
+  bool first_piece = true;
+  ReqDesc rd = p.one;                                          // a batch of one request comes with the launch
+  if (p.items) {
+    const WorkItem wi = p.items[it];
+    tile = wi.q_tile; sub_begin = wi.sub_begin; sub_end = wi.sub_end; n_splits = wi.n_splits;
+    first_piece = wi.first_item == it;
+    if (p.n_reqs > 1) rd = p.reqs[wi.req];
+  } else {
+    // uncut tiles without a work item list (one request, or descriptors that have to stay small): count them
+    int t = it, nt, req = 0;
+    for (;;) {
+      if (p.n_reqs > 1) rd = p.reqs[req];
+      nt = (int)(((unsigned)rd.suffix_len * G + RT - 1) / RT);
+      if (t < nt || req + 1 == p.n_reqs) break;
+      t -= nt;
+      req++;
+    }
+    tile = nt - 1 - t;                                         // longest context first
+    const unsigned last = min((unsigned)rd.suffix_len * G, (unsigned)(tile + 1) * RT) - 1;
+    sub_end = (rd.prefix_len + (int)(last / G) + 32) / 32;
+  }
+  const int P = rd.prefix_len, S = rd.suffix_len, ctx_len = P + S;
+  const unsigned n_rows = (unsigned)S * G, row0 = (unsigned)tile * RT;
+
+  // ---- rows of this lane: row 16 * qb + c of the tile
+  int64_t qrow[NQB];                                           // row of q / out, in heads
+  int posq[NQB];
+  bool ok[NQB];
+#pragma unroll
+  for (int qb = 0; qb < NQB; qb++) {
+    const unsigned rho = row0 + 16 * qb + c;
+    ok[qb] = rho < n_rows;
+    const unsigned rr = ok[qb] ? rho : n_rows - 1, tok = rr / G;
+    posq[qb] = P + (int)tok;
+    qrow[qb] = (int64_t)(rd.q_off + (int)tok) * Hq + kv * (int)G + (int)(rr - tok * G);
+  }
+  // first and last row of the tile
+  const int pos_min = __builtin_amdgcn_readfirstlane(posq[0]), pos_max = __builtin_amdgcn_readlane(posq[NQB - 1], 15);
+
+  // ---- addressing: block b of the request; 16-byte offsets inside it
+  const unsigned char* pool = (const unsigned char*)p.pool_layer;
+  const unsigned rs = (unsigned)(Hkv * D * E);                 // bytes between token rows
+  const int64_t half = (int64_t)kBlockTokens * rs;
+  const const_i32p table = (const_i32p)(uintptr_t)(p.tables + rd.table_off);
+  const int p_blk = P / kBlockTokens, last_blk = (ctx_len + kBlockTokens - 1) / kBlockTokens - 1;
+  const unsigned char* ks = (const unsigned char*)p.k_suffix;
+  const unsigned char* vs = (const unsigned char*)p.v_suffix;
+  const int64_t s_base = (int64_t)rd.q_off * rs;
+  const bool from_suffix = ks != nullptr;
+  const unsigned head_b = (unsigned)(kv * D * E);
+  bool k_ok[KJ];                                               // operand chunk j of this lane lies inside the head
+  unsigned k_off[KJ];
+#pragma unroll
+  for (int j = 0; j < KJ; j++) {
+    const int d = F32 ? 16 * j + 4 * g : 32 * j + 8 * g;
+    k_ok[j] = C::FULL || d < D;
+    k_off[j] = (unsigned)((k_ok[j] ? d : 0) * E);
+  }
+  unsigned v_off[VQ];
+#pragma unroll
+  for (int q = 0; q < VQ; q++) {
+    const int d = VW * (16 * q + c);
+    v_off[q] = (unsigned)((C::FULL || d < D ? d : 0) * E);     // past the head: output rows that are not stored
+  }
+  const unsigned k_row = head_b + c * rs, v_row = head_b + 4 * g * rs;
+  typedef typename std::conditional<(VW * E == 16), u32x4, u32x2>::type vreg;
+
+  u32x4 kreg[KB][KJ];
+  vreg vr[KB][4][VQ];
+  int slot[KB];                                                // pool slots of the step that load_k takes next
+  const unsigned char* vp[KB];                                 // V rows of the step that load_v takes next
+  auto look_up = [&](int st) {
+#pragma unroll
+    for (int kb = 0; kb < KB; kb++) slot[kb] = table[min(st * KB + kb, last_blk)];
+  };
+  // Rows past the end of the context are not read: the last row again (their scores are masked).
+  auto load_k = [&](int st) {
+#pragma unroll
+    for (int kb = 0; kb < KB; kb++) {
+      const int b = min(st * KB + kb, last_blk);
+      const bool sfx = from_suffix && b >= p_blk;
+      const int64_t off = sfx ? s_base + (int64_t)(b - p_blk) * half : (int64_t)slot[kb] * (2 * half);
+      const unsigned char* kp = (sfx ? ks : pool) + off;
+      vp[kb] = sfx ? vs + off : kp + half;
+      const int rest = ctx_len - kBlockTokens * b;             // token rows the block holds
+      const unsigned row = rest >= kBlockTokens ? k_row : head_b + (unsigned)min(c, rest - 1) * rs;
+#pragma unroll
+      for (int j = 0; j < KJ; j++) {
+        kreg[kb][j] = *(const u32x4*)(kp + (row + k_off[j]));
+        if (!C::FULL && !k_ok[j]) kreg[kb][j] = (u32x4){0u, 0u, 0u, 0u};
+      }
+    }
+  };
+  auto load_v = [&](int st) {
+#pragma unroll
+    for (int kb = 0; kb < KB; kb++) {
+      const int rest = ctx_len - kBlockTokens * min(st * KB + kb, last_blk);
+      if (rest >= kBlockTokens) {
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+#pragma unroll
+          for (int q = 0; q < VQ; q++) vr[kb][r][q] = *(const vreg*)(vp[kb] + r * rs + (v_row + v_off[q]));
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          const unsigned row = head_b + (unsigned)min(4 * g + r, rest - 1) * rs;
+#pragma unroll
+          for (int q = 0; q < VQ; q++) vr[kb][r][q] = *(const vreg*)(vp[kb] + (row + v_off[q]));
+        }
+      }
+    }
+  };
+
+  // ---- this wave's steps: KB blocks each, alternating between the key waves
+  constexpr int SPS = 2 / KB;                                  // steps per 32-key sub-tile
+  int st = sub_begin * SPS + wave;
+  const int st_end = min(sub_end * SPS, pos_max / (kBlockTokens * KB) + 1);
+  if (st < st_end) look_up(st);
+  u32x4 qreg[NQB][KJ];                                         // requested before K, so that waiting for K does not wait for V
+#pragma unroll
+  for (int qb = 0; qb < NQB; qb++)
+#pragma unroll
+    for (int j = 0; j < KJ; j++) {
+      qreg[qb][j] = *(const u32x4*)((const unsigned char*)p.q + qrow[qb] * (D * E) + k_off[j]);
+      if (!C::FULL && !k_ok[j]) qreg[qb][j] = (u32x4){0u, 0u, 0u, 0u};
+    }
+  if (st < st_end) {
+    load_k(st);
+    look_up(st + NW);
+    load_v(st);
+  }
+
+  const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+  f32x4 o[NQB][C::NACC];                                       // tile (q, e): d = VW * (16q + 4g + r) + e of query row c
+#pragma unroll
+  for (int qb = 0; qb < NQB; qb++)
+#pragma unroll
+    for (int a = 0; a < C::NACC; a++) o[qb][a] = zero4;
+  float m[NQB], l[NQB];                                        // reference (exponent units; -inf: no key seen), row sum of this lane
+#pragma unroll
+  for (int qb = 0; qb < NQB; qb++) { m[qb] = -INFINITY; l[qb] = 0.f; }
+  const float c2 = p.scale * 1.4426950408889634f;
+
+  // Second product: o += V^T * w for the keys in vr.  keep(kb, r, x) passes the operand bits of the lane's
+  // key 16kb + 4g + r through or drops them.
+  auto weights_bf16 = [&](const float (&w)[NQB][KB][4], bf16x8 (&pb)[NQB][3], auto keep) {
+#pragma unroll
+    for (int qb = 0; qb < NQB; qb++) {
+      u32x4 x[3];
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        float v[2];
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+          const int k = 2 * i + h;
+          v[h] = __builtin_bit_cast(float, keep(k >> 2, k & 3, __builtin_bit_cast(unsigned, w[qb][k >> 2][k & 3])));
+        }
+#pragma unroll
+        for (int t = 0; t < 3; t++) {
+          const bf16x2 top = {(__bf16)v[0], (__bf16)v[1]};
+          x[t][i] = __builtin_bit_cast(unsigned, top);
+          v[0] -= bf16_widen(x[t][i] & 0xffffu);
+          v[1] -= __builtin_bit_cast(float, x[t][i] & 0xffff0000u);
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < 3; t++) pb[qb][t] = __builtin_bit_cast(bf16x8, x[t]);
+    }
+  };
+  // V^T operand of tile (q, e): the lane's keys in k-slot order (kb, r)
+  auto v_bf16 = [&](int q, int e, auto keep) {
+    u32x4 x;
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+      x[i] = __builtin_amdgcn_perm(keep(i >> 1, 2 * (i & 1) + 1, vr[(KB - 1) & (i >> 1)][2 * (i & 1) + 1][q][e >> 1]),
+                                   keep(i >> 1, 2 * (i & 1), vr[(KB - 1) & (i >> 1)][2 * (i & 1)][q][e >> 1]), e & 1 ? 0x07060302u : 0x05040100u);
+    return __builtin_bit_cast(bf16x8, x);
+  };
+  auto all_keys = [](int, int, unsigned x) { return x; };
+  auto pv = [&](const float (&w)[NQB][KB][4]) {
+    if constexpr (F32) {
+#pragma unroll
+      for (int kb = 0; kb < KB; kb++)
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+#pragma unroll
+          for (int q = 0; q < VQ; q++)
+#pragma unroll
+            for (int e = 0; e < VW; e++)
+#pragma unroll
+              for (int qb = 0; qb < NQB; qb++)
+                o[qb][q * VW + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(as_float(vr[kb][r][q][e]), w[qb][kb][r],
+                                                                         o[qb][q * VW + e], 0, 0, 0);
+    } else {
+      bf16x8 pb[NQB][3];
+      weights_bf16(w, pb, all_keys);
+#pragma unroll
+      for (int q = 0; q < VQ; q++)
+#pragma unroll
+        for (int e0 = 0; e0 < VW; e0 += 4) {
+          bf16x8 a[4];
+#pragma unroll
+          for (int e = 0; e < 4; e++) a[e] = v_bf16(q, e0 + e, all_keys);
+#pragma unroll
+          for (int t = 0; t < 3; t++)
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+#pragma unroll
+              for (int qb = 0; qb < NQB; qb++)
+                o[qb][q * VW + e0 + e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[e], pb[qb][t], o[qb][q * VW + e0 + e], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);                   // one group's operands at a time in registers
+        }
+    }
+  };
+  // The same key by key, each key only into the rows that see it (see the loop).
+  auto pv_by_key = [&](const float (&w)[NQB][KB][4], int k0) {
+    for (int key = 0; key < 16 * KB; key++) {
+      const bool mine = g == ((key >> 2) & 3);
+      auto keep = [&](int kb, int r, unsigned x) { return mine && key >> 4 == kb && (key & 3) == r ? x : 0u; };
+      bf16x8 pb[NQB][3];
+      if constexpr (!F32) weights_bf16(w, pb, keep);
+#pragma unroll
+      for (int q = 0; q < VQ; q++)
+#pragma unroll
+        for (int e = 0; e < VW; e++) {
+          bf16x8 a;
+          if constexpr (!F32) a = v_bf16(q, e, keep);
+#pragma unroll
+          for (int qb = 0; qb < NQB; qb++) {
+            f32x4 one = zero4;
+            if constexpr (F32) {
+#pragma unroll
+              for (int kb = 0; kb < KB; kb++)
+#pragma unroll
+                for (int r = 0; r < 4; r++)
+                  one = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                      __builtin_bit_cast(float, keep(kb, r, vr[kb][r][q][e])),
+                      __builtin_bit_cast(float, keep(kb, r, __builtin_bit_cast(unsigned, w[qb][kb][r]))), one, 0, 0, 0);
+            } else {
+#pragma unroll
+              for (int t = 0; t < 3; t++) one = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pb[qb][t], one, 0, 0, 0);
+            }
+            if (k0 + key <= posq[qb]) o[qb][q * VW + e] += one;
+          }
+        }
+    }
+  };
+
+  for (; st < st_end; st += NW) {
+    const int k0 = st * (kBlockTokens * KB);
+    f32x4 s[KB][NQB];
+#pragma unroll
+    for (int kb = 0; kb < KB; kb++)
+#pragma unroll
+      for (int qb = 0; qb < NQB; qb++) s[kb][qb] = zero4;
+#pragma unroll
+    for (int j = 0; j < KJ; j++) {
+      if constexpr (F32) {
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+#pragma unroll
+          for (int kb = 0; kb < KB; kb++)
+#pragma unroll
+            for (int qb = 0; qb < NQB; qb++)
+              s[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x4f32(as_float(kreg[kb][j][i]),
+                                                               as_float(qreg[qb][j][i]), s[kb][qb], 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int kb = 0; kb < KB; kb++)
+#pragma unroll
+          for (int qb = 0; qb < NQB; qb++)
+            s[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kreg[kb][j]),
+                                                                __builtin_bit_cast(bf16x8, qreg[qb][j]), s[kb][qb], 0, 0, 0);
+      }
+    }
+    const bool more = st + NW < st_end;
+    if (more) {
+      load_k(st + NW);
+      look_up(st + 2 * NW);                                    // clamped to the last block
+    }
+    const bool diag = k0 + kBlockTokens * KB - 1 > pos_min;    // some row does not see all of these keys
+    if (diag) {
+#pragma unroll
+      for (int kb = 0; kb < KB; kb++)
+#pragma unroll
+        for (int qb = 0; qb < NQB; qb++)
+#pragma unroll
+          for (int r = 0; r < 4; r++)
+            if (k0 + 16 * kb + 4 * g + r > posq[qb]) s[kb][qb][r] = -INFINITY;
+    }
+    float mx[NQB];
+    bool raise = false;
+#pragma unroll
+    for (int qb = 0; qb < NQB; qb++) {
+      mx[qb] = -INFINITY;
+#pragma unroll
+      for (int kb = 0; kb < KB; kb++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) mx[qb] = fmaxf(mx[qb], s[kb][qb][r]);
+      raise |= mx[qb] * c2 > m[qb] + 16.f;
+    }
+    if (__builtin_amdgcn_ballot_w64(raise) != 0) {
+#pragma unroll
+      for (int qb = 0; qb < NQB; qb++) {
+        const float mn = fmaxf(m[qb], quad_max(mx[qb]) * c2);
+        const float a = __builtin_amdgcn_exp2f(m[qb] - (mn == -INFINITY ? 0.f : mn));
+        m[qb] = mn;
+        l[qb] *= a;
+#pragma unroll
+        for (int i = 0; i < C::NACC; i++) o[qb][i] *= a;
+      }
+    }
+    float w[NQB][KB][4];
+#pragma unroll
+    for (int qb = 0; qb < NQB; qb++) {
+      const float ref = m[qb] == -INFINITY ? 0.f : m[qb];      // a row that has seen no key yet: all its weights are 0
+      float sum = 0.f;
+#pragma unroll
+      for (int kb = 0; kb < KB; kb++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          w[qb][kb][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][qb][r], c2, -ref));
+          sum += w[qb][kb][r];
+        }
+      l[qb] += sum;
+    }
+    // A masked weight is 0, and 0 times an infinity or NaN that a later token's V may hold is NaN: such
+    // a step goes key by key and adds only what each row sees.
+    bool odd = false;
+    if (diag) {
+#pragma unroll
+      for (int kb = 0; kb < KB; kb++)
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+#pragma unroll
+          for (int q = 0; q < VQ; q++)
+#pragma unroll
+            for (int i = 0; i < VW * E / 4; i++) {
+              const unsigned x = vr[kb][r][q][i];
+              if constexpr (F32) odd |= (x & 0x7f800000u) == 0x7f800000u;
+              else odd |= (x & 0x7f800000u) == 0x7f800000u || (x & 0x7f80u) == 0x7f80u;
+            }
+      odd = __builtin_amdgcn_ballot_w64(odd) != 0;
+    }
+    if (!odd) pv(w);
+    else pv_by_key(w, k0);
+    if (more) load_v(st + NW);
+  }
+
+  // ---- suffix rows of the tokens whose first row lies in this tile: caller's arrays -> pool.  The first
+  // chunk of every thread is on its way while the key waves are combined.
+  const int cpr = D * E / 16;
+  int n_copy = 0, t0 = 0;
+  if (from_suffix && first_piece) {
+    t0 = (int)((tile * RT + G - 1) / G);
+    n_copy = ((int)((min((tile + 1) * RT, n_rows) + G - 1) / G) - t0) * cpr;
+  }
+  auto copy_at = [&](int i, int64_t& src, int64_t& dst) {
+    const int tok = t0 + i / cpr, pos = P + tok;
+    const unsigned in_row = head_b + 16 * (i % cpr);
+    src = s_base + (int64_t)tok * rs + in_row;
+    dst = (int64_t)p.tables[rd.table_off + pos / kBlockTokens] * (2 * half) + (int64_t)(pos % kBlockTokens) * rs + in_row;
+  };
+  unsigned char* wpool = (unsigned char*)p.pool_layer;
+  u32x4 copy_k, copy_v;
+  int64_t copy_dst = 0;
+  if ((int)threadIdx.x < n_copy) {
+    int64_t src;
+    copy_at(threadIdx.x, src, copy_dst);
+    copy_k = *(const u32x4*)(ks + src);
+    copy_v = *(const u32x4*)(vs + src);
+  }
+
+  // ---- row sums over the four lanes of a row, then over the waves
+  float* lds_o = (float*)smem + (size_t)wave * (C::UNITS * VW * 64) + lane;
+  float* lds_ml = (float*)(smem + C::LDS_O);
+#pragma unroll
+  for (int qb = 0; qb < NQB; qb++) l[qb] = quad_sum(l[qb]);
+#pragma unroll
+  for (int qb = 0; qb < NQB; qb++)
+    if (g == 0) *(f32x2*)(lds_ml + (wave * C::ROWS + 16 * qb + c) * 2) = (f32x2){m[qb], l[qb]};
+  __syncthreads();
+#pragma unroll
+  for (int qb = 0; qb < NQB; qb++) {
+    const f32x2* ml = (const f32x2*)lds_ml + 16 * qb + c;
+    f32x2 x[NW];
+    float all = -INFINITY, sum = 0.f;
+#pragma unroll
+    for (int k = 0; k < NW; k++) x[k] = ml[k * C::ROWS];
+#pragma unroll
+    for (int k = 0; k < NW; k++) all = fmaxf(all, x[k][0]);
+    const float ref = all == -INFINITY ? 0.f : all;
+    const float a = __builtin_amdgcn_exp2f(m[qb] - ref);
+#pragma unroll
+    for (int k = 0; k < NW; k++) sum += __builtin_amdgcn_exp2f(x[k][0] - ref) * x[k][1];
+    m[qb] = all;
+    l[qb] = sum;
+#pragma unroll
+    for (int q = 0; q < VQ; q++)
+#pragma unroll
+      for (int r = 0; r < 4; r++)
+#pragma unroll
+        for (int e = 0; e < VW; e++) lds_o[(((qb * VQ + q) * 4 + r) * VW + e) * 64] = o[qb][q * VW + e][r] * a;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < n_copy) {
+    *(u32x4*)(wpool + copy_dst) = copy_k;
+    *(u32x4*)(wpool + copy_dst + half) = copy_v;
+    for (int i = threadIdx.x + 64 * NW; i < n_copy; i += 64 * NW) {
+      int64_t src, dst;
+      copy_at(i, src, dst);
+      *(u32x4*)(wpool + dst) = *(const u32x4*)(ks + src);
+      *(u32x4*)(wpool + dst + half) = *(const u32x4*)(vs + src);
+    }
+  }
+  const int64_t part = (int64_t)it * Hkv + kv;
+  if (n_splits > 1 && wave == 0 && g == 0) {
+#pragma unroll
+    for (int qb = 0; qb < NQB; qb++) {
+      float* pm = p.part_ml + (part * C::ROWS + 16 * qb + c) * 2;
+      pm[0] = m[qb];
+      pm[1] = l[qb];
+    }
+  }
+#pragma unroll
+  for (int qb = 0; qb < NQB; qb++)
+#pragma unroll
+    for (int q = 0; q < VQ; q++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const int unit = (qb * VQ + q) * 4 + r;
+        if (unit % NW != wave) continue;                       // the waves share the stores
+        const float* src = (const float*)smem + unit * VW * 64 + lane;
+        float v[NW][VW], x[VW];
+#pragma unroll
+        for (int k = 0; k < NW; k++)
+#pragma unroll
+          for (int e = 0; e < VW; e++) v[k][e] = src[(k * C::UNITS * VW + e) * 64];
+#pragma unroll
+        for (int e = 0; e < VW; e++) {
+          x[e] = v[0][e];
+#pragma unroll
+          for (int k = 1; k < NW; k++) x[e] += v[k][e];
+        }
+        const int d = VW * (16 * q + 4 * g + r);
+        if (n_splits > 1) {
+          float* po = p.part_o + (part * C::ROWS + 16 * qb + c) * DP + d;
+#pragma unroll
+          for (int e = 0; e < VW; e += 4) *(f32x4*)(po + e) = (f32x4){x[e], x[e + 1], x[e + 2], x[e + 3]};
+        } else if (ok[qb] && (C::FULL || d < D)) {
+          const float inv = 1.f / l[qb];
+          T* po = (T*)p.out + qrow[qb] * D + d;
+          if constexpr (F32) {
+            *(f32x4*)po = (f32x4){x[0] * inv, x[1] * inv, x[2] * inv, x[3] * inv};
+          } else {
+            vreg v;
+#pragma unroll
+            for (int e = 0; e < VW; e += 2) v[e / 2] = bf16_rne(x[e] * inv) | bf16_rne(x[e + 1] * inv) << 16;
+            *(vreg*)po = v;
+          }
+        }
+      }
+}
+
+// Combines the pieces of cut tiles as merge_splits_kernel does, for this file's layout: one wave per row.
+// A row that saw no key in a piece has m = -inf, l = 0, O = 0 there and adds nothing.
+template <typename T, int DP, int ROWS>
+__global__ void __launch_bounds__(256) merge_rows_kernel(RowsParams p, const int32_t* split_tiles) {
+  constexpr int W = DP / 64;                                   // consecutive floats of a lane
+  typedef typename std::conditional<W == 4, f32x4, typename std::conditional<W == 2, f32x2, float>::type>::type vec;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int Hkv = p.n_kv_heads, Hq = p.n_q_heads, D = p.head_dim;
+  const unsigned G = p.group;
+  const int row = (blockIdx.x % (ROWS / 4)) * 4 + wave;
+  const int slot_id = blockIdx.x / (ROWS / 4), kv = slot_id % Hkv, first = split_tiles[slot_id / Hkv];
+  const WorkItem wi = p.items[first];
+  const ReqDesc rd = p.reqs[wi.req];
+  const unsigned rho = (unsigned)wi.q_tile * ROWS + row;
+  if (rho >= (unsigned)rd.suffix_len * G) return;
+  const int n = wi.n_splits;
+  const int64_t base = ((int64_t)first * Hkv + kv) * ROWS + row;
+  const int64_t step = (int64_t)Hkv * ROWS;
+  const f32x2* ml = (const f32x2*)p.part_ml + base;
+  const float* po = p.part_o + base * DP + W * lane;
+  // at most 64 pieces per tile (attn_plan.cpp): lane i holds piece i
+  const f32x2 mine = lane < n ? ml[lane * step] : (f32x2){-INFINITY, 0.f};
+  float all = mine[0];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) all = fmaxf(all, __shfl_xor(all, o));
+  const float wgt = mine[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mine[0] - all);
+  float l = wgt * mine[1];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
+  float acc[W];
+#pragma unroll
+  for (int e = 0; e < W; e++) acc[e] = 0.f;
+  constexpr int B = 8;                                         // loads in flight
+  for (int c0 = 0; c0 < n; c0 += B) {
+    vec v[B];
+#pragma unroll
+    for (int i = 0; i < B; i++) v[i] = *(const vec*)(po + min(c0 + i, n - 1) * step * DP);
+#pragma unroll
+    for (int i = 0; i < B; i++) {
+      if (c0 + i >= n) break;
+      const float w = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wgt), c0 + i));
+#pragma unroll
+      for (int e = 0; e < W; e++) {
+        float x;
+        if constexpr (W == 1) x = v[i];
+        else x = v[i][e];
+        acc[e] = __builtin_fmaf(w, x, acc[e]);
+      }
+    }
+  }
+  const int d = W * lane;
+  if (d >= D) return;
+  const float inv = 1.f / l;
+  const unsigned tok = rho / G;
+  T* out = (T*)p.out + ((int64_t)(rd.q_off + (int)tok) * Hq + kv * (int)G + (int)(rho - tok * G)) * D + d;
+#pragma unroll
+  for (int e = 0; e < W; e++) {
+    if constexpr (sizeof(T) == 4) out[e] = acc[e] * inv;
+    else out[e] = (T)bf16_rne(acc[e] * inv);
+  }
+}
+
+template <class C>
+hipError_t launch(const RowsParams& p, unsigned grid, const int32_t* split_tiles, int n_split_tiles, hipStream_t stream) {
+  hipLaunchKernelGGL(attn_rows_kernel<C>, dim3(grid), dim3(64 * C::NW), C::LDS_BYTES, stream, p);
+  if (n_split_tiles > 0) {
+    const unsigned slots = (unsigned)n_split_tiles * (unsigned)p.n_kv_heads;
+    hipLaunchKernelGGL((merge_rows_kernel<typename C::T, C::DP, C::ROWS>), dim3(slots * (C::ROWS / 4)), dim3(256), 0, stream, p,
+                       split_tiles);
+  }
+  return hipGetLastError();
+}
+
+// f(configuration) for an element type and head width
+template <typename F>
+auto with_cfg(int dtype, int head_dim, F&& f) {
+  typedef uint16_t B16;
+  if (dtype == CALVO_F32) {
+    if (head_dim == 64) return f(RowsCfg<float, 64, 2, 2, 8, true>{});
+    if (head_dim < 64) return f(RowsCfg<float, 64, 2, 2, 8, false>{});
+    if (head_dim == 128) return f(RowsCfg<float, 128, 2, 1, 4, true>{});
+    if (head_dim < 128) return f(RowsCfg<float, 128, 2, 1, 4, false>{});
+    if (head_dim == 256) return f(RowsCfg<float, 256, 1, 1, 4, true>{});
+    return f(RowsCfg<float, 256, 1, 1, 4, false>{});
+  }
+  if (head_dim == 64) return f(RowsCfg<B16, 64, 2, 2, 8, true>{});
+  if (head_dim < 64) return f(RowsCfg<B16, 64, 2, 2, 8, false>{});
+  if (head_dim == 128) return f(RowsCfg<B16, 128, 2, 2, 8, true>{});
+  if (head_dim < 128) return f(RowsCfg<B16, 128, 2, 2, 8, false>{});
+  if (head_dim == 256) return f(RowsCfg<B16, 256, 1, 2, 4, true>{});
+  return f(RowsCfg<B16, 256, 1, 2, 4, false>{});
+}
+
+}  // namespace rows
+
+hipError_t attn_rows_prepare(int dtype, int head_dim) {
+  return rows::with_cfg(dtype, head_dim, [](auto cfg) {
+    typedef decltype(cfg) C;
+    return hipFuncSetAttribute((const void*)rows::attn_rows_kernel<C>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
+  });
+}
+
+hipError_t launch_attn_rows(const RowsParams& p, int dtype, int n_items, const int32_t* split_tiles, int n_split_tiles,
+                            hipStream_t stream) {
+  if (n_items <= 0) return hipSuccess;
+  const unsigned grid = (unsigned)n_items * (unsigned)p.n_kv_heads;
+  return rows::with_cfg(dtype, p.head_dim, [&](auto cfg) {
+    return rows::launch<decltype(cfg)>(p, grid, split_tiles, n_split_tiles, stream);
+  });
+}
+
+}  // namespace calvo

@@ -240,7 +240,7 @@ int ensure_att_blob(calvo_ctx* c, size_t n) {
 // Room for the split-KV partial results of `slots` (work item, head group, wave) triples.  Growing
 // frees the old buffers, hence waits for the compute stream; contexts for bf16 / head-dim-128
 // pools start with room for the short-query batches (kPartialSlots0), so only long chunk-granular
-// layers ever grow it.
+// layers ever grow it; the others start with all that a packed-rows launch may use (kStaticPartSlots).
 constexpr size_t kPartialSlots0 = 4096;      // 68 MB
 
 int ensure_partials(calvo_ctx* c, size_t slots) {
@@ -250,7 +250,6 @@ int ensure_partials(calvo_ctx* c, size_t slots) {
   if (c->part_ml) (void)hipFree(c->part_ml);
   c->part_o = c->part_ml = nullptr;
   c->part_slots = 0;
-  slots = std::max(slots, kPartialSlots0);
   HIP_TRY(hipMalloc((void**)&c->part_o, slots * 32 * 128 * sizeof(float)));
   HIP_TRY(hipMalloc((void**)&c->part_ml, slots * 32 * 2 * sizeof(float)));
   c->part_slots = slots;
@@ -581,8 +580,13 @@ int calvo_create(const calvo_config* cfg, calvo_ctx** out) {
     if (e == hipSuccess) e = attn_duo_prepare();
     if (e != hipSuccess) { const int prc = fail_hip(e, "hipFuncSetAttribute(dynamic LDS)"); destroy_partial(c); return prc; }
   }
-  if (cfg->dtype == CALVO_BF16 && cfg->head_dim == 128) {
-    const int prc = ensure_partials(c, kPartialSlots0);
+  if (!(cfg->dtype == CALVO_BF16 && cfg->head_dim == 128)) {
+    hipError_t e = attn_rows_prepare(cfg->dtype, cfg->head_dim);
+    if (e != hipSuccess) { const int prc = fail_hip(e, "hipFuncSetAttribute(dynamic LDS)"); destroy_partial(c); return prc; }
+  }
+  {
+    const bool mfma = cfg->dtype == CALVO_BF16 && cfg->head_dim == 128;
+    const int prc = ensure_partials(c, mfma ? kPartialSlots0 : kStaticPartSlots);
     if (prc != CALVO_OK) { destroy_partial(c); return prc; }
   }
   *out = c;
@@ -714,7 +718,7 @@ struct BlobLayout {
 };
 
 BlobLayout build_descriptor_blob(const calvo_ctx* c, const calvo_request* reqs, int n_reqs, const int32_t* cu_suffix,
-                                 const PlanItems& plan, std::vector<int32_t>& blob) {
+                                 const PlanItems& plan, bool with_offs, std::vector<int32_t>& blob) {
   BlobLayout lay;
   auto table_len = [&](int r) { return (int64_t)reqs[r].n_prefix_blocks + (reqs[r].suffix_len + kBlockTokens - 1) / kBlockTokens; };
   blob.clear();
@@ -747,6 +751,7 @@ BlobLayout build_descriptor_blob(const calvo_ctx* c, const calvo_request* reqs, 
   }
   if (blob.size() & 1) blob.push_back(0);                       // 8-byte alignment of the offsets
   lay.offs_off = blob.size();
+  if (!with_offs) return lay;
   size_t base = lay.tables_off;
   for (int r = 0; r < n_reqs; r++) {
     const int64_t nt = table_len(r);
@@ -1059,6 +1064,7 @@ struct AttnPlan {
   int n_reqs = 0, total = 0;            // requests, suffix tokens over all of them
   bool chunked = false;
   int nck = 0;
+  int row_tiles = 0;                    // packed-rows kernel: tiles over all requests
   PlanItems plan;
   std::vector<int32_t> blob;
   BlobLayout lay;
@@ -1090,9 +1096,26 @@ int check_pointer_args(const void* q, const void* k_suffix, const void* v_suffix
   return CALVO_OK;
 }
 
+// Pieces per tile.  The decision (a replay of the launch, attn_plan.cpp) depends only on the batch's
+// lengths and is kept for the following layers.
+int kept_pieces(calvo_ctx* c, int variant, const calvo_request* reqs, int n_reqs, const std::vector<PlanTile>& tiles,
+                const PlanParams& pp, int64_t max_slots) {
+  if (c->force_splits) return plan_pieces(tiles, pp);
+  std::vector<int64_t> key;
+  key.reserve(2 * n_reqs + 1);
+  key.push_back(variant);
+  for (int r = 0; r < n_reqs; r++) { key.push_back(reqs[r].n_prefix_blocks); key.push_back(reqs[r].suffix_len); }
+  if (key != c->plan_key) {
+    c->plan_want = plan_pieces(tiles, pp, max_slots);
+    c->plan_key = key;
+  }
+  return c->plan_want;
+}
+
 // cb > 0: the layer was loaded in nck chunks of cb block indices and attention follows the chunks.
+// compact: a packed-rows launch without work items (uncut tiles): the smallest descriptors.
 void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const int32_t* cu_suffix, int total, int cb,
-                    int nck, AttnPlan& ap) {
+                    int nck, AttnPlan& ap, bool compact = false) {
   const calvo_config& cf = c->cfg;
   ap.n_reqs = n_reqs;
   ap.total = total;
@@ -1115,25 +1138,24 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
     if (ap.chunked) {
       ap.plan = plan_items_chunked(tiles, pblocks.data(), cb, nck);
     } else {
-      // the decision (a replay of the launch, attn_plan.cpp) depends only on the batch's lengths and
-      // is kept for the following layers
-      std::vector<int64_t> key;
-      key.reserve(2 * n_reqs + 1);
-      key.push_back(ap.variant);
-      for (int r = 0; r < n_reqs; r++) { key.push_back(reqs[r].n_prefix_blocks); key.push_back(reqs[r].suffix_len); }
-      int want = 1;
-      if (!c->force_splits && key == c->plan_key) want = c->plan_want;
-      else {
-        want = plan_pieces(tiles, pp);
-        if (!c->force_splits) { c->plan_key = key; c->plan_want = want; }
-      }
-      ap.plan = plan_items(tiles, want, pp);
+      ap.plan = plan_items(tiles, kept_pieces(c, ap.variant, reqs, n_reqs, tiles, pp, INT64_MAX), pp);
+    }
+  } else {
+    const RowsShape shape = attn_rows_shape(cf.dtype == CALVO_F32, cf.head_dim);
+    const std::vector<PlanTile> tiles = plan_row_tiles(pblocks.data(), slens.data(), n_reqs, cf.n_q_heads / cf.n_kv_heads, shape.tile_rows);
+    ap.row_tiles = (int)tiles.size();
+    if (!compact) {
+      const PlanParams pp = rows_plan_params(shape, cf.n_kv_heads, c->n_cus, c->force_splits);
+      ap.plan = plan_items(tiles, kept_pieces(c, ap.variant, reqs, n_reqs, tiles, pp, kStaticPartSlots), pp);
+      if (ap.plan.items.size() * (size_t)cf.n_kv_heads > kStaticPartSlots && !ap.plan.split_tiles.empty())
+        ap.plan = plan_items(tiles, 1, pp);                // forced pieces beyond the room for partial results
     }
   }
-  ap.lay = build_descriptor_blob(c, reqs, n_reqs, cu_suffix, ap.plan, ap.blob);
+  ap.lay = build_descriptor_blob(c, reqs, n_reqs, cu_suffix, ap.plan, ap.mfma, ap.blob);
   ap.part_need = ap.plan.split_tiles.empty()
                      ? 0
-                     : ap.plan.items.size() * (size_t)(cf.n_q_heads / ap.HW) * (size_t)attn_mfma_waves_per_wg(ap.variant);
+                     : ap.mfma ? ap.plan.items.size() * (size_t)(cf.n_q_heads / ap.HW) * (size_t)attn_mfma_waves_per_wg(ap.variant)
+                               : ap.plan.items.size() * (size_t)cf.n_kv_heads;
 }
 
 hipError_t launch_attn(int variant, const AttnParams& p, hipStream_t stream) {
@@ -1159,7 +1181,10 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
   const ReqDesc* d_reqs = (const ReqDesc*)d_att;
   const int32_t* d_tables = d_att + ap.lay.tables_off;
 
-  if (k_suffix) {
+  // A packed-rows launch of one request takes the suffix rows along.  With several requests a cached
+  // prefix may be slots that another request of the call appends to: all rows are stored first.
+  const bool rows_append = !ap.mfma && ap.n_reqs == 1;
+  if (k_suffix && !rows_append) {
     AppendParams app{};
     app.k_suffix = k_suffix; app.v_suffix = v_suffix; app.pool_layer = pool_layer;
     app.reqs = d_reqs; app.tables = d_tables; app.n_reqs = ap.n_reqs; app.total_tokens = ap.total;
@@ -1202,8 +1227,19 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
     }
     HIP_TRY(launch_merge_splits(p, d_att + ap.lay.split_off, (int)ap.plan.split_tiles.size(), c->s_compute));
   } else {
-    p.n_items = ap.n_reqs;
-    HIP_TRY(launch_attn_simple(p, cf.dtype, ap.total, c->s_compute));
+    RowsParams rp{};
+    rp.q = q; rp.out = out; rp.pool_layer = pool_layer;
+    if (rows_append) { rp.k_suffix = k_suffix; rp.v_suffix = v_suffix; }
+    rp.reqs = d_reqs; rp.tables = d_tables;
+    const bool listed = ap.n_reqs > 1 ? !ap.plan.items.empty() : !ap.plan.split_tiles.empty();
+    rp.items = listed ? p.items : nullptr;
+    memcpy(&rp.one, ap.blob.data(), sizeof rp.one);      // the blob begins with the request descriptors
+    rp.n_reqs = ap.n_reqs; rp.n_q_heads = cf.n_q_heads; rp.n_kv_heads = cf.n_kv_heads; rp.head_dim = cf.head_dim;
+    rp.group = (uint32_t)(cf.n_q_heads / cf.n_kv_heads);
+    rp.scale = p.scale;
+    rp.part_o = part_o; rp.part_ml = part_ml;
+    HIP_TRY(launch_attn_rows(rp, cf.dtype, listed ? (int)ap.plan.items.size() : ap.row_tiles,
+                             d_att + ap.lay.split_off, (int)ap.plan.split_tiles.size(), c->s_compute));
   }
   HIP_TRY(hipEventRecord(c->ev_t1[layer], c->s_compute));
   c->timed[layer] = 1;
@@ -1316,6 +1352,7 @@ int calvo::host::prefill_attn_impl(calvo_ctx* c, int layer, const void* q, const
   int32_t* d_att = c->d_att;
   float *part_o = c->part_o, *part_ml = c->part_ml;
   if (use_static) {
+    if (!ap.mfma && blob.size() > kStaticBlobInts) make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, ap, true);
     // fixed capacity, no allocation: the array is shared by every call on this GPU, so its
     // descriptors are uploaded on every call (another context may have used it in between)
     if (blob.size() > kStaticBlobInts)

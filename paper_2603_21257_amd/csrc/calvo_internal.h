@@ -56,7 +56,30 @@ hipError_t launch_scatter_blocks(const void* src, void* pool_layer, const int32_
 hipError_t launch_suffix_append(const AppendParams& p, hipStream_t stream);
 // test hook: occupies `stream` for about us microseconds (bounded), see kernels_ingest.hip
 hipError_t launch_delay(int us, hipStream_t stream);
-hipError_t launch_attn_simple(const AttnParams& p, int dtype, int total_tokens, hipStream_t stream);
+
+// The packed-rows kernel (attn_rows.hip): fp32 pools and head widths other than 128.
+struct RowsParams {
+  const void* q;
+  const void* k_suffix;     // suffix K and V are read from here and stored to the pool by the launch ...
+  const void* v_suffix;     // ... or NULL: they are in the pool already
+  void* out;
+  void* pool_layer;
+  const ReqDesc* reqs;      // read if n_reqs > 1 ...
+  ReqDesc one;              // ... the request of a batch of one: no descriptor load in front of the block table
+  const WorkItem* items;    // NULL: uncut tiles, found by counting through the requests
+  const int32_t* tables;
+  int32_t n_reqs;
+  int32_t n_q_heads, n_kv_heads, head_dim;
+  uint32_t group;           // query heads per KV head
+  float scale;
+  // partial results of cut tiles: per work item and KV head [rows][padded head_dim] in part_o, [rows][2] in part_ml
+  float* part_o;
+  float* part_ml;
+};
+// raises the kernel's dynamic LDS limit; once per device and shape, before the first launch
+hipError_t attn_rows_prepare(int dtype, int head_dim);
+hipError_t launch_attn_rows(const RowsParams& p, int dtype, int n_items, const int32_t* split_tiles, int n_split_tiles,
+                            hipStream_t stream);
 // The pipelined bf16 / head-dim-128 kernels (attn_pipeline.h).  The *_prepare calls raise the
 // kernels' dynamic LDS limit; once per device, before the first launch.
 hipError_t attn_pipe_prepare();
