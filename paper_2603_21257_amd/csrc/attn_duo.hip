@@ -12,6 +12,7 @@ using Cfg = PipeCfg<4, 4>;
 
 __global__ void __launch_bounds__(256, 2) __attribute__((amdgpu_num_vgpr(120))) attn_duo_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  clock_begin(p.clock);
   attn_pipeline<Cfg>(p, smem);
 }
 

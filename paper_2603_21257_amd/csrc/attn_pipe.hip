@@ -15,6 +15,7 @@ using Cfg = PipeCfg<8, 8>;
 // moving while attention occupies every CU.
 __global__ void __launch_bounds__(512, 2) __attribute__((amdgpu_num_vgpr(120))) attn_pipe_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  clock_begin(p.clock);
   attn_pipeline<Cfg>(p, smem);
 }
 
@@ -111,6 +112,7 @@ __global__ void __launch_bounds__(256) merge_splits_kernel(AttnParams p, const i
     w[1] = (__bf16)(acc[r][1] * inv);
     *(unsigned int*)(out + (int64_t)r * p.n_q_heads * kD) = __builtin_bit_cast(unsigned int, w);
   }
+  if (threadIdx.x == 0) clock_end_tail(p.clock.words);
 }
 
 }  // namespace pipe

@@ -213,7 +213,7 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
 #pragma unroll
     for (int h = 0; h < NI; h++) {
       const bool live = (jb + j) * kSK + wblk * 16 + brow0 + 4 * h < ctx_len;
-      const unsigned l_k = dma_lds + (j & RM) * kSlot + h * 1024;
+      const unsigned l_k = __builtin_amdgcn_readfirstlane(dma_lds + (j & RM) * kSlot + h * 1024);
       if (live) {
         dma_1k(pool + boff + h * rows4, h ? voff_k ^ 64u : voff_k, l_k);
         dma_1k(pool + boff + half_b + h * rows4, h ? voff_v ^ 128u : voff_v, l_k + kVBase);
@@ -556,6 +556,12 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
     if (j1 < n_sub) __syncthreads();      // the next group overwrites these slots
   }
 
+  // What the end of the kernel needs of its arguments is loaded again here: held in scalar registers through the
+  // loop, which has none to spare, it would be spilled.
+  typedef const __attribute__((address_space(4))) AttnParams* const_paramsp;
+  const_paramsp pe = (const_paramsp)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(pe));
+
   // ---- one piece of a split tile: leave the unnormalised O, the reference (exponent units) and
   // the row sum for merge_splits_kernel (32 rows x 128 floats per wave, row = 16qb + c).  Lane holds
   // d = 16db + 4g + r of the query rows 16qb + c.
@@ -566,23 +572,24 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
       for (int qb = 0; qb < 2; qb++) {
         const float lt = quad_sum(l_run[qb]);
         if (wq0 + 16 * qb + c < S) {
-          float* po = p.part_o + (slot * 32 + 16 * qb + c) * kD + 4 * g;
+          float* po = pe->part_o + (slot * 32 + 16 * qb + c) * kD + 4 * g;
 #pragma unroll
           for (int db = 0; db < 8; db++) *(f32x4*)(po + 16 * db) = o[db][qb];
           if (g == 0) {
-            float* pm = p.part_ml + (slot * 32 + 16 * qb + c) * 2;
+            float* pm = pe->part_ml + (slot * 32 + 16 * qb + c) * 2;
             pm[0] = m_run[qb];
             pm[1] = lt;
           }
         }
       }
     }
+    if (threadIdx.x == 0) clock_end(pe->clock.words);
     return;
   }
 
   // ---- normalise and write O[token][head][d]; lane holds d = 16db + 4g + r of the rows 16qb + c
   if (wave_active) {
-    unsigned short* out = (unsigned short*)p.out;
+    unsigned short* out = (unsigned short*)pe->out;
 #pragma unroll
     for (int qb = 0; qb < 2; qb++) {
       const float lt = quad_sum(l_run[qb]);
@@ -603,6 +610,7 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
       }
     }
   }
+  if (threadIdx.x == 0) clock_end(pe->clock.words);
 }
 
 }  // namespace attn

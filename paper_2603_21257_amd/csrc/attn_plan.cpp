@@ -82,7 +82,7 @@ int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t
   double best = 0;
   std::vector<int64_t> heap;
   for (int n : cands) {
-    if (n > 1 && wgs * n > 16 * (int64_t)p.wg_slots) break;
+    if (n > 1 && wgs * n > (p.step_cost ? 4 : 16) * (int64_t)p.wg_slots) break;
     heap.assign((size_t)p.wg_slots, 0);            // min-heap of the times at which workgroup slots become free
     auto cmp = std::greater<int64_t>();
     bool cut = false;

@@ -80,6 +80,7 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  clock_begin(p.clock);
   const int c = lane & 15, g = lane >> 4;
   const int Hkv = p.n_kv_heads, Hq = p.n_q_heads, D = p.head_dim;
   const unsigned G = p.group;
@@ -561,6 +562,7 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
           }
         }
       }
+  if (threadIdx.x == 0) clock_end(p.clock.words);
 }
 
 // Combines the pieces of cut tiles as merge_splits_kernel does, for this file's layout: one wave per row.
@@ -614,6 +616,7 @@ __global__ void __launch_bounds__(256) merge_rows_kernel(RowsParams p, const int
       }
     }
   }
+  if (threadIdx.x == 0) clock_end_tail(p.clock.words);
   const int d = W * lane;
   if (d >= D) return;
   const float inv = 1.f / l;

@@ -101,8 +101,7 @@ void destroy_partial(calvo_ctx* c) {
   for (auto e : c->ev_layer) if (e) (void)hipEventDestroy(e);
   for (auto& v : c->ev_chunk)
     for (auto e : v) if (e) (void)hipEventDestroy(e);
-  for (auto e : c->ev_t0) if (e) (void)hipEventDestroy(e);
-  for (auto e : c->ev_t1) if (e) (void)hipEventDestroy(e);
+  if (c->d_clock) (void)hipFree(c->d_clock);
   for (void* p : c->l2_ring)
     if (p) (void)hipHostFree(p);
   for (auto e : c->ev_l2_free) if (e) (void)hipEventDestroy(e);
@@ -549,8 +548,6 @@ int calvo_create(const calvo_config* cfg, calvo_ctx** out) {
     CREATE_TRY(hipEventCreateWithFlags(&c->ev_free[i], hipEventDisableTiming));
   }
   c->ev_layer.assign(cfg->n_layers, nullptr);
-  c->ev_t0.assign(cfg->n_layers, nullptr);
-  c->ev_t1.assign(cfg->n_layers, nullptr);
   c->layer_issued.assign(cfg->n_layers, 0);
   c->chunk_blocks.assign(cfg->n_layers, 0);
   c->n_chunks.assign(cfg->n_layers, 0);
@@ -562,9 +559,9 @@ int calvo_create(const calvo_config* cfg, calvo_ctx** out) {
   c->last_wgs.assign(cfg->n_layers, 0);
   for (int l = 0; l < cfg->n_layers; l++) {
     CREATE_TRY(hipEventCreateWithFlags(&c->ev_layer[l], hipEventDisableTiming));
-    CREATE_TRY(hipEventCreate(&c->ev_t0[l]));
-    CREATE_TRY(hipEventCreate(&c->ev_t1[l]));
   }
+  CREATE_TRY(hipMalloc((void**)&c->d_clock, (size_t)cfg->n_layers * kClockWords * sizeof(unsigned long long)));
+  CREATE_TRY(hipMemset(c->d_clock, 0, (size_t)cfg->n_layers * kClockWords * sizeof(unsigned long long)));
   CREATE_TRY(hipEventCreateWithFlags(&c->ev_tab_ing, hipEventDisableTiming));
   for (auto& e : c->ev_att) CREATE_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   for (auto& e : c->ev_static) CREATE_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -1200,7 +1197,7 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
   p.heads_per_wg = ap.HW; p.tile_tokens = ap.tile_tokens;
   p.waves_per_wg = attn_mfma_waves_per_wg(ap.variant);
   p.scale = scale > 0.f ? scale : 1.0f / sqrtf((float)cf.head_dim);
-  HIP_TRY(hipEventRecord(c->ev_t0[layer], c->s_compute));
+  p.clock = {c->d_clock + kClockWords * (size_t)layer, 1};
   if (ap.mfma) {
     p.part_o = part_o;
     p.part_ml = part_ml;
@@ -1219,6 +1216,7 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
         p.n_items = (int32_t)groups[g].size();
         p.item_index = d_att + ap.lay.group_off[g];
         HIP_TRY(launch_attn(ap.variant, p, c->s_compute));
+        p.clock.starts = 0;
       }
       p.item_index = nullptr;
     } else {
@@ -1238,10 +1236,10 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
     rp.group = (uint32_t)(cf.n_q_heads / cf.n_kv_heads);
     rp.scale = p.scale;
     rp.part_o = part_o; rp.part_ml = part_ml;
+    rp.clock = p.clock;
     HIP_TRY(launch_attn_rows(rp, cf.dtype, listed ? (int)ap.plan.items.size() : ap.row_tiles,
                              d_att + ap.lay.split_off, (int)ap.plan.split_tiles.size(), c->s_compute));
   }
-  HIP_TRY(hipEventRecord(c->ev_t1[layer], c->s_compute));
   c->timed[layer] = 1;
   c->last_variant[layer] = ap.mfma ? ap.variant : -1;
   c->last_wgs[layer] = ap.mfma ? (int32_t)(ap.plan.items.size() * (size_t)(cf.n_q_heads / ap.HW)) : 0;
@@ -1515,8 +1513,11 @@ int calvo_attn_kernel_ms(calvo_ctx* c, int layer, float* ms) {
   if (!c || !ms) return fail(CALVO_EINVAL, "NULL argument");
   if (layer < 0 || layer >= c->cfg.n_layers) return fail(CALVO_EINVAL, "layer %d outside [0, %d)", layer, c->cfg.n_layers);
   if (!c->timed[layer]) return fail(CALVO_ENOTREADY, "no attention kernel was queued for layer %d", layer);
-  HIP_TRY(hipEventSynchronize(c->ev_t1[layer]));
-  HIP_TRY(hipEventElapsedTime(ms, c->ev_t0[layer], c->ev_t1[layer]));
+  unsigned long long t[kClockWords], end = 0;
+  HIP_TRY(hipStreamSynchronize(c->s_compute));
+  HIP_TRY(hipMemcpy(t, c->d_clock + kClockWords * (size_t)layer, sizeof t, hipMemcpyDeviceToHost));
+  for (int i = 1; i <= kClockEnds; i++) end = std::max(end, t[i * kClockStride]);
+  *ms = end > t[0] ? (float)((double)(end - t[0]) * 1e-5) : 0.f;        // 100 MHz ticks
   return CALVO_OK;
 }
 

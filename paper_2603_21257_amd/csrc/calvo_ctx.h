@@ -52,7 +52,7 @@ struct calvo_ctx {
   int att_cur = 0;
   hipEvent_t ev_att[kShadows] = {nullptr, nullptr, nullptr, nullptr};
   bool att_pending[kShadows] = {false, false, false, false};
-  std::vector<hipEvent_t> ev_t0, ev_t1;
+  unsigned long long* d_clock = nullptr;         // per layer: start and end of its most recent attention launch (LaunchClock)
   std::vector<char> timed;
   std::vector<int32_t> last_variant, last_wgs;   // per layer: attention kernel chosen, workgroups launched
   int scatter_grid = 64;

@@ -17,6 +17,29 @@ struct ReqDesc {
 };
 
 
+// When an attention launch ran, in ticks of the constant 100 MHz counter, in device memory per layer: the
+// first workgroup stores the start, every workgroup raises an end (the counter only grows, so the words need
+// no reset between launches).  A pair of timing events around the launch costs 8 us of host time and two
+// barrier packets per call, more than the launch itself (2.5 us).  The ends are kept in sixteen words a cache
+// line apart: on a single word 2048 workgroups that finish together queue up for 18 us.
+constexpr int kClockEnds = 16, kClockStride = 16;                              // words; stride in 8-byte words
+constexpr int kClockWords = (1 + kClockEnds) * kClockStride;                   // per layer: the start's line, then the ends
+struct LaunchClock {
+  unsigned long long* words;
+  int32_t starts;           // this launch is the first of its call
+};
+__device__ inline void clock_begin(const LaunchClock& k) {
+  // a scalar branch: all lanes of the first wave store the same value
+  if (k.starts && blockIdx.x == 0 && __builtin_amdgcn_readfirstlane(threadIdx.x) == 0) k.words[0] = wall_clock64();
+}
+__device__ inline void clock_end(unsigned long long* words) {
+  atomicMax(words + (1 + blockIdx.x % kClockEnds) * kClockStride, (unsigned long long)wall_clock64());
+}
+// for launches of many short workgroups: the last ones to be dispatched stand for all
+__device__ inline void clock_end_tail(unsigned long long* words) {
+  if (blockIdx.x + 256 >= gridDim.x) clock_end(words);
+}
+
 struct AttnParams {
   const void* q;
   void* out;
@@ -37,6 +60,7 @@ struct AttnParams {
   // part_ml [32 rows][2] = (softmax reference in exponent units, i.e. score * scale * log2 e, row sum)
   float* part_o;
   float* part_ml;
+  LaunchClock clock;
 };
 
 struct AppendParams {
@@ -75,6 +99,7 @@ struct RowsParams {
   // partial results of cut tiles: per work item and KV head [rows][padded head_dim] in part_o, [rows][2] in part_ml
   float* part_o;
   float* part_ml;
+  LaunchClock clock;
 };
 // raises the kernel's dynamic LDS limit; once per device and shape, before the first launch
 hipError_t attn_rows_prepare(int dtype, int head_dim);

@@ -1,0 +1,45 @@
+"""calvo_attn_kernel_ms: the kernels' own clock, for every kernel and for launches that are merged or follow chunks."""
+import time
+
+import pytest
+import torch
+
+from paper_2603_21257_amd import binding as cb
+from paper_2603_21257_amd import workload as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _give_memory_back():
+    yield
+    torch.cuda.empty_cache()          # other files count on large tensors being allocations of their own
+
+
+@pytest.mark.parametrize("hq,D,dtype,P,S", [(8, 64, "f32", 1024, 40), (8, 64, "bf16", 4096, 3), (8, 128, "bf16", 16384, 8),
+                                            (8, 128, "bf16", 4096, 1024), (10, 128, "bf16", 32768, 200)])
+def test_duration_of_the_latest_launch(hq, D, dtype, P, S):
+    s = wl.Shape(2, hq, 2, D, dtype, (P + S) // 16 + 8)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    mk = lambda *shape: torch.randn(shape, device="cuda:0").to(dt)
+    pool, q, ks, vs = mk(2, s.pool_blocks, s.blk_elems), mk(S, hq, D), mk(S, 2, D), mk(S, 2, D)
+    out = torch.empty_like(q)
+    r = wl.single_request(s, P, S, 5)[0]
+    torch.cuda.synchronize()
+    ctx = cb.calvo_create(2, hq, 2, D, cb.CALVO_BF16 if dtype == "bf16" else cb.CALVO_F32, s.pool_blocks, pool)
+    try:
+        req = cb.make_request(None, 0, r.table, r.n_prefix_blocks, S, r.n_prefix_blocks)
+        with pytest.raises(cb.CalvoError) as ei:
+            cb.calvo_attn_kernel_ms(ctx, 1)
+        assert ei.value.code == cb.CALVO_ENOTREADY
+        for _ in range(5):
+            t = time.perf_counter()
+            cb.calvo_prefill_attn(ctx, 1, q, ks, vs, out, [req], [0, S])
+            ms = cb.calvo_attn_kernel_ms(ctx, 1)
+            wall = (time.perf_counter() - t) * 1e3
+            assert 0 < ms < wall                     # inside the call's own wall time, also on repetition
+            assert ms < 50
+        with pytest.raises(cb.CalvoError):
+            cb.calvo_attn_kernel_ms(ctx, 0)          # nothing was queued for that layer
+    finally:
+        cb.calvo_destroy(ctx)
