@@ -37,7 +37,7 @@
  * Environment (for tests and tuning; results stay within the stated tolerance
  * whatever they are set to).  Read by calvo_create: CALVO_ATTN_SPLITS = n
  * cuts every attention tile's context into n pieces; CALVO_SPLIT_MIN,
- * CALVO_SPLIT_FILL = parameters of the automatic cut (shortest piece, cost of
+ * CALVO_SPLIT_FILL = parameters of the automatic cut (shortest piece of a long tile, cost of
  * a workgroup's start and end, both in 32-key steps); CALVO_SCATTER_GRID =
  * workgroups of the zero-copy scatter; CALVO_MERGE_MIB = most bytes of
  * consecutive small layers that one transfer carries (default 256, 0 = every
@@ -494,7 +494,8 @@ int calvo_ingest_plan(const calvo_request* reqs, int32_t n_reqs, int32_t layer_b
  * dim 128 batch with these lengths on a device with n_cus compute units.  prefix_blocks / suffix_lens:
  * HOST arrays of n_reqs.  Outputs (any may be NULL): *kernel as in calvo_attn_kernel_info,
  * *tile_tokens = suffix tokens per work item, *pieces = split-KV pieces a tile's context is cut into at
- * most (1 = no cut; pieces are never shorter than 48 sub-tiles of 32 keys), *n_workgroups of the
+ * most (1 = no cut; pieces are never shorter than a 32nd of the tile, at least 8 and at most 48
+ * sub-tiles of 32 keys), *n_workgroups of the
  * launch.  The choice replays the launch on the device's workgroup slots and cuts tiles when that
  * shortens it: too few tiles for the chip (the paper's requests: long contexts with short queries), or a
  * workgroup count just above a whole number of rounds.  CALVO_EINVAL for bad arguments. */

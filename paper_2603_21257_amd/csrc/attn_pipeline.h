@@ -204,8 +204,10 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
     dma_1k(pool + half_b + off, voff_v, dma_lds + kVBase + slot * kSlot);
     if constexpr (NI == 2) dma_1k(pool + half_b + off + rows4, voff_v ^ 128u, dma_lds + kVBase + slot * kSlot + 1024);
   };
-  auto request_k = [&](int j) { request_k_at(fetch_off(j), j & RM); };
-  auto request_v = [&](int j) { request_v_at(fetch_off(j), j & RM); };
+  // fill and drain: what lies past the piece is not fetched - the last sub-tile's blocks once more (they are in
+  // the caches), so that the number of requests in flight stays what the waits count on
+  auto request_k = [&](int j) { request_k_at(fetch_off(min(j, n_sub - 1)), j & RM); };
+  auto request_v = [&](int j) { request_v_at(fetch_off(min(j, n_sub - 1)), j & RM); };
   // synchronous variant for the sub-tiles at the end: rows past the context are not fetched,
   // their V is written as zeros so that undefined pool bytes cannot reach the PV product
   auto request_tail = [&](int j) {

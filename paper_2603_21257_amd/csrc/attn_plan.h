@@ -28,9 +28,10 @@ struct PlanTile {
 struct PlanParams {
   int n_head_groups;  // workgroups per work item
   int wg_slots;       // workgroups resident on the device at a time
-  int split_min;      // shortest piece of a cut tile, in sub-tiles
+  int split_min;      // shortest piece of a long tile, in sub-tiles (plan_piece_len scales it down for short ones)
   int split_fill;     // cost of a workgroup's pipeline fill and drain, in sub-tile steps
   int force_splits;   // > 0: cut every tile into this many pieces (test knob)
+  bool long_pieces = false;   // never below split_min: the fewest partial results
   int step_cost = 0;  // packed-rows kernel: cost of a wave's 32-key step, in units of split_fill; else 0
 };
 
@@ -59,14 +60,15 @@ struct PlanItems {
 // the batch's tiles of tile_tokens suffix tokens, heaviest first
 std::vector<PlanTile> plan_tiles(const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int tile_tokens);
 
-// length of the pieces a tile of n_sub sub-tiles is cut into when `want` pieces are asked for
-int plan_piece_len(int n_sub, int want, const PlanParams& p);
+// length of the pieces a tile of n_sub sub-tiles is cut into when `want` pieces are asked for of the
+// longest tile, which has n_max
+int plan_piece_len(int n_sub, int n_max, int want, const PlanParams& p);
 
-// pieces per tile to ask for (1 = no cut), from a replay of the launch; packed rows: at most max_slots
+// pieces of the longest tile to ask for (1 = no cut), from a replay of the launch; packed rows: at most max_slots
 // (piece, head group) pairs (partial results there is room for)
 int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots = INT64_MAX);
 
-// work items of a whole-layer launch: every tile cut into pieces of plan_piece_len(n_sub, want)
+// work items of a whole-layer launch: every tile cut into pieces of plan_piece_len
 PlanItems plan_items(const std::vector<PlanTile>& tiles, int want, const PlanParams& p);
 
 // Tiling of the packed-rows kernel (attn_rows.hip): (token, head) rows of one KV head per work item, and what a

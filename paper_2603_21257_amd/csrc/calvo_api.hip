@@ -1110,9 +1110,10 @@ int kept_pieces(calvo_ctx* c, int variant, const calvo_request* reqs, int n_reqs
 }
 
 // cb > 0: the layer was loaded in nck chunks of cb block indices and attention follows the chunks.
-// compact: a packed-rows launch without work items (uncut tiles): the smallest descriptors.
+// small: what needs the least room for descriptors and partial results - a packed-rows launch without work
+// items (uncut tiles), the long pieces only of the others.
 void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const int32_t* cu_suffix, int total, int cb,
-                    int nck, AttnPlan& ap, bool compact = false) {
+                    int nck, AttnPlan& ap, bool small = false) {
   const calvo_config& cf = c->cfg;
   ap.n_reqs = n_reqs;
   ap.total = total;
@@ -1131,17 +1132,17 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
   if (ap.mfma) {
     const std::vector<PlanTile> tiles = plan_tiles(pblocks.data(), slens.data(), n_reqs, ap.tile_tokens);
     const PlanParams pp{cf.n_q_heads / ap.HW, c->n_cus * (8 / attn_mfma_waves_per_wg(ap.variant)), c->split_min, c->split_fill,
-                        c->force_splits};
+                        c->force_splits, small};
     if (ap.chunked) {
       ap.plan = plan_items_chunked(tiles, pblocks.data(), cb, nck);
     } else {
-      ap.plan = plan_items(tiles, kept_pieces(c, ap.variant, reqs, n_reqs, tiles, pp, INT64_MAX), pp);
+      ap.plan = plan_items(tiles, kept_pieces(c, ap.variant + (small ? 16 : 0), reqs, n_reqs, tiles, pp, INT64_MAX), pp);
     }
   } else {
     const RowsShape shape = attn_rows_shape(cf.dtype == CALVO_F32, cf.head_dim);
     const std::vector<PlanTile> tiles = plan_row_tiles(pblocks.data(), slens.data(), n_reqs, cf.n_q_heads / cf.n_kv_heads, shape.tile_rows);
     ap.row_tiles = (int)tiles.size();
-    if (!compact) {
+    if (!small) {
       const PlanParams pp = rows_plan_params(shape, cf.n_kv_heads, c->n_cus, c->force_splits);
       ap.plan = plan_items(tiles, kept_pieces(c, ap.variant, reqs, n_reqs, tiles, pp, kStaticPartSlots), pp);
       if (ap.plan.items.size() * (size_t)cf.n_kv_heads > kStaticPartSlots && !ap.plan.split_tiles.empty())
@@ -1350,7 +1351,7 @@ int calvo::host::prefill_attn_impl(calvo_ctx* c, int layer, const void* q, const
   int32_t* d_att = c->d_att;
   float *part_o = c->part_o, *part_ml = c->part_ml;
   if (use_static) {
-    if (!ap.mfma && blob.size() > kStaticBlobInts) make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, ap, true);
+    if (blob.size() > kStaticBlobInts || ap.part_need > kStaticPartSlots) make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, ap, true);
     // fixed capacity, no allocation: the array is shared by every call on this GPU, so its
     // descriptors are uploaded on every call (another context may have used it in between)
     if (blob.size() > kStaticBlobInts)
