@@ -84,25 +84,36 @@ int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t
   if (p.force_splits) return p.force_splits;
   const int64_t wgs = (int64_t)tiles.size() * p.n_head_groups;
   if (wgs <= 0 || wgs > 16 * (int64_t)p.wg_slots) return 1;     // many rounds: the last one hardly matters
-  const int cands[] = {1, 2, 3, 4, 5, 6, 8, 12, 16, 24, 32, 48, 64};
+  const int cands[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 20, 24, 32, 48, 64};
   const int n_max = tiles.front().n_sub;           // heaviest first
   int want = 1;
   double best = 0;
   std::vector<int64_t> heap;
   for (int n : cands) {
     if (n > 1 && wgs * n > (p.step_cost ? 4 : 16) * (int64_t)p.wg_slots) break;
-    heap.assign((size_t)p.wg_slots, 0);            // min-heap of the times at which workgroup slots become free
-    auto cmp = std::greater<int64_t>();
+    auto cost_of = [&](int64_t subs) { return (p.step_cost ? (subs + 3) / 4 * p.step_cost : subs) + p.split_fill; };
     bool cut = false;
-    int64_t end = 0, slots = 0;
+    int64_t end = 0, slots = 0, work = 0;
     for (const PlanTile& t : tiles) {
       const int len = plan_piece_len(t.n_sub, n_max, n, p);
       const int np = (t.n_sub + len - 1) / len;
       cut |= np > 1;
       slots += (int64_t)np * p.n_head_groups;
+      work += ((np - 1) * cost_of(len) + cost_of(t.n_sub - (np - 1) * len)) * p.n_head_groups;
+    }
+    if (n > 1 && slots > max_slots) break;
+    // no order of the pieces beats the average load: most candidates need no replay
+    if (n > 1 && (double)(work / p.wg_slots) + (cut ? p.split_fill : 0) >= best * 0.98) {
+      if (!cut) break;
+      continue;
+    }
+    heap.assign((size_t)p.wg_slots, 0);            // min-heap of the times at which workgroup slots become free
+    auto cmp = std::greater<int64_t>();
+    for (const PlanTile& t : tiles) {
+      const int len = plan_piece_len(t.n_sub, n_max, n, p);
+      const int np = (t.n_sub + len - 1) / len;
       for (int k = 0; k < np; k++) {
-        const int64_t subs = std::min(t.n_sub, (k + 1) * len) - k * len;
-        const int64_t cost = (p.step_cost ? (subs + 3) / 4 * p.step_cost : subs) + p.split_fill;
+        const int64_t cost = cost_of(std::min(t.n_sub, (k + 1) * len) - k * len);
         for (int h = 0; h < p.n_head_groups; h++) {
           std::pop_heap(heap.begin(), heap.end(), cmp);
           heap.back() += cost;
@@ -111,7 +122,6 @@ int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t
         }
       }
     }
-    if (n > 1 && slots > max_slots) break;
     const double span = (double)end + (cut ? p.split_fill : 0);
     if (n == 1 || span < best * 0.98) {            // a cut has to win by 2 % over what is chosen so far
       best = span;
