@@ -69,6 +69,12 @@ __device__ inline void dma_1k(const unsigned char* sbase, unsigned voff, unsigne
                :
                : "v"(voff), "s"(sbase), "s"(lds_addr));
 }
+// a wave-uniform address that the compiler keeps in vector registers, back in scalar ones
+__device__ inline const unsigned char* scalar_ptr(const unsigned char* p) {
+  const unsigned long long x = (unsigned long long)p;
+  return (const unsigned char*)((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)x) |
+                                (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32);
+}
 // compiler-level fence for one value: it is 'rewritten' here, so its producers stay above this
 // point and its consumers below it; emits no instruction
 template <typename T>

@@ -208,22 +208,6 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
   // the caches), so that the number of requests in flight stays what the waits count on
   auto request_k = [&](int j) { request_k_at(fetch_off(min(j, n_sub - 1)), j & RM); };
   auto request_v = [&](int j) { request_v_at(fetch_off(min(j, n_sub - 1)), j & RM); };
-  // synchronous variant for the sub-tiles at the end: rows past the context are not fetched,
-  // their V is written as zeros so that undefined pool bytes cannot reach the PV product
-  auto request_tail = [&](int j) {
-    const int64_t boff = fetch_off(j);
-#pragma unroll
-    for (int h = 0; h < NI; h++) {
-      const bool live = (jb + j) * kSK + wblk * 16 + brow0 + 4 * h < ctx_len;
-      const unsigned l_k = __builtin_amdgcn_readfirstlane(dma_lds + (j & RM) * kSlot + h * 1024);
-      if (live) {
-        dma_1k(pool + boff + h * rows4, h ? voff_k ^ 64u : voff_k, l_k);
-        dma_1k(pool + boff + half_b + h * rows4, h ? voff_v ^ 128u : voff_v, l_k + kVBase);
-      } else {
-        *(u32x4*)(smem + (l_k - lds0) + kVBase + (lane << 4)) = (u32x4){0u, 0u, 0u, 0u};
-      }
-    }
-  };
 
   // ---- lane-constant operand addresses inside a slot
   // K operand (kb, ks): key row 16kb + c, logical chunk 4ks + g (d = 32ks + 8g .. +8); the key block
@@ -522,11 +506,43 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
     ahead_sm = false;
   }
 
+  // What the end of the kernel needs of its arguments is loaded again here: held in scalar registers through the
+  // loop, which has none to spare, it would be spilled.
+  typedef const __attribute__((address_space(4))) AttnParams* const_paramsp;
+  const_paramsp pe = (const_paramsp)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(pe));
+
   // ---- sub-tiles on or past the diagonal: loaded synchronously, plain path.  The ring slots are
   // written again below (by requests and, for rows past the context, by plain LDS stores), so
   // every request of the pipelined part has to have landed first.  There are at most
   // tile tokens / 32 + 1 of them, fewer than ring slots: they are requested together and computed
   // after one wait (a group of RING at a time, should there ever be more).
+  // Rows past the context are not fetched, their V is written as zeros so that undefined pool bytes cannot
+  // reach the PV product.  Suffix rows come from the caller's arrays where the launch is given them: a
+  // block of 16 keys lies wholly in the prefix or wholly in the suffix.
+  const unsigned char* ks = (const unsigned char*)pe->k_suffix;
+  const unsigned char* vs = (const unsigned char*)pe->v_suffix;
+  auto request_tail = [&](int j) {
+    const int sfx_blk = 2 * (jb + j) + wblk - P / kBlockTokens;          // block of the suffix, negative: of the prefix
+    const int64_t boff = fetch_off(j);
+    const unsigned char *kb = pool + boff, *vb = kb + half_b;
+    if (ks && sfx_blk >= 0) {
+      const int64_t soff = (int64_t)rd.q_off * (half_b / kBlockTokens) + sfx_blk * half_b;
+      kb = ks + soff;
+      vb = vs + soff;
+    }
+#pragma unroll
+    for (int h = 0; h < NI; h++) {
+      const bool live = (jb + j) * kSK + wblk * 16 + brow0 + 4 * h < ctx_len;
+      const unsigned l_k = __builtin_amdgcn_readfirstlane(dma_lds + (j & RM) * kSlot + h * 1024);
+      if (live) {
+        dma_1k(scalar_ptr(kb + h * rows4), h ? voff_k ^ 64u : voff_k, l_k);
+        dma_1k(scalar_ptr(vb + h * rows4), h ? voff_v ^ 128u : voff_v, l_k + kVBase);
+      } else {
+        *(u32x4*)(smem + (l_k - lds0) + kVBase + (lane << 4)) = (u32x4){0u, 0u, 0u, 0u};
+      }
+    }
+  };
   wait_vm<0>();
   __syncthreads();
   for (int j0 = n_pipe; j0 < n_sub; j0 += RING) {
@@ -558,11 +574,20 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
     if (j1 < n_sub) __syncthreads();      // the next group overwrites these slots
   }
 
-  // What the end of the kernel needs of its arguments is loaded again here: held in scalar registers through the
-  // loop, which has none to spare, it would be spilled.
-  typedef const __attribute__((address_space(4))) AttnParams* const_paramsp;
-  const_paramsp pe = (const_paramsp)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(pe));
+  // ---- suffix rows -> pool: by the workgroup that has the end of the context, once per KV head
+  if (ks && wi.sub_end * kSK >= ctx_len && hg * HW % (Hq / Hkv) == 0) {
+    unsigned char* wpool = (unsigned char*)const_cast<void*>(pe->pool_layer);
+    const int32_t* table = pe->tables + rd.table_off;
+    const int64_t rs = half_b / kBlockTokens;                            // bytes between token rows
+    for (int i = tid; i < S * (kRow / 16); i += 64 * NW) {
+      const int tok = i / (kRow / 16), pos = P + tok;
+      const int64_t in_row = kv * kRow + (i % (kRow / 16)) * 16;
+      const int64_t src = (int64_t)(rd.q_off + tok) * rs + in_row;
+      const int64_t dst = (int64_t)table[pos / kBlockTokens] * (2 * half_b) + (int64_t)(pos % kBlockTokens) * rs + in_row;
+      *(u32x4*)(wpool + dst) = *(const u32x4*)(ks + src);
+      *(u32x4*)(wpool + dst + half_b) = *(const u32x4*)(vs + src);
+    }
+  }
 
   // ---- one piece of a split tile: leave the unnormalised O, the reference (exponent units) and
   // the row sum for merge_splits_kernel (32 rows x 128 floats per wave, row = 16qb + c).  Lane holds

@@ -1182,7 +1182,9 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
   // A packed-rows launch of one request takes the suffix rows along.  With several requests a cached
   // prefix may be slots that another request of the call appends to: all rows are stored first.
   const bool rows_append = !ap.mfma && ap.n_reqs == 1;
-  if (k_suffix && !rows_append) {
+  // The same for a suffix of one tile in the pipelined kernels: no other tile reads its rows.
+  const bool tile_append = ap.mfma && ap.n_reqs == 1 && !ap.chunked && ap.total <= ap.tile_tokens;
+  if (k_suffix && !rows_append && !tile_append) {
     AppendParams app{};
     app.k_suffix = k_suffix; app.v_suffix = v_suffix; app.pool_layer = pool_layer;
     app.reqs = d_reqs; app.tables = d_tables; app.n_reqs = ap.n_reqs; app.total_tokens = ap.total;
@@ -1202,6 +1204,7 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
   if (ap.mfma) {
     p.part_o = part_o;
     p.part_ml = part_ml;
+    if (tile_append) { p.k_suffix = k_suffix; p.v_suffix = v_suffix; }
     const auto& groups = ap.plan.groups;
     if (ap.chunked) {
       for (size_t g = 0; g < groups.size(); g++) {

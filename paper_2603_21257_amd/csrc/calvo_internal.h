@@ -60,6 +60,10 @@ struct AttnParams {
   // part_ml [32 rows][2] = (softmax reference in exponent units, i.e. score * scale * log2 e, row sum)
   float* part_o;
   float* part_ml;
+  // Suffix K / V of a batch of one request whose suffix is one tile, or NULL: the keys past the prefix are then
+  // read from here and stored to the pool by the launch itself (tables), no append launch in front of it.
+  const void* k_suffix;
+  const void* v_suffix;
   LaunchClock clock;
 };
 
