@@ -348,7 +348,9 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
     }
   };
 
-  for (; st < st_end; st += NW) {
+  // One step.  DIAG: some row does not see all of its keys.
+  auto step = [&](auto diag_tag) {
+    constexpr bool DIAG = decltype(diag_tag)::value != 0;
     const int k0 = st * (kBlockTokens * KB);
     f32x4 s[KB][NQB];
 #pragma unroll
@@ -380,8 +382,7 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
       load_k(st + NW);
       look_up(st + 2 * NW);                                    // clamped to the last block
     }
-    const bool diag = k0 + kBlockTokens * KB - 1 > pos_min;    // some row does not see all of these keys
-    if (diag) {
+    if constexpr (DIAG) {
 #pragma unroll
       for (int kb = 0; kb < KB; kb++)
 #pragma unroll
@@ -429,7 +430,7 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
     // A masked weight is 0, and 0 times an infinity or NaN that a later token's V may hold is NaN: such
     // a step goes key by key and adds only what each row sees.
     bool odd = false;
-    if (diag) {
+    if constexpr (DIAG) {
 #pragma unroll
       for (int kb = 0; kb < KB; kb++)
 #pragma unroll
@@ -447,7 +448,11 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
     if (!odd) pv(w);
     else pv_by_key(w, k0);
     if (more) load_v(st + NW);
-  }
+  };
+  // Two loops: the masks and the key-by-key path of the last steps cost the others registers otherwise.
+  const int st_full = min(st_end, (pos_min + 1) / (kBlockTokens * KB));
+  for (; st < st_full; st += NW) step(Tag<0>{});
+  for (; st < st_end; st += NW) step(Tag<1>{});
 
   // ---- suffix rows of the tokens whose first row lies in this tile: caller's arrays -> pool.  The first
   // chunk of every thread is on its way while the key waves are combined.
