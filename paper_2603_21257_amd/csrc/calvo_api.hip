@@ -231,7 +231,7 @@ int ensure_att_blob(calvo_ctx* c, size_t n) {
     if (c->h_att[k]) (void)hipHostFree(c->h_att[k]);
     c->h_att[k] = h[k];
   }
-  c->d_att = d; c->att_cap = cap; c->att_len = 0; c->att_cur = 0;
+  c->d_att = d; c->att_cap = cap; c->att_cur = 0;
   return CALVO_OK;
 }
 
@@ -1156,6 +1156,50 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
                                : ap.plan.items.size() * (size_t)cf.n_kv_heads;
 }
 
+// What calvo_prefill_attn works out for a batch - checks, plan, descriptor words - kept for the next call: a
+// prefill runs one batch through all its layers.  It is found again by content, every table entry compared;
+// nothing of the caller's memory is referred to.
+struct KeptBatch {
+  struct Req { int32_t n_prefix_blocks, first_ingest_block, suffix_len; int64_t n_tab; };
+  std::vector<Req> reqs;
+  std::vector<int32_t> tables, cu;
+  int cb = 0, nck = 0;
+  bool small = false, on_device = false;      // see make_attn_plan; ap.blob is what the context's device buffer holds
+  AttnPlan ap;
+
+  bool holds(const calvo_request* rq, int n_reqs, const int32_t* cu_suffix) const {
+    if (n_reqs <= 0 || (size_t)n_reqs != reqs.size() || !rq || !cu_suffix) return false;
+    size_t off = 0;
+    for (int r = 0; r < n_reqs; r++) {
+      const Req& k = reqs[(size_t)r];
+      if (rq[r].n_prefix_blocks != k.n_prefix_blocks || rq[r].first_ingest_block != k.first_ingest_block ||
+          rq[r].suffix_len != k.suffix_len)
+        return false;
+      if (k.n_tab && (!rq[r].block_table || memcmp(rq[r].block_table, tables.data() + off, (size_t)k.n_tab * 4) != 0)) return false;
+      off += (size_t)k.n_tab;
+    }
+    return memcmp(cu_suffix, cu.data(), cu.size() * 4) == 0;
+  }
+  void take(const calvo_request* rq, int n_reqs, const int32_t* cu_suffix) {
+    reqs.clear();
+    tables.clear();
+    for (int r = 0; r < n_reqs; r++) {
+      const int64_t nt = (int64_t)rq[r].n_prefix_blocks + (rq[r].suffix_len + kBlockTokens - 1) / kBlockTokens;
+      reqs.push_back({rq[r].n_prefix_blocks, rq[r].first_ingest_block, rq[r].suffix_len, nt});
+      tables.insert(tables.end(), rq[r].block_table, rq[r].block_table + nt);
+    }
+    cu.assign(cu_suffix, cu_suffix + n_reqs + 1);
+  }
+};
+
+// The kernel shape the plan was made for is still the one to take (an environment variable can force it per call).
+bool same_shape(const calvo_ctx* c, const KeptBatch& k) {
+  if (!k.ap.mfma) return true;
+  std::vector<int32_t> slens(k.reqs.size());
+  for (size_t r = 0; r < slens.size(); r++) slens[r] = k.reqs[r].suffix_len;
+  return attn_mfma_choose(slens.data(), (int)slens.size(), k.ap.HW) == k.ap.variant;
+}
+
 hipError_t launch_attn(int variant, const AttnParams& p, hipStream_t stream) {
   return variant == kAttnDuo ? launch_attn_duo(p, stream) : launch_attn_pipe(p, stream);
 }
@@ -1328,8 +1372,11 @@ int calvo::host::prefill_attn_impl(calvo_ctx* c, int layer, const void* q, const
                                    hipEvent_t ready) {
   if (!c) return fail(CALVO_EINVAL, "ctx is NULL");
   if (layer < 0 || layer >= c->cfg.n_layers) return fail(CALVO_EINVAL, "layer %d outside [0, %d)", layer, c->cfg.n_layers);
-  int total = 0;
-  int rc = check_batch_args(c, reqs, n_reqs, cu_suffix, &total);
+  KeptBatch* kept = (KeptBatch*)c->kept.get();
+  const bool known = kept && kept->holds(reqs, n_reqs, cu_suffix);
+  int total = 0, rc = CALVO_OK;
+  if (known) total = kept->ap.total;
+  else rc = check_batch_args(c, reqs, n_reqs, cu_suffix, &total);
   if (rc != CALVO_OK) return rc;
   rc = check_pointer_args(q, k_suffix, v_suffix, out, total);
   if (rc != CALVO_OK) return rc;
@@ -1347,14 +1394,30 @@ int calvo::host::prefill_attn_impl(calvo_ctx* c, int layer, const void* q, const
     cb = c->chunk_blocks[layer];
     nck = c->n_chunks[layer];
   }
-  AttnPlan ap;
-  make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, ap);
+  if (!known || kept->cb != cb || kept->nck != nck || (kept->small && !use_static) || !same_shape(c, *kept)) {
+    if (!kept) {
+      c->kept = std::make_shared<KeptBatch>();
+      kept = (KeptBatch*)c->kept.get();
+    }
+    kept->reqs.clear();                       // holds nothing until the plan is made
+    kept->on_device = kept->small = false;
+    kept->ap = AttnPlan();
+    kept->cb = cb;
+    kept->nck = nck;
+    make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, kept->ap);
+    if (use_static && (kept->ap.blob.size() > kStaticBlobInts || kept->ap.part_need > kStaticPartSlots)) {
+      kept->small = true;
+      kept->ap = AttnPlan();
+      make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, kept->ap, true);
+    }
+    kept->take(reqs, n_reqs, cu_suffix);
+  }
+  const AttnPlan& ap = kept->ap;
   const std::vector<int32_t>& blob = ap.blob;
 
   int32_t* d_att = c->d_att;
   float *part_o = c->part_o, *part_ml = c->part_ml;
   if (use_static) {
-    if (blob.size() > kStaticBlobInts || ap.part_need > kStaticPartSlots) make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, ap, true);
     // fixed capacity, no allocation: the array is shared by every call on this GPU, so its
     // descriptors are uploaded on every call (another context may have used it in between)
     if (blob.size() > kStaticBlobInts)
@@ -1383,17 +1446,15 @@ int calvo::host::prefill_attn_impl(calvo_ctx* c, int layer, const void* q, const
     d_att = c->d_att;
     part_o = c->part_o;
     part_ml = c->part_ml;
-    const bool same = c->att_len == blob.size() && memcmp(c->h_att[c->att_cur], blob.data(), blob.size() * 4) == 0;
-    if (!same) {
+    if (!kept->on_device) {
       const int k = (c->att_cur + 1) % calvo_ctx::kShadows;      // the shadow whose upload is the oldest
       if (c->att_pending[k]) { HIP_TRY(hipEventSynchronize(c->ev_att[k])); c->att_pending[k] = false; }
-      c->att_len = 0;                       // the device copy is unknown until the transfer is queued
       memcpy(c->h_att[k], blob.data(), blob.size() * 4);
       HIP_TRY(hipMemcpyAsync(c->d_att, c->h_att[k], blob.size() * 4, hipMemcpyHostToDevice, c->s_compute));
       c->att_cur = k;
-      c->att_len = blob.size();
       HIP_TRY(hipEventRecord(c->ev_att[k], c->s_compute));
       c->att_pending[k] = true;
+      kept->on_device = true;
     }
   }
   return launch_layer(c, layer, q, k_suffix, v_suffix, out, scale, ap, d_att, part_o, part_ml, ready);

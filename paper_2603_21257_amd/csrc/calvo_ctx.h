@@ -3,6 +3,7 @@
 // Not part of the public ABI (see include/calvo.h).
 #pragma once
 #include <condition_variable>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <thread>
@@ -48,7 +49,6 @@ struct calvo_ctx {
   static constexpr int kShadows = 4;
   int32_t* h_att[kShadows] = {nullptr, nullptr, nullptr, nullptr};
   size_t att_cap = 0;     // in int32
-  size_t att_len = 0;     // valid int32 in shadow att_cur == on device
   int att_cur = 0;
   hipEvent_t ev_att[kShadows] = {nullptr, nullptr, nullptr, nullptr};
   bool att_pending[kShadows] = {false, false, false, false};
@@ -61,6 +61,7 @@ struct calvo_ctx {
   int split_min = 48;             // shortest piece of a cut tile, in 32-key sub-tiles
   int split_fill = 30;            // cost of a workgroup's pipeline fill and drain, in sub-tile steps (launch replay)
   int n_cus = 256;                // compute units of the device
+  std::shared_ptr<void> kept;     // checked and planned batch of the latest calvo_prefill_attn (KeptBatch, calvo_api.hip)
   std::vector<int64_t> plan_key;  // lengths of the batch the cached decision belongs to
   int plan_want = 1;
   float* part_o = nullptr;        // split-KV partial results (compute stream only)
