@@ -1343,7 +1343,7 @@ int upload_prepared(calvo_ctx* c, PreparedPlan& pp) {
     if (rc != CALVO_OK) return rc;
   }
   memcpy(pp.h_blob, pp.ap.blob.data(), pp.ap.blob.size() * 4);
-  HIP_TRY(hipMemcpyAsync(pp.d_blob, pp.h_blob, pp.ap.blob.size() * 4, hipMemcpyHostToDevice, c->s_compute));
+  HIP_TRY(launch_upload_words(pp.h_blob, pp.d_blob, pp.ap.blob.size(), c->s_compute));
   return CALVO_OK;
 }
 
@@ -1432,7 +1432,7 @@ int calvo::host::prefill_attn_impl(calvo_ctx* c, int layer, const void* q, const
     const int k = (c->static_cur + 1) % calvo_ctx::kShadows;
     if (c->static_pending[k]) { HIP_TRY(hipEventSynchronize(c->ev_static[k])); c->static_pending[k] = false; }
     memcpy(c->h_static[k], blob.data(), blob.size() * 4);
-    HIP_TRY(hipMemcpyAsync(d_att, c->h_static[k], blob.size() * 4, hipMemcpyHostToDevice, c->s_compute));
+    HIP_TRY(launch_upload_words(c->h_static[k], d_att, blob.size(), c->s_compute));
     HIP_TRY(hipEventRecord(c->ev_static[k], c->s_compute));
     c->static_pending[k] = true;
     c->static_cur = k;
@@ -1450,7 +1450,7 @@ int calvo::host::prefill_attn_impl(calvo_ctx* c, int layer, const void* q, const
       const int k = (c->att_cur + 1) % calvo_ctx::kShadows;      // the shadow whose upload is the oldest
       if (c->att_pending[k]) { HIP_TRY(hipEventSynchronize(c->ev_att[k])); c->att_pending[k] = false; }
       memcpy(c->h_att[k], blob.data(), blob.size() * 4);
-      HIP_TRY(hipMemcpyAsync(c->d_att, c->h_att[k], blob.size() * 4, hipMemcpyHostToDevice, c->s_compute));
+      HIP_TRY(launch_upload_words(c->h_att[k], c->d_att, blob.size(), c->s_compute));
       c->att_cur = k;
       HIP_TRY(hipEventRecord(c->ev_att[k], c->s_compute));
       c->att_pending[k] = true;

@@ -82,6 +82,8 @@ struct AppendParams {
 hipError_t launch_scatter_blocks(const void* src, void* pool_layer, const int32_t* table, int64_t n_blocks,
                                  int32_t blk_bytes, int grid, hipStream_t stream);
 hipError_t launch_suffix_append(const AppendParams& p, hipStream_t stream);
+// n_words 32-bit words of page-locked host memory to the device; both 16-byte aligned
+hipError_t launch_upload_words(const int32_t* pinned_src, int32_t* dst, size_t n_words, hipStream_t stream);
 // test hook: occupies `stream` for about us microseconds (bounded), see kernels_ingest.hip
 hipError_t launch_delay(int us, hipStream_t stream);
 
