@@ -1508,6 +1508,17 @@ void calvo::host::batch_free_completed(calvo_batch* b) {
   delete b;
 }
 
+// No exception leaves the C interface: host memory that cannot be had forgets the kept batch.
+static int prefill_attn_guarded(calvo_ctx* c, int layer, const void* q, const void* k_suffix, const void* v_suffix, void* out,
+                                const calvo_request* reqs, int n_reqs, const int32_t* cu_suffix, float scale, bool use_static) {
+  try {
+    return prefill_attn_impl(c, layer, q, k_suffix, v_suffix, out, reqs, n_reqs, cu_suffix, scale, use_static, nullptr);
+  } catch (const std::bad_alloc&) {
+    c->kept.reset();
+    return fail(CALVO_ENOMEM, "out of host memory");
+  }
+}
+
 extern "C" {
 
 int calvo_batch_prepare(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const int32_t* cu_suffix, calvo_batch** out) {
@@ -1557,12 +1568,12 @@ int calvo_prefill_attn_batch(calvo_ctx* c, calvo_batch* b, int layer, const void
 
 int calvo_prefill_attn(calvo_ctx* c, int layer, const void* q, const void* k_suffix, const void* v_suffix, void* out,
                        const calvo_request* reqs, int n_reqs, const int32_t* cu_suffix, float scale) {
-  return prefill_attn_impl(c, layer, q, k_suffix, v_suffix, out, reqs, n_reqs, cu_suffix, scale, false, nullptr);
+  return prefill_attn_guarded(c, layer, q, k_suffix, v_suffix, out, reqs, n_reqs, cu_suffix, scale, false);
 }
 
 int calvo_prefill_attn_noalloc(calvo_ctx* c, int layer, const void* q, const void* k_suffix, const void* v_suffix, void* out,
                                const calvo_request* reqs, int n_reqs, const int32_t* cu_suffix, float scale) {
-  return prefill_attn_impl(c, layer, q, k_suffix, v_suffix, out, reqs, n_reqs, cu_suffix, scale, true, nullptr);
+  return prefill_attn_guarded(c, layer, q, k_suffix, v_suffix, out, reqs, n_reqs, cu_suffix, scale, true);
 }
 
 int calvo_attn_kernel_info(calvo_ctx* c, int layer, int* kernel, int* n_workgroups) {
