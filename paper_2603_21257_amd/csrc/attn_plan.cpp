@@ -19,8 +19,8 @@ namespace calvo {
 // keys for one wave's rows with both waves of its SIMD at work (measured per element type and padded head width).
 constexpr int kRowsFill = 60;
 static int rows_step_cost(bool f32, int head_dim) {
-  if (f32) return head_dim <= 64 ? 23 : head_dim <= 128 ? 53 : 64;
-  return head_dim <= 64 ? 7 : head_dim <= 128 ? 23 : 25;
+  if (f32) return head_dim <= 64 ? 23 : head_dim <= 128 ? 48 : 64;
+  return head_dim <= 64 ? 7 : head_dim <= 128 ? 12 : 25;
 }
 
 int attn_pipe_tile_tokens(int heads_per_wg);

@@ -36,7 +36,7 @@
 // sixteenth of bf16; 2.3 us per 32 keys of a wave's 32 rows at D = 64 against 1.8 us of MFMA), bf16 the
 // vector ALU (exponentials, weight split, V permutes; 0.7 us per step against 0.2 us of MFMA).
 // Measured against the kernel it replaces (one wave per token and head on the vector ALU), us a call:
-// fp32 8Q/2KV D = 64, 1024+128 tokens 194 -> 21; bf16 16Q/4KV D = 64, 4096+300 tokens 1170 -> 27.5.
+// fp32 8Q/2KV D = 64, 1024+128 tokens 193 -> 12.5; bf16 16Q/4KV D = 64, 4096+300 tokens 1168 -> 22.7.
 #include "attn_common.h"
 #include "../../include/calvo.h"
 
@@ -659,8 +659,7 @@ auto with_cfg(int dtype, int head_dim, F&& f) {
   }
   if (head_dim == 64) return f(RowsCfg<B16, 64, 2, 2, 8, true>{});
   if (head_dim < 64) return f(RowsCfg<B16, 64, 2, 2, 8, false>{});
-  if (head_dim == 128) return f(RowsCfg<B16, 128, 2, 2, 8, true>{});
-  if (head_dim < 128) return f(RowsCfg<B16, 128, 2, 2, 8, false>{});
+  if (head_dim <= 128) return f(RowsCfg<B16, 128, 2, 2, 8, false>{});     // 128 itself: attn_pipeline.h
   if (head_dim == 256) return f(RowsCfg<B16, 256, 1, 2, 4, true>{});
   return f(RowsCfg<B16, 256, 1, 2, 4, false>{});
 }
