@@ -16,6 +16,9 @@
 //   bf16: v_mfma_f32_16x16x32_bf16.  V rows are read 8 or 16 bytes per lane in the same way and the four
 //         keys of a lane are brought together with v_perm_b32.  The weights stay fp32: each is split into
 //         three bf16 terms (24 significant bits), three products with the exact bf16 V.
+// Neither product tells an infinite or NaN V of a key that a row does not see from one that it does (0 times
+// infinity), and the lower terms of a weight are negative or 0.  Such V leave sums that are not finite; a wave
+// that finds one walks its keys again with every row adding its own keys' fp32 products (walk_by_row).
 //
 // No LDS on the way in: 16 keys are exactly one pool block, so a block's address is one scalar table
 // lookup and the lanes' offsets inside it are constants; K and V go straight to registers, K(next) is
@@ -215,7 +218,8 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
 
   // ---- this wave's steps: KB blocks each, alternating between the key waves
   constexpr int SPS = 2 / KB;                                  // steps per 32-key sub-tile
-  int st = sub_begin * SPS + wave;
+  const int st_begin = sub_begin * SPS + wave;
+  int st = st_begin;
   const int st_end = min(sub_end * SPS, pos_max / (kBlockTokens * KB) + 1);
   if (st < st_end) look_up(st);
   u32x4 qreg[NQB][KJ];                                         // requested before K, so that waiting for K does not wait for V
@@ -243,20 +247,14 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
   for (int qb = 0; qb < NQB; qb++) { m[qb] = -INFINITY; l[qb] = 0.f; }
   const float c2 = p.scale * 1.4426950408889634f;
 
-  // Second product: o += V^T * w for the keys in vr.  keep(kb, r, x) passes the operand bits of the lane's
-  // key 16kb + 4g + r through or drops them.
-  auto weights_bf16 = [&](const float (&w)[NQB][KB][4], bf16x8 (&pb)[NQB][3], auto keep) {
+  // Second product: o += V^T * w for the keys in vr.
+  auto weights_bf16 = [&](const float (&w)[NQB][KB][4], bf16x8 (&pb)[NQB][3]) {
 #pragma unroll
     for (int qb = 0; qb < NQB; qb++) {
       u32x4 x[3];
 #pragma unroll
       for (int i = 0; i < 4; i++) {
-        float v[2];
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-          const int k = 2 * i + h;
-          v[h] = __builtin_bit_cast(float, keep(k >> 2, k & 3, __builtin_bit_cast(unsigned, w[qb][k >> 2][k & 3])));
-        }
+        float v[2] = {w[qb][i >> 1][2 * (i & 1)], w[qb][i >> 1][2 * (i & 1) + 1]};
 #pragma unroll
         for (int t = 0; t < 3; t++) {
           const bf16x2 top = {(__bf16)v[0], (__bf16)v[1]};
@@ -270,15 +268,14 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
     }
   };
   // V^T operand of tile (q, e): the lane's keys in k-slot order (kb, r)
-  auto v_bf16 = [&](int q, int e, auto keep) {
+  auto v_bf16 = [&](int q, int e) {
     u32x4 x;
 #pragma unroll
     for (int i = 0; i < 4; i++)
-      x[i] = __builtin_amdgcn_perm(keep(i >> 1, 2 * (i & 1) + 1, vr[(KB - 1) & (i >> 1)][2 * (i & 1) + 1][q][e >> 1]),
-                                   keep(i >> 1, 2 * (i & 1), vr[(KB - 1) & (i >> 1)][2 * (i & 1)][q][e >> 1]), e & 1 ? 0x07060302u : 0x05040100u);
+      x[i] = __builtin_amdgcn_perm(vr[(KB - 1) & (i >> 1)][2 * (i & 1) + 1][q][e >> 1],
+                                   vr[(KB - 1) & (i >> 1)][2 * (i & 1)][q][e >> 1], e & 1 ? 0x07060302u : 0x05040100u);
     return __builtin_bit_cast(bf16x8, x);
   };
-  auto all_keys = [](int, int, unsigned x) { return x; };
   auto pv = [&](const float (&w)[NQB][KB][4]) {
     if constexpr (F32) {
 #pragma unroll
@@ -295,14 +292,14 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
                                                                          o[qb][q * VW + e], 0, 0, 0);
     } else {
       bf16x8 pb[NQB][3];
-      weights_bf16(w, pb, all_keys);
+      weights_bf16(w, pb);
 #pragma unroll
       for (int q = 0; q < VQ; q++)
 #pragma unroll
         for (int e0 = 0; e0 < VW; e0 += 4) {
           bf16x8 a[4];
 #pragma unroll
-          for (int e = 0; e < 4; e++) a[e] = v_bf16(q, e0 + e, all_keys);
+          for (int e = 0; e < 4; e++) a[e] = v_bf16(q, e0 + e);
 #pragma unroll
           for (int t = 0; t < 3; t++)
 #pragma unroll
@@ -311,39 +308,6 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
               for (int qb = 0; qb < NQB; qb++)
                 o[qb][q * VW + e0 + e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[e], pb[qb][t], o[qb][q * VW + e0 + e], 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);                   // one group's operands at a time in registers
-        }
-    }
-  };
-  // The same key by key, each key only into the rows that see it (see the loop).
-  auto pv_by_key = [&](const float (&w)[NQB][KB][4], int k0) {
-    for (int key = 0; key < 16 * KB; key++) {
-      const bool mine = g == ((key >> 2) & 3);
-      auto keep = [&](int kb, int r, unsigned x) { return mine && key >> 4 == kb && (key & 3) == r ? x : 0u; };
-      bf16x8 pb[NQB][3];
-      if constexpr (!F32) weights_bf16(w, pb, keep);
-#pragma unroll
-      for (int q = 0; q < VQ; q++)
-#pragma unroll
-        for (int e = 0; e < VW; e++) {
-          bf16x8 a;
-          if constexpr (!F32) a = v_bf16(q, e, keep);
-#pragma unroll
-          for (int qb = 0; qb < NQB; qb++) {
-            f32x4 one = zero4;
-            if constexpr (F32) {
-#pragma unroll
-              for (int kb = 0; kb < KB; kb++)
-#pragma unroll
-                for (int r = 0; r < 4; r++)
-                  one = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                      __builtin_bit_cast(float, keep(kb, r, vr[kb][r][q][e])),
-                      __builtin_bit_cast(float, keep(kb, r, __builtin_bit_cast(unsigned, w[qb][kb][r]))), one, 0, 0, 0);
-            } else {
-#pragma unroll
-              for (int t = 0; t < 3; t++) one = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pb[qb][t], one, 0, 0, 0);
-            }
-            if (k0 + key <= posq[qb]) o[qb][q * VW + e] += one;
-          }
         }
     }
   };
@@ -427,32 +391,101 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
         }
       l[qb] += sum;
     }
-    // A masked weight is 0, and 0 times an infinity or NaN that a later token's V may hold is NaN: such
-    // a step goes key by key and adds only what each row sees.
-    bool odd = false;
-    if constexpr (DIAG) {
-#pragma unroll
-      for (int kb = 0; kb < KB; kb++)
-#pragma unroll
-        for (int r = 0; r < 4; r++)
-#pragma unroll
-          for (int q = 0; q < VQ; q++)
-#pragma unroll
-            for (int i = 0; i < VW * E / 4; i++) {
-              const unsigned x = vr[kb][r][q][i];
-              if constexpr (F32) odd |= (x & 0x7f800000u) == 0x7f800000u;
-              else odd |= (x & 0x7f800000u) == 0x7f800000u || (x & 0x7f80u) == 0x7f80u;
-            }
-      odd = __builtin_amdgcn_ballot_w64(odd) != 0;
-    }
-    if (!odd) pv(w);
-    else pv_by_key(w, k0);
+    pv(w);
     if (more) load_v(st + NW);
   };
-  // Two loops: the masks and the key-by-key path of the last steps cost the others registers otherwise.
+  // Two loops: the masks of the last steps cost the others registers otherwise.
   const int st_full = min(st_end, (pos_min + 1) / (kBlockTokens * KB));
   for (; st < st_full; st += NW) step(Tag<0>{});
   for (; st < st_end; st += NW) step(Tag<1>{});
+
+  // The same keys for the rows of one block, a key at a time: a row adds weight times V of the keys that it sees and
+  // touches no other.  Weights are taken against the running maximum.  Rare, so it is written for few registers.
+  auto walk_by_row = [&](auto qb_tag) {
+    constexpr int qb = decltype(qb_tag)::value;
+    const unsigned char* qp = (const unsigned char*)p.q + qrow[qb] * (D * E);
+#pragma unroll
+    for (int a = 0; a < C::NACC; a++) o[qb][a] = zero4;
+    m[qb] = -INFINITY;
+    l[qb] = 0.f;
+#pragma unroll 1
+    for (int s0 = st_begin; s0 < st_end; s0 += NW)
+#pragma unroll 1
+      for (int b = s0 * KB; b < (s0 + 1) * KB; b++) {
+        const int k0 = kBlockTokens * b;
+        if (k0 > pos_max) break;
+        const bool sfx = from_suffix && b >= p_blk;
+        const int64_t off = (sfx ? s_base + (int64_t)(b - p_blk) * half : (int64_t)table[b] * (2 * half)) + head_b;
+        const unsigned char* kp = (sfx ? ks : pool) + off;
+        const unsigned char* vb = sfx ? vs + off : kp + half;
+        const int rest = min(kBlockTokens, ctx_len - k0);      // token rows the block holds
+        kp += (int64_t)min(c, rest - 1) * rs;
+        f32x4 s = zero4;
+#pragma unroll 1
+        for (int j = 0; j < KJ; j++) {
+          const int d = F32 ? 16 * j + 4 * g : 32 * j + 8 * g;
+          u32x4 kx = {0u, 0u, 0u, 0u}, qx = kx;
+          if (C::FULL || d < D) {
+            kx = *(const u32x4*)(kp + d * E);
+            qx = *(const u32x4*)(qp + d * E);
+          }
+          if constexpr (F32) {
+#pragma unroll
+            for (int i = 0; i < 4; i++) s = __builtin_amdgcn_mfma_f32_16x16x4f32(as_float(kx[i]), as_float(qx[i]), s, 0, 0, 0);
+          } else {
+            s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kx), __builtin_bit_cast(bf16x8, qx), s, 0, 0, 0);
+          }
+        }
+        float mx = -INFINITY, sum = 0.f, w[4];
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          if (k0 + 4 * g + r > posq[qb]) s[r] = -INFINITY;
+          mx = fmaxf(mx, s[r]);
+        }
+        const float mn = fmaxf(m[qb], quad_max(mx) * c2), ref = mn == -INFINITY ? 0.f : mn;
+        const float a = __builtin_amdgcn_exp2f(m[qb] - ref);
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          w[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c2, -ref));
+          sum += w[r];
+        }
+        m[qb] = mn;
+        l[qb] = l[qb] * a + sum;
+#pragma unroll
+        for (int i = 0; i < C::NACC; i++) o[qb][i] *= a;
+#pragma unroll 1
+        for (int key = 0; key < rest; key++) {
+          const float w4 = key & 2 ? (key & 1 ? w[3] : w[2]) : (key & 1 ? w[1] : w[0]);
+          const float wk = __shfl(w4, 16 * (key >> 2) + c);
+          const bool sees = k0 + key <= posq[qb];
+          const unsigned char* vrow = vb + (int64_t)key * rs;
+#pragma unroll
+          for (int q = 0; q < VQ; q++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+              const int d = VW * (16 * q + 4 * g + r);
+              if (!sees || !(C::FULL || d < D)) continue;
+              const vreg x = *(const vreg*)(vrow + d * E);
+#pragma unroll
+              for (int e = 0; e < VW; e++) {
+                float v;
+                if constexpr (F32) v = as_float(x[e]);
+                else v = e & 1 ? as_float(x[e >> 1] & 0xffff0000u) : bf16_widen(x[e >> 1] & 0xffffu);
+                o[qb][q * VW + e][r] = __builtin_fmaf(wk, v, o[qb][q * VW + e][r]);
+              }
+            }
+        }
+      }
+  };
+  float mag[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int qb = 0; qb < NQB; qb++)
+#pragma unroll
+    for (int a = 0; a < C::NACC; a++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) mag[r] += __builtin_fabsf(o[qb][a][r]);
+  if (__builtin_amdgcn_ballot_w64(!((mag[0] + mag[1]) + (mag[2] + mag[3]) < INFINITY)) != 0)
+    static_for<0, NQB>(walk_by_row);
 
   // ---- suffix rows of the tokens whose first row lies in this tile: caller's arrays -> pool.  The first
   // chunk of every thread is on its way while the key waves are combined.

@@ -1,0 +1,51 @@
+"""Infinities and NaNs in K, Q and V reach exactly the rows and columns that they reach in the oracle, and values near
+the end of the element type's range do not overflow on the way."""
+import numpy as np
+import pytest
+
+import hip_harness as hh
+from paper_2603_21257_amd import workload as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def stored(value, dtype):
+    return np.uint16(np.float32(value).view(np.uint32) >> 16) if dtype == "bf16" else np.float32(value)
+
+
+def assert_like_oracle(got_stored, want, dtype):
+    got = hh.orc.widen(got_stored) if dtype == "bf16" else got_stored.astype(np.float64)
+    for name, f in (("NaN", np.isnan), ("+inf", np.isposinf), ("-inf", np.isneginf)):
+        bad = np.argwhere(f(got) != f(want))
+        assert len(bad) == 0, f"{name} differs at {len(bad)} elements, first (layer, token, head, d) = {bad[0].tolist()}"
+    ok = np.isfinite(want)
+    d = np.abs(got[ok] - want[ok])
+    tmx, tmean = hh.TOL[dtype]
+    assert d.max() <= tmx and d.mean() <= tmean, (d.max(), d.mean())
+
+
+def poisoned(shape, P, S, seed):
+    """V: +inf at a cached token and -inf / NaN at two suffix tokens, in some columns only."""
+    w = wl.make_custom(shape, [(P, S)], seed=seed)
+    v = w.host_kv.reshape(shape.n_layers, w.host_blocks, 2, 16, shape.n_kv_heads, shape.head_dim)
+    start = w.requests[0].host_block_start
+    v[:, start + 2, 1, 7, :, ::4] = stored(np.inf, shape.dtype)
+    w.v_suffix[:, 20, :, 2::4] = stored(-np.inf, shape.dtype)
+    w.v_suffix[:, 30, :, ::8] = stored(-np.inf, shape.dtype)
+    w.v_suffix[:, 30, :, 5] = stored(np.nan, shape.dtype)
+    return w
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 96), ("f32", 128), ("f32", 256), ("bf16", 40), ("bf16", 64),
+                                     ("bf16", 96), ("bf16", 200), ("bf16", 256)])
+@pytest.mark.parametrize("pieces", [1, 3])
+def test_v_of_packed_rows(dtype, D, pieces, monkeypatch):
+    if pieces > 1:
+        monkeypatch.setenv("CALVO_ATTN_SPLITS", str(pieces))
+    s = wl.Shape(1, 6, 2, D, dtype, 40)
+    w = poisoned(s, 400, 45, seed=800 + D)
+    print(f"[case] {dtype} D={D} pieces={pieces}", flush=True)
+    _, got = hh.run_hip(w)
+    with np.errstate(invalid="ignore"):
+        _, want = hh.run_oracle(w)
+    assert_like_oracle(got, want, dtype)

@@ -72,8 +72,8 @@ def test_entry_points(dtype, fn):
 @pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 256), ("bf16", 64), ("bf16", 256)])
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
 def test_later_tokens_do_not_reach_earlier_rows(dtype, D, value):
-    """V of token 20 is not finite: rows 0..19 are what the oracle gives for finite values (their step goes key by
-    key then, a different order of the same sums), rows from 20 on are not finite."""
+    """V of token 20 is not finite: rows 0..19 are what the oracle gives for finite values (their keys are walked again
+    one by one, a different order of the same sums), rows from 20 on what it gives for this one."""
     w = wl.make_custom(wl.Shape(1, 6, 2, D, dtype, 32), [(64, 40)], seed=31)
     _, want = hh.run_oracle(w)
     bad = np.float32(value).view(np.uint32)
@@ -81,7 +81,9 @@ def test_later_tokens_do_not_reach_earlier_rows(dtype, D, value):
     _, got = hh.run_hip(w)
     hh.assert_attn_close(got[:, :20], want[:, :20], dtype)
     wide = hh.orc.widen(got) if dtype == "bf16" else got
-    assert not np.isfinite(wide[0, 20:]).any()
+    with np.errstate(invalid="ignore"):
+        _, want = hh.run_oracle(w)
+    assert np.array_equal(wide[0, 20:], want[0, 20:], equal_nan=True)
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
