@@ -18,7 +18,8 @@
 //         three bf16 terms (24 significant bits), three products with the exact bf16 V.
 // Neither product tells an infinite or NaN V of a key that a row does not see from one that it does (0 times
 // infinity), and the lower terms of a weight are negative or 0.  Such V leave sums that are not finite; a wave
-// that finds one walks its keys again with every row adding its own keys' fp32 products (walk_by_row).
+// that finds one, or sums so large that weights above 1 (see the softmax reference) could be the reason, walks
+// its keys again with every row adding its own keys' fp32 products, weights at most 1 (walk_by_row).
 //
 // No LDS on the way in: 16 keys are exactly one pool block, so a block's address is one scalar table
 // lookup and the lanes' offsets inside it are constants; K and V go straight to registers, K(next) is
@@ -400,7 +401,8 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
   for (; st < st_end; st += NW) step(Tag<1>{});
 
   // The same keys for the rows of one block, a key at a time: a row adds weight times V of the keys that it sees and
-  // touches no other.  Weights are taken against the running maximum.  Rare, so it is written for few registers.
+  // touches no other.  Weights are taken against the running maximum: sums stay within those of a textbook loop.
+  // Rare, so it is written for few registers.
   auto walk_by_row = [&](auto qb_tag) {
     constexpr int qb = decltype(qb_tag)::value;
     const unsigned char* qp = (const unsigned char*)p.q + qrow[qb] * (D * E);
@@ -477,6 +479,7 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
         }
       }
   };
+  // With sums below 2^110 a wave's share leaves 18 powers of two for adding 8 waves and 64 pieces.
   float mag[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int qb = 0; qb < NQB; qb++)
@@ -484,7 +487,7 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
     for (int a = 0; a < C::NACC; a++)
 #pragma unroll
       for (int r = 0; r < 4; r++) mag[r] += __builtin_fabsf(o[qb][a][r]);
-  if (__builtin_amdgcn_ballot_w64(!((mag[0] + mag[1]) + (mag[2] + mag[3]) < INFINITY)) != 0)
+  if (__builtin_amdgcn_ballot_w64(!((mag[0] + mag[1]) + (mag[2] + mag[3]) < 0x1p110f)) != 0)
     static_for<0, NQB>(walk_by_row);
 
   // ---- suffix rows of the tokens whose first row lies in this tile: caller's arrays -> pool.  The first

@@ -49,3 +49,33 @@ def test_v_of_packed_rows(dtype, D, pieces, monkeypatch):
     with np.errstate(invalid="ignore"):
         _, want = hh.run_oracle(w)
     assert_like_oracle(got, want, dtype)
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("f32", 256), ("bf16", 64), ("bf16", 96), ("bf16", 256)])
+@pytest.mark.parametrize("value,columns", [(1e35, slice(None)), (1e32, slice(0, 1))])
+@pytest.mark.parametrize("pieces", [1, 2])
+def test_large_v_under_rising_scores(dtype, D, value, columns, pieces, monkeypatch):
+    """All scores are 0 up to a token from which on they are 15 powers of two higher.  The softmax reference lags by up
+    to 16 powers of two; sums of V taken with weights of 2^15 would leave the range where the result does not - in one
+    wave, or (1e32 in one column) where the waves' sums are added."""
+    monkeypatch.setenv("CALVO_ATTN_SPLITS", str(pieces))
+    P, S = 1024, 20
+    s = wl.Shape(1, 4, 2, D, dtype, (P + S) // 16 + 9)
+    w = wl.make_custom(s, [(P, S)], seed=903)
+    w.q[...] = stored(1.0, dtype)
+    first = w.requests[0].host_block_start
+    kv = w.host_kv.reshape(1, w.host_blocks, 2, 16, 2, D)[0, first:first + P // 16]
+    kv[:, 0] = stored(0.0, dtype)
+    kv[16:, 0, :, :, 0] = stored(np.round(15 * np.log(2) * np.sqrt(D)), dtype)
+    w.k_suffix[...] = stored(0.0, dtype)
+    factor = np.ones(D)
+    factor[columns] = value
+    for v in (kv[:, 1], w.v_suffix):
+        x = (np.abs(hh.orc.widen(v)) * factor).astype(np.float32)
+        v[...] = (x.view(np.uint32) >> 16).astype(np.uint16) if dtype == "bf16" else x
+    _, got = hh.run_hip(w)
+    _, want = hh.run_oracle(w)
+    g = hh.orc.widen(got) if dtype == "bf16" else got.astype(np.float64)
+    tmx, tmean = hh.TOL[dtype]
+    d = np.abs(g / factor - want / factor)
+    assert np.isfinite(g).all() and d.max() <= tmx and d.mean() <= tmean, (d.max(), d.mean())
