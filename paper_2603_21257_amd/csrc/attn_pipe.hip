@@ -22,7 +22,7 @@ __global__ void __launch_bounds__(512, 2) __attribute__((amdgpu_num_vgpr(120))) 
 // Combines the pieces of split tiles: for every row and head, with m = max_c m_c,
 //     O = sum_c 2^(m_c - m) O_c  /  sum_c 2^(m_c - m) l_c
 // (the pieces' O_c, l_c are sums of weights 2^(x - m_c), x the exponent of a score).  A piece in which a
-// row saw no key has l_c = 0 and m_c = -inf and drops out.
+// row saw no key has l_c = 0 and drops out; every other one counts, also with l_c = NaN or a weight that is 0 here.
 // What counts is how many loads are in flight and how often the chain of descriptor loads is paid: the
 // partials are a few MB to a few tens of MB that the caches still hold.  A wave merges ROWS rows: lane
 // (row, i) reads (m, l) of piece i of its row, the maximum and the denominator are reductions over the
@@ -72,10 +72,10 @@ __global__ void __launch_bounds__(256) merge_splits_kernel(AttnParams p, const i
 #pragma unroll
   for (int r = 0; r < ROWS; r++) acc[r] = (f32x2){0.f, 0.f};
   for (int c0 = 0; c0 < n; c0 += kLanes) {
-    float wgt = 0.f;
+    float wgt = -1.f;                                            // drops out
     if (row_ok && c0 + my_c < n) {
       const f32x2 v = ml[(c0 + my_c) * step];
-      if (v[1] > 0.f) {
+      if (v[1] != 0.f) {
         wgt = __builtin_amdgcn_exp2f(v[0] - m);
         l = __builtin_fmaf(wgt, v[1], l);
       }
@@ -86,14 +86,14 @@ __global__ void __launch_bounds__(256) merge_splits_kernel(AttnParams p, const i
 #pragma unroll
       for (int i = 0; i < kPieces; i++)
 #pragma unroll
-        for (int r = 0; r < ROWS; r++)                     // past the end: the last piece / row again, with weight 0 below
+        for (int r = 0; r < ROWS; r++)                     // past the end: the last piece / row again, dropped below
           v[i][r] = po[((c0 + min(c + i, nc - 1)) * step + min(r, n_rows - 1)) * (kD / 2)];
 #pragma unroll
       for (int i = 0; i < kPieces; i++)
 #pragma unroll
         for (int r = 0; r < ROWS; r++) {
           const float w = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wgt), r * kLanes + c + i));
-          if (w > 0.f) {                                         // also skips a dropped piece, whose O is not a number
+          if (!(w < 0.f)) {
             acc[r][0] = __builtin_fmaf(w, v[i][r][0], acc[r][0]);
             acc[r][1] = __builtin_fmaf(w, v[i][r][1], acc[r][1]);
           }

@@ -591,7 +591,8 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
 
   // ---- one piece of a split tile: leave the unnormalised O, the reference (exponent units) and
   // the row sum for merge_splits_kernel (32 rows x 128 floats per wave, row = 16qb + c).  Lane holds
-  // d = 16db + 4g + r of the query rows 16qb + c.
+  // d = 16db + 4g + r of the query rows 16qb + c.  A row that lies before the piece's first key saw none: its sums
+  // are no numbers by now, a row sum of 0 says so.  NaN of a row that did see keys stays.
   if (wi.n_splits > 1) {
     if (wave_active) {                       // wave-uniform: every lane takes part in the exchanges
       const int64_t slot = ((int64_t)it * NHG + hg) * NW + wave;
@@ -605,7 +606,7 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
           if (g == 0) {
             float* pm = pe->part_ml + (slot * 32 + 16 * qb + c) * 2;
             pm[0] = m_run[qb];
-            pm[1] = lt;
+            pm[1] = pq_min + 16 * qb + c < jb * kSK ? 0.f : lt;
           }
         }
       }

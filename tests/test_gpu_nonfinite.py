@@ -79,3 +79,43 @@ def test_large_v_under_rising_scores(dtype, D, value, columns, pieces, monkeypat
     tmx, tmean = hh.TOL[dtype]
     d = np.abs(g / factor - want / factor)
     assert np.isfinite(g).all() and d.max() <= tmx and d.mean() <= tmean, (d.max(), d.mean())
+
+
+def long_one_token(seed, P=8192):
+    s = wl.Shape(1, 8, 2, 128, "bf16", P // 16 + 9)
+    w = wl.make_custom(s, [(P, 1)], seed=seed)
+    first = w.requests[0].host_block_start
+    return w, w.host_kv.reshape(1, w.host_blocks, 2, 16, 2, 128)[0, first:first + P // 16]
+
+
+@pytest.mark.parametrize("tokens", [slice(5, 6), slice(0, 1024), slice(7000, 7001)])
+@pytest.mark.parametrize("pieces", [0, 1])
+def test_nan_score_in_a_piece_of_a_cut_context(tokens, pieces, monkeypatch):
+    """One token over 8K cached ones: the planner cuts the context, the pieces are merged.  A NaN in K is in no piece's
+    sum alone: the whole row is NaN, as in a launch that is not cut."""
+    if pieces:
+        monkeypatch.setenv("CALVO_ATTN_SPLITS", str(pieces))
+    w, kv = long_one_token(901)
+    idx = np.arange(8192)[tokens]
+    kv[idx // 16, 0, idx % 16, 1, 3] = stored(np.nan, "bf16")        # KV head 1: query heads 4..7
+    _, got = hh.run_hip(w)
+    with np.errstate(invalid="ignore"):
+        _, want = hh.run_oracle(w)
+    assert np.isnan(want[0, 0, 4:]).all()
+    assert_like_oracle(got, want, "bf16")
+
+
+def test_infinite_v_behind_a_weight_that_underflows_in_the_merge():
+    """V of an early token is infinite in some columns and a late token's score is 300 powers of two above the others:
+    the early piece's weight in the merge is 0 in 32 bits, its infinities are not: those columns are not finite."""
+    w, kv = long_one_token(902)
+    kv[0, 1, 5, 0, ::4] = stored(np.inf, "bf16")
+    q = hh.orc.widen(w.q)[0, 0, 0].astype(np.float32)                # query head 0
+    k = (q * np.float32(300 * np.log(2) * np.sqrt(128.0) / np.dot(q, q))).astype(np.float32)
+    kv[8000 // 16, 0, 0, 0] = (k.view(np.uint32) >> 16).astype(np.uint16)
+    _, got = hh.run_hip(w)
+    _, want = hh.run_oracle(w)
+    g = hh.orc.widen(got)[0, 0, 0]
+    assert not np.isfinite(g[::4]).any()
+    cols = np.arange(128) % 4 != 0
+    assert np.abs(g[cols] - want[0, 0, 0][cols]).max() <= hh.TOL["bf16"][0]
