@@ -72,7 +72,7 @@ std::vector<PlanTile> plan_tiles(const int32_t* prefix_blocks, const int32_t* su
 int plan_piece_len(int n_sub, int n_max, int want, const PlanParams& p) {
   const int floor = p.step_cost ? 1 : p.long_pieces ? p.split_min : std::min(p.split_min, std::max(8, n_sub / 32));
   // a shorter tile gets as many pieces as it has of the longest tile's piece lengths (a quarter over is let go)
-  if (!p.force_splits) want = (int)(((int64_t)4 * n_sub * want + 3 * (int64_t)n_max - 1) / (4 * (int64_t)n_max));
+  if (!p.force_splits && !p.long_pieces) want = (int)(((int64_t)4 * n_sub * want + 3 * (int64_t)n_max - 1) / (4 * (int64_t)n_max));
   const int n = std::max(1, std::min(want, p.force_splits ? n_sub : n_sub / floor));
   int len = (n_sub + n - 1) / n;
   if (p.step_cost) return (len + 3) / 4 * 4;       // packed rows: the same number of wave steps on each of the four SIMDs
@@ -84,12 +84,13 @@ int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t
   if (p.force_splits) return p.force_splits;
   const int64_t wgs = (int64_t)tiles.size() * p.n_head_groups;
   if (wgs <= 0 || wgs > 16 * (int64_t)p.wg_slots) return 1;     // many rounds: the last one hardly matters
-  const int cands[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 20, 24, 32, 48, 64};
+  static const std::vector<int> all = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 20, 24, 32, 48, 64};
+  static const std::vector<int> coarse = {1, 2, 3, 4, 5, 6, 8, 12, 16, 24, 32, 48, 64};
   const int n_max = tiles.front().n_sub;           // heaviest first
   int want = 1;
   double best = 0;
   std::vector<int64_t> heap;
-  for (int n : cands) {
+  for (int n : p.long_pieces ? coarse : all) {
     if (n > 1 && wgs * n > (p.step_cost ? 4 : 16) * (int64_t)p.wg_slots) break;
     auto cost_of = [&](int64_t subs) { return (p.step_cost ? (subs + 3) / 4 * p.step_cost : subs) + p.split_fill; };
     bool cut = false;

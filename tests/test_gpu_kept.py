@@ -79,3 +79,24 @@ def test_forced_shapes_are_seen_by_a_kept_batch(monkeypatch):
             assert not variant or kernel == int(variant)
     finally:
         cb.calvo_destroy(c.ctx)
+
+
+PREFILL, NOALLOC = cb.calvo_prefill_attn, cb.calvo_prefill_attn_noalloc
+
+
+@pytest.mark.parametrize("lens", [(1024, 4096), (7648, 3284)])
+@pytest.mark.parametrize("calls", [(NOALLOC,)])
+def test_plans_beyond_the_fixed_array(lens, calls):
+    """The best plans of these batches have more partial results than the fixed-size array holds; the allocation-free
+    entry point runs them with longer pieces."""
+    c = Case("bf16", 128, [lens], seed=53)
+    try:
+        for fn in calls:
+            out = c.run(fn)[0]
+            pool = hh.to_numpy_stored(c.pool, c.s)
+            rows = [0, 31, 32, 1500, lens[1] - 1]
+            want = hh.orc.prefill_attn_sampled(pool[0].reshape(-1, 2, 16, 2, 128), c.w.q[0], c.w.requests[0].table, *lens, 16, rows)
+            assert np.isfinite(hh.orc.widen(out)).all()
+            hh.assert_attn_close(out[rows], want, "bf16")
+    finally:
+        cb.calvo_destroy(c.ctx)
