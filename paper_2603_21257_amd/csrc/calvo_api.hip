@@ -1394,7 +1394,10 @@ int calvo::host::prefill_attn_impl(calvo_ctx* c, int layer, const void* q, const
     cb = c->chunk_blocks[layer];
     nck = c->n_chunks[layer];
   }
-  if (!known || kept->cb != cb || kept->nck != nck || (kept->small && !use_static) || !same_shape(c, *kept)) {
+  auto fits = [](const AttnPlan& a) { return a.blob.size() <= kStaticBlobInts && a.part_need <= kStaticPartSlots; };
+  // a plan made for the other entry point is taken over only if this one would make the same
+  if (!known || kept->cb != cb || kept->nck != nck || (use_static ? !kept->small && !fits(kept->ap) : kept->small) ||
+      !same_shape(c, *kept)) {
     if (!kept) {
       c->kept = std::make_shared<KeptBatch>();
       kept = (KeptBatch*)c->kept.get();
@@ -1405,7 +1408,7 @@ int calvo::host::prefill_attn_impl(calvo_ctx* c, int layer, const void* q, const
     kept->cb = cb;
     kept->nck = nck;
     make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, kept->ap);
-    if (use_static && (kept->ap.blob.size() > kStaticBlobInts || kept->ap.part_need > kStaticPartSlots)) {
+    if (use_static && !fits(kept->ap)) {
       kept->small = true;
       kept->ap = AttnPlan();
       make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, kept->ap, true);

@@ -85,10 +85,10 @@ PREFILL, NOALLOC = cb.calvo_prefill_attn, cb.calvo_prefill_attn_noalloc
 
 
 @pytest.mark.parametrize("lens", [(1024, 4096), (7648, 3284)])
-@pytest.mark.parametrize("calls", [(NOALLOC,)])
+@pytest.mark.parametrize("calls", [(NOALLOC,), (PREFILL, NOALLOC), (NOALLOC, PREFILL, NOALLOC)])
 def test_plans_beyond_the_fixed_array(lens, calls):
     """The best plans of these batches have more partial results than the fixed-size array holds; the allocation-free
-    entry point runs them with longer pieces."""
+    entry point runs them with longer pieces, whatever call was made before."""
     c = Case("bf16", 128, [lens], seed=53)
     try:
         for fn in calls:
