@@ -1224,10 +1224,16 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
   const int32_t* d_tables = d_att + ap.lay.tables_off;
 
   // A packed-rows launch of one request takes the suffix rows along.  With several requests a cached
-  // prefix may be slots that another request of the call appends to: all rows are stored first.
-  const bool rows_append = !ap.mfma && ap.n_reqs == 1;
+  // prefix may be slots that another request of the call appends to: all rows are stored first.  So they are where
+  // the output goes over the suffix rows: a workgroup that is done would overwrite what others still read.
+  const size_t row_b = (size_t)ap.total * cf.head_dim * c->elt;
+  auto in_out = [&](const void* sfx) {
+    return (uintptr_t)sfx < (uintptr_t)out + row_b * cf.n_q_heads && (uintptr_t)out < (uintptr_t)sfx + row_b * cf.n_kv_heads;
+  };
+  const bool append_along = ap.n_reqs == 1 && k_suffix && !in_out(k_suffix) && !in_out(v_suffix);
+  const bool rows_append = !ap.mfma && append_along;
   // The same for a suffix of one tile in the pipelined kernels: no other tile reads its rows.
-  const bool tile_append = ap.mfma && ap.n_reqs == 1 && !ap.chunked && ap.total <= ap.tile_tokens;
+  const bool tile_append = ap.mfma && append_along && !ap.chunked && ap.total <= ap.tile_tokens;
   if (k_suffix && !rows_append && !tile_append) {
     AppendParams app{};
     app.k_suffix = k_suffix; app.v_suffix = v_suffix; app.pool_layer = pool_layer;
