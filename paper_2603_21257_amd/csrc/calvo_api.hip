@@ -102,6 +102,8 @@ void destroy_partial(calvo_ctx* c) {
   for (auto& v : c->ev_chunk)
     for (auto e : v) if (e) (void)hipEventDestroy(e);
   if (c->d_clock) (void)hipFree(c->d_clock);
+  for (auto e : c->ev_end) if (e) (void)hipEventDestroy(e);
+  if (c->s_clock) (void)hipStreamDestroy(c->s_clock);
   for (void* p : c->l2_ring)
     if (p) (void)hipHostFree(p);
   for (auto e : c->ev_l2_free) if (e) (void)hipEventDestroy(e);
@@ -555,6 +557,7 @@ int calvo_create(const calvo_config* cfg, calvo_ctx** out) {
   c->ev_chunk.resize(cfg->n_layers);
   c->layer_pending.assign(cfg->n_layers, 0);
   c->timed.assign(cfg->n_layers, 0);
+  c->end_marked.assign(cfg->n_layers, 0);
   c->last_variant.assign(cfg->n_layers, -1);
   c->last_wgs.assign(cfg->n_layers, 0);
   for (int l = 0; l < cfg->n_layers; l++) {
@@ -1294,6 +1297,9 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
     HIP_TRY(launch_attn_rows(rp, cf.dtype, listed ? (int)ap.plan.items.size() : ap.row_tiles,
                              d_att + ap.lay.split_off, (int)ap.plan.split_tiles.size(), c->s_compute));
   }
+  const bool mark = c->mark_ends.load(std::memory_order_acquire);
+  if (mark) HIP_TRY(hipEventRecord(c->ev_end[(size_t)layer], c->s_compute));
+  c->end_marked[layer] = mark;
   c->timed[layer] = 1;
   c->last_variant[layer] = ap.mfma ? ap.variant : -1;
   c->last_wgs[layer] = ap.mfma ? (int32_t)(ap.plan.items.size() * (size_t)(cf.n_q_heads / ap.HW)) : 0;
@@ -1598,9 +1604,20 @@ int calvo_attn_kernel_ms(calvo_ctx* c, int layer, float* ms) {
   if (!c || !ms) return fail(CALVO_EINVAL, "NULL argument");
   if (layer < 0 || layer >= c->cfg.n_layers) return fail(CALVO_EINVAL, "layer %d outside [0, %d)", layer, c->cfg.n_layers);
   if (!c->timed[layer]) return fail(CALVO_ENOTREADY, "no attention kernel was queued for layer %d", layer);
+  // Only the layer's own launch is waited for, also with others queued behind it: by its event, and with the clock
+  // read on a stream that waits for nothing.  The first call finds no events.
+  if (!c->mark_ends.load(std::memory_order_relaxed)) {
+    if (!c->s_clock) HIP_TRY(hipStreamCreateWithFlags(&c->s_clock, hipStreamNonBlocking));
+    if (c->ev_end.empty()) c->ev_end.assign((size_t)c->cfg.n_layers, nullptr);
+    for (auto& e : c->ev_end)
+      if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    c->mark_ends.store(true, std::memory_order_release);
+  }
+  if (c->end_marked[layer]) HIP_TRY(hipEventSynchronize(c->ev_end[(size_t)layer]));
+  else HIP_TRY(hipStreamSynchronize(c->s_compute));
   unsigned long long t[kClockWords], end = 0;
-  HIP_TRY(hipStreamSynchronize(c->s_compute));
-  HIP_TRY(hipMemcpy(t, c->d_clock + kClockWords * (size_t)layer, sizeof t, hipMemcpyDeviceToHost));
+  HIP_TRY(hipMemcpyAsync(t, c->d_clock + kClockWords * (size_t)layer, sizeof t, hipMemcpyDeviceToHost, c->s_clock));
+  HIP_TRY(hipStreamSynchronize(c->s_clock));
   for (int i = 1; i <= kClockEnds; i++) end = std::max(end, t[i * kClockStride]);
   *ms = end > t[0] ? (float)((double)(end - t[0]) * 1e-5) : 0.f;        // 100 MHz ticks
   return CALVO_OK;

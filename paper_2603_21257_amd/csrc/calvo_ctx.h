@@ -2,6 +2,7 @@
 // attention calls; calvo_dispatch.hip: the multi-request dispatcher), and the helpers they share.
 // Not part of the public ABI (see include/calvo.h).
 #pragma once
+#include <atomic>
 #include <condition_variable>
 #include <memory>
 #include <mutex>
@@ -53,6 +54,12 @@ struct calvo_ctx {
   hipEvent_t ev_att[kShadows] = {nullptr, nullptr, nullptr, nullptr};
   bool att_pending[kShadows] = {false, false, false, false};
   unsigned long long* d_clock = nullptr;         // per layer: start and end of its most recent attention launch (LaunchClock)
+  // made by the first calvo_attn_kernel_ms: events behind every attention launch from then on (a program that does
+  // not measure does not pay for them), and the stream that the clock is read on
+  std::atomic<bool> mark_ends{false};
+  std::vector<hipEvent_t> ev_end;
+  std::vector<char> end_marked;                  // per layer: the most recent launch has its event
+  hipStream_t s_clock = nullptr;
   std::vector<char> timed;
   std::vector<int32_t> last_variant, last_wgs;   // per layer: attention kernel chosen, workgroups launched
   int scatter_grid = 64;

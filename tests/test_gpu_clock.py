@@ -43,3 +43,33 @@ def test_duration_of_the_latest_launch(hq, D, dtype, P, S):
             cb.calvo_attn_kernel_ms(ctx, 0)          # nothing was queued for that layer
     finally:
         cb.calvo_destroy(ctx)
+
+
+@pytest.mark.timing
+def test_waits_for_the_layer_that_is_asked_for():
+    """Layer 0's launch, then 60 ms of other layers' on the compute stream and of the default stream's work: the time of
+    layer 0 is there before either is done."""
+    P, S = 49152, 4096
+    s = wl.Shape(2, 32, 8, 128, "bf16", (P + S) // 16 + 8)
+    mk = lambda *shape: torch.randn(shape, device="cuda:0", dtype=torch.bfloat16)
+    pool, q, ks, vs = mk(2, s.pool_blocks, s.blk_elems), mk(S, 32, 128), mk(S, 8, 128), mk(S, 8, 128)
+    out, a, b = torch.empty_like(q), mk(8192, 8192), mk(8192, 8192)
+    r = wl.single_request(s, P, S, 5)[0]
+    torch.cuda.synchronize()
+    ctx = cb.calvo_create(2, 32, 8, 128, cb.CALVO_BF16, s.pool_blocks, pool)
+    try:
+        req = cb.make_request(None, 0, r.table, r.n_prefix_blocks, S, r.n_prefix_blocks)
+        run = lambda l: cb.calvo_prefill_attn(ctx, l, q, ks, vs, out, [req], [0, S])
+        run(0)
+        first = cb.calvo_attn_kernel_ms(ctx, 0)
+        run(0)
+        for _ in range(20):
+            run(1)
+            torch.mm(a, b)
+        ms = cb.calvo_attn_kernel_ms(ctx, 0)
+        t = time.perf_counter()
+        torch.cuda.synchronize()
+        rest = (time.perf_counter() - t) * 1e3
+        assert rest > 10 * first, (rest, first, ms)     # most of the twenty are still to come
+    finally:
+        cb.calvo_destroy(ctx)
