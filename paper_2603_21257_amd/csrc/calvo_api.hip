@@ -504,6 +504,9 @@ int calvo_create(const calvo_config* cfg, calvo_ctx** out) {
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0) c->n_cus = cus;
     else (void)hipGetLastError();
+    int khz = 0;
+    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) == hipSuccess && khz > 0) c->clock_khz = khz;
+    else (void)hipGetLastError();
   }
   c->elt = cfg->dtype == CALVO_BF16 ? 2 : 4;
   c->blk_bytes = (size_t)2 * kBlockTokens * cfg->n_kv_heads * cfg->head_dim * c->elt;
@@ -1619,7 +1622,7 @@ int calvo_attn_kernel_ms(calvo_ctx* c, int layer, float* ms) {
   HIP_TRY(hipMemcpyAsync(t, c->d_clock + kClockWords * (size_t)layer, sizeof t, hipMemcpyDeviceToHost, c->s_clock));
   HIP_TRY(hipStreamSynchronize(c->s_clock));
   for (int i = 1; i <= kClockEnds; i++) end = std::max(end, t[i * kClockStride]);
-  *ms = end > t[0] ? (float)((double)(end - t[0]) * 1e-5) : 0.f;        // 100 MHz ticks
+  *ms = end > t[0] ? (float)((double)(end - t[0]) / c->clock_khz) : 0.f;
   return CALVO_OK;
 }
 

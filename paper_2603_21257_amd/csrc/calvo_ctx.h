@@ -68,6 +68,7 @@ struct calvo_ctx {
   int split_min = 48;             // shortest piece of a cut tile, in 32-key sub-tiles
   int split_fill = 30;            // cost of a workgroup's pipeline fill and drain, in sub-tile steps (launch replay)
   int n_cus = 256;                // compute units of the device
+  int clock_khz = 100000;         // rate of the counter behind d_clock
   std::shared_ptr<void> kept;     // checked and planned batch of the latest calvo_prefill_attn (KeptBatch, calvo_api.hip)
   std::vector<int64_t> plan_key;  // lengths of the batch the cached decision belongs to
   int plan_want = 1;

@@ -17,9 +17,9 @@ struct ReqDesc {
 };
 
 
-// When an attention launch ran, in ticks of the constant 100 MHz counter, in device memory per layer: the
-// first workgroup stores the start, every workgroup raises an end (the counter only grows, so the words need
-// no reset between launches).  A pair of timing events around the launch costs 8 us of host time and two
+// When an attention launch ran, in ticks of the constant counter (100 MHz), in device memory per layer: the
+// first workgroup stores the start, the first wave of every workgroup raises an end when it is done (the counter
+// only grows, so the words need no reset between launches).  A pair of timing events around the launch costs 8 us of host time and two
 // barrier packets per call, more than the launch itself (2.5 us).  The ends are kept in sixteen words a cache
 // line apart: on a single word 2048 workgroups that finish together queue up for 18 us.
 constexpr int kClockEnds = 16, kClockStride = 16;                              // words; stride in 8-byte words

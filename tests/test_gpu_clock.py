@@ -46,6 +46,42 @@ def test_duration_of_the_latest_launch(hq, D, dtype, P, S):
 
 
 @pytest.mark.timing
+@pytest.mark.parametrize("hq,hkv,D,dtype,P,S,pieces", [(32, 8, 128, "bf16", 61440, 4096, 0), (32, 8, 128, "bf16", 4096, 1024, 64),
+                                                       (8, 2, 256, "f32", 8192, 2048, 0), (8, 2, 64, "bf16", 512, 2048, 16)])
+def test_agrees_with_events(hq, hkv, D, dtype, P, S, pieces, monkeypatch):
+    """Against a pair of events on the compute stream, which have the launches' own start and end on top (30 us at most):
+    launches of several milliseconds, and launches of which the merge of many pieces is the larger part."""
+    if pieces:
+        monkeypatch.setenv("CALVO_ATTN_SPLITS", str(pieces))
+    s = wl.Shape(1, hq, hkv, D, dtype, (P + S) // 16 + 8)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    mk = lambda *shape: torch.randn(shape, device="cuda:0").to(dt)
+    pool, q = mk(1, s.pool_blocks, s.blk_elems), mk(S, hq, D)
+    out = torch.empty_like(q)
+    r = wl.single_request(s, P, S, 5)[0]
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    ctx = cb.calvo_create(1, hq, hkv, D, cb.CALVO_BF16 if dtype == "bf16" else cb.CALVO_F32, s.pool_blocks, pool,
+                          compute_stream=stream.cuda_stream)
+    try:
+        req = cb.make_request(None, 0, r.table, r.n_prefix_blocks, S, r.n_prefix_blocks)
+        got = []
+        for _ in range(5):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record(stream)
+            cb.calvo_prefill_attn(ctx, 0, q, None, None, out, [req], [0, S])
+            e1.record(stream)
+            ms = cb.calvo_attn_kernel_ms(ctx, 0)
+            e1.synchronize()
+            got.append((ms, e0.elapsed_time(e1)))
+        print(got, flush=True)
+        ms, ev = sorted(got, key=lambda x: x[1] - x[0])[0]
+        assert 0.98 * ev - 0.03 <= ms <= ev, got
+    finally:
+        cb.calvo_destroy(ctx)
+
+
+@pytest.mark.timing
 def test_waits_for_the_layer_that_is_asked_for():
     """Layer 0's launch, then 60 ms of other layers' on the compute stream and of the default stream's work: the time of
     layer 0 is there before either is done."""
