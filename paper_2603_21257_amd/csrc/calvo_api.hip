@@ -1166,44 +1166,41 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
 // prefill runs one batch through all its layers.  It is found again by content, every table entry compared;
 // nothing of the caller's memory is referred to.
 struct KeptBatch {
-  struct Req { int32_t n_prefix_blocks, first_ingest_block, suffix_len; int64_t n_tab; };
+  struct Req { int32_t n_prefix_blocks, first_ingest_block; int64_t n_tab; };
   std::vector<Req> reqs;
-  std::vector<int32_t> tables, cu;
+  std::vector<int32_t> slens, cu;
   int cb = 0, nck = 0;
   bool small = false, on_device = false;      // see make_attn_plan; ap.blob is what the context's device buffer holds
-  AttnPlan ap;
+  AttnPlan ap;                                // ap.blob has the block tables
 
   bool holds(const calvo_request* rq, int n_reqs, const int32_t* cu_suffix) const {
     if (n_reqs <= 0 || (size_t)n_reqs != reqs.size() || !rq || !cu_suffix) return false;
-    size_t off = 0;
-    for (int r = 0; r < n_reqs; r++) {
-      const Req& k = reqs[(size_t)r];
-      if (rq[r].n_prefix_blocks != k.n_prefix_blocks || rq[r].first_ingest_block != k.first_ingest_block ||
-          rq[r].suffix_len != k.suffix_len)
+    for (int r = 0; r < n_reqs; r++)
+      if (rq[r].n_prefix_blocks != reqs[r].n_prefix_blocks || rq[r].first_ingest_block != reqs[r].first_ingest_block ||
+          rq[r].suffix_len != slens[r])
         return false;
-      if (k.n_tab && (!rq[r].block_table || memcmp(rq[r].block_table, tables.data() + off, (size_t)k.n_tab * 4) != 0)) return false;
-      off += (size_t)k.n_tab;
+    if (memcmp(cu_suffix, cu.data(), cu.size() * 4) != 0) return false;
+    for (int r = 0; r < n_reqs; r++) {
+      const int32_t* tab = ap.blob.data() + ap.lay.tables_off + ap.blob[4 * (size_t)r];      // ReqDesc::table_off
+      if (reqs[r].n_tab && (!rq[r].block_table || memcmp(rq[r].block_table, tab, (size_t)reqs[r].n_tab * 4) != 0)) return false;
     }
-    return memcmp(cu_suffix, cu.data(), cu.size() * 4) == 0;
+    return true;
   }
   void take(const calvo_request* rq, int n_reqs, const int32_t* cu_suffix) {
     reqs.clear();
-    tables.clear();
+    slens.clear();
     for (int r = 0; r < n_reqs; r++) {
       const int64_t nt = (int64_t)rq[r].n_prefix_blocks + (rq[r].suffix_len + kBlockTokens - 1) / kBlockTokens;
-      reqs.push_back({rq[r].n_prefix_blocks, rq[r].first_ingest_block, rq[r].suffix_len, nt});
-      tables.insert(tables.end(), rq[r].block_table, rq[r].block_table + nt);
+      reqs.push_back({rq[r].n_prefix_blocks, rq[r].first_ingest_block, nt});
+      slens.push_back(rq[r].suffix_len);
     }
     cu.assign(cu_suffix, cu_suffix + n_reqs + 1);
   }
 };
 
 // The kernel shape the plan was made for is still the one to take (an environment variable can force it per call).
-bool same_shape(const calvo_ctx* c, const KeptBatch& k) {
-  if (!k.ap.mfma) return true;
-  std::vector<int32_t> slens(k.reqs.size());
-  for (size_t r = 0; r < slens.size(); r++) slens[r] = k.reqs[r].suffix_len;
-  return attn_mfma_choose(slens.data(), (int)slens.size(), k.ap.HW) == k.ap.variant;
+bool same_shape(const KeptBatch& k) {
+  return !k.ap.mfma || attn_mfma_choose(k.slens.data(), (int)k.slens.size(), k.ap.HW) == k.ap.variant;
 }
 
 hipError_t launch_attn(int variant, const AttnParams& p, hipStream_t stream) {
@@ -1412,7 +1409,7 @@ int calvo::host::prefill_attn_impl(calvo_ctx* c, int layer, const void* q, const
   auto fits = [](const AttnPlan& a) { return a.blob.size() <= kStaticBlobInts && a.part_need <= kStaticPartSlots; };
   // a plan made for the other entry point is taken over only if this one would make the same
   if (!known || kept->cb != cb || kept->nck != nck || (use_static ? !kept->small && !fits(kept->ap) : kept->small) ||
-      !same_shape(c, *kept)) {
+      !same_shape(*kept)) {
     if (!kept) {
       c->kept = std::make_shared<KeptBatch>();
       kept = (KeptBatch*)c->kept.get();
