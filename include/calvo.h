@@ -474,8 +474,8 @@ int calvo_dispatch_destroy(calvo_dispatcher* d);
 /* Measurement helper: duration in milliseconds of the most recent attention kernel queued by
  * calvo_prefill_attn for `layer` (from its first workgroup's start to the end of the last workgroup's first wave,
  * merge of split-KV pieces included, taken by the kernels themselves).  Blocks until that kernel has finished; the first call on a
- * context until the compute stream is idle.  From then on attention calls on the context record an event behind
- * their launches (2 to 4 us of host time each).  CALVO_ENOTREADY if none was queued. */
+ * context until the compute stream is idle.  From then on attention calls on the context queue a small launch
+ * and an event behind theirs (5 to 7 us of host time each).  CALVO_ENOTREADY if none was queued. */
 int calvo_attn_kernel_ms(calvo_ctx* ctx, int layer, float* ms);
 
 /* Planning helper (host code, needs no GPU; host_kv is only used as an address): how

@@ -103,7 +103,7 @@ void destroy_partial(calvo_ctx* c) {
     for (auto e : v) if (e) (void)hipEventDestroy(e);
   if (c->d_clock) (void)hipFree(c->d_clock);
   for (auto e : c->ev_end) if (e) (void)hipEventDestroy(e);
-  if (c->s_clock) (void)hipStreamDestroy(c->s_clock);
+  if (c->h_clock) (void)hipHostFree(c->h_clock);
   for (void* p : c->l2_ring)
     if (p) (void)hipHostFree(p);
   for (auto e : c->ev_l2_free) if (e) (void)hipEventDestroy(e);
@@ -1298,7 +1298,10 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
                              d_att + ap.lay.split_off, (int)ap.plan.split_tiles.size(), c->s_compute));
   }
   const bool mark = c->mark_ends.load(std::memory_order_acquire);
-  if (mark) HIP_TRY(hipEventRecord(c->ev_end[(size_t)layer], c->s_compute));
+  if (mark) {
+    HIP_TRY(launch_clock_out(p.clock.words, c->h_clock + 2 * (size_t)layer, c->s_compute));
+    HIP_TRY(hipEventRecord(c->ev_end[(size_t)layer], c->s_compute));
+  }
   c->end_marked[layer] = mark;
   c->timed[layer] = 1;
   c->last_variant[layer] = ap.mfma ? ap.variant : -1;
@@ -1604,22 +1607,24 @@ int calvo_attn_kernel_ms(calvo_ctx* c, int layer, float* ms) {
   if (!c || !ms) return fail(CALVO_EINVAL, "NULL argument");
   if (layer < 0 || layer >= c->cfg.n_layers) return fail(CALVO_EINVAL, "layer %d outside [0, %d)", layer, c->cfg.n_layers);
   if (!c->timed[layer]) return fail(CALVO_ENOTREADY, "no attention kernel was queued for layer %d", layer);
-  // Only the layer's own launch is waited for, also with others queued behind it: by its event, and with the clock
-  // read on a stream that waits for nothing.  The first call finds no events.
+  // Only the layer's own launch is waited for, also with others queued behind it, and nothing is queued for the
+  // answer: a copy on a stream of its own was measured to wait for the compute stream where the two share a hardware
+  // queue (45 of 76 ms of launches behind).  The first call finds no event.
   if (!c->mark_ends.load(std::memory_order_relaxed)) {
-    if (!c->s_clock) HIP_TRY(hipStreamCreateWithFlags(&c->s_clock, hipStreamNonBlocking));
+    if (!c->h_clock) HIP_TRY(hipHostMalloc((void**)&c->h_clock, (size_t)c->cfg.n_layers * 2 * sizeof(unsigned long long), hipHostMallocDefault));
     if (c->ev_end.empty()) c->ev_end.assign((size_t)c->cfg.n_layers, nullptr);
     for (auto& e : c->ev_end)
       if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     c->mark_ends.store(true, std::memory_order_release);
   }
-  if (c->end_marked[layer]) HIP_TRY(hipEventSynchronize(c->ev_end[(size_t)layer]));
-  else HIP_TRY(hipStreamSynchronize(c->s_compute));
-  unsigned long long t[kClockWords], end = 0;
-  HIP_TRY(hipMemcpyAsync(t, c->d_clock + kClockWords * (size_t)layer, sizeof t, hipMemcpyDeviceToHost, c->s_clock));
-  HIP_TRY(hipStreamSynchronize(c->s_clock));
-  for (int i = 1; i <= kClockEnds; i++) end = std::max(end, t[i * kClockStride]);
-  *ms = end > t[0] ? (float)((double)(end - t[0]) / c->clock_khz) : 0.f;
+  unsigned long long* t = c->h_clock + 2 * (size_t)layer;
+  if (c->end_marked[layer]) {
+    HIP_TRY(hipEventSynchronize(c->ev_end[(size_t)layer]));
+  } else {
+    HIP_TRY(launch_clock_out(c->d_clock + kClockWords * (size_t)layer, t, c->s_compute));
+    HIP_TRY(hipStreamSynchronize(c->s_compute));
+  }
+  *ms = t[1] > t[0] ? (float)((double)(t[1] - t[0]) / c->clock_khz) : 0.f;
   return CALVO_OK;
 }
 

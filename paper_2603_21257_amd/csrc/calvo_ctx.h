@@ -54,12 +54,12 @@ struct calvo_ctx {
   hipEvent_t ev_att[kShadows] = {nullptr, nullptr, nullptr, nullptr};
   bool att_pending[kShadows] = {false, false, false, false};
   unsigned long long* d_clock = nullptr;         // per layer: start and end of its most recent attention launch (LaunchClock)
-  // made by the first calvo_attn_kernel_ms: events behind every attention launch from then on (a program that does
-  // not measure does not pay for them), and the stream that the clock is read on
+  // made by the first calvo_attn_kernel_ms: from then on every attention launch is followed by one that copies its start
+  // and end to pinned memory and by an event (a program that does not measure does not pay for them)
   std::atomic<bool> mark_ends{false};
+  unsigned long long* h_clock = nullptr;         // per layer: start, end
   std::vector<hipEvent_t> ev_end;
   std::vector<char> end_marked;                  // per layer: the most recent launch has its event
-  hipStream_t s_clock = nullptr;
   std::vector<char> timed;
   std::vector<int32_t> last_variant, last_wgs;   // per layer: attention kernel chosen, workgroups launched
   int scatter_grid = 64;

@@ -84,6 +84,8 @@ hipError_t launch_scatter_blocks(const void* src, void* pool_layer, const int32_
 hipError_t launch_suffix_append(const AppendParams& p, hipStream_t stream);
 // n_words 32-bit words of page-locked host memory to the device; both 16-byte aligned
 hipError_t launch_upload_words(const int32_t* pinned_src, int32_t* dst, size_t n_words, hipStream_t stream);
+// start and end of a layer's attention launch (LaunchClock) to two words of page-locked host memory
+hipError_t launch_clock_out(const unsigned long long* words, unsigned long long* pinned, hipStream_t stream);
 // test hook: occupies `stream` for about us microseconds (bounded), see kernels_ingest.hip
 hipError_t launch_delay(int us, hipStream_t stream);
 

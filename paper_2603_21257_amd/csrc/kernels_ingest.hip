@@ -94,6 +94,20 @@ hipError_t launch_upload_words(const int32_t* pinned_src, int32_t* dst, size_t n
   return hipGetLastError();
 }
 
+__global__ void __launch_bounds__(64) clock_out_kernel(const unsigned long long* words, unsigned long long* out) {
+  unsigned long long end = 0;
+  for (int i = 1; i <= kClockEnds; i++) {
+    const unsigned long long x = words[i * kClockStride];
+    end = x > end ? x : end;
+  }
+  if (threadIdx.x < 2) out[threadIdx.x] = threadIdx.x ? end : words[0];
+}
+
+hipError_t launch_clock_out(const unsigned long long* words, unsigned long long* pinned, hipStream_t stream) {
+  hipLaunchKernelGGL(clock_out_kernel, dim3(1), dim3(64), 0, stream, words, pinned);
+  return hipGetLastError();
+}
+
 // Suffix token i of request r sits at absolute position P_r + i: slot table_r[pos / 16],
 // row pos % 16 of the K half and of the V half.  One lane per 16-byte chunk of a row.
 __global__ void __launch_bounds__(256) suffix_append_kernel(AppendParams p) {

@@ -91,6 +91,7 @@ def test_waits_for_the_layer_that_is_asked_for():
     pool, q, ks, vs = mk(2, s.pool_blocks, s.blk_elems), mk(S, 32, 128), mk(S, 8, 128), mk(S, 8, 128)
     out, a, b = torch.empty_like(q), mk(8192, 8192), mk(8192, 8192)
     r = wl.single_request(s, P, S, 5)[0]
+    torch.mm(a, b)                                       # its library is loaded before, not while the launches run
     torch.cuda.synchronize()
     ctx = cb.calvo_create(2, 32, 8, 128, cb.CALVO_BF16, s.pool_blocks, pool)
     try:
@@ -106,6 +107,7 @@ def test_waits_for_the_layer_that_is_asked_for():
         t = time.perf_counter()
         torch.cuda.synchronize()
         rest = (time.perf_counter() - t) * 1e3
-        assert rest > 10 * first, (rest, first, ms)     # most of the twenty are still to come
+        print(rest, first, ms, flush=True)
+        assert rest > 10 * first                         # most of the twenty are still to come
     finally:
         cb.calvo_destroy(ctx)
