@@ -37,8 +37,8 @@
  * Environment (for tests and tuning; results stay within the stated tolerance
  * whatever they are set to).  Read by calvo_create: CALVO_ATTN_SPLITS = n
  * cuts every attention tile's context into n pieces; CALVO_SPLIT_MIN,
- * CALVO_SPLIT_FILL = parameters of the automatic cut (shortest piece of a long tile, cost of
- * a workgroup's start and end, both in 32-key steps); CALVO_SCATTER_GRID =
+ * CALVO_SPLIT_FILL = parameters of the automatic cut for bf16 pools of head dim 128 (shortest piece of a
+ * long tile, cost of a workgroup's start and end, both in 32-key steps); CALVO_SCATTER_GRID =
  * workgroups of the zero-copy scatter; CALVO_MERGE_MIB = most bytes of
  * consecutive small layers that one transfer carries (default 256, 0 = every
  * layer by itself).  Read by every calvo_prefill_attn:
@@ -104,7 +104,8 @@ typedef struct {
   int32_t        suffix_len;         /* S >= 0 */
 } calvo_request;
 
-/* Create a context for one pool.  Allocates the staging ring, one event per layer and
+/* Create a context for one pool.  Allocates the staging ring, one event per layer, room for the partial
+ * results of cut contexts (68 MB for bf16 pools of head dim 128, 34 MB for others) and
  * the internal streams on the current device.  CALVO_EINVAL for a bad shape or NULL pool,
  * CALVO_ENOMEM / CALVO_EHIP if a device resource cannot be obtained (nothing is leaked). */
 int calvo_create(const calvo_config* cfg, calvo_ctx** out);
@@ -265,7 +266,8 @@ int calvo_prefill_attn_batch(calvo_ctx* ctx, calvo_batch* batch, int layer, cons
  * context is cut into pieces - lives in one array of fixed size inside the library's device image
  * (35.5 MiB per GPU, held until the process ends; its address is looked up once per device by
  * calvo_create).  Limits: 262144 descriptor words (about 80000 table entries over the batch) and
- * 2048 partial-result slots (pieces x head groups x waves per workgroup); a batch beyond either gets
+ * 2048 partial-result slots (pieces x head groups x waves per workgroup).  A batch whose best plan is beyond either is
+ * planned again with few, long pieces (slower); if that does not fit either it gets
  * CALVO_ENOMEM with nothing queued - use calvo_prefill_attn for it (long layers loaded in chunks are
  * the usual case).  The array is shared by every call on the GPU, whatever the context: calls are
  * ordered by the compute stream they are queued on, and calls that overlap on one GPU from different
@@ -496,9 +498,8 @@ int calvo_ingest_plan(const calvo_request* reqs, int32_t n_reqs, int32_t layer_b
  * dim 128 batch with these lengths on a device with n_cus compute units.  prefix_blocks / suffix_lens:
  * HOST arrays of n_reqs.  Outputs (any may be NULL): *kernel as in calvo_attn_kernel_info,
  * *tile_tokens = suffix tokens per work item, *pieces = split-KV pieces a tile's context is cut into at
- * most (1 = no cut; pieces are never shorter than a 32nd of the tile, at least 8 and at most 48
- * sub-tiles of 32 keys), *n_workgroups of the
- * launch.  The choice replays the launch on the device's workgroup slots and cuts tiles when that
+ * most (1 = no cut; pieces are not shorter than a 32nd of the tile, at least 8 and at most 48 sub-tiles of
+ * 32 keys, except a tile's last one, which is what is left), *n_workgroups of the launch.  The choice replays the launch on the device's workgroup slots and cuts tiles when that
  * shortens it: too few tiles for the chip (the paper's requests: long contexts with short queries), or a
  * workgroup count just above a whole number of rounds.  CALVO_EINVAL for bad arguments. */
 int calvo_attn_plan(int32_t n_q_heads, int32_t n_kv_heads, int32_t n_cus, const int32_t* prefix_blocks,

@@ -204,8 +204,10 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
     dma_1k(pool + half_b + off, voff_v, dma_lds + kVBase + slot * kSlot);
     if constexpr (NI == 2) dma_1k(pool + half_b + off + rows4, voff_v ^ 128u, dma_lds + kVBase + slot * kSlot + 1024);
   };
-  // fill and drain: what lies past the piece is not fetched - the last sub-tile's blocks once more (they are in
-  // the caches), so that the number of requests in flight stays what the waits count on
+  // Fill and drain ask for the piece's last sub-tile again instead of what lies past it (its blocks are in the caches),
+  // so that the number of requests in flight stays what the waits count on.  The steady steps do not: the last of
+  // them run up to KD - 1 K and VD - 1 V sub-tiles past the piece, into blocks that may be another piece's, a chunk
+  // that has not landed or the padding of the table.  Those bytes land in LDS and are never consumed.
   auto request_k = [&](int j) { request_k_at(fetch_off(min(j, n_sub - 1)), j & RM); };
   auto request_v = [&](int j) { request_v_at(fetch_off(min(j, n_sub - 1)), j & RM); };
 

@@ -395,7 +395,7 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
     pv(w);
     if (more) load_v(st + NW);
   };
-  // Two loops: the masks of the last steps cost the others registers otherwise.
+  // Two loops: the steps that every row sees in full spend nothing on masks.
   const int st_full = min(st_end, (pos_min + 1) / (kBlockTokens * KB));
   for (; st < st_full; st += NW) step(Tag<0>{});
   for (; st < st_end; st += NW) step(Tag<1>{});

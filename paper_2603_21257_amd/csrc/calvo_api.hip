@@ -240,8 +240,9 @@ int ensure_att_blob(calvo_ctx* c, size_t n) {
 
 // Room for the split-KV partial results of `slots` (work item, head group, wave) triples.  Growing
 // frees the old buffers, hence waits for the compute stream; contexts for bf16 / head-dim-128
-// pools start with room for the short-query batches (kPartialSlots0), so only long chunk-granular
-// layers ever grow it; the others start with all that a packed-rows launch may use (kStaticPartSlots).
+// pools start with room for the short-query batches (kPartialSlots0) - large batches that are cut to fill the last
+// round and long chunk-granular layers grow it; the others start with all that a packed-rows launch may use
+// (kStaticPartSlots, 34 MB).
 constexpr size_t kPartialSlots0 = 4096;      // 68 MB
 
 int ensure_partials(calvo_ctx* c, size_t slots) {

@@ -1,6 +1,6 @@
 """Host-side planning of an attention launch (calvo_attn_plan): which kernel, how many split-KV pieces.
 Runs without a GPU.  The expectations are properties of the plan, not of any timing: pieces cover a tile
-and are never shorter than 48 sub-tiles, nothing is cut when the chip is full anyway, short suffixes get
+and are not shorter than 48 sub-tiles in long contexts, nothing is cut when the chip is full anyway, short suffixes get
 the small-tile kernel, and a launch just above a whole number of rounds is cut."""
 import numpy as np
 import pytest
@@ -30,7 +30,7 @@ def test_short_suffix_gets_small_tiles_and_pieces():
     assert r["pieces"] > 1
     tiles = 1 + 2 + 7
     assert tiles * 8 < r["workgroups"] <= tiles * 8 * r["pieces"]
-    # pieces are never shorter than 48 sub-tiles: at most n_sub / 48 per tile
+    # the pieces chosen for these contexts have at least 48 sub-tiles: at most n_sub / 48 per tile
     assert r["workgroups"] <= 8 * sum(((p + min((t + 1) * 32, s) + 31) // 32) // 48
                                       for p, s in [(28096, 28), (28304, 61), (38304, 209)] for t in range(-(-s // 32)))
 

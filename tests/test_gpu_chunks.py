@@ -59,8 +59,8 @@ def test_group_sizes_other_than_four():
 
 
 def test_fp32_pool_loads_in_chunks_and_attends_per_layer():
-    """The vector-ALU kernel (fp32 pools, other head dims) has no partial results: chunked loads still
-    give the same bytes and attention waits for the whole layer."""
+    """The packed-rows kernel (fp32 pools, other head dims) does not follow chunks: chunked loads still give the same
+    bytes, and attention (cut into seven pieces here, and merged) waits for the whole layer."""
     shape = wl.Shape(2, 8, 2, 64, "f32", 96)
     w = wl.make_custom(shape, [(48 * 16, 40)], seed=1305)
     check(w, [8, 0])

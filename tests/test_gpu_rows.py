@@ -55,7 +55,7 @@ def test_cut_contexts(dtype, D, pieces, monkeypatch):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_many_rows_several_requests(dtype):
-    """Enough rows for workgroups whose waves all own rows of their own, next to tiny requests."""
+    """Enough tiles for several rounds of workgroups, next to tiny requests."""
     lens = [(64, 700), (0, 1), (320, 515), (16, 0), (1600, 3)]
     w = wl.make_custom(wl.Shape(1, 64, 16, 64, dtype, slots(lens)), lens, seed=11)
     check(w)

@@ -50,7 +50,7 @@ def test_noalloc_matches_prefill_attn_twice_second_smaller(monkeypatch):
 
 
 def test_noalloc_fp32_path_and_repeat_in_one_context():
-    # the vector-ALU kernel (fp32 pool) reads its descriptors from the same array
+    # the packed-rows kernel (fp32 pool) has its descriptors and partial results in the same array
     w = wl.make_custom(wl.Shape(1, 8, 2, 64, "f32", 96), [(512, 50)], seed=73)
     ref, new = _both(w)
     _check(w, ref, new)
