@@ -92,6 +92,10 @@ int scratch_for_device(int dev, unsigned char** out) {
 
 namespace {
 
+// Page-locked memory that kernels read (descriptor uploads) or write (clock) while the host writes and reads it:
+// coherent, whatever the default of the process is.
+constexpr unsigned kShadowFlags = hipHostMallocMapped | hipHostMallocCoherent;
+
 void destroy_partial(calvo_ctx* c) {
   if (!c) return;
   for (void* p : c->staging)
@@ -221,7 +225,7 @@ int ensure_att_blob(calvo_ctx* c, size_t n) {
   int32_t* h[calvo_ctx::kShadows] = {nullptr, nullptr, nullptr, nullptr};
   HIP_TRY(hipMalloc((void**)&d, cap * 4));
   for (int k = 0; k < calvo_ctx::kShadows; k++) {
-    hipError_t e = hipHostMalloc((void**)&h[k], cap * 4, hipHostMallocDefault);
+    hipError_t e = hipHostMalloc((void**)&h[k], cap * 4, kShadowFlags);
     if (e != hipSuccess) {
       (void)hipFree(d);
       for (int j = 0; j < k; j++) (void)hipHostFree(h[j]);
@@ -572,7 +576,7 @@ int calvo_create(const calvo_config* cfg, calvo_ctx** out) {
   CREATE_TRY(hipEventCreateWithFlags(&c->ev_tab_ing, hipEventDisableTiming));
   for (auto& e : c->ev_att) CREATE_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   for (auto& e : c->ev_static) CREATE_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-  for (auto& h : c->h_static) CREATE_TRY(hipHostMalloc((void**)&h, kStaticBlobBytes, hipHostMallocDefault));
+  for (auto& h : c->h_static) CREATE_TRY(hipHostMalloc((void**)&h, kStaticBlobBytes, kShadowFlags));
 #undef CREATE_TRY
   {
     const int src = scratch_for_device(dev, &c->d_static);
@@ -1351,7 +1355,7 @@ int upload_prepared(calvo_ctx* c, PreparedPlan& pp) {
   if (!pp.d_blob) {
     const size_t cap = (bytes + 65535) / 65536 * 65536;
     HIP_TRY(hipMalloc((void**)&pp.d_blob, cap));
-    HIP_TRY(hipHostMalloc((void**)&pp.h_blob, cap, hipHostMallocDefault));
+    HIP_TRY(hipHostMalloc((void**)&pp.h_blob, cap, kShadowFlags));
     pp.blob_bytes = cap;
   }
   if (pp.ap.part_need) {
@@ -1612,7 +1616,7 @@ int calvo_attn_kernel_ms(calvo_ctx* c, int layer, float* ms) {
   // answer: a copy on a stream of its own was measured to wait for the compute stream where the two share a hardware
   // queue (45 of 76 ms of launches behind).  The first call finds no event.
   if (!c->mark_ends.load(std::memory_order_relaxed)) {
-    if (!c->h_clock) HIP_TRY(hipHostMalloc((void**)&c->h_clock, (size_t)c->cfg.n_layers * 2 * sizeof(unsigned long long), hipHostMallocDefault));
+    if (!c->h_clock) HIP_TRY(hipHostMalloc((void**)&c->h_clock, (size_t)c->cfg.n_layers * 2 * sizeof(unsigned long long), kShadowFlags));
     if (c->ev_end.empty()) c->ev_end.assign((size_t)c->cfg.n_layers, nullptr);
     for (auto& e : c->ev_end)
       if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
