@@ -31,7 +31,8 @@ __device__ inline void static_for(F&& f) {
     static_for<B + 1, E>(f);
   }
 }
-constexpr int kPD = 4;   // LDS operand reads run this many MFMAs ahead
+constexpr int kPD = 4;   // LDS operand reads run this many operands ahead
+constexpr float kLazyBound = 65536.f;   // a lane's partial row sum of a sub-tile may reach 2^16 before the reference is raised
 
 // lanes [32,64) of a <-> lanes [0,32) of b (the compiler builtin for this instruction returns
 // its first result twice, hence inline asm)
@@ -58,6 +59,67 @@ __device__ inline float quad_max(float v) {
 __device__ inline float quad_sum(float v) {
   v += __shfl_xor(v, 16, 64);
   return half_swap_sum(v);
+}
+
+// two weights rounded to bf16 (nearest even), packed
+__device__ inline unsigned pack_bf16(float a, float b) {
+  bf16x2 w;
+  w[0] = (__bf16)a;
+  w[1] = (__bf16)b;
+  return __builtin_bit_cast(unsigned, w);
+}
+
+// odd rows of 16 lanes of a <-> even rows of b
+__device__ inline void row_swap(unsigned& a, unsigned& b) {
+  asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
+// One output row's d = 32p .. 32p + 31 from two accumulator tiles (d blocks 2p and 2p + 1, lane (c, g): d = 4g + r of
+// row c), times inv, as 16 bytes per lane; row: the lane's output row.  Lanes g and g ^ 1 exchange halves first: 64
+// consecutive bytes per row and instruction instead of 32.
+__device__ inline void store_out(unsigned short* row, int p, int g, const f32x4& a, const f32x4& b, float inv, bool ok) {
+  unsigned a0 = pack_bf16(a[0] * inv, a[1] * inv), a1 = pack_bf16(a[2] * inv, a[3] * inv);
+  unsigned b0 = pack_bf16(b[0] * inv, b[1] * inv), b1 = pack_bf16(b[2] * inv, b[3] * inv);
+  row_swap(a0, b0);
+  row_swap(a1, b1);
+  if (ok) *(u32x4*)(row + 32 * p + 16 * (g & 1) + 8 * (g >> 1)) = (u32x4){a0, a1, b0, b1};
+}
+
+// O of one block of 16 rows of a piece (tile db: d = 16db + 4g + r of row c); po: the lane's row
+template <int QB>
+__device__ inline void store_piece(float* po, int g, const f32x4 (&o)[8][QB], int qb) {
+#pragma unroll
+  for (int db = 0; db < 8; db++) *(f32x4*)(po + 16 * db + 4 * g) = o[db][qb];
+}
+
+// The suffix rows of request rd and KV head kv from the caller's arrays to the pool, by THREADS threads: four chunks of K and
+// of V in flight per thread while there are that many.
+template <int THREADS>
+__device__ inline void append_rows(const unsigned char* ks, const unsigned char* vs, unsigned char* pool, const int32_t* table,
+                                   const ReqDesc& rd, int n_kv_heads, int kv, int tid) {
+  const int64_t rs = (int64_t)n_kv_heads * kRow, half_b = kBlockTokens * rs;
+  const int n = rd.suffix_len * (kRow / 16);
+  auto move = [&](int i0, auto count) {
+    constexpr int N = decltype(count)::value;
+    u32x4 k[N], v[N];
+    int64_t dst[N];
+#pragma unroll
+    for (int u = 0; u < N; u++) {
+      const int i = i0 + u * THREADS, tok = i / (kRow / 16), pos = rd.prefix_len + tok;
+      const int64_t in_row = kv * kRow + (i % (kRow / 16)) * 16;
+      const int64_t src = (int64_t)(rd.q_off + tok) * rs + in_row;
+      dst[u] = (int64_t)table[pos / kBlockTokens] * (2 * half_b) + (int64_t)(pos % kBlockTokens) * rs + in_row;
+      k[u] = *(const u32x4*)(ks + src);
+      v[u] = *(const u32x4*)(vs + src);
+    }
+#pragma unroll
+    for (int u = 0; u < N; u++) {
+      *(u32x4*)(pool + dst[u]) = k[u];
+      *(u32x4*)(pool + dst[u] + half_b) = v[u];
+    }
+  };
+  int i = tid;
+  for (; i + 3 * THREADS < n; i += 4 * THREADS) move(i, Tag<4>{});
+  for (; i < n; i += THREADS) move(i, Tag<1>{});
 }
 
 // 64 lanes x 16 bytes from global memory (uniform base + per-lane byte offset) to 1 KiB of LDS

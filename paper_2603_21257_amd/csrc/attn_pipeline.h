@@ -1,6 +1,6 @@
-// Paged causal GQA prefill attention for gfx950 (CDNA4), software-pipelined kernel body shared by
-// the 8-wave and the 4-wave workgroup shapes: bf16 storage, head_dim 128,
-// v_mfma_f32_16x16x32_bf16 for both contractions, fp32 online softmax.
+// Paged causal GQA prefill attention for gfx950 (CDNA4), software-pipelined kernel body for short suffixes and little
+// work (attn_wide.h has the one for the rest): bf16 storage, head_dim 128, v_mfma_f32_16x16x32_bf16 for both
+// contractions, fp32 online softmax.
 //
 // Why the 16x16x32 shape: the part is power limited under matrix load, and on normally
 // distributed operands this shape sustains 12 % more flop/s than 32x32x16 at the power limit
@@ -31,13 +31,8 @@
 // produced P_j, P_j is dead once MF(j) has consumed it.  The steady loop is unrolled by the ring
 // depth so that LDS ring slots are immediates.
 //
-// Two workgroup shapes (PipeCfg):
-//   8 waves, ring of 8 slots, one workgroup per CU: waves w and w+4 share a SIMD.  In a step
-//     waves 0-3 run SM(t) then MF(t); waves 4-7 run MF(t) then SM(t+1) (they are half a cycle
-//     ahead), so one wave of a SIMD feeds the matrix pipe while the other uses the vector ALU.
-//   4 waves, ring of 4 slots, two workgroups per CU: every wave runs SM(t) then MF(t); the two
-//     waves of a SIMD belong to different workgroups and nothing couples them.  Tiles of 32 query
-//     tokens per head instead of 64: for short suffixes.
+// Workgroup (PipeCfg): 4 waves, ring of 4 slots, two workgroups per CU: every wave runs SM(t) then MF(t); the two waves of
+// a SIMD belong to different workgroups and nothing couples them.  Tiles of 32 query tokens per head: for short suffixes.
 //
 // (Measured alternatives on the 32x32x16 shape: running QK(t+1), SM(t), PV(t-1) as one interleaved stream in every wave
 // keeps the matrix pipe 96 % busy in a microbenchmark where the two waves of a SIMD run free, but
@@ -79,14 +74,11 @@ template <int NW_, int RING_>
 struct PipeCfg {
   static constexpr int NW = NW_;                       // waves per workgroup
   static constexpr int RING = RING_;                   // LDS ring slots per operand
-  static constexpr int KD = RING_ == 8 ? 7 : 4;        // step t requests K(t + KD) ...
+  static constexpr int KD = RING_;                     // step t requests K(t + KD) ...
   static constexpr int VD = KD - 1;                    // ... and V(t + VD)
-  static constexpr bool TWO_ROLES = NW_ == 8;          // waves NW/2.. run half a cycle ahead
   static constexpr int NI = 8 / NW_;                   // 1 KiB requests per wave, operand and sub-tile
   static constexpr int LDS_BYTES = 2 * RING_ * kSlot;
 };
-
-constexpr float kLazyBound = 65536.f;   // a lane's partial row sum of 16 weights may reach 2^16 before the reference is raised
 
 template <class Cfg_>
 __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char* smem) {
@@ -226,14 +218,6 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
   for (int db = 0; db < 8; db++)
     va_addr[db] = lds + kVBase + v_row * kRow + ((2 * (db ^ (v_row & 7)) + ((c & 3) >> 1)) << 4) + (c & 1) * 8;
 
-  // two weights rounded to bf16 (nearest even), packed
-  auto pack_bf16 = [](float a, float b) -> unsigned {
-    bf16x2 w;
-    w[0] = (__bf16)a;
-    w[1] = (__bf16)b;
-    return __builtin_bit_cast(unsigned, w);
-  };
-
   // ---- pipeline registers: S and P of the sub-tile in flight
   // S tile (kb, qb): keys 16kb + 4g + r of query 16qb + c.  P operand of query block qb: the lane's
   // eight weights in k-slot order (kb, r).
@@ -326,16 +310,13 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
     static_for<0, kPD>([&](auto idx) { pre[decltype(idx)::value] = load_opnd(idx, ks, vs); });
   };
 
-  // ---- steady step t (t & RM == TR).  ahead == false: SM(t), MF(t).  ahead == true: MF(t), SM(t+1).
-  // One body serves both kinds of wave (the flag is wave-uniform: two scalar branches per step),
-  // so that the register allocation of the loop is one and the same for all waves.
-  auto step_steady = [&](auto tr, bool ahead) {
+  // ---- steady step t (t & RM == TR): SM(t), MF(t)
+  auto step_steady = [&](auto tr) {
     constexpr int TR = decltype(tr)::value;
     constexpr int I = (TR + RM) & RM;                // position inside the unrolled iteration
     constexpr int KS = (TR + 1) & RM, VS = TR;       // ring slots of K(t+1), V(t)
     // K(t+KD) and V(t+VD) go into ring slots that nobody reads after the barrier that ended step
-    // t-1.  The waves that run ahead issue theirs after their MFMAs, which keeps the requests out
-    // of the way of the matrix pipe at the start of the step.
+    // t-1.
     auto requests = [&]() {
       constexpr int ik = I + KD - RING, iv = I + VD - RING;      // index into off_cur, negative: previous iteration
       request_k_at(ik == -1 ? off_prev1 : off_cur[ik < 0 ? 0 : ik], (TR + KD) & RM);
@@ -417,36 +398,26 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
         pin(o[db][1]);
       }
     };
-    if (!ahead) {
-      requests();
-      prefetch(Tag<KS>{}, Tag<VS>{});          // lands while the softmax runs
-      valu_half();
-    }
-    mfma_half();                               // ahead: pre[] was read at the end of the previous step
-    if (ahead) {
-      requests();
-      valu_half();
-      prefetch(Tag<(KS + 1) & RM>{}, Tag<(VS + 1) & RM>{});   // K(t+2), V(t+1): first operands of step t+1
-    }
+    requests();
+    prefetch(Tag<KS>{}, Tag<VS>{});            // lands while the softmax runs
+    valu_half();
+    mfma_half();
     // End of the step: everything but the eight most recent requests of this wave has landed, i.e.
-    // K up to t+2 and V up to t+1: what step t+1 reads, and what the waves that run ahead prefetch
-    // at its end for step t+2.  The barrier also separates the LDS reads before it from the
+    // K up to t+2 and V up to t+1: what step t+1 reads.  The barrier also separates the LDS reads before it from the
     // requests after it into the same ring slots.
     wait_vm<8>();
     __syncthreads();
   };
 
   // fill and drain of the pipeline: the same parts one after the other, each guarded.  On entry
-  // sbuf holds S(t) (if t < n_pipe); sm_done: SM(t) has already run (a wave that ran ahead).
-  auto step_edge = [&](int t, bool sm_done) {
+  // sbuf holds S(t) (if t < n_pipe).
+  auto step_edge = [&](int t) {
     request_k(t + KD);
     request_v(t + VD);
     if (t < n_pipe) {
-      if (!sm_done) {
-        bool chg;
-        sm_textbook(sbuf, pbuf, al, chg);
-        needed = __builtin_amdgcn_ballot_w64(chg) != 0;
-      }
+      bool chg;
+      sm_textbook(sbuf, pbuf, al, chg);
+      needed = __builtin_amdgcn_ballot_w64(chg) != 0;
       if (needed) rescale(al);
       pv(t & RM, pbuf);
     }
@@ -467,8 +438,7 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
   __syncthreads();   // all of QK(0) is done before any wave starts requesting into the ring again
 
   int t = 0;
-  step_edge(t++, false);                                      // t = 0: SM(0), PV(0), QK(1)
-  bool ahead_sm = false;                                      // this wave has already run SM(t)
+  step_edge(t++);                                             // t = 0: SM(0), PV(0), QK(1)
   if (t + RING < n_pipe) {
     // steady steps need 1 <= t and t + 1 < n_pipe; the unrolled loop is entered at t = 1 with the
     // block offsets of sub-tiles t+RING-2 .. t+2*RING-1 at hand; each iteration fetches the next RING
@@ -487,26 +457,13 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
 #pragma unroll
       for (int i = 0; i < RING; i++) off_cur[i] = off_nxt[i];
     };
-    const bool ahead = Cfg_::TWO_ROLES && wave >= NW / 2;
-    if (ahead) {
-      // run half a cycle ahead: SM(1) now (textbook update: S(1) comes from the fill step), and the
-      // first operands of MF(1) = {PV(1), QK(2)}
-      bool chg;
-      sm_textbook(sbuf, pbuf, al, chg);
-      needed = __builtin_amdgcn_ballot_w64(chg) != 0;
-      prefetch(Tag<2 & RM>{}, Tag<1>{});
-    }
     for (; t + RING < n_pipe; t += RING) {
       fetch_next(t);
-      static_for<0, RING>([&](auto idx) { step_steady(Tag<(decltype(idx)::value + 1) & RM>{}, ahead); });
+      static_for<0, RING>([&](auto idx) { step_steady(Tag<(decltype(idx)::value + 1) & RM>{}); });
       rotate();
     }
-    ahead_sm = ahead;                                         // SM(t) of the first step after the loop is done
   }
-  for (; t < n_pipe; t++) {                                   // remaining pipelined steps
-    step_edge(t, ahead_sm);
-    ahead_sm = false;
-  }
+  for (; t < n_pipe; t++) step_edge(t);                       // remaining pipelined steps
 
   // What the end of the kernel needs of its arguments is loaded again here: held in scalar registers through the
   // loop, which has none to spare, it would be spilled.
@@ -577,66 +534,30 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
   }
 
   // ---- suffix rows -> pool: by the workgroup that has the end of the context, once per KV head
-  if (ks && wi.sub_end * kSK >= ctx_len && hg * HW % (Hq / Hkv) == 0) {
-    unsigned char* wpool = (unsigned char*)const_cast<void*>(pe->pool_layer);
-    const int32_t* table = pe->tables + rd.table_off;
-    const int64_t rs = half_b / kBlockTokens;                            // bytes between token rows
-    for (int i = tid; i < S * (kRow / 16); i += 64 * NW) {
-      const int tok = i / (kRow / 16), pos = P + tok;
-      const int64_t in_row = kv * kRow + (i % (kRow / 16)) * 16;
-      const int64_t src = (int64_t)(rd.q_off + tok) * rs + in_row;
-      const int64_t dst = (int64_t)table[pos / kBlockTokens] * (2 * half_b) + (int64_t)(pos % kBlockTokens) * rs + in_row;
-      *(u32x4*)(wpool + dst) = *(const u32x4*)(ks + src);
-      *(u32x4*)(wpool + dst + half_b) = *(const u32x4*)(vs + src);
-    }
-  }
+  if (ks && wi.sub_end * kSK >= ctx_len && hg * HW % (Hq / Hkv) == 0)
+    append_rows<64 * NW>(ks, vs, (unsigned char*)const_cast<void*>(pe->pool_layer), pe->tables + rd.table_off, rd, Hkv, kv, tid);
 
-  // ---- one piece of a split tile: leave the unnormalised O, the reference (exponent units) and
-  // the row sum for merge_splits_kernel (32 rows x 128 floats per wave, row = 16qb + c).  Lane holds
-  // d = 16db + 4g + r of the query rows 16qb + c.  A row that lies before the piece's first key saw none: its sums
-  // are no numbers by now, a row sum of 0 says so.  NaN of a row that did see keys stays.
-  if (wi.n_splits > 1) {
-    if (wave_active) {                       // wave-uniform: every lane takes part in the exchanges
-      const int64_t slot = ((int64_t)it * NHG + hg) * NW + wave;
-#pragma unroll
-      for (int qb = 0; qb < 2; qb++) {
-        const float lt = quad_sum(l_run[qb]);
-        if (wq0 + 16 * qb + c < S) {
-          float* po = pe->part_o + (slot * 32 + 16 * qb + c) * kD + 4 * g;
-#pragma unroll
-          for (int db = 0; db < 8; db++) *(f32x4*)(po + 16 * db) = o[db][qb];
-          if (g == 0) {
-            float* pm = pe->part_ml + (slot * 32 + 16 * qb + c) * 2;
-            pm[0] = m_run[qb];
-            pm[1] = pq_min + 16 * qb + c < jb * kSK ? 0.f : lt;
-          }
-        }
-      }
-    }
-    if (threadIdx.x == 0) clock_end(pe->clock.words);
-    return;
-  }
-
-  // ---- normalise and write O[token][head][d]; lane holds d = 16db + 4g + r of the rows 16qb + c
-  if (wave_active) {
-    unsigned short* out = (unsigned short*)pe->out;
+  // ---- results: of a cut tile's piece the unnormalised O, the reference (exponent units) and the row sum, else the
+  // output.  Lane holds d = 16db + 4g + r of the rows 16qb + c.  A row that lies before the piece's first key saw none:
+  // its sums are no numbers by now, a row sum of 0 says so.  NaN of a row that did see keys stays.
+  {
 #pragma unroll
     for (int qb = 0; qb < 2; qb++) {
+      if (wq0 + 16 * qb >= S) continue;      // wave-uniform: every lane takes part in the exchanges
       const float lt = quad_sum(l_run[qb]);
-      const float inv = 1.f / lt;
       const int tokq = wq0 + 16 * qb + c;
-      if (tokq < S) {
-        unsigned short* row = out + ((int64_t)(rd.q_off + tokq) * Hq + hq) * kD + 4 * g;
-#pragma unroll
-        for (int db = 0; db < 8; db++) {
-          bf16x2 a, b;
-          a[0] = (__bf16)(o[db][qb][0] * inv);
-          a[1] = (__bf16)(o[db][qb][1] * inv);
-          b[0] = (__bf16)(o[db][qb][2] * inv);
-          b[1] = (__bf16)(o[db][qb][3] * inv);
-          u32x2 w = {__builtin_bit_cast(unsigned int, a), __builtin_bit_cast(unsigned int, b)};
-          *(u32x2*)(row + 16 * db) = w;
+      if (wi.n_splits > 1) {
+        const int64_t slot = ((int64_t)it * NHG + hg) * NW + wave;
+        if (tokq < S) {
+          const int64_t prow = slot * 32 + 16 * qb + c;
+          store_piece(pe->part_o + prow * kD, g, o, qb);
+          if (g == 0) *(f32x2*)(pe->part_ml + prow * 2) = (f32x2){m_run[qb], P + tokq < jb * kSK ? 0.f : lt};
         }
+      } else {
+        const float inv = 1.f / lt;
+        unsigned short* row = (unsigned short*)pe->out + ((int64_t)(rd.q_off + tokq) * Hq + hq) * kD;
+#pragma unroll
+        for (int d = 0; d < 4; d++) store_out(row, d, g, o[2 * d][qb], o[2 * d + 1][qb], inv, tokq < S);
       }
     }
   }

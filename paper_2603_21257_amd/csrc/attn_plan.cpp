@@ -26,24 +26,37 @@ static int rows_step_cost(bool f32, int head_dim) {
 int attn_pipe_tile_tokens(int heads_per_wg);
 int attn_duo_tile_tokens(int heads_per_wg);
 
-// Two shapes of the pipelined kernel serve bf16 / head-dim-128 batches: kAttnPipe (8-wave workgroups,
-// 64-token tiles for four heads: half the K/V traffic into LDS per query row) and kAttnDuo (two
-// 4-wave workgroups per CU, 32-token tiles).  With the short queries of the paper's Table 1 half of
-// a 64-token tile's waves would idle, so the smaller tiles win there.  The environment variable
-// CALVO_ATTN_VARIANT (3 or 4, read per call: tests switch it inside one process) forces one.
-int attn_mfma_choose(const int32_t* suffix_lens, int n_reqs, int heads_per_wg) {
+// Two kernels serve bf16 / head-dim-128 batches: kAttnPipe (attn_wide.h: 64 query rows per wave, 64-token tiles for four
+// heads: half the K/V traffic into LDS and out of it per query row) and kAttnDuo (attn_pipeline.h: 32 rows per wave, two
+// 4-wave workgroups per CU, 32-token tiles).  The smaller tiles win where half of a 64-token tile would be empty (the short
+// queries of the paper's Table 1), and where the whole batch is little work: they spread it over twice as many workgroups,
+// which fill and drain faster.  Measured, us a call, kAttnPipe / kAttnDuo: 0+1024 tokens (8.5 steps of 32 keys per CU)
+// 34.6 / 29.1, 1024+1000 (25) 51.9 / 45.3, 2048+1000 (41) 59.4 / 60.2, 4096+1000 (73) 82.5 / 87.3, 0+4096 (130)
+// 122 / 134, 61440+4096 2961 / 3362.  One request whose suffix is a single tile of kAttnPipe only takes its append along
+// (launch_layer): there the line lies lower, 2048+64 (2) 22.6 / 19.4, 8192+64 (8) 29.6 / 30.3, 16384+64 (16) 35.6 / 37.7,
+// 65536+64 78 / 87.  The environment variable CALVO_ATTN_VARIANT (3 or 4, read per call: tests switch it
+// inside one process) forces one.
+constexpr int kPipeStepsPerCu = 40, kPipeStepsPerCuOneTile = 12;
+
+int attn_mfma_choose(const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int heads_per_wg, int n_head_groups, int n_cus,
+                     bool by_rows) {
   const char* e = getenv("CALVO_ATTN_VARIANT");
   if (e && (e[0] == '3' || e[0] == '4') && e[1] == 0) return e[0] - '0';
-  // query rows the tiles of each kernel would hold, empty ones included
+  // query rows the tiles of each kernel would hold, empty ones included, and the steps of kAttnPipe
   const int t3 = attn_pipe_tile_tokens(heads_per_wg), t4 = attn_duo_tile_tokens(heads_per_wg);
-  int64_t rows3 = 0, rows4 = 0;
+  int64_t rows3 = 0, rows4 = 0, steps = 0;
   for (int r = 0; r < n_reqs; r++) {
-    rows3 += (int64_t)((suffix_lens[r] + t3 - 1) / t3) * t3;
+    const int64_t tiles = (suffix_lens[r] + t3 - 1) / t3;
+    rows3 += tiles * t3;
     rows4 += (int64_t)((suffix_lens[r] + t4 - 1) / t4) * t4;
+    steps += tiles * (16 * (int64_t)prefix_blocks[r] + (suffix_lens[r] + t3) / 2) / 32;
   }
-  return rows3 * 9 > rows4 * 10 ? kAttnDuo : kAttnPipe;       // the larger tiles would carry over 10 % more rows
+  if (rows3 * 9 > rows4 * 10) return kAttnDuo;                // the larger tiles would carry over 10 % more rows
+  const int line = n_reqs == 1 && suffix_lens[0] <= t3 ? kPipeStepsPerCuOneTile : kPipeStepsPerCu;
+  return !by_rows && steps * n_head_groups < (int64_t)line * n_cus ? kAttnDuo : kAttnPipe;
 }
 
+// blocks of 32 query rows in a workgroup: a wave each, but two per wave in kAttnPipe
 int attn_mfma_waves_per_wg(int variant) { return variant == kAttnPipe ? 8 : 4; }
 
 int attn_mfma_tile_tokens(int variant, int heads_per_wg) {
@@ -204,7 +217,7 @@ extern "C" int calvo_attn_plan_items(int32_t n_q_heads, int32_t n_kv_heads, int3
     max_blocks = std::max(max_blocks, prefix_blocks[r]);
   }
   const int hw = attn_heads_per_wg(n_q_heads, n_kv_heads);
-  const int variant = attn_mfma_choose(suffix_lens, n_reqs, hw);
+  const int variant = attn_mfma_choose(prefix_blocks, suffix_lens, n_reqs, hw, n_q_heads / hw, n_cus);
   const std::vector<PlanTile> tiles = plan_tiles(prefix_blocks, suffix_lens, n_reqs, attn_mfma_tile_tokens(variant, hw));
   const PlanParams p{n_q_heads / hw, n_cus * (8 / attn_mfma_waves_per_wg(variant)), 48, 30, 0};
   PlanItems pi;
@@ -235,7 +248,7 @@ extern "C" int calvo_attn_plan(int32_t n_q_heads, int32_t n_kv_heads, int32_t n_
   for (int r = 0; r < n_reqs; r++)
     if (prefix_blocks[r] < 0 || suffix_lens[r] < 0) return CALVO_EINVAL;
   const int hw = attn_heads_per_wg(n_q_heads, n_kv_heads);
-  const int variant = attn_mfma_choose(suffix_lens, n_reqs, hw);
+  const int variant = attn_mfma_choose(prefix_blocks, suffix_lens, n_reqs, hw, n_q_heads / hw, n_cus);
   const int tt = attn_mfma_tile_tokens(variant, hw);
   const std::vector<PlanTile> tiles = plan_tiles(prefix_blocks, suffix_lens, n_reqs, tt);
   PlanParams p{n_q_heads / hw, n_cus * (8 / attn_mfma_waves_per_wg(variant)), 48, 30, 0};

@@ -6,11 +6,12 @@
 
 namespace calvo {
 
-// which shape of the pipelined MFMA kernel serves a batch with these suffix lengths (attn_plan.cpp);
+// which of the bf16 / head-dim-128 kernels serves a batch with these lengths (attn_plan.cpp);
 // the other calls take its answer
-constexpr int kAttnPipe = 3;   // 8-wave workgroups, 64-token tiles
-constexpr int kAttnDuo = 4;    // two 4-wave workgroups per CU, 32-token tiles
-int attn_mfma_choose(const int32_t* suffix_lens, int n_reqs, int heads_per_wg);
+constexpr int kAttnPipe = 3;   // 64 query rows per wave, 64-token tiles
+constexpr int kAttnDuo = 4;    // 32 query rows per wave, two workgroups per CU, 32-token tiles
+int attn_mfma_choose(const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int heads_per_wg, int n_head_groups, int n_cus,
+                     bool by_rows = false);      // by_rows: by the empty rows of the tiles alone
 int attn_mfma_tile_tokens(int variant, int heads_per_wg);
 int attn_mfma_waves_per_wg(int variant);
 

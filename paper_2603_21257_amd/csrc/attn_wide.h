@@ -1,0 +1,572 @@
+// Paged causal GQA prefill attention for gfx950 (CDNA4): the kernel body for long suffixes.  bf16 storage, head_dim 128,
+// v_mfma_f32_16x16x32_bf16 for both contractions, fp32 online softmax with a lazily raised reference; formulation,
+// operand layouts, swizzles and softmax are those of attn_pipeline.h.
+//
+// What differs: a wave owns 64 query rows instead of 32 and has a SIMD to itself (512 registers), and the softmax runs in
+// the issue gaps of its own MFMAs instead of beside another wave's.  Why: under matrix load the part is at its power limit,
+// and what a step costs beyond its MFMAs is K and V: 16 KB a step from L2 into LDS, and out of LDS once per wave.  With 64
+// rows per wave every operand read feeds four MFMAs instead of two, half the LDS reads per product.  61440+4096 tokens,
+// 32Q/8KV: 3170 -> 2960 us on N(0,1) data, 2605 -> 2370 on zeros (where no power limit hides the schedule); without the
+// requests (wrong results, timing only) 2720 and 2200, so what is left there is the movement of K and V itself.
+//
+// Schedule.  Steady step t:  QK(t+1): 32 MFMAs, PV(t-1): 32 MFMAs, SM(t) between them (S and P double-buffered).
+// Measured for one wave alone on its SIMD: an MFMA of this shape holds the matrix pipe for 16 cycles and the wave's vector
+// instructions back for 8, anything else for 4; a vector instruction takes 4 cycles, an exponential 8.  So behind every
+// MFMA goes at most one instruction of another kind (LDS read, request, wait), which is free, and then two vector
+// instructions or one exponential, which fill the 16 cycles.  A step's 64 MFMAs, 32 exponentials, 83 other vector
+// instructions and 24 LDS reads take 1220 cycles that way (1320 with the same instructions in the order of the
+// dependences); 1380 in the kernel, with the requests and the barrier.
+// The step is written in this order, with scheduling barriers in between.  MFMAs are inline assembly so that O stays in
+// accumulation registers and S in architectural ones, in place: left to the compiler, every value that vector instructions
+// touch as well is moved back and forth (45 to 250 moves a step).  What the compiler then does not know are the wait states
+// between an MFMA and vector instructions around it; in a step the operands are at least sixteen MFMAs apart, elsewhere
+// mfma_settle() is in between.  A spilled register would break that: the kernel must compile without any
+// (tests/test_wide_registers.py).
+// v_mfma_f32_32x32x16_bf16 was measured in the same schedule: 2304 us on zeros, 3292 on N(0,1) data (against 2632 and 3080
+// of this shape at that point): fewer issue slots, more power.
+//
+// Data movement: as in attn_pipeline.h, in rings of eight slots, requests seven sub-tiles ahead for K, five for V (which is
+// read two steps later), one barrier for two steps.  Cache policy bits on the requests (nt, sc0, sc1) do nothing or harm
+// (nt: +5 %).
+#pragma once
+#include "attn_common.h"
+
+namespace calvo {
+namespace attn {
+
+template <int NW_, int RING_>
+struct WideCfg {
+  static constexpr int NW = NW_;                       // waves per workgroup, 64 query rows each
+  static constexpr int RING = RING_;                   // LDS ring slots per operand
+  static constexpr int KA = RING_ - 1;                 // step t requests K(t + KA) ...
+  static constexpr int VA = RING_ - 3;                 // ... and V(t + VA)
+  static constexpr int NI = 8 / NW_;                   // 1 KiB requests per wave, operand and sub-tile
+  static constexpr int LDS_BYTES = 2 * RING_ * kSlot;
+};
+
+// m0 = lds_base + off for the dma_1k_m0 that follows at least one instruction later
+template <int OFF>
+__device__ inline void set_m0(unsigned lds_base, Tag<OFF>) {
+  asm volatile("s_add_u32 m0, %0, %1" : : "s"(lds_base), "n"(OFF) : "scc");
+}
+__device__ inline void set_m0(unsigned lds_base, int off) {
+  asm volatile("s_add_u32 m0, %0, %1" : : "s"(lds_base), "s"(off) : "scc");
+}
+// 64 lanes x 16 bytes from sbase + voff to 1 KiB of LDS at m0
+__device__ inline void dma_1k_m0(const unsigned char* sbase, unsigned voff) {
+  asm volatile("global_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(sbase));
+}
+// byte offset of a ring slot, for slots known at compile time and for others
+template <int S, int ADD>
+__device__ inline constexpr Tag<S * kSlot + ADD> slot_off(Tag<S>, Tag<ADD>) { return {}; }
+template <int ADD>
+__device__ inline int slot_off(int s, Tag<ADD>) { return s * kSlot + ADD; }
+template <int V>
+__device__ inline constexpr int value_of(Tag<V>) { return V; }
+__device__ inline int value_of(int v) { return v; }
+
+// o += a * b with o in accumulation registers.
+__device__ inline void mfma_acc(f32x4& o, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(o) : "v"(a), "v"(b));
+}
+// s = a * b (+ s), in architectural registers
+__device__ inline void mfma_first(f32x4& s, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(s) : "v"(a), "v"(b));
+}
+__device__ inline void mfma_next(f32x4& s, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(s) : "v"(a), "v"(b));
+}
+// The compiler knows nothing of the waits that these need where vector instructions write an operand or touch a result
+// before or after them.
+__device__ inline void mfma_settle() { asm volatile("s_nop 15"); }
+__device__ inline void acc_ready(f32x4 (&o)[8][4]) {
+  mfma_settle();
+#pragma unroll
+  for (int db = 0; db < 8; db++) asm volatile("" : "+a"(o[db][0]), "+a"(o[db][1]), "+a"(o[db][2]), "+a"(o[db][3]));
+}
+
+// largest of four numbers (a NaN counts as nothing)
+__device__ inline float max4(const float (&v)[4]) {
+  float m;
+  asm("v_max3_f32 %0, %1, %2, %3\n\tv_max_f32 %0, %0, %4" : "=&v"(m) : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]));
+  return m;
+}
+
+template <class Cfg_>
+__device__ __forceinline__ void attn_wide(const AttnParams& p, unsigned char* smem) {
+  constexpr int NW = Cfg_::NW, RING = Cfg_::RING, KA = Cfg_::KA, VA = Cfg_::VA, NI = Cfg_::NI;
+  constexpr int RM = RING - 1;
+  constexpr int kVBase = RING * kSlot;                 // V ring follows the K ring
+  const lds_u8* lds = (const lds_u8*)smem;
+  const unsigned lds0 = (unsigned)(size_t)lds;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 15;
+  const int g = lane >> 4;
+
+  // ---- work item decode (wave-uniform)
+  const int HW = p.heads_per_wg;
+  const int TPW = 2 * NW / HW;                         // 32-token blocks of the tile
+  const int NHG = p.n_q_heads / HW;
+  int it, hg;
+  {
+    const int bid = blockIdx.x;
+    if ((NHG & 7) == 0) {
+      const int per = NHG >> 3, rest = bid >> 3;
+      hg = (bid & 7) * per + rest % per;
+      it = rest / per;
+    } else {
+      hg = bid % NHG;
+      it = bid / NHG;
+    }
+  }
+  if (p.item_index) it = p.item_index[it];
+  const WorkItem wi = p.items[it];
+  const ReqDesc rd = p.reqs[wi.req];
+  const int P = rd.prefix_len, S = rd.suffix_len;
+  const int TQ = 32 * TPW;
+  const int q_base = wi.q_tile * TQ;
+  const int Hkv = p.n_kv_heads, Hq = p.n_q_heads;
+  const int kv = hg * HW / (Hq / Hkv);
+  // A wave owns two of the tile's row blocks of 32, one from either end: block vw is (head vw % HW, token block vw / HW).
+  // Blocks with later tokens see more of the diagonal, so the waves have about the same number of sub-tiles there.
+  int hq[2], wq0[2];
+  auto row_block = [&](int h) { return h ? 2 * NW - 1 - wave : wave; };
+#pragma unroll
+  for (int h = 0; h < 2; h++) {
+    const int vw = row_block(h);
+    hq[h] = hg * HW + vw % HW;
+    wq0[h] = q_base + (vw / HW) * 32;
+  }
+  const int ctx_len = P + S;
+  const int jb = wi.sub_begin;
+  const int n_sub = wi.sub_end - jb;
+  const int n_pipe = max(0, min(wi.sub_end, (P + q_base + 1) / kSK) - jb);
+  const int last_blk = (ctx_len + kBlockTokens - 1) / kBlockTokens - 1;
+  typedef const __attribute__((address_space(4))) int64_t* const_i64p;
+  const int n_blk_pad = last_blk + 1 + kTablePad + ((last_blk + 1) & 1);
+  const int wblk = wave / (NW / 2);
+  const const_i64p boffs = (const_i64p)(uintptr_t)(p.blk_offs + rd.table_off + wblk * (n_blk_pad >> 1));
+  const float c2 = p.scale * 1.4426950408889634f;
+
+  // ---- pool -> LDS
+  const unsigned char* pool = (const unsigned char*)p.pool_layer;
+  const unsigned row_b = (unsigned)(Hkv * kD * 2);
+  const unsigned half_b = kBlockTokens * row_b;
+  const int brow0 = (32 / NW) * (wave % (NW / 2)) + (lane >> 4);
+  unsigned voff_k[NI], voff_v[NI];
+#pragma unroll
+  for (int h = 0; h < NI; h++) {
+    const int row = brow0 + 4 * h;
+    voff_k[h] = row * row_b + kv * kRow + (((lane & 15) ^ (row & 15)) << 4);
+    voff_v[h] = half_b + row * row_b + kv * kRow + (((lane & 15) ^ ((row & 7) << 1)) << 4);
+  }
+  const unsigned dma_lds = lds0 + wave * (1024 * NI);
+
+  auto fetch_off = [&](int j) -> int64_t { return boffs[jb + j]; };
+  // request I of a step: the NI of a K sub-tile, then the NI of a V sub-tile, into their ring slots
+  auto request_m0 = [&](auto kslot, auto vslot, auto idx) {
+    constexpr int I = decltype(idx)::value;
+    if constexpr (I < NI) set_m0(dma_lds, slot_off(kslot, Tag<I * 1024>{}));
+    else set_m0(dma_lds, slot_off(vslot, Tag<kVBase + (I - NI) * 1024>{}));
+  };
+  auto request_one = [&](const unsigned char* kbase, const unsigned char* vbase, auto idx) {
+    constexpr int I = decltype(idx)::value;
+    if constexpr (I < NI) dma_1k_m0(kbase, voff_k[I]);
+    else dma_1k_m0(vbase, voff_v[I - NI]);
+  };
+
+  // ---- Q as the B operand of QK^T
+  bf16x8 qB[4][4];
+  {
+    const unsigned short* q = (const unsigned short*)p.q;
+#pragma unroll
+    for (int qb = 0; qb < 4; qb++) {
+      const int tokq = wq0[qb >> 1] + 16 * (qb & 1) + c;
+      const bool ok = tokq < S;
+      const unsigned short* row = q + ((int64_t)(rd.q_off + (ok ? tokq : 0)) * Hq + hq[qb >> 1]) * kD + 8 * g;
+#pragma unroll
+      for (int ks = 0; ks < 4; ks++) {
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (ok) v = *(const u32x4*)(row + 32 * ks);
+        qB[qb][ks] = __builtin_bit_cast(bf16x8, v);
+      }
+    }
+  }
+
+  const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+  f32x4 o[8][4];
+  float m_run[4], l_run[4];
+#pragma unroll
+  for (int qb = 0; qb < 4; qb++) { m_run[qb] = -INFINITY; l_run[qb] = 0.f; }
+
+  // ---- lane-constant operand addresses inside a slot
+  const lds_u8* ka_addr[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ks++) ka_addr[ks] = lds + c * kRow + (((4 * ks + g) ^ c) << 4);
+  const int v_row = 4 * g + (c >> 2);
+  const lds_u8* va_addr[8];
+#pragma unroll
+  for (int db = 0; db < 8; db++)
+    va_addr[db] = lds + kVBase + v_row * kRow + ((2 * (db ^ (v_row & 7)) + ((c & 3) >> 1)) << 4) + (c & 1) * 8;
+
+  f32x4 sb[2][2][4];                                   // [parity][kb][qb]
+  bf16x8 pb[2][4];
+
+  auto expo = [&](float s, int qb) -> float { return __builtin_fmaf(s, c2, -m_run[qb]); };
+  auto row_max = [&](const f32x4& a, const f32x4& b) -> float {
+    float mx = fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]));
+    mx = fmaxf(mx, fmaxf(fmaxf(b[0], b[1]), fmaxf(b[2], b[3])));
+    return quad_max(mx);
+  };
+  auto weights_of = [&](const f32x4& s0, const f32x4& s1, int qb, float& ps, bf16x8& pw) {
+    float w[8];
+#pragma unroll
+    for (int e = 0; e < 8; e++) w[e] = __builtin_amdgcn_exp2f(expo(e < 4 ? s0[e & 3] : s1[e & 3], qb));
+    ps = ((w[0] + w[1]) + (w[2] + w[3])) + ((w[4] + w[5]) + (w[6] + w[7]));
+    pw = __builtin_bit_cast(bf16x8, (u32x4){pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3]), pack_bf16(w[4], w[5]), pack_bf16(w[6], w[7])});
+  };
+  // Softmax of query blocks QB0 .. QB0 + N - 1 of one sub-tile (scores possibly masked with -inf): weights against the
+  // current reference, unless a partial row sum passes the bound (or is not a number, or there is no reference yet).
+  auto softmax = [&](auto qb0, auto&& s, bf16x8* pw) {
+    constexpr int QB0 = decltype(qb0)::value, N = sizeof(s[0]) / sizeof(f32x4);
+    float ps[N];
+    bool above = false;
+#pragma unroll
+    for (int q = 0; q < N; q++) {
+      weights_of(s[0][q], s[1][q], QB0 + q, ps[q], pw[q]);
+      above |= !(ps[q] <= kLazyBound);
+    }
+    if (__builtin_amdgcn_ballot_w64(above) != 0) {
+      float alpha[N];
+      bool changed = false;
+#pragma unroll
+      for (int q = 0; q < N; q++) {
+        const int qb = QB0 + q;
+        const float m_new = fmaxf(m_run[qb], row_max(s[0][q], s[1][q]) * c2);
+        alpha[q] = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
+        changed |= m_run[qb] != -INFINITY && !(alpha[q] == 1.f);         // without a reference O is 0
+        m_run[qb] = m_new;
+        l_run[qb] = l_run[qb] * alpha[q];
+        weights_of(s[0][q], s[1][q], qb, ps[q], pw[q]);
+      }
+      if (__builtin_amdgcn_ballot_w64(changed) != 0) {
+        acc_ready(o);
+#pragma unroll
+        for (int db = 0; db < 8; db++)
+#pragma unroll
+          for (int q = 0; q < N; q++) o[db][QB0 + q] *= alpha[q];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < N; q++) l_run[QB0 + q] += ps[q];
+  };
+  // S of N query blocks from QB0 on
+  auto qk = [&](int slot, auto qb0, auto&& s) {
+    constexpr int QB0 = decltype(qb0)::value, N = sizeof(s[0]) / sizeof(f32x4);
+#pragma unroll
+    for (int kb = 0; kb < 2; kb++)
+#pragma unroll
+      for (int ks = 0; ks < 4; ks++) {
+        const bf16x8 ka = read_k(ka_addr[ks] + 16 * kb * kRow + slot * kSlot);
+#pragma unroll
+        for (int q = 0; q < N; q++) {
+          if (ks == 0) mfma_first(s[kb][q], ka, qB[QB0 + q][ks]);
+          else mfma_next(s[kb][q], ka, qB[QB0 + q][ks]);
+        }
+      }
+    mfma_settle();
+#pragma unroll
+    for (int q = 0; q < N; q++) asm volatile("" : "+v"(s[0][q]), "+v"(s[1][q]));
+  };
+  // O of N query blocks from QB0 on
+  auto pv = [&](int slot, auto qb0, auto n, const bf16x8* pw) {
+    constexpr int QB0 = decltype(qb0)::value, N = decltype(n)::value;
+    acc_ready(o);
+#pragma unroll
+    for (int db = 0; db < 8; db++) {
+      const bf16x8 a = read_vt(va_addr[db] + slot * kSlot);
+#pragma unroll
+      for (int q = 0; q < N; q++) mfma_acc(o[db][QB0 + q], a, pw[q]);
+    }
+  };
+  auto qk4 = [&](int slot, f32x4 (&s)[2][4]) { qk(slot, Tag<0>{}, s); };
+  auto softmax4 = [&](const f32x4 (&s)[2][4], bf16x8 (&pw)[4]) { softmax(Tag<0>{}, s, pw); };
+  auto pv4 = [&](int slot, const bf16x8 (&pw)[4]) { pv(slot, Tag<0>{}, Tag<4>{}, pw); };
+
+  // operand i of a step: K operand (key block i%2, d slice i/2) for i < 8, V^T operand of d block i - 8 beyond
+  auto load_opnd = [&](auto idx, auto ks, auto vs) -> bf16x8 {
+    constexpr int i = decltype(idx)::value, k = i & 7;
+    if constexpr (i >= 8) return read_vt(va_addr[k] + value_of(slot_off(vs, Tag<0>{})));
+    else return read_k(ka_addr[k >> 1] + value_of(slot_off(ks, Tag<16 * (k & 1) * kRow>{})));
+  };
+  bf16x8 pre[kPD];
+
+  // ---- steady step t in ring slot TR: QK(t+1), SM(t), PV(t-1); requests K and V of t + LA from base
+  auto step = [&](auto par, auto&& slot, const unsigned char* kbase, const unsigned char* vbase) {
+    constexpr int C = decltype(par)::value;
+    const auto KS = slot(Tag<1>{});
+    const auto VS = slot(Tag<-1>{});
+    const auto KN = slot(Tag<2>{});
+    const auto KR = slot(Tag<KA>{});
+    const auto VR = slot(Tag<VA>{});
+    f32x4 (&s)[2][4] = sb[C];
+    f32x4 (&sn)[2][4] = sb[C ^ 1];
+    const bf16x8 (&pp)[4] = pb[C ^ 1];
+    u32x4 pn[4];
+    float x[2], ps[4], w[2];
+    bf16x8 op[16 + kPD];
+    static_for<0, kPD>([&](auto idx) { op[decltype(idx)::value] = pre[decltype(idx)::value]; });
+    static_for<0, 16>([&](auto idx) {
+      constexpr int i = decltype(idx)::value, k = i & 7;
+      constexpr int wq = i >> 2, wkb = (i >> 1) & 1, wr = 2 * (i & 1);     // weight pair i: query block, key block, row
+      // request of this group, where a group reads one operand half only
+      constexpr int rq = i < 4 ? i * NI / 4 : i >= 12 ? NI + (i - 12) * NI / 4 : -1;
+      constexpr bool rq_on = NI == 4 ? rq >= 0 : rq >= 0 && (i & 1) == 0;
+      static_for<0, 4>([&](auto qtag) {
+        constexpr int qb = decltype(qtag)::value, kb = k & 1, ks = k >> 1;
+        if constexpr (i >= 8) mfma_acc(o[k][qb], op[i], pp[qb]);
+        else if constexpr (ks == 0) mfma_first(sn[kb][qb], op[i], qB[qb][ks]);
+        else mfma_next(sn[kb][qb], op[i], qB[qb][ks]);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (qb == 0) {
+          if constexpr (i + kPD < 16) op[i + kPD] = load_opnd(Tag<i + kPD>{}, KS, VS);
+          else op[i + kPD] = load_opnd(Tag<i + kPD - 16>{}, KN, VS);
+          x[0] = expo(s[wkb][wq][wr], wq);
+          x[1] = expo(s[wkb][wq][wr + 1], wq);
+        } else if constexpr (qb == 1) {
+          if constexpr (rq_on) request_m0(KR, VR, Tag<rq>{});
+          __builtin_amdgcn_sched_barrier(0);
+          w[0] = __builtin_amdgcn_exp2f(x[0]);
+          pin(w[0]);
+        } else if constexpr (qb == 2) {
+          if constexpr (rq_on) request_one(kbase, vbase, Tag<rq>{});
+          __builtin_amdgcn_sched_barrier(0);
+          w[1] = __builtin_amdgcn_exp2f(x[1]);
+          pin(w[1]);
+        } else {
+          if constexpr (i < 15) pin(op[i + 1]);                       // its wait goes here
+          __builtin_amdgcn_sched_barrier(0);
+          ps[wq] = (i & 3) == 0 ? w[0] + w[1] : (ps[wq] + w[0]) + w[1];
+          unsigned pk = pack_bf16(w[0], w[1]);
+          pin(pk);
+          pn[wq][i & 3] = pk;
+          pin(ps[wq]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    });
+    static_for<0, kPD>([&](auto idx) { pre[decltype(idx)::value] = op[16 + decltype(idx)::value]; });
+#pragma unroll
+    for (int qb = 0; qb < 4; qb++) pb[C][qb] = __builtin_bit_cast(bf16x8, pn[qb]);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(max4(ps) <= kLazyBound)) != 0, 0)) {
+      acc_ready(o);
+#pragma unroll
+      for (int qb = 0; qb < 4; qb++) {
+        const float d = fmaxf(expo(row_max(s[0][qb], s[1][qb]), qb), 0.f);
+        const float a = __builtin_amdgcn_exp2f(-d);
+        l_run[qb] *= a;
+        m_run[qb] += d;
+        weights_of(s[0][qb], s[1][qb], qb, ps[qb], pb[C][qb]);
+#pragma unroll
+        for (int db = 0; db < 8; db++) o[db][qb] *= a;
+      }
+      acc_ready(o);
+    }
+#pragma unroll
+    for (int qb = 0; qb < 4; qb++) l_run[qb] += ps[qb];
+    // One barrier for two steps.  At the end of an even step t K up to t + 4 and V up to t + 1 have landed (everything
+    // but the requests of the last three steps), which is what steps t + 1 and t + 2 read and prefetch; their requests
+    // go into slots that nobody reads until the next barrier.
+    if constexpr (C == 0) {
+      wait_vm<3 * 2 * NI>();
+      __syncthreads();
+    }
+  };
+
+  // ---- fill: K(0..KA) and V(0..VA).  What the first sub-tile needs comes first: the wait for Q, which the compiler puts
+  // in front of the first product, is a wait for every request before it.
+  auto request_range = [&](auto k0, auto k1, auto v0, auto v1) {
+    static_for<0, KA + 1>([&](auto j) {
+      constexpr int J = decltype(j)::value;
+      constexpr bool K = J >= decltype(k0)::value && J < decltype(k1)::value, V = J >= decltype(v0)::value && J < decltype(v1)::value;
+      if constexpr (K || V) {
+        const unsigned char* base = pool + fetch_off(min(J, n_pipe - 1));
+        static_for<K ? 0 : NI, V ? 2 * NI : NI>([&](auto idx) {
+          request_m0(j, j, idx);
+          asm volatile("s_nop 0");
+          request_one(base, base, idx);
+        });
+      }
+    });
+  };
+  int t = 0;
+  if (n_pipe > 0) request_range(Tag<0>{}, Tag<2>{}, Tag<0>{}, Tag<1>{});
+#pragma unroll
+  for (int db = 0; db < 8; db++)
+#pragma unroll
+    for (int qb = 0; qb < 4; qb++) {
+      o[db][qb] = zero4;
+      asm volatile("" : "+a"(o[db][qb]));               // set here, under the first requests
+    }
+  if (n_pipe > 0) {
+#pragma unroll
+    for (int qb = 0; qb < 4; qb++)
+#pragma unroll
+      for (int ks = 0; ks < 4; ks++) pin(qB[qb][ks]);
+    wait_vm<0>();
+    __syncthreads();
+    request_range(Tag<2>{}, Tag<5>{}, Tag<1>{}, Tag<2>{});
+    request_range(Tag<5>{}, Tag<KA + 1>{}, Tag<2>{}, Tag<VA + 1>{});
+    qk4(0, sb[0]);
+    softmax4(sb[0], pb[0]);
+    t = 1;
+    if (n_pipe > 1) {
+      qk4(1, sb[1]);
+      // K(0..4), V(0..1) have landed; K(0), whose slot the first steady step asks for, is done with
+      wait_vm<(KA - 4 + VA - 1) * NI>();
+      __syncthreads();
+      if (t + 2 < n_pipe) {
+        static_for<0, kPD>([&](auto idx) { pre[decltype(idx)::value] = load_opnd(idx, Tag<2>{}, Tag<0>{}); });
+        constexpr int DV = KA - VA;
+        if (t + RING < n_pipe) {
+          // offsets of sub-tiles t + VA .. t + KA + RING - 1
+          int64_t off_cur[RING + DV], off_nxt[RING];
+#pragma unroll
+          for (int i = 0; i < RING + DV; i++) off_cur[i] = fetch_off(min(t + VA + i, n_pipe - 1));
+          for (; t + RING < n_pipe; t += RING) {
+#pragma unroll
+            for (int i = 0; i < RING; i++) off_nxt[i] = fetch_off(min(t + KA + RING + i, n_pipe - 1));
+            static_for<0, RING>([&](auto h) {
+              constexpr int H = decltype(h)::value;
+              step(Tag<(H + 1) & 1>{}, [](auto d) { return Tag<(H + 1 + decltype(d)::value) & RM>{}; }, pool + off_cur[H + DV], pool + off_cur[H]);
+            });
+#pragma unroll
+            for (int i = 0; i < DV; i++) off_cur[i] = off_cur[RING + i];
+#pragma unroll
+            for (int i = 0; i < RING; i++) off_cur[DV + i] = off_nxt[i];
+          }
+        }
+        // pairs of steps, ring slots at run time
+        for (; t + 2 < n_pipe; t += 2) {
+          auto base = [&](int j) { return pool + fetch_off(min(j, n_pipe - 1)); };
+          const unsigned char *k0 = base(t + KA), *k1 = base(t + 1 + KA), *v0 = base(t + VA), *v1 = base(t + 1 + VA);
+          step(Tag<1>{}, [&](auto d) -> int { return (t + decltype(d)::value) & RM; }, k0, v0);
+          step(Tag<0>{}, [&](auto d) -> int { return (t + 1 + decltype(d)::value) & RM; }, k1, v1);
+        }
+      }
+    }
+  }
+
+  typedef const __attribute__((address_space(4))) AttnParams* const_paramsp;
+  const_paramsp pe = (const_paramsp)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(pe));
+
+  // ---- sub-tiles on or past the diagonal: requested in groups of at most RING - 2
+  const unsigned char* ks = (const unsigned char*)pe->k_suffix;
+  const unsigned char* vs = (const unsigned char*)pe->v_suffix;
+  auto request_tail = [&](int j) {
+    const int sfx_blk = 2 * (jb + j) + wblk - P / kBlockTokens;
+    const int64_t boff = fetch_off(j);
+    const unsigned char *kb = pool + boff, *vb = kb;
+    if (ks && sfx_blk >= 0) {
+      const int64_t soff = (int64_t)rd.q_off * row_b + (int64_t)sfx_blk * half_b;
+      kb = ks + soff;
+      vb = vs + soff - half_b;
+    }
+#pragma unroll
+    for (int h = 0; h < NI; h++) {
+      const bool live = (jb + j) * kSK + wblk * 16 + brow0 + 4 * h < ctx_len;
+      const unsigned l_k = __builtin_amdgcn_readfirstlane(dma_lds + (j & RM) * kSlot + h * 1024);
+      if (live) {
+        dma_1k(scalar_ptr(kb), voff_k[h], l_k);
+        dma_1k(scalar_ptr(vb), voff_v[h], l_k + kVBase);
+      } else {
+        *(u32x4*)(smem + (l_k - lds0) + kVBase + (lane << 4)) = (u32x4){0u, 0u, 0u, 0u};
+      }
+    }
+  };
+  constexpr int TG = RING - 2;
+  auto request_group = [&](int j0) {
+    for (int j = j0; j < min(n_sub, j0 + TG); j++) request_tail(j);
+  };
+
+  // ---- drain: PV(t-1), then the one or two sub-tiles that are left; S(t) is in sb[1] (t odd), P(t-1) in pb[0].  The first
+  // group of the tail is requested before them: the slots of sub-tiles t and t + 1 are not among its own.
+  if (n_pipe > 0) pv4((t - 1) & RM, pb[0]);
+  wait_vm<0>();
+  __syncthreads();
+  request_group(n_pipe);
+  if (t > 0 && t < n_pipe) {
+    softmax4(sb[1], pb[1]);
+    pv4(t & RM, pb[1]);
+    if (t + 1 < n_pipe) {
+      qk4((t + 1) & RM, sb[0]);
+      softmax4(sb[0], pb[0]);
+      pv4((t + 1) & RM, pb[0]);
+    }
+  }
+  for (int j0 = n_pipe; j0 < n_sub; j0 += TG) {
+    if (j0 > n_pipe) {
+      __syncthreads();                                   // everyone has read the group before
+      request_group(j0);
+    }
+    wait_vm<0>();
+    __syncthreads();
+    for (int j = j0; j < min(n_sub, j0 + TG); j++) {
+      const int k0 = (jb + j) * kSK;
+      // row block by row block: V of a sub-tile that a block sees nothing of stays away from it (0 times infinity)
+      static_for<0, 2>([&](auto hh) {
+        constexpr int H = decltype(hh)::value;
+        const int pq_min = P + wq0[H];
+        if (!(wq0[H] < S && k0 <= P + min(wq0[H] + 32, S) - 1)) return;
+        f32x4 s2[2][2];
+        qk(j & RM, Tag<2 * H>{}, s2);
+        if (k0 + 31 > pq_min) {
+#pragma unroll
+          for (int kb = 0; kb < 2; kb++)
+#pragma unroll
+            for (int q = 0; q < 2; q++)
+#pragma unroll
+              for (int r = 0; r < 4; r++)
+                if (k0 + 16 * kb + 4 * g + r > pq_min + 16 * q + c) s2[kb][q][r] = -INFINITY;
+        }
+        bf16x8 pw[2];
+        softmax(Tag<2 * H>{}, s2, pw);
+        pv(j & RM, Tag<2 * H>{}, Tag<2>{}, pw);
+      });
+    }
+  }
+
+  // ---- suffix rows -> pool: once per KV head, by the workgroup of the tile's first piece (the last one has the diagonal)
+  if (ks && jb == 0 && hg * HW % (Hq / Hkv) == 0)
+    append_rows<64 * NW>(ks, vs, (unsigned char*)const_cast<void*>(pe->pool_layer), pe->tables + rd.table_off, rd, Hkv, kv, tid);
+
+  // ---- results: of a cut tile's piece the unnormalised O, the reference (exponent units) and the row sum, else the output
+  acc_ready(o);
+#pragma unroll
+  for (int qb = 0; qb < 4; qb++) {
+    if (wq0[qb >> 1] + 16 * (qb & 1) >= S) continue;     // wave-uniform: every lane takes part in the exchanges
+    const float lt = quad_sum(l_run[qb]);
+    const int tokq = wq0[qb >> 1] + 16 * (qb & 1) + c;
+    if (wi.n_splits > 1) {
+      const int64_t slot = ((int64_t)it * NHG + hg) * (2 * NW) + row_block(qb >> 1);
+      // a row that lies before the piece's first key saw none: a row sum of 0 says so
+      if (tokq < S) {
+        const int64_t prow = slot * 32 + 16 * (qb & 1) + c;
+        store_piece(pe->part_o + prow * kD, g, o, qb);
+        if (g == 0) *(f32x2*)(pe->part_ml + prow * 2) = (f32x2){m_run[qb], P + tokq < jb * kSK ? 0.f : lt};
+      }
+    } else {
+      const float inv = 1.f / lt;
+      unsigned short* row = (unsigned short*)pe->out + ((int64_t)(rd.q_off + tokq) * Hq + hq[qb >> 1]) * kD;
+#pragma unroll
+      for (int d = 0; d < 4; d++) store_out(row, d, g, o[2 * d][qb], o[2 * d + 1][qb], inv, tokq < S);
+    }
+  }
+  if (threadIdx.x == 0) clock_end(pe->clock.words);
+}
+
+}  // namespace attn
+}  // namespace calvo

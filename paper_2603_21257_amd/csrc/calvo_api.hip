@@ -1122,9 +1122,9 @@ int kept_pieces(calvo_ctx* c, int variant, const calvo_request* reqs, int n_reqs
 
 // cb > 0: the layer was loaded in nck chunks of cb block indices and attention follows the chunks.
 // small: what needs the least room for descriptors and partial results - a packed-rows launch without work
-// items (uncut tiles), the long pieces only of the others.
+// items (uncut tiles), the long pieces only of the others.  by_rows: see attn_mfma_choose.
 void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const int32_t* cu_suffix, int total, int cb,
-                    int nck, AttnPlan& ap, bool small = false) {
+                    int nck, AttnPlan& ap, bool small = false, bool by_rows = false) {
   const calvo_config& cf = c->cfg;
   ap.n_reqs = n_reqs;
   ap.total = total;
@@ -1133,7 +1133,7 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
   ap.variant = 0;
   std::vector<int32_t> pblocks(n_reqs), slens(n_reqs);
   for (int r = 0; r < n_reqs; r++) { pblocks[r] = reqs[r].n_prefix_blocks; slens[r] = reqs[r].suffix_len; }
-  if (ap.mfma) ap.variant = attn_mfma_choose(slens.data(), n_reqs, ap.HW);
+  if (ap.mfma) ap.variant = attn_mfma_choose(pblocks.data(), slens.data(), n_reqs, ap.HW, cf.n_q_heads / ap.HW, c->n_cus, by_rows);
   ap.tile_tokens = ap.mfma ? attn_mfma_tile_tokens(ap.variant, ap.HW) : 1;
   // Work items: tiles of suffix tokens, heaviest first, each possibly cut into split-KV pieces
   // (consecutive work items) that the merge kernel combines; see attn_plan.cpp.
@@ -1173,9 +1173,9 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
 struct KeptBatch {
   struct Req { int32_t n_prefix_blocks, first_ingest_block; int64_t n_tab; };
   std::vector<Req> reqs;
-  std::vector<int32_t> slens, cu;
+  std::vector<int32_t> pblocks, slens, cu;
   int cb = 0, nck = 0;
-  bool small = false, on_device = false;      // see make_attn_plan; ap.blob is what the context's device buffer holds
+  bool small = false, by_rows = false, on_device = false;      // see make_attn_plan; ap.blob is what the context's device buffer holds
   AttnPlan ap;                                // ap.blob has the block tables
 
   bool holds(const calvo_request* rq, int n_reqs, const int32_t* cu_suffix) const {
@@ -1193,10 +1193,12 @@ struct KeptBatch {
   }
   void take(const calvo_request* rq, int n_reqs, const int32_t* cu_suffix) {
     reqs.clear();
+    pblocks.clear();
     slens.clear();
     for (int r = 0; r < n_reqs; r++) {
       const int64_t nt = (int64_t)rq[r].n_prefix_blocks + (rq[r].suffix_len + kBlockTokens - 1) / kBlockTokens;
       reqs.push_back({rq[r].n_prefix_blocks, rq[r].first_ingest_block, nt});
+      pblocks.push_back(rq[r].n_prefix_blocks);
       slens.push_back(rq[r].suffix_len);
     }
     cu.assign(cu_suffix, cu_suffix + n_reqs + 1);
@@ -1204,8 +1206,9 @@ struct KeptBatch {
 };
 
 // The kernel shape the plan was made for is still the one to take (an environment variable can force it per call).
-bool same_shape(const KeptBatch& k) {
-  return !k.ap.mfma || attn_mfma_choose(k.slens.data(), (int)k.slens.size(), k.ap.HW) == k.ap.variant;
+bool same_shape(const calvo_ctx* c, const KeptBatch& k) {
+  return !k.ap.mfma || attn_mfma_choose(k.pblocks.data(), k.slens.data(), (int)k.slens.size(), k.ap.HW, c->cfg.n_q_heads / k.ap.HW, c->n_cus,
+                                        k.by_rows) == k.ap.variant;
 }
 
 hipError_t launch_attn(int variant, const AttnParams& p, hipStream_t stream) {
@@ -1417,13 +1420,13 @@ int calvo::host::prefill_attn_impl(calvo_ctx* c, int layer, const void* q, const
   auto fits = [](const AttnPlan& a) { return a.blob.size() <= kStaticBlobInts && a.part_need <= kStaticPartSlots; };
   // a plan made for the other entry point is taken over only if this one would make the same
   if (!known || kept->cb != cb || kept->nck != nck || (use_static ? !kept->small && !fits(kept->ap) : kept->small) ||
-      !same_shape(*kept)) {
+      !same_shape(c, *kept)) {
     if (!kept) {
       c->kept = std::make_shared<KeptBatch>();
       kept = (KeptBatch*)c->kept.get();
     }
     kept->reqs.clear();                       // holds nothing until the plan is made
-    kept->on_device = kept->small = false;
+    kept->on_device = kept->small = kept->by_rows = false;
     kept->ap = AttnPlan();
     kept->cb = cb;
     kept->nck = nck;
@@ -1432,6 +1435,13 @@ int calvo::host::prefill_attn_impl(calvo_ctx* c, int layer, const void* q, const
       kept->small = true;
       kept->ap = AttnPlan();
       make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, kept->ap, true);
+      // What this entry point accepts depends on the kernel that the suffix lengths alone ask for: a batch that fits
+      // with it fits for good.
+      if (!fits(kept->ap) && kept->ap.mfma) {
+        kept->by_rows = true;
+        kept->ap = AttnPlan();
+        make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, kept->ap, true, true);
+      }
     }
     kept->take(reqs, n_reqs, cu_suffix);
   }

@@ -53,7 +53,7 @@ struct AttnParams {
   int32_t n_q_heads, n_kv_heads, head_dim;
   int32_t heads_per_wg;     // MFMA kernel: 1, 2 or 4 query heads of one KV group per workgroup
   int32_t tile_tokens;      // suffix tokens per work item
-  int32_t waves_per_wg;     // waves of an attention workgroup (8 or 4): layout of the split-KV partials
+  int32_t waves_per_wg;     // blocks of 32 query rows in an attention workgroup (8 or 4): layout of the split-KV partials
   float scale;              // softmax scale (natural-exponent units)
   // split-KV partial results, used by work items with n_splits > 1: per work item, head group, wave
   // (head of the group x 32-token half of the tile): part_o [32 rows][D] fp32 unnormalised,
