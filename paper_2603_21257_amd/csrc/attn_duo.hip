@@ -1,14 +1,14 @@
-// The 4-wave shape of the pipelined attention kernel (attn_pipeline.h): workgroup = 4 query heads
-// of one KV group x one token tile of 32, two workgroups per CU (64 KiB of LDS each: K and V rings
-// of four 8 KiB slots), so the two waves of a SIMD belong to different workgroups.  Tiles of 32 query tokens instead of 64: with the short queries of the paper's
-// Table 1 (28 / 61 / 209 tokens) half of a 64-token tile's waves would idle.
+// The small-tile shape of the pipelined attention kernel (attn_pipeline.h): workgroup = 4 query heads of one KV group x one
+// token tile of 32 (128 rows in any case), four waves of 32 rows, two workgroups per CU (80 KiB of LDS each: K and V rings
+// of five 8 KiB slots), so the two waves of a SIMD belong to different workgroups.  With the short queries of the paper's
+// Table 1 (28 / 61 / 209 tokens) half of a 64-token tile's rows would be empty.
 #include "attn_pipeline.h"
 
 namespace calvo {
 namespace duo {
 
 using namespace attn;
-using Cfg = PipeCfg<4, 4>;
+using Cfg = PipeCfg<4, 5, 1>;
 
 __global__ void __launch_bounds__(256, 2) __attribute__((amdgpu_num_vgpr(120))) attn_duo_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];

@@ -1,13 +1,13 @@
-// The attention kernel for long suffixes (attn_wide.h): workgroup = 4 query heads of one KV group x 64 tokens (256 rows in
+// The attention kernel for long suffixes (attn_pipeline.h): workgroup = 4 query heads of one KV group x 64 tokens (256 rows in
 // any case), four waves of 64 rows, one workgroup per CU, K and V rings of eight 8 KiB slots.
 // Also the kernel that merges the partial results of tiles whose context was cut into pieces.
-#include "attn_wide.h"
+#include "attn_pipeline.h"
 
 namespace calvo {
 namespace pipe {
 
 using namespace attn;
-using Cfg = WideCfg<4, 8>;
+using Cfg = PipeCfg<4, 8, 2>;
 
 // 480 of the 512 registers that a wave alone on its SIMD may have (the attribute counts half of
 // the unified VGPR+AGPR file on this target): the remaining 32 per SIMD lane let a wave of the
@@ -16,7 +16,7 @@ using Cfg = WideCfg<4, 8>;
 __global__ void __launch_bounds__(256, 1) __attribute__((amdgpu_num_vgpr(240))) attn_pipe_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   clock_begin(p.clock);
-  attn_wide<Cfg>(p, smem);
+  attn_pipeline<Cfg>(p, smem);
 }
 
 // Combines the pieces of split tiles: for every row and head, with m = max_c m_c,
@@ -42,7 +42,7 @@ __global__ void __launch_bounds__(256) merge_splits_kernel(AttnParams p, const i
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   constexpr int kLanes = 64 / ROWS, kPieces = kMergeLoads / ROWS;
   constexpr int kWgs = 8 / ROWS;                                 // workgroups per 32-row slot
-  // a head group is merged on the XCD whose L2 its pieces were written through (the workgroup order of attn_wide.h and
+  // a head group is merged on the XCD whose L2 its pieces were written through (the workgroup order of
   // attn_pipeline.h): 2048+209 tokens 35.7 -> 31.8 us a call, 4096+28 20.4 -> 18.1
   int hg, rest = blockIdx.x;
   if ((NHG & 7) == 0) {
@@ -127,7 +127,7 @@ __global__ void __launch_bounds__(256) merge_splits_kernel(AttnParams p, const i
 
 }  // namespace pipe
 
-int attn_pipe_tile_tokens(int heads_per_wg) { return 64 * pipe::Cfg::NW / heads_per_wg; }
+int attn_pipe_tile_tokens(int heads_per_wg) { return 32 * pipe::Cfg::HB * pipe::Cfg::NW / heads_per_wg; }
 
 hipError_t attn_pipe_prepare() {
   return hipFuncSetAttribute((const void*)pipe::attn_pipe_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -1,6 +1,7 @@
-// Paged causal GQA prefill attention for gfx950 (CDNA4), software-pipelined kernel body for short suffixes and little
-// work (attn_wide.h has the one for the rest): bf16 storage, head_dim 128, v_mfma_f32_16x16x32_bf16 for both
-// contractions, fp32 online softmax.
+// Paged causal GQA prefill attention for gfx950 (CDNA4), software-pipelined kernel body: bf16 storage, head_dim 128,
+// v_mfma_f32_16x16x32_bf16 for both contractions, fp32 online softmax.  Two shapes of it (PipeCfg):
+//   HB = 2: a wave owns 64 query rows and has a SIMD to itself (512 registers), one workgroup per CU (attn_pipe.hip)
+//   HB = 1: 32 query rows per wave, two workgroups per CU: tiles half as large, for short suffixes (attn_duo.hip)
 //
 // Why the 16x16x32 shape: the part is power limited under matrix load, and on normally
 // distributed operands this shape sustains 12 % more flop/s than 32x32x16 at the power limit
@@ -11,9 +12,9 @@
 // Transposed formulation (every softmax statistic stays in a lane's own registers):
 //   S^T[key][query] = K[key][:] . Q[query][:]       A = K rows from LDS, B = Q in registers
 //   O^T[d][query]  += V^T[d][key] * P^T[key][query]  A = V^T, B = P^T
-// A wave owns 32 queries = two blocks of 16 (qb); a 32-key sub-tile is two blocks of 16 keys (kb).
+// A wave owns QB blocks of 16 queries (qb); a 32-key sub-tile is two blocks of 16 keys (kb).
 // Lane (c = lane % 16, g = lane / 16) of a 16x16 accumulator tile (kb, qb) holds query 16qb + c and
-// the keys 16kb + 4g + r, r = 0..3: a lane works on two query columns with 8 keys each, the four
+// the keys 16kb + 4g + r, r = 0..3: a lane works on QB query columns with 8 keys each, the four
 // lanes c, c+16, c+32, c+48 share a query (row max and row sum cross them only in the rare slow
 // path and at the end), the O rescale is one scalar per lane and query block, and the weights of a
 // lane are exactly the eight k-slots 8g..8g+7 of the B operand of the second MFMA when the k-slot
@@ -21,24 +22,35 @@
 // (as in the pool); the d-major A operand in that key order comes from two LDS transpose reads
 // (ds_read_b64_tr_b16: keys 4g..4g+3 and 16+4g..16+4g+3 for d = 16db + c).
 //
-// Schedule.  The key loop advances in 32-key sub-tiles.  For sub-tile j
-//     QK(j):  S_j = K_j Q^T                                     16 MFMA
-//     SM(j):  P_j = 2^(c (S_j - m)), row sums                   vector ALU
-//     PV(j):  O^T += V_j^T P_j^T                                16 MFMA
-// A wave runs the cycle  SM(j) -> MF(j) = {PV(j), QK(j+1)} -> SM(j+1) -> ...: MF(j) reads 16 A
-// operands from LDS, alternately a K operand (16 keys x 32 d) and a V^T operand (16 d x 32 keys),
-// each used by two MFMAs (one per query block), four operands ahead of the MFMAs that consume them.  S and P are single-buffered: S_j is dead once SM(j) has
-// produced P_j, P_j is dead once MF(j) has consumed it.  The steady loop is unrolled by the ring
-// depth so that LDS ring slots are immediates.
+// Schedule.  The key loop advances in 32-key sub-tiles.  Steady step t:
+//     QK(t+1):  S_t+1 = K_t+1 Q^T                               8 QB MFMA
+//     SM(t):    P_t = 2^(c (S_t - m)), row sums                 vector ALU, in between
+//     PV(t-1):  O^T += V_t-1^T P_t-1^T                          8 QB MFMA
+// S and P are double-buffered; each of the 16 A operands of a step (8 of K: 16 keys x 32 d, 8 of V^T: 16 d x 32 keys) is read
+// from LDS PD operands ahead and feeds QB MFMAs.  The loop is unrolled by the ring depth so that ring slots are immediates.
+// Measured for one wave alone on its SIMD: an MFMA of this shape holds the matrix pipe for 16 cycles and the wave's vector
+// instructions back for 8, anything else for 4; a vector instruction takes 4 cycles, an exponential 8.  So behind every
+// MFMA goes at most one instruction of another kind (LDS read, request, wait), which is free, and then two vector
+// instructions or one exponential, which fill the 16 cycles.  A step of HB = 2 (64 MFMAs, 32 exponentials, 83 other vector
+// instructions, 24 LDS reads) takes 1220 cycles that way, 1320 with the same instructions in the order of the dependences;
+// 1380 in the kernel, with the requests and the barrier.
+// The step is written in this order, with scheduling barriers in between.  MFMAs are inline assembly so that their results
+// stay in place, O of HB = 2 in accumulation registers: left to the compiler, every value that vector instructions
+// touch as well is moved back and forth (45 to 250 moves a step).  What the compiler then does not know are the wait states
+// between an MFMA and vector instructions around it; in a step the operands are at least eight MFMAs apart, elsewhere
+// mfma_settle() is in between.  A spilled register would break that: the kernels must compile without any
+// (tests/test_attn_registers.py).
 //
-// Workgroup (PipeCfg): 4 waves, ring of 4 slots, two workgroups per CU: every wave runs SM(t) then MF(t); the two waves of
-// a SIMD belong to different workgroups and nothing couples them.  Tiles of 32 query tokens per head: for short suffixes.
-//
-// (Measured alternatives on the 32x32x16 shape: running QK(t+1), SM(t), PV(t-1) as one interleaved stream in every wave
-// keeps the matrix pipe 96 % busy in a microbenchmark where the two waves of a SIMD run free, but
-// not behind the per-step barrier the shared K/V ring needs: the lower-numbered wave wins every
-// arbitration, finishes its step in 1180 cycles and waits 480 for the other one.  Wave priorities
-// (s_setprio) around either half change nothing.)
+// Why 64 rows per wave: under matrix load the part is at its power limit, and what a step costs beyond its MFMAs is K and
+// V: 16 KB a step from L2 into LDS, and out of LDS once per wave.  With 64 rows every operand read feeds four MFMAs, half the
+// LDS reads per product of 32 rows.  61440+4096 tokens, 32Q/8KV, against the kernel before (32 rows per wave, the two waves
+// of a SIMD taking turns on the matrix pipe and the vector ALU): 3170 -> 2960 us on N(0,1) data, 2605 -> 2370 on zeros
+// (where no power limit hides the schedule); without the requests (wrong results, timing only) 2720 and 2200, so what is
+// left there is the movement of K and V itself.  The schedule alone, at 32 rows per wave and two workgroups per CU, against
+// SM(t) followed by its MFMAs: 28096+28 tokens 34.3 -> 31.0 us a call, three short queries over 28K-38K tokens
+// 202 -> 187, 512+1 15.3 -> 13.2, 0+1024 29.1 -> 25.3.
+// v_mfma_f32_32x32x16_bf16 was measured in the schedule of HB = 2: 2304 us on zeros, 3292 on N(0,1) data (against 2632 and
+// 3080 of this shape at that point): fewer issue slots, more power.
 //
 // Softmax with a lazily raised reference.  A weight is 2^(c s - c m) with c = scale * log2(e); the row
 // sum adds the fp32 weights with v_add_f32, the PV product takes them rounded to bf16 (nearest even,
@@ -51,60 +63,129 @@
 // taken, m raised, l and O rescaled and the weights computed again.  m is always the exact maximum
 // of an earlier sub-tile, so the largest weight of a row is >= 1: nothing underflows, and with
 // fp32 accumulation and bf16 weights (relative precision) the result is that of the textbook
-// recurrence up to rounding.  Fill / drain steps and diagonal sub-tiles use the textbook update.
+// recurrence up to rounding.
 //
-// Data movement.  K and V go from the pool straight into LDS with global_load_lds_dwordx4 (no
-// register staging), 1 KiB (4 token rows x 256 B) per wave instruction, into two rings (K and V)
-// of RING 8 KiB slots.  Step t requests K(t+KD) and V(t+VD), reads K(t+1) and V(t), and ends with
-// s_waitcnt vmcnt(8) + one barrier: everything requested more than 8 instructions ago has landed.
+// Data movement.  K and V go from the pool straight into LDS with global_load_lds_dwordx4 (no register staging), 1 KiB
+// (4 token rows x 256 B) per wave instruction, into two rings (K and V) of RING 8 KiB slots.  Step t requests K(t+KA) and
+// V(t+VA), reads K(t+1), V(t-1) and the first operands of K(t+2).  A ring of eight has one barrier for two steps; HB = 1 has
+// a ring of five, the most that two workgroups leave each other of a CU's LDS, and one for each.
 // Rows are unpadded; 16-byte chunks are XOR-swizzled on the way in (the lane that owns LDS chunk
 // position c fetches logical chunk c ^ f(row)) so that operand reads are bank-conflict free:
 // K f = row & 15 (a 16-lane group reads one chunk of 16 different rows), V f = (row & 7) << 1 (half
 // a wave reads two chunks of 8 different rows).  Operand addresses are lane constants plus immediates.
+// Cache policy bits on the requests (nt, sc0, sc1) do nothing or harm (nt: +5 %).
 //
-// Sub-tiles that touch the causal diagonal or the end of the context are not pipelined: they are
-// at most a handful per workgroup, are loaded synchronously and run QK -> mask -> SM -> PV.
+// Sub-tiles that touch the causal diagonal or the end of the context are not pipelined: they are at most a handful per
+// workgroup, are requested before the drain of the pipeline and run QK -> mask -> SM -> PV.
 #pragma once
 #include "attn_common.h"
 
 namespace calvo {
 namespace attn {
 
-template <int NW_, int RING_>
+template <int NW_, int RING_, int HB_>
 struct PipeCfg {
   static constexpr int NW = NW_;                       // waves per workgroup
+  static constexpr int HB = HB_;                       // blocks of 32 query rows per wave
+  static constexpr int QB = 2 * HB_;                   // blocks of 16
   static constexpr int RING = RING_;                   // LDS ring slots per operand
-  static constexpr int KD = RING_;                     // step t requests K(t + KD) ...
-  static constexpr int VD = KD - 1;                    // ... and V(t + VD)
+  static constexpr bool BAR2 = RING_ == 8;             // one barrier for two steps, else one for each
+  static constexpr int KA = BAR2 ? RING_ - 1 : RING_;  // step t requests K(t + KA) ...
+  static constexpr int VA = KA - 2;                    // ... and V(t + VA)
   static constexpr int NI = 8 / NW_;                   // 1 KiB requests per wave, operand and sub-tile
+  static constexpr int UNROLL = RING_ % 2 ? 2 * RING_ : RING_;
+  static constexpr int PD = 4;         // LDS operand reads run this many operands ahead
   static constexpr int LDS_BYTES = 2 * RING_ * kSlot;
 };
 
+// m0 = lds_base + off for the dma_1k_m0 that follows at least one instruction later
+template <int OFF>
+__device__ inline void set_m0(unsigned lds_base, Tag<OFF>) {
+  asm volatile("s_add_u32 m0, %0, %1" : : "s"(lds_base), "n"(OFF) : "scc");
+}
+__device__ inline void set_m0(unsigned lds_base, int off) {
+  asm volatile("s_add_u32 m0, %0, %1" : : "s"(lds_base), "s"(off) : "scc");
+}
+// 64 lanes x 16 bytes from sbase + voff to 1 KiB of LDS at m0
+__device__ inline void dma_1k_m0(const unsigned char* sbase, unsigned voff) {
+  asm volatile("global_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(sbase));
+}
+// byte offset of a ring slot, for slots known at compile time and for others
+template <int S, int ADD>
+__device__ inline constexpr Tag<S * kSlot + ADD> slot_off(Tag<S>, Tag<ADD>) { return {}; }
+template <int ADD>
+__device__ inline int slot_off(int s, Tag<ADD>) { return s * kSlot + ADD; }
+template <int V>
+__device__ inline void opaque(Tag<V>&) {}
+__device__ inline void opaque(int& s) { asm volatile("" : "+s"(s)); }
+template <int V>
+__device__ inline constexpr int value_of(Tag<V>) { return V; }
+__device__ inline int value_of(int v) { return v; }
+
+// o += a * b.  ACC: o in accumulation registers (where the wave has the SIMD's 512 registers, of which vector
+// instructions reach 256), else in architectural ones.
+template <bool ACC>
+__device__ inline void mfma_acc(f32x4& o, const bf16x8& a, const bf16x8& b) {
+  if constexpr (ACC) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(o) : "v"(a), "v"(b));
+  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(o) : "v"(a), "v"(b));
+}
+template <bool ACC>
+__device__ inline void pin_acc(f32x4& o) {
+  if constexpr (ACC) asm volatile("" : "+a"(o));
+  else asm volatile("" : "+v"(o));
+}
+// s = a * b (+ s), in architectural registers
+__device__ inline void mfma_first(f32x4& s, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(s) : "v"(a), "v"(b));
+}
+__device__ inline void mfma_next(f32x4& s, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(s) : "v"(a), "v"(b));
+}
+// The compiler knows nothing of the waits that these need where vector instructions write an operand or touch a result
+// before or after them.
+__device__ inline void mfma_settle() { asm volatile("s_nop 15"); }
+template <bool ACC, int QB>
+__device__ inline void acc_ready(f32x4 (&o)[8][QB]) {
+  mfma_settle();
+#pragma unroll
+  for (int db = 0; db < 8; db++)
+#pragma unroll
+    for (int qb = 0; qb < QB; qb++) pin_acc<ACC>(o[db][qb]);
+}
+
+// largest of the numbers (a NaN counts as nothing)
+__device__ inline float max_of(const float (&v)[4]) {
+  float m;
+  asm("v_max3_f32 %0, %1, %2, %3\n\tv_max_f32 %0, %0, %4" : "=&v"(m) : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]));
+  return m;
+}
+__device__ inline float max_of(const float (&v)[2]) {
+  float m;
+  asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"(v[0]), "v"(v[1]));
+  return m;
+}
+
 template <class Cfg_>
 __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char* smem) {
-  constexpr int NW = Cfg_::NW, RING = Cfg_::RING, KD = Cfg_::KD, VD = Cfg_::VD, NI = Cfg_::NI;
-  constexpr int RM = RING - 1;
+  constexpr int NW = Cfg_::NW, HB = Cfg_::HB, QB = Cfg_::QB, RING = Cfg_::RING, KA = Cfg_::KA, VA = Cfg_::VA, NI = Cfg_::NI, PD = Cfg_::PD;
+  constexpr bool ACC = HB == 2;
   constexpr int kVBase = RING * kSlot;                 // V ring follows the K ring
-  // furthest sub-tile whose block offsets are fetched: n_pipe + 2 * RING - 2, with n_pipe at most
-  // half the number of real blocks (rounded up); each parity half of the padded table holds
-  // (real blocks + kTablePad) / 2 entries
-  static_assert(kTablePad >= 4 * RING, "block table padding too small for the ring depth");
   const lds_u8* lds = (const lds_u8*)smem;
-  const unsigned lds0 = (unsigned)(size_t)lds;         // LDS byte address of the ring
+  const unsigned lds0 = (unsigned)(size_t)lds;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int c = lane & 15;                             // query column inside a block of 16 / row of an A operand
-  const int g = lane >> 4;                             // k-slots 8g..8g+7 of an operand, rows 4g..4g+3 of a result tile
+  const int c = lane & 15;
+  const int g = lane >> 4;
 
   // ---- work item decode (wave-uniform)
   const int HW = p.heads_per_wg;
-  const int TPW = NW / HW;
+  const int TPW = HB * NW / HW;                        // 32-token blocks of the tile
   const int NHG = p.n_q_heads / HW;
   int it, hg;
   {
     const int bid = blockIdx.x;
-    if ((NHG & 7) == 0) {                         // keep one KV head's workgroups on one XCD
+    if ((NHG & 7) == 0) {
       const int per = NHG >> 3, rest = bid >> 3;
       hg = (bid & 7) * per + rest % per;
       it = rest / per;
@@ -113,43 +194,71 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
       it = bid / NHG;
     }
   }
-  if (p.item_index) it = p.item_index[it];       // this launch runs a subset of the work items
+  if (p.item_index) it = p.item_index[it];
   const WorkItem wi = p.items[it];
   const ReqDesc rd = p.reqs[wi.req];
   const int P = rd.prefix_len, S = rd.suffix_len;
   const int TQ = 32 * TPW;
   const int q_base = wi.q_tile * TQ;
-  const int hq = hg * HW + wave % HW;
-  const int kv = hq / (p.n_q_heads / p.n_kv_heads);
-  const int wq0 = q_base + (wave / HW) * 32;
-  const bool wave_active = wq0 < S;
-  const int pq_min = P + wq0;
-  const int pq_max = P + min(wq0 + 32, S) - 1;
+  const int Hkv = p.n_kv_heads, Hq = p.n_q_heads;
+  const int kv = hg * HW / (Hq / Hkv);
+  // A wave owns HB of the tile's row blocks of 32, one from either end: block vw is (head vw % HW, token block vw / HW).
+  // Blocks with later tokens see more of the diagonal, so the waves have about the same number of sub-tiles there.
+  int hq[HB], wq0[HB];
+  auto row_block = [&](int h) { return h ? HB * NW - 1 - wave : wave; };
+#pragma unroll
+  for (int h = 0; h < HB; h++) {
+    const int vw = row_block(h);
+    hq[h] = hg * HW + vw % HW;
+    wq0[h] = q_base + (vw / HW) * 32;
+  }
   const int ctx_len = P + S;
-  // This work item covers the sub-tiles [jb, je) of the tile's context; t and j below count from jb.
   const int jb = wi.sub_begin;
-  const int n_sub = wi.sub_end - jb;                           // sub-tiles this workgroup visits
-  const int n_pipe = max(0, min(wi.sub_end, (P + q_base + 1) / kSK) - jb);   // ... fully visible to all its rows
+  const int n_sub = wi.sub_end - jb;
+  const int n_pipe = max(0, min(wi.sub_end, (P + q_base + 1) / kSK) - jb);
   const int last_blk = (ctx_len + kBlockTokens - 1) / kBlockTokens - 1;
-  // the block offsets are read-only for the whole launch: reading them through the constant address
-  // space keeps the lookups on the scalar unit, outside the vmcnt accounting of the K/V requests
   typedef const __attribute__((address_space(4))) int64_t* const_i64p;
-  const int n_blk_pad = last_blk + 1 + kTablePad + ((last_blk + 1) & 1);            // entries of the padded table
-  // this wave's half of every sub-tile: block 2j + wblk; offsets of one parity are contiguous
+  const int n_blk_pad = last_blk + 1 + kTablePad + ((last_blk + 1) & 1);
   const int wblk = wave / (NW / 2);
   const const_i64p boffs = (const_i64p)(uintptr_t)(p.blk_offs + rd.table_off + wblk * (n_blk_pad >> 1));
-  const int Hkv = p.n_kv_heads, Hq = p.n_q_heads;
   const float c2 = p.scale * 1.4426950408889634f;
 
-  // ---- Q as the B operand of QK^T: lane (c, g) holds Q[query 16qb + c][32ks + 8g .. +8]
-  bf16x8 qB[2][4];
+  // ---- pool -> LDS
+  const unsigned char* pool = (const unsigned char*)p.pool_layer;
+  const unsigned row_b = (unsigned)(Hkv * kD * 2);
+  const unsigned half_b = kBlockTokens * row_b;
+  const int brow0 = (32 / NW) * (wave % (NW / 2)) + (lane >> 4);
+  unsigned voff_k[NI], voff_v[NI];
+#pragma unroll
+  for (int h = 0; h < NI; h++) {
+    const int row = brow0 + 4 * h;
+    voff_k[h] = row * row_b + kv * kRow + (((lane & 15) ^ (row & 15)) << 4);
+    voff_v[h] = half_b + row * row_b + kv * kRow + (((lane & 15) ^ ((row & 7) << 1)) << 4);
+  }
+  const unsigned dma_lds = lds0 + wave * (1024 * NI);
+
+  auto fetch_off = [&](int j) -> int64_t { return boffs[jb + j]; };
+  // request I of a step: the NI of a K sub-tile, then the NI of a V sub-tile, into their ring slots
+  auto request_m0 = [&](auto kslot, auto vslot, auto idx) {
+    constexpr int I = decltype(idx)::value;
+    if constexpr (I < NI) set_m0(dma_lds, slot_off(kslot, Tag<I * 1024>{}));
+    else set_m0(dma_lds, slot_off(vslot, Tag<kVBase + (I - NI) * 1024>{}));
+  };
+  auto request_one = [&](const unsigned char* kbase, const unsigned char* vbase, auto idx) {
+    constexpr int I = decltype(idx)::value;
+    if constexpr (I < NI) dma_1k_m0(kbase, voff_k[I]);
+    else dma_1k_m0(vbase, voff_v[I - NI]);
+  };
+
+  // ---- Q as the B operand of QK^T
+  bf16x8 qB[QB][4];
   {
     const unsigned short* q = (const unsigned short*)p.q;
 #pragma unroll
-    for (int qb = 0; qb < 2; qb++) {
-      const int tokq = wq0 + 16 * qb + c;
+    for (int qb = 0; qb < QB; qb++) {
+      const int tokq = wq0[qb >> 1] + 16 * (qb & 1) + c;
       const bool ok = tokq < S;
-      const unsigned short* row = q + ((int64_t)(rd.q_off + (ok ? tokq : 0)) * Hq + hq) * kD + 8 * g;
+      const unsigned short* row = q + ((int64_t)(rd.q_off + (ok ? tokq : 0)) * Hq + hq[qb >> 1]) * kD + 8 * g;
 #pragma unroll
       for (int ks = 0; ks < 4; ks++) {
         u32x4 v = {0u, 0u, 0u, 0u};
@@ -160,405 +269,404 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
   }
 
   const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-  f32x4 o[8][2];                                       // O^T tile (db, qb): d = 16db + 4g + r, query 16qb + c
+  f32x4 o[8][QB];
+  float m_run[QB], l_run[QB];
 #pragma unroll
-  for (int db = 0; db < 8; db++) {
-    o[db][0] = zero4;
-    o[db][1] = zero4;
-  }
-  // Softmax state per query.  O and l_run are sums of weights 2^(x - m_run), x the exponent of a
-  // score (c * score): m_run is kept in exponent units.  In the steady loop m_run
-  // is a reference that is only raised when a lane's partial row sum would pass kLazyBound; it is
-  // always the exact maximum of some earlier sub-tile, so the largest weight of a row is at least 1.
-  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};     // per query block
-  // ---- pool -> LDS.  Sub-tile j = blocks 2j and 2j+1.  Wave w fetches 32 / NW rows of block
-  // 2j + wblk with NI instructions of 4 rows for K and as many for V.  In instruction h lane l owns
-  // row brow0 + 4h + l/16 and LDS chunk position l%16, and fetches the logical chunk that the
-  // swizzle maps there.  The second instruction's rows lie 4 rows further on: bit 2 of the row
-  // number flips, i.e. bit 2 of the chunk index for K (bit 6 of the byte offset) and bit 3 for V
-  // (bit 7 of the byte offset).
-  const unsigned char* pool = (const unsigned char*)p.pool_layer;
-  const int64_t half_b = (int64_t)kBlockTokens * Hkv * kD * 2;         // K half of a block, bytes
-  const int brow0 = (32 / NW) * (wave % (NW / 2)) + (lane >> 4);       // row inside the block, first instruction
-  const unsigned rowoff = (unsigned)(brow0 * Hkv * kD * 2 + kv * kD * 2);
-  const unsigned voff_k = rowoff + (((lane & 15) ^ (brow0 & 15)) << 4);
-  const unsigned voff_v = rowoff + (((lane & 15) ^ ((brow0 & 7) << 1)) << 4);
-  const int64_t rows4 = (int64_t)4 * Hkv * kD * 2;
-  const unsigned dma_lds = lds0 + wave * (1024 * NI);                  // + h*1024 + slot*8192 (+ V ring)
-
-  // byte offset of this wave's block of sub-tile j (the table is padded, so j may run past the end)
-  auto fetch_off = [&](int j) -> int64_t { return boffs[jb + j]; };
-  auto request_k_at = [&](int64_t off, int slot) {
-    dma_1k(pool + off, voff_k, dma_lds + slot * kSlot);
-    if constexpr (NI == 2) dma_1k(pool + off + rows4, voff_k ^ 64u, dma_lds + slot * kSlot + 1024);
-  };
-  auto request_v_at = [&](int64_t off, int slot) {
-    dma_1k(pool + half_b + off, voff_v, dma_lds + kVBase + slot * kSlot);
-    if constexpr (NI == 2) dma_1k(pool + half_b + off + rows4, voff_v ^ 128u, dma_lds + kVBase + slot * kSlot + 1024);
-  };
-  // Fill and drain ask for the piece's last sub-tile again instead of what lies past it (its blocks are in the caches),
-  // so that the number of requests in flight stays what the waits count on.  The steady steps do not: the last of
-  // them run up to KD - 1 K and VD - 1 V sub-tiles past the piece, into blocks that may be another piece's, a chunk
-  // that has not landed or the padding of the table.  Those bytes land in LDS and are never consumed.
-  auto request_k = [&](int j) { request_k_at(fetch_off(min(j, n_sub - 1)), j & RM); };
-  auto request_v = [&](int j) { request_v_at(fetch_off(min(j, n_sub - 1)), j & RM); };
+  for (int qb = 0; qb < QB; qb++) { m_run[qb] = -INFINITY; l_run[qb] = 0.f; }
 
   // ---- lane-constant operand addresses inside a slot
-  // K operand (kb, ks): key row 16kb + c, logical chunk 4ks + g (d = 32ks + 8g .. +8); the key block
-  // adds 16 rows, which leaves the swizzle alone
   const lds_u8* ka_addr[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ks++) ka_addr[ks] = lds + c * kRow + (((4 * ks + g) ^ c) << 4);
-  // V^T operand db: the 16 lanes of group g read keys 4g..4g+3 (and, 16 rows further, 16+4g..) for
-  // d = 16db..16db+15: source lane c points at key 4g + c/4, d offset 16db + 4*(c%4); after the
-  // transpose lane c holds the four keys for d = 16db + c
   const int v_row = 4 * g + (c >> 2);
   const lds_u8* va_addr[8];
 #pragma unroll
   for (int db = 0; db < 8; db++)
     va_addr[db] = lds + kVBase + v_row * kRow + ((2 * (db ^ (v_row & 7)) + ((c & 3) >> 1)) << 4) + (c & 1) * 8;
 
-  // ---- pipeline registers: S and P of the sub-tile in flight
-  // S tile (kb, qb): keys 16kb + 4g + r of query 16qb + c.  P operand of query block qb: the lane's
-  // eight weights in k-slot order (kb, r).
-  struct STile { f32x4 t[2][2]; };
-  STile sbuf;
-  bf16x8 pbuf[2];
-  // Rescale of O that a raised reference asks for before the next PV: al per lane and query block,
-  // needed for the wave (a scalar: the steady path spends no vector instruction on it).
-  float al[2] = {1.f, 1.f};
-  bool needed = false;
+  f32x4 sb[2][2][QB];                                  // [parity][kb][qb]
+  bf16x8 pb[2][QB];
 
-  auto rescale = [&](const float (&a)[2]) {
-#pragma unroll
-    for (int db = 0; db < 8; db++) {
-      o[db][0] *= a[0];
-      o[db][1] *= a[1];
-    }
-  };
-  // exponent of score s of query block qb against the current reference
   auto expo = [&](float s, int qb) -> float { return __builtin_fmaf(s, c2, -m_run[qb]); };
-  auto qk = [&](int slot, STile& s) {
-#pragma unroll
-    for (int kb = 0; kb < 2; kb++) {
-      bf16x8 ka[4];
-#pragma unroll
-      for (int ks = 0; ks < 4; ks++) ka[ks] = read_k(ka_addr[ks] + 16 * kb * kRow + slot * kSlot);
-#pragma unroll
-      for (int qb = 0; qb < 2; qb++) {
-        f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[0], qB[qb][0], zero4, 0, 0, 0);
-#pragma unroll
-        for (int ks = 1; ks < 4; ks++) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[ks], qB[qb][ks], acc, 0, 0, 0);
-        s.t[kb][qb] = acc;
-      }
-    }
-  };
-  // largest score of the lane's query of block qb over the whole sub-tile (all four lanes of the query)
-  auto row_max = [&](const STile& s, int qb) -> float {
-    float mx = fmaxf(fmaxf(s.t[0][qb][0], s.t[0][qb][1]), fmaxf(s.t[0][qb][2], s.t[0][qb][3]));
-    mx = fmaxf(mx, fmaxf(fmaxf(s.t[1][qb][0], s.t[1][qb][1]), fmaxf(s.t[1][qb][2], s.t[1][qb][3])));
+  auto row_max = [&](const f32x4& a, const f32x4& b) -> float {
+    float mx = fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]));
+    mx = fmaxf(mx, fmaxf(fmaxf(b[0], b[1]), fmaxf(b[2], b[3])));
     return quad_max(mx);
   };
-  // weights of query block qb against the current reference: fp32 sum, bf16 operand
-  auto weights_of = [&](const STile& s, int qb, float& ps, bf16x8& pb) {
+  auto weights_of = [&](const f32x4& s0, const f32x4& s1, int qb, float& ps, bf16x8& pw) {
     float w[8];
 #pragma unroll
-    for (int e = 0; e < 8; e++) w[e] = __builtin_amdgcn_exp2f(expo(s.t[e >> 2][qb][e & 3], qb));
+    for (int e = 0; e < 8; e++) w[e] = __builtin_amdgcn_exp2f(expo(e < 4 ? s0[e & 3] : s1[e & 3], qb));
     ps = ((w[0] + w[1]) + (w[2] + w[3])) + ((w[4] + w[5]) + (w[6] + w[7]));
-    pb = __builtin_bit_cast(bf16x8, (u32x4){pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3]), pack_bf16(w[4], w[5]), pack_bf16(w[6], w[7])});
+    pw = __builtin_bit_cast(bf16x8, (u32x4){pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3]), pack_bf16(w[4], w[5]), pack_bf16(w[6], w[7])});
   };
-  // Textbook update for one sub-tile whose scores are in s (possibly masked with -inf): new
-  // running maximum, rescale factor alpha for l and O, weights against the new maximum (summed in
-  // fp32, rounded to bf16 once for the PV product).
-  auto sm_textbook = [&](const STile& s, bf16x8 (&pb)[2], float (&alpha)[2], bool& changed) {
-    changed = false;
+  // Softmax of query blocks QB0 .. QB0 + N - 1 of one sub-tile (scores possibly masked with -inf): weights against the
+  // current reference, unless a partial row sum passes the bound (or is not a number, or there is no reference yet).
+  auto softmax = [&](auto qb0, auto&& s, bf16x8* pw) {
+    constexpr int QB0 = decltype(qb0)::value, N = sizeof(s[0]) / sizeof(f32x4);
+    float ps[N];
+    bool above = false;
 #pragma unroll
-    for (int qb = 0; qb < 2; qb++) {
-      const float m_new = fmaxf(m_run[qb], row_max(s, qb) * c2);
-      alpha[qb] = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
-      changed |= (m_new != m_run[qb]);
-      m_run[qb] = m_new;
-      float ps;
-      weights_of(s, qb, ps, pb[qb]);
-      l_run[qb] = l_run[qb] * alpha[qb] + ps;
+    for (int q = 0; q < N; q++) {
+      weights_of(s[0][q], s[1][q], QB0 + q, ps[q], pw[q]);
+      above |= !(ps[q] <= kLazyBound);
     }
+    if (__builtin_amdgcn_ballot_w64(above) != 0) {
+      float alpha[N];
+      bool changed = false;
+#pragma unroll
+      for (int q = 0; q < N; q++) {
+        const int qb = QB0 + q;
+        const float m_new = fmaxf(m_run[qb], row_max(s[0][q], s[1][q]) * c2);
+        alpha[q] = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
+        changed |= m_run[qb] != -INFINITY && !(alpha[q] == 1.f);         // without a reference O is 0
+        m_run[qb] = m_new;
+        l_run[qb] = l_run[qb] * alpha[q];
+        weights_of(s[0][q], s[1][q], qb, ps[q], pw[q]);
+      }
+      if (__builtin_amdgcn_ballot_w64(changed) != 0) {
+        acc_ready<ACC>(o);
+#pragma unroll
+        for (int db = 0; db < 8; db++)
+#pragma unroll
+          for (int q = 0; q < N; q++) o[db][QB0 + q] *= alpha[q];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < N; q++) l_run[QB0 + q] += ps[q];
   };
-  auto pv = [&](int slot, const bf16x8 (&pb)[2]) {
+  // S of N query blocks from QB0 on
+  auto qk = [&](int slot, auto qb0, auto&& s) {
+    constexpr int QB0 = decltype(qb0)::value, N = sizeof(s[0]) / sizeof(f32x4);
+#pragma unroll
+    for (int kb = 0; kb < 2; kb++)
+#pragma unroll
+      for (int ks = 0; ks < 4; ks++) {
+        const bf16x8 ka = read_k(ka_addr[ks] + 16 * kb * kRow + slot * kSlot);
+#pragma unroll
+        for (int q = 0; q < N; q++) {
+          if (ks == 0) mfma_first(s[kb][q], ka, qB[QB0 + q][ks]);
+          else mfma_next(s[kb][q], ka, qB[QB0 + q][ks]);
+        }
+      }
+    mfma_settle();
+#pragma unroll
+    for (int q = 0; q < N; q++) asm volatile("" : "+v"(s[0][q]), "+v"(s[1][q]));
+  };
+  // O of N query blocks from QB0 on
+  auto pv = [&](int slot, auto qb0, auto n, const bf16x8* pw) {
+    constexpr int QB0 = decltype(qb0)::value, N = decltype(n)::value;
+    acc_ready<ACC>(o);
 #pragma unroll
     for (int db = 0; db < 8; db++) {
       const bf16x8 a = read_vt(va_addr[db] + slot * kSlot);
-      o[db][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pb[0], o[db][0], 0, 0, 0);
-      o[db][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pb[1], o[db][1], 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < N; q++) mfma_acc<ACC>(o[db][QB0 + q], a, pw[q]);
     }
   };
+  auto qk_all = [&](int slot, f32x4 (&s)[2][QB]) { qk(slot, Tag<0>{}, s); };
+  auto softmax_all = [&](const f32x4 (&s)[2][QB], bf16x8 (&pw)[QB]) { softmax(Tag<0>{}, s, pw); };
+  auto pv_all = [&](int slot, const bf16x8 (&pw)[QB]) { pv(slot, Tag<0>{}, Tag<QB>{}, pw); };
 
-  // Block offsets for the requests of one unrolled iteration (steps t0 .. t0+RING-1, t0 & RM == 1):
-  // off_cur[i] belongs to sub-tile t0 + RING + i, off_prev1 / off_prev2 to sub-tiles t0 + RING - 1
-  // and t0 + RING - 2.
-  int64_t off_cur[RING], off_prev1 = 0, off_prev2 = 0;
-  // first kPD MFMA operands of the coming MFMA half (see step_steady)
-  bf16x8 pre[kPD];
-  // operand i of MF(j), k = i % 8: the K operand (key block k%2, d slice k/2) of K(j+1) for i < 8, the
-  // V^T operand of d block k of V(j) for i >= 8
+  // operand i of a step: K operand (key block i%2, d slice i/2) for i < 8, V^T operand of d block i - 8 beyond
   auto load_opnd = [&](auto idx, auto ks, auto vs) -> bf16x8 {
     constexpr int i = decltype(idx)::value, k = i & 7;
-    constexpr int KS = decltype(ks)::value, VS = decltype(vs)::value;
-    if constexpr (i >= 8) return read_vt(va_addr[k] + VS * kSlot);
-    else return read_k(ka_addr[k >> 1] + 16 * (k & 1) * kRow + KS * kSlot);
+    if constexpr (i >= 8) return read_vt(va_addr[k] + value_of(slot_off(vs, Tag<0>{})));
+    else return read_k(ka_addr[k >> 1] + value_of(slot_off(ks, Tag<16 * (k & 1) * kRow>{})));
   };
-  auto prefetch = [&](auto ks, auto vs) {
-    static_for<0, kPD>([&](auto idx) { pre[decltype(idx)::value] = load_opnd(idx, ks, vs); });
-  };
+  auto ring_slot = [](int j) { return (int)((unsigned)j % (unsigned)RING); };
+  bf16x8 pre[PD];
 
-  // ---- steady step t (t & RM == TR): SM(t), MF(t)
-  auto step_steady = [&](auto tr) {
-    constexpr int TR = decltype(tr)::value;
-    constexpr int I = (TR + RM) & RM;                // position inside the unrolled iteration
-    constexpr int KS = (TR + 1) & RM, VS = TR;       // ring slots of K(t+1), V(t)
-    // K(t+KD) and V(t+VD) go into ring slots that nobody reads after the barrier that ended step
-    // t-1.
-    auto requests = [&]() {
-      constexpr int ik = I + KD - RING, iv = I + VD - RING;      // index into off_cur, negative: previous iteration
-      request_k_at(ik == -1 ? off_prev1 : off_cur[ik < 0 ? 0 : ik], (TR + KD) & RM);
-      request_v_at(iv == -2 ? off_prev2 : iv == -1 ? off_prev1 : off_cur[iv < 0 ? 0 : iv], (TR + VD) & RM);
-    };
-    // Softmax of the sub-tile in sbuf -> pbuf.  The empty asm statements tie the inputs and results
-    // of each half to its side: the compiler may not move them across.
-    auto valu_half = [&]() {
-      pin(m_run[0]);
-      pin(m_run[1]);
-      const STile& s = sbuf;
-      bool raised = false;
-      float ps[2];
-      weights_of(s, 0, ps[0], pbuf[0]);
-      weights_of(s, 1, ps[1], pbuf[1]);
-      // Accept unless a partial row sum is above the bound (or not a number).  Otherwise raise the
-      // references to this sub-tile's maxima, rescale the running sums (O is rescaled at the start
-      // of the next MFMA half through al / needed) and compute the weights again: now all are <= 1.
-      if (__builtin_amdgcn_ballot_w64(!(ps[0] <= kLazyBound) || !(ps[1] <= kLazyBound)) != 0) {
-#pragma unroll
-        for (int qb = 0; qb < 2; qb++) {
-          // this sub-tile's maximum, as an exponent relative to the current reference
-          const float d = fmaxf(expo(row_max(s, qb), qb), 0.f);
-          const float a_acc = __builtin_amdgcn_exp2f(-d);
-          raised |= __builtin_amdgcn_ballot_w64(d > 0.f) != 0;
-          l_run[qb] *= a_acc;
-          al[qb] = a_acc;
-          m_run[qb] += d;
-          weights_of(s, qb, ps[qb], pbuf[qb]);
+  // ---- steady step t in ring slot TR: QK(t+1), SM(t), PV(t-1); requests K and V of t + LA from base
+  auto step = [&](auto par, auto&& slot, const unsigned char* kbase, const unsigned char* vbase) {
+    constexpr int C = decltype(par)::value;
+    auto KS = slot(Tag<1>{});
+    auto VS = slot(Tag<-1>{});
+    auto KN = slot(Tag<2>{});
+    const auto KR = slot(Tag<KA>{});
+    const auto VR = slot(Tag<VA>{});
+    opaque(KS);                                          // run-time slots: operand addresses are made where they are used,
+    opaque(VS);                                          // not kept in registers through the step
+    opaque(KN);
+    f32x4 (&s)[2][QB] = sb[C];
+    f32x4 (&sn)[2][QB] = sb[C ^ 1];
+    const bf16x8 (&pp)[QB] = pb[C ^ 1];
+    u32x4 pn[QB];
+    float x[2], ps[QB], w[2];
+    bf16x8 op[16 + PD];
+    static_for<0, PD>([&](auto idx) { op[decltype(idx)::value] = pre[decltype(idx)::value]; });
+    static_for<0, 16>([&](auto idx) {
+      constexpr int i = decltype(idx)::value, k = i & 7;
+      // request of this group, where a group reads one operand half only
+      constexpr int rq = i < 4 ? i * NI / 4 : i >= 12 ? NI + (i - 12) * NI / 4 : -1;
+      constexpr bool rq_on = NI == 4 ? rq >= 0 : rq >= 0 && (i & 1) == 0;
+      static_for<0, QB>([&](auto qtag) {
+        constexpr int qb = decltype(qtag)::value, kb = k & 1, ks = k >> 1;
+        // four MFMAs per pair of weights: query block, key block and row of the pair
+        constexpr int n = i * QB + qb, pair = n >> 2, part = n & 3, wq = pair >> 2, wkb = (pair >> 1) & 1, wr = 2 * (pair & 1);
+        if constexpr (i >= 8) mfma_acc<ACC>(o[k][qb], op[i], pp[qb]);
+        else if constexpr (ks == 0) mfma_first(sn[kb][qb], op[i], qB[qb][ks]);
+        else mfma_next(sn[kb][qb], op[i], qB[qb][ks]);
+        __builtin_amdgcn_sched_barrier(0);
+        // what is free behind an MFMA
+        if constexpr (qb == 0) {
+          if constexpr (i + PD < 16) op[i + PD] = load_opnd(Tag<i + PD>{}, KS, VS);
+          else op[i + PD] = load_opnd(Tag<i + PD - 16>{}, KN, VS);
         }
-      }
-      l_run[0] += ps[0];
-      l_run[1] += ps[1];
-      needed = raised;
-      pin(pbuf[0]);
-      pin(pbuf[1]);
-      pin(l_run[0]);
-      pin(l_run[1]);
-    };
-    // Eight K operands, then eight V^T operands, two MFMAs each (query blocks 0 and 1): all of QK(t+1)
-    // before all of PV(t).  Keeping the MFMAs of one contraction together is worth 2 % over alternating
-    // them (measured; the B operands then change between Q and P once per step, not every instruction,
-    // and the part is power limited).  Operand i is read from LDS kPD operands ahead of the MFMAs that
-    // consume it; the first kPD operands (pre[]) are read by prefetch() well before the MFMA half
-    // starts, so no LDS latency is exposed.
-    bf16x8 opnd[16];
-    auto mfma_half = [&]() {
-      pin(qB[0][0]);
-      pin(pbuf[0]);
-      pin(pbuf[1]);
-      if (needed) rescale(al);
-      STile sn;
-      static_for<0, kPD>([&](auto idx) { opnd[decltype(idx)::value] = pre[decltype(idx)::value]; });
-      static_for<0, 16>([&](auto idx) {
-        constexpr int i = decltype(idx)::value, k = i & 7;
-        if constexpr (i >= 8) {
-          o[k][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(opnd[i], pbuf[0], o[k][0], 0, 0, 0);
-          o[k][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(opnd[i], pbuf[1], o[k][1], 0, 0, 0);
+        if constexpr (rq_on && qb == QB / 2 - 1) request_m0(KR, VR, Tag<rq>{});
+        if constexpr (rq_on && qb == QB / 2) request_one(kbase, vbase, Tag<rq>{});
+        if constexpr (qb == QB - 1 && i < 15) pin(op[i + 1]);         // its wait goes here
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (part == 0) {
+          x[0] = expo(s[wkb][wq][wr], wq);
+          x[1] = expo(s[wkb][wq][wr + 1], wq);
+        } else if constexpr (part == 1) {
+          w[0] = __builtin_amdgcn_exp2f(x[0]);
+          pin(w[0]);
+        } else if constexpr (part == 2) {
+          w[1] = __builtin_amdgcn_exp2f(x[1]);
+          pin(w[1]);
         } else {
-          constexpr int kb = k & 1, ks = k >> 1;
-          sn.t[kb][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(opnd[i], qB[0][ks], ks == 0 ? zero4 : sn.t[kb][0], 0, 0, 0);
-          sn.t[kb][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(opnd[i], qB[1][ks], ks == 0 ? zero4 : sn.t[kb][1], 0, 0, 0);
+          ps[wq] = (pair & 3) == 0 ? w[0] + w[1] : (ps[wq] + w[0]) + w[1];
+          unsigned pk = pack_bf16(w[0], w[1]);
+          pin(pk);
+          pn[wq][pair & 3] = pk;
+          pin(ps[wq]);
         }
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-        if constexpr (i + kPD < 16) {
-          opnd[i + kPD] = load_opnd(Tag<i + kPD>{}, Tag<KS>{}, Tag<VS>{});
-          __builtin_amdgcn_sched_group_barrier(0x100, (i + kPD >= 8) ? 2 : 1, 0);
-        }
+        __builtin_amdgcn_sched_barrier(0);
       });
-      sbuf = sn;
+    });
+    static_for<0, PD>([&](auto idx) { pre[decltype(idx)::value] = op[16 + decltype(idx)::value]; });
 #pragma unroll
-      for (int kb = 0; kb < 2; kb++) {
-        pin(sbuf.t[kb][0]);
-        pin(sbuf.t[kb][1]);
-      }
+    for (int qb = 0; qb < QB; qb++) pb[C][qb] = __builtin_bit_cast(bf16x8, pn[qb]);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(max_of(ps) <= kLazyBound)) != 0, 0)) {
+      acc_ready<ACC>(o);
 #pragma unroll
-      for (int db = 0; db < 8; db++) {
-        pin(o[db][0]);
-        pin(o[db][1]);
+      for (int qb = 0; qb < QB; qb++) {
+        const float d = fmaxf(expo(row_max(s[0][qb], s[1][qb]), qb), 0.f);
+        const float a = __builtin_amdgcn_exp2f(-d);
+        l_run[qb] *= a;
+        m_run[qb] += d;
+        weights_of(s[0][qb], s[1][qb], qb, ps[qb], pb[C][qb]);
+#pragma unroll
+        for (int db = 0; db < 8; db++) o[db][qb] *= a;
       }
-    };
-    requests();
-    prefetch(Tag<KS>{}, Tag<VS>{});            // lands while the softmax runs
-    valu_half();
-    mfma_half();
-    // End of the step: everything but the eight most recent requests of this wave has landed, i.e.
-    // K up to t+2 and V up to t+1: what step t+1 reads.  The barrier also separates the LDS reads before it from the
-    // requests after it into the same ring slots.
-    wait_vm<8>();
-    __syncthreads();
-  };
-
-  // fill and drain of the pipeline: the same parts one after the other, each guarded.  On entry
-  // sbuf holds S(t) (if t < n_pipe).
-  auto step_edge = [&](int t) {
-    request_k(t + KD);
-    request_v(t + VD);
-    if (t < n_pipe) {
-      bool chg;
-      sm_textbook(sbuf, pbuf, al, chg);
-      needed = __builtin_amdgcn_ballot_w64(chg) != 0;
-      if (needed) rescale(al);
-      pv(t & RM, pbuf);
+      acc_ready<ACC>(o);
     }
-    if (t + 1 < n_pipe) qk((t + 1) & RM, sbuf);
-    wait_vm<8>();      // as in a steady step
-    __syncthreads();
+#pragma unroll
+    for (int qb = 0; qb < QB; qb++) l_run[qb] += ps[qb];
+    // What the next steps read and prefetch has landed; their requests go into slots that nobody reads until the next
+    // barrier.  One barrier for two steps: at the end of an even step t K up to t + 4 and V up to t + 1, i.e. everything
+    // but the requests of the last three steps.  One for each: K up to t + 3 and V up to t, i.e. everything but the requests
+    // of the last two steps and those for V before them.
+    if constexpr (!Cfg_::BAR2) {
+      wait_vm<5 * NI>();
+      __syncthreads();
+    } else if constexpr (C == 0) {
+      wait_vm<3 * 2 * NI>();
+      __syncthreads();
+    }
   };
 
-  // ---- prologue: K(0..KD-1), V(0..VD-1) resident, S_0 computed.  From here on K(< t+KD) and
-  // V(< t+VD) have been requested before step t starts.
-#pragma unroll
-  for (int j = 0; j < KD; j++) request_k(j);
-#pragma unroll
-  for (int j = 0; j < VD; j++) request_v(j);
-  wait_vm<0>();
-  __syncthreads();
-  if (n_pipe > 0) qk(0, sbuf);
-  __syncthreads();   // all of QK(0) is done before any wave starts requesting into the ring again
-
+  // ---- fill: one sub-tile of K or of V into its slot
+  auto request_k = [&](auto j) {
+    constexpr int J = decltype(j)::value;
+    const unsigned char* base = pool + fetch_off(min(J, n_pipe - 1));
+    static_for<0, NI>([&](auto idx) {
+      request_m0(Tag<J % RING>{}, Tag<0>{}, idx);
+      asm volatile("s_nop 0");
+      request_one(base, base, idx);
+    });
+  };
+  auto request_v = [&](auto j) {
+    constexpr int J = decltype(j)::value;
+    const unsigned char* base = pool + fetch_off(min(J, n_pipe - 1));
+    static_for<NI, 2 * NI>([&](auto idx) {
+      request_m0(Tag<0>{}, Tag<J % RING>{}, idx);
+      asm volatile("s_nop 0");
+      request_one(base, base, idx);
+    });
+  };
   int t = 0;
-  step_edge(t++);                                             // t = 0: SM(0), PV(0), QK(1)
-  if (t + RING < n_pipe) {
-    // steady steps need 1 <= t and t + 1 < n_pipe; the unrolled loop is entered at t = 1 with the
-    // block offsets of sub-tiles t+RING-2 .. t+2*RING-1 at hand; each iteration fetches the next RING
-    off_prev2 = fetch_off(t + RING - 2);
-    off_prev1 = fetch_off(t + RING - 1);
+  // What the first sub-tile needs comes first: the wait for Q, which the compiler puts in front of the first product, is a
+  // wait for every request before it.
+  if (n_pipe > 0) {
+    request_k(Tag<0>{});
+    request_v(Tag<0>{});
+    request_k(Tag<1>{});
+  }
 #pragma unroll
-    for (int i = 0; i < RING; i++) off_cur[i] = fetch_off(t + RING + i);
-    int64_t off_nxt[RING];
-    auto fetch_next = [&](int t0) {
+  for (int db = 0; db < 8; db++)
 #pragma unroll
-      for (int i = 0; i < RING; i++) off_nxt[i] = fetch_off(t0 + 2 * RING + i);
-    };
-    auto rotate = [&]() {
-      off_prev2 = off_cur[RING - 2];
-      off_prev1 = off_cur[RING - 1];
+    for (int qb = 0; qb < QB; qb++) {
+      o[db][qb] = zero4;
+      pin_acc<ACC>(o[db][qb]);                          // set here, under the first requests
+    }
+  if (n_pipe > 0) {
 #pragma unroll
-      for (int i = 0; i < RING; i++) off_cur[i] = off_nxt[i];
-    };
-    for (; t + RING < n_pipe; t += RING) {
-      fetch_next(t);
-      static_for<0, RING>([&](auto idx) { step_steady(Tag<(decltype(idx)::value + 1) & RM>{}); });
-      rotate();
+    for (int qb = 0; qb < QB; qb++)
+#pragma unroll
+      for (int ks = 0; ks < 4; ks++) pin(qB[qb][ks]);
+    wait_vm<0>();
+    __syncthreads();
+    // K(0..K2-1), V(0), V(1): what the first steady steps read.  The rest in the order in which steps would have asked for
+    // it, K(j) in front of V(j - KA + VA): the waits of the steady steps count on that order.
+    constexpr int K2 = Cfg_::BAR2 ? 5 : 4, DV = KA - VA;
+    static_for<2, K2>([&](auto j) { request_k(j); });
+    static_for<1, K2 - DV>([&](auto j) { request_v(j); });
+    static_for<K2, RING>([&](auto j) {
+      request_k(j);
+      request_v(Tag<decltype(j)::value - DV>{});
+    });
+    qk_all(0, sb[0]);
+    softmax_all(sb[0], pb[0]);
+    t = 1;
+    if (n_pipe > 1) {
+      qk_all(1, sb[1]);
+      // K(0), whose slot is asked for next, is done with
+      wait_vm<((K2 - DV - 2) + 2 * (RING - K2)) * NI>();
+      __syncthreads();
+      if constexpr (KA == RING) {
+        request_k(Tag<KA>{});
+        request_v(Tag<VA>{});
+      }
+      if (t + 2 < n_pipe) {
+        static_for<0, PD>([&](auto idx) { pre[decltype(idx)::value] = load_opnd(idx, Tag<2>{}, Tag<0>{}); });
+        constexpr int U = Cfg_::UNROLL;
+        if (t + U < n_pipe) {
+          // offsets of sub-tiles t + VA .. t + KA + RING - 1
+          int64_t off_cur[U + DV], off_nxt[U];
+#pragma unroll
+          for (int i = 0; i < U + DV; i++) off_cur[i] = fetch_off(min(t + VA + i, n_pipe - 1));
+          for (; t + U < n_pipe; t += U) {
+#pragma unroll
+            for (int i = 0; i < U; i++) off_nxt[i] = fetch_off(min(t + KA + U + i, n_pipe - 1));
+            static_for<0, U>([&](auto h) {
+              constexpr int H = decltype(h)::value;
+              step(Tag<(H + 1) & 1>{}, [](auto d) { return Tag<(H + 1 + decltype(d)::value + RING) % RING>{}; }, pool + off_cur[H + DV], pool + off_cur[H]);
+            });
+#pragma unroll
+            for (int i = 0; i < DV; i++) off_cur[i] = off_cur[U + i];
+#pragma unroll
+            for (int i = 0; i < U; i++) off_cur[DV + i] = off_nxt[i];
+          }
+        }
+        // pairs of steps, ring slots at run time
+        for (; t + 2 < n_pipe; t += 2) {
+          auto base = [&](int j) { return pool + fetch_off(min(j, n_pipe - 1)); };
+          const unsigned char *k0 = base(t + KA), *k1 = base(t + 1 + KA), *v0 = base(t + VA), *v1 = base(t + 1 + VA);
+          step(Tag<1>{}, [&](auto d) -> int { return ring_slot(t + decltype(d)::value); }, k0, v0);
+          step(Tag<0>{}, [&](auto d) -> int { return ring_slot(t + 1 + decltype(d)::value); }, k1, v1);
+        }
+      }
     }
   }
-  for (; t < n_pipe; t++) step_edge(t);                       // remaining pipelined steps
 
-  // What the end of the kernel needs of its arguments is loaded again here: held in scalar registers through the
-  // loop, which has none to spare, it would be spilled.
   typedef const __attribute__((address_space(4))) AttnParams* const_paramsp;
   const_paramsp pe = (const_paramsp)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(pe));
 
-  // ---- sub-tiles on or past the diagonal: loaded synchronously, plain path.  The ring slots are
-  // written again below (by requests and, for rows past the context, by plain LDS stores), so
-  // every request of the pipelined part has to have landed first.  There are at most
-  // tile tokens / 32 + 1 of them, fewer than ring slots: they are requested together and computed
-  // after one wait (a group of RING at a time, should there ever be more).
-  // Rows past the context are not fetched, their V is written as zeros so that undefined pool bytes cannot
-  // reach the PV product.  Suffix rows come from the caller's arrays where the launch is given them: a
-  // block of 16 keys lies wholly in the prefix or wholly in the suffix.
+  // ---- sub-tiles on or past the diagonal: requested in groups of at most RING - 2
   const unsigned char* ks = (const unsigned char*)pe->k_suffix;
   const unsigned char* vs = (const unsigned char*)pe->v_suffix;
   auto request_tail = [&](int j) {
-    const int sfx_blk = 2 * (jb + j) + wblk - P / kBlockTokens;          // block of the suffix, negative: of the prefix
+    const int sfx_blk = 2 * (jb + j) + wblk - P / kBlockTokens;
     const int64_t boff = fetch_off(j);
-    const unsigned char *kb = pool + boff, *vb = kb + half_b;
+    const unsigned char *kb = pool + boff, *vb = kb;
     if (ks && sfx_blk >= 0) {
-      const int64_t soff = (int64_t)rd.q_off * (half_b / kBlockTokens) + sfx_blk * half_b;
+      const int64_t soff = (int64_t)rd.q_off * row_b + (int64_t)sfx_blk * half_b;
       kb = ks + soff;
-      vb = vs + soff;
+      vb = vs + soff - half_b;
     }
 #pragma unroll
     for (int h = 0; h < NI; h++) {
       const bool live = (jb + j) * kSK + wblk * 16 + brow0 + 4 * h < ctx_len;
-      const unsigned l_k = __builtin_amdgcn_readfirstlane(dma_lds + (j & RM) * kSlot + h * 1024);
+      const unsigned l_k = __builtin_amdgcn_readfirstlane(dma_lds + ring_slot(j) * kSlot + h * 1024);
       if (live) {
-        dma_1k(scalar_ptr(kb + h * rows4), h ? voff_k ^ 64u : voff_k, l_k);
-        dma_1k(scalar_ptr(vb + h * rows4), h ? voff_v ^ 128u : voff_v, l_k + kVBase);
+        dma_1k(scalar_ptr(kb), voff_k[h], l_k);
+        dma_1k(scalar_ptr(vb), voff_v[h], l_k + kVBase);
       } else {
         *(u32x4*)(smem + (l_k - lds0) + kVBase + (lane << 4)) = (u32x4){0u, 0u, 0u, 0u};
       }
     }
   };
+  constexpr int TG = RING - 2;
+  auto request_group = [&](int j0) {
+    for (int j = j0; j < min(n_sub, j0 + TG); j++) request_tail(j);
+  };
+
+  // ---- drain: PV(t-1), then the one or two sub-tiles that are left; S(t) is in sb[1] (t odd), P(t-1) in pb[0].  The first
+  // group of the tail is requested before them: the slots of sub-tiles t and t + 1 are not among its own.
+  if (n_pipe > 0) pv_all(ring_slot(t - 1), pb[0]);
   wait_vm<0>();
   __syncthreads();
-  for (int j0 = n_pipe; j0 < n_sub; j0 += RING) {
-    const int j1 = min(n_sub, j0 + RING);
-    for (int j = j0; j < j1; j++) request_tail(j);
+  request_group(n_pipe);
+  if (t > 0 && t < n_pipe) {
+    softmax_all(sb[1], pb[1]);
+    pv_all(ring_slot(t), pb[1]);
+    if (t + 1 < n_pipe) {
+      qk_all(ring_slot(t + 1), sb[0]);
+      softmax_all(sb[0], pb[0]);
+      pv_all(ring_slot(t + 1), pb[0]);
+    }
+  }
+  for (int j0 = n_pipe; j0 < n_sub; j0 += TG) {
+    if (j0 > n_pipe) {
+      __syncthreads();                                   // everyone has read the group before
+      request_group(j0);
+    }
     wait_vm<0>();
     __syncthreads();
-    for (int j = j0; j < j1; j++) {
+    for (int j = j0; j < min(n_sub, j0 + TG); j++) {
       const int k0 = (jb + j) * kSK;
-      if (!(wave_active && k0 <= pq_max)) continue;
-      STile s;
-      qk(j & RM, s);
-      if (k0 + 31 > pq_min) {
+      // row block by row block: V of a sub-tile that a block sees nothing of stays away from it (0 times infinity)
+      static_for<0, HB>([&](auto hh) {
+        constexpr int H = decltype(hh)::value;
+        const int pq_min = P + wq0[H];
+        if (!(wq0[H] < S && k0 <= P + min(wq0[H] + 32, S) - 1)) return;
+        f32x4 s2[2][2];
+        qk(ring_slot(j), Tag<2 * H>{}, s2);
+        if (k0 + 31 > pq_min) {
 #pragma unroll
-        for (int kb = 0; kb < 2; kb++)
+          for (int kb = 0; kb < 2; kb++)
 #pragma unroll
-          for (int qb = 0; qb < 2; qb++)
+            for (int q = 0; q < 2; q++)
 #pragma unroll
-            for (int r = 0; r < 4; r++)
-              if (k0 + 16 * kb + 4 * g + r > pq_min + 16 * qb + c) s.t[kb][qb][r] = -INFINITY;
-      }
-      bf16x8 pb[2];
-      float alpha[2];
-      bool changed;
-      sm_textbook(s, pb, alpha, changed);
-      if (__builtin_amdgcn_ballot_w64(changed) != 0) rescale(alpha);
-      pv(j & RM, pb);
+              for (int r = 0; r < 4; r++)
+                if (k0 + 16 * kb + 4 * g + r > pq_min + 16 * q + c) s2[kb][q][r] = -INFINITY;
+        }
+        bf16x8 pw[2];
+        softmax(Tag<2 * H>{}, s2, pw);
+        pv(ring_slot(j), Tag<2 * H>{}, Tag<2>{}, pw);
+      });
     }
-    if (j1 < n_sub) __syncthreads();      // the next group overwrites these slots
   }
 
-  // ---- suffix rows -> pool: by the workgroup that has the end of the context, once per KV head
-  if (ks && wi.sub_end * kSK >= ctx_len && hg * HW % (Hq / Hkv) == 0)
+  // ---- suffix rows -> pool: once per KV head, by the workgroup of the tile's first piece (the last one has the
+  // diagonal, up to nine sub-tiles) or, for small tiles, of the last one (which is the shorter)
+  if (ks && (HB == 2 ? jb == 0 : wi.sub_end * kSK >= ctx_len) && hg * HW % (Hq / Hkv) == 0)
     append_rows<64 * NW>(ks, vs, (unsigned char*)const_cast<void*>(pe->pool_layer), pe->tables + rd.table_off, rd, Hkv, kv, tid);
 
-  // ---- results: of a cut tile's piece the unnormalised O, the reference (exponent units) and the row sum, else the
-  // output.  Lane holds d = 16db + 4g + r of the rows 16qb + c.  A row that lies before the piece's first key saw none:
-  // its sums are no numbers by now, a row sum of 0 says so.  NaN of a row that did see keys stays.
-  {
+  // ---- results: of a cut tile's piece the unnormalised O, the reference (exponent units) and the row sum, else the output
+  acc_ready<ACC>(o);
 #pragma unroll
-    for (int qb = 0; qb < 2; qb++) {
-      if (wq0 + 16 * qb >= S) continue;      // wave-uniform: every lane takes part in the exchanges
-      const float lt = quad_sum(l_run[qb]);
-      const int tokq = wq0 + 16 * qb + c;
-      if (wi.n_splits > 1) {
-        const int64_t slot = ((int64_t)it * NHG + hg) * NW + wave;
-        if (tokq < S) {
-          const int64_t prow = slot * 32 + 16 * qb + c;
-          store_piece(pe->part_o + prow * kD, g, o, qb);
-          if (g == 0) *(f32x2*)(pe->part_ml + prow * 2) = (f32x2){m_run[qb], P + tokq < jb * kSK ? 0.f : lt};
-        }
-      } else {
-        const float inv = 1.f / lt;
-        unsigned short* row = (unsigned short*)pe->out + ((int64_t)(rd.q_off + tokq) * Hq + hq) * kD;
-#pragma unroll
-        for (int d = 0; d < 4; d++) store_out(row, d, g, o[2 * d][qb], o[2 * d + 1][qb], inv, tokq < S);
+  for (int qb = 0; qb < QB; qb++) {
+    if (wq0[qb >> 1] + 16 * (qb & 1) >= S) continue;     // wave-uniform: every lane takes part in the exchanges
+    const float lt = quad_sum(l_run[qb]);
+    const int tokq = wq0[qb >> 1] + 16 * (qb & 1) + c;
+    if (wi.n_splits > 1) {
+      const int64_t slot = ((int64_t)it * NHG + hg) * (HB * NW) + row_block(qb >> 1);
+      // a row that lies before the piece's first key saw none: a row sum of 0 says so
+      if (tokq < S) {
+        const int64_t prow = slot * 32 + 16 * (qb & 1) + c;
+        store_piece(pe->part_o + prow * kD, g, o, qb);
+        if (g == 0) *(f32x2*)(pe->part_ml + prow * 2) = (f32x2){m_run[qb], P + tokq < jb * kSK ? 0.f : lt};
       }
+    } else {
+      const float inv = 1.f / lt;
+      unsigned short* row = (unsigned short*)pe->out + ((int64_t)(rd.q_off + tokq) * Hq + hq[qb >> 1]) * kD;
+#pragma unroll
+      for (int d = 0; d < 4; d++) store_out(row, d, g, o[2 * d][qb], o[2 * d + 1][qb], inv, tokq < S);
     }
   }
   if (threadIdx.x == 0) clock_end(pe->clock.words);

@@ -26,8 +26,8 @@ static int rows_step_cost(bool f32, int head_dim) {
 int attn_pipe_tile_tokens(int heads_per_wg);
 int attn_duo_tile_tokens(int heads_per_wg);
 
-// Two kernels serve bf16 / head-dim-128 batches: kAttnPipe (attn_wide.h: 64 query rows per wave, 64-token tiles for four
-// heads: half the K/V traffic into LDS and out of it per query row) and kAttnDuo (attn_pipeline.h: 32 rows per wave, two
+// Two kernels serve bf16 / head-dim-128 batches: kAttnPipe (64 query rows per wave, 64-token tiles for four
+// heads: half the K/V traffic into LDS and out of it per query row) and kAttnDuo (32 rows per wave, two
 // 4-wave workgroups per CU, 32-token tiles).  The smaller tiles win where half of a 64-token tile would be empty (the short
 // queries of the paper's Table 1), and where the whole batch is little work: they spread it over twice as many workgroups,
 // which fill and drain faster.  Measured, us a call, kAttnPipe / kAttnDuo: 0+1024 tokens (8.5 steps of 32 keys per CU)
@@ -76,8 +76,7 @@ std::vector<PlanTile> plan_tiles(const int32_t* prefix_blocks, const int32_t* su
   return tiles;
 }
 
-// The kernels run a piece of n sub-tiles as one fill step, unrolled steady iterations and a few
-// slower drain steps; lengths of the form 8k + 2 leave two drain steps in either kernel.
+// The kernels run a piece of n sub-tiles as a fill step, pairs of steady steps and one (n even) or two drain steps.
 // The shortest piece is a 32nd of the tile, between 8 and split_min (48): a piece of 8 sub-tiles is mostly
 // fill, but with one or two tiles the alternative is an idle chip.  Measured (8B shape, us a call with three
 // callers in turn, floor 48 -> this): 2048+1 tokens 29.2 -> 13.7, 8192+1 31.0 -> 14.1, 16384+28 34.2 -> 23.0,
@@ -89,9 +88,14 @@ int plan_piece_len(int n_sub, int n_max, int want, const PlanParams& p) {
   const int n = std::max(1, std::min(want, p.force_splits ? n_sub : n_sub / floor));
   int len = (n_sub + n - 1) / n;
   if (p.step_cost) return (len + 3) / 4 * 4;       // packed rows: the same number of wave steps on each of the four SIMDs
-  if (n > 1 && !p.force_splits) len = (len + 5) / 8 * 8 + 2;
+  if (n > 1 && !p.force_splits) len = p.long_pieces ? (len + 5) / 8 * 8 + 2 : (len + 1) / 2 * 2;
   return len;
 }
+
+// kAttnDuo: what a step of a workgroup costs that has its CU to itself, of a step of one that shares it (0.69 us against
+// 0.95 at 65536+100 tokens).  What this decides: 61440+28 tokens in 30 pieces (240 workgroups) 51 us a call, in 39 (312) 66;
+// 8192+100 in 8 pieces (256) 31.9, in 16 (512) 36.3.
+constexpr double kAlone = 0.7;
 
 int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots) {
   if (p.force_splits) return p.force_splits;
@@ -117,7 +121,7 @@ int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t
     }
     if (n > 1 && slots > max_slots) break;
     // no order of the pieces beats the average load: most candidates need no replay
-    if (n > 1 && (double)(work / p.wg_slots) + (cut ? p.split_fill : 0) >= best * 0.98) {
+    if (n > 1 && (slots <= p.alone ? kAlone : 1.) * (double)(work / p.wg_slots) + (cut ? p.split_fill : 0) >= best * 0.98) {
       if (!cut) break;
       continue;
     }
@@ -136,7 +140,7 @@ int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t
         }
       }
     }
-    const double span = (double)end + (cut ? p.split_fill : 0);
+    const double span = (slots <= p.alone ? kAlone * (double)end : (double)end) + (cut ? p.split_fill : 0);
     if (n == 1 || span < best * 0.98) {            // a cut has to win by 2 % over what is chosen so far
       best = span;
       want = n;
@@ -219,7 +223,7 @@ extern "C" int calvo_attn_plan_items(int32_t n_q_heads, int32_t n_kv_heads, int3
   const int hw = attn_heads_per_wg(n_q_heads, n_kv_heads);
   const int variant = attn_mfma_choose(prefix_blocks, suffix_lens, n_reqs, hw, n_q_heads / hw, n_cus);
   const std::vector<PlanTile> tiles = plan_tiles(prefix_blocks, suffix_lens, n_reqs, attn_mfma_tile_tokens(variant, hw));
-  const PlanParams p{n_q_heads / hw, n_cus * (8 / attn_mfma_waves_per_wg(variant)), 48, 30, 0};
+  const PlanParams p{n_q_heads / hw, n_cus * (8 / attn_mfma_waves_per_wg(variant)), 48, 30, 0, false, 0, variant == kAttnDuo ? n_cus : 0};
   PlanItems pi;
   if (chunk_blocks > 0) {
     pi = plan_items_chunked(tiles, prefix_blocks, chunk_blocks, (max_blocks + chunk_blocks - 1) / chunk_blocks);
@@ -251,7 +255,7 @@ extern "C" int calvo_attn_plan(int32_t n_q_heads, int32_t n_kv_heads, int32_t n_
   const int variant = attn_mfma_choose(prefix_blocks, suffix_lens, n_reqs, hw, n_q_heads / hw, n_cus);
   const int tt = attn_mfma_tile_tokens(variant, hw);
   const std::vector<PlanTile> tiles = plan_tiles(prefix_blocks, suffix_lens, n_reqs, tt);
-  PlanParams p{n_q_heads / hw, n_cus * (8 / attn_mfma_waves_per_wg(variant)), 48, 30, 0};
+  PlanParams p{n_q_heads / hw, n_cus * (8 / attn_mfma_waves_per_wg(variant)), 48, 30, 0, false, 0, variant == kAttnDuo ? n_cus : 0};
   const int want = plan_pieces(tiles, p);
   int64_t items = 0;
   for (const PlanTile& t : tiles) {

@@ -1143,7 +1143,7 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
   if (ap.mfma) {
     const std::vector<PlanTile> tiles = plan_tiles(pblocks.data(), slens.data(), n_reqs, ap.tile_tokens);
     const PlanParams pp{cf.n_q_heads / ap.HW, c->n_cus * (8 / attn_mfma_waves_per_wg(ap.variant)), c->split_min, c->split_fill,
-                        c->force_splits, small};
+                        c->force_splits, small, 0, ap.variant == kAttnDuo && !small ? c->n_cus : 0};
     if (ap.chunked) {
       ap.plan = plan_items_chunked(tiles, pblocks.data(), cb, nck);
     } else {
