@@ -42,7 +42,7 @@
  * workgroups of the zero-copy scatter; CALVO_MERGE_MIB = most bytes of
  * consecutive small layers that one transfer carries (default 256, 0 = every
  * layer by itself).  Read by every calvo_prefill_attn:
- * CALVO_ATTN_VARIANT = 3 or 4 forces the 8-wave or the 4-wave bf16 kernel.
+ * CALVO_ATTN_VARIANT = 3 or 4 forces the bf16 kernel with 64 or with 32 query rows per wave.
  * Test hooks, read by calvo_create: CALVO_INGEST_DELAY_US = n makes the host
  * sleep n microseconds before it queues each transfer of the L2 -> L1 stage
  * (the loading stage becomes the slow one; nothing on the device changes);
@@ -522,7 +522,7 @@ int calvo_attn_plan_items(int32_t n_q_heads, int32_t n_kv_heads, int32_t n_cus, 
                           int32_t capacity, int32_t* n_items);
 
 /* Measurement helper: which attention kernel the most recent calvo_prefill_attn for `layer` chose
- * (*kernel: 3 = 8-wave workgroups with 64-token tiles, 4 = two 4-wave workgroups per CU with 32-token
+ * (*kernel: 3 = 64 query rows per wave, 64-token tiles, 4 = 32 rows per wave, two workgroups per CU, 32-token
  * tiles, 0-2 = comparison variants, -1 = the packed-rows kernel for fp32 pools / other head dims) and
  * how many workgroups its work items made (*n_workgroups; 0 for the packed-rows kernel).  Either
  * output may be NULL.  CALVO_ENOTREADY if none was queued. */

@@ -126,8 +126,8 @@ hipError_t launch_merge_splits(const AttnParams& p, const int32_t* split_tiles, 
 int attn_pipe_tile_tokens(int heads_per_wg);
 
 constexpr int kBlockTokens = 16;
-// Entries appended to every request's device-side block table (copies of its last entry): the
-// pipelined attention kernel requests blocks up to 2 * (ring depth + 1) + 2 past the last one.
+// Entries appended to every request's device-side block table (copies of its last entry): the last sub-tile may be half
+// a block pair, the rest is slack.
 constexpr int kTablePad = 32;
 
 }  // namespace calvo
