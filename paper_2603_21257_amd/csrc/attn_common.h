@@ -32,7 +32,8 @@ __device__ inline void static_for(F&& f) {
   }
 }
 constexpr int kPD = 4;   // LDS operand reads run this many operands ahead
-constexpr float kLazyBound = 65536.f;   // a lane's partial row sum of a sub-tile may reach 2^16 before the reference is raised
+constexpr float kRefShift = 16.f;       // the softmax reference is this far above the maximum it was taken from (exponent units)
+constexpr float kLazyBound = 1.f;       // a lane's partial row sum of a sub-tile may reach this before the reference is raised
 
 // lanes [32,64) of a <-> lanes [0,32) of b (the compiler builtin for this instruction returns
 // its first result twice, hence inline asm)

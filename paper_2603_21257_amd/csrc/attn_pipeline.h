@@ -57,13 +57,14 @@
 // unbiased; a row's result moves by at most 2^-9 relative, the size of the output's own rounding).
 // The row sum must not use v_dot2_f32_bf16: measured on MI355X, a dot-product instruction waits for
 // the matrix pipe (16 of them take 616 cycles beside another wave's MFMA stream against 104 alone),
-// whereas v_exp_f32, v_fma_f32, v_add_f32 and v_cvt_pk_bf16_f32 issue in the shadow of MFMAs.  In the steady
-// loop m is not the running maximum: the weights of a sub-tile are computed against the current m,
-// and only if a lane's partial row sum passes 2^16 (or is not a number) is the sub-tile's maximum
-// taken, m raised, l and O rescaled and the weights computed again.  m is always the exact maximum
-// of an earlier sub-tile, so the largest weight of a row is >= 1: nothing underflows, and with
-// fp32 accumulation and bf16 weights (relative precision) the result is that of the textbook
-// recurrence up to rounding.
+// whereas v_exp_f32, v_fma_f32, v_add_f32 and v_cvt_pk_bf16_f32 issue in the shadow of MFMAs.
+// m is not the running maximum: it lies 16 (kRefShift) above the maximum of some earlier sub-tile.  The weights of a sub-tile
+// are computed against the current m, and only if a lane's partial row sum passes 1 (kLazyBound), i.e. a score is
+// about 16 powers of two above that maximum, is the sub-tile's own taken, m raised, l and O rescaled and the weights computed
+// again.  So no weight is above 1, as in the textbook recurrence: a sum w V leaves the range of fp32 only where that one's
+// does.  The largest weight of a row is at least 2^-16: scores down to 2^-110 of the largest count, and with fp32
+// accumulation and bf16 weights (relative precision) the result is the textbook one's up to rounding; the products keep
+// subnormal sums (measured: the error is the same down to |V| of 2^-120).
 //
 // Data movement.  K and V go from the pool straight into LDS with global_load_lds_dwordx4 (no register staging), 1 KiB
 // (4 token rows x 256 B) per wave instruction, into two rings (K and V) of RING 8 KiB slots.  Step t requests K(t+KA) and
@@ -317,7 +318,7 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
 #pragma unroll
       for (int q = 0; q < N; q++) {
         const int qb = QB0 + q;
-        const float m_new = fmaxf(m_run[qb], row_max(s[0][q], s[1][q]) * c2);
+        const float m_new = fmaxf(m_run[qb], __builtin_fmaf(row_max(s[0][q], s[1][q]), c2, kRefShift));
         alpha[q] = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
         changed |= m_run[qb] != -INFINITY && !(alpha[q] == 1.f);         // without a reference O is 0
         m_run[qb] = m_new;
@@ -443,7 +444,7 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
       acc_ready<ACC>(o);
 #pragma unroll
       for (int qb = 0; qb < QB; qb++) {
-        const float d = fmaxf(expo(row_max(s[0][qb], s[1][qb]), qb), 0.f);
+        const float d = fmaxf(expo(row_max(s[0][qb], s[1][qb]), qb) + kRefShift, 0.f);
         const float a = __builtin_amdgcn_exp2f(-d);
         l_run[qb] *= a;
         m_run[qb] += d;

@@ -81,6 +81,45 @@ def test_large_v_under_rising_scores(dtype, D, value, columns, pieces, monkeypat
     assert np.isfinite(g).all() and d.max() <= tmx and d.mean() <= tmean, (d.max(), d.mean())
 
 
+@pytest.mark.parametrize("variant", ["3", "4"])
+@pytest.mark.parametrize("value,columns", [(1e35, slice(None)), (1e33, slice(0, 1))])
+@pytest.mark.parametrize("P,S,rise", [
+    (0, 64, (32, 33)), (0, 300, (33, 300)), (48, 200, (64, 70)),                         # diagonal
+    (96, 5, (64, 96)), (352, 5, (320, 352)),                                             # drain
+    (128, 5, (32, 33)), (160, 64, (64, 96)), (1024, 20, (256, 1024)), (4096, 70, (3000, 3001))])
+@pytest.mark.parametrize("pieces", [0, 2])
+def test_large_v_under_rising_scores_of_128_wide_heads(variant, value, columns, P, S, rise, pieces, monkeypatch):
+    """Scores of the keys `rise` are 12 powers of two above the others (eight of them stay below the 2^16 at which the
+    reference moves), wherever they lie: in the pipelined steps, behind them or on the diagonal."""
+    monkeypatch.setenv("CALVO_ATTN_VARIANT", variant)
+    if pieces:
+        monkeypatch.setenv("CALVO_ATTN_SPLITS", str(pieces))
+    D = 128
+    w = wl.make_custom(wl.Shape(1, 4, 1, D, "bf16", (P + S) // 16 + 9), [(P, S)], seed=904)
+    w.q[...] = stored(1.0, "bf16")
+    first = w.requests[0].host_block_start
+    kv = w.host_kv.reshape(1, w.host_blocks, 2, 16, 1, D)[0, first:first + P // 16]
+    kv[:, 0] = 0
+    w.k_suffix[...] = 0
+    high = stored(np.round(12 * np.log(2) * np.sqrt(D)), "bf16")
+    for t in range(*rise):
+        if t < P:
+            kv[t // 16, 0, t % 16, :, 0] = high
+        else:
+            w.k_suffix[0, t - P, :, 0] = high
+    factor = np.ones(D)
+    factor[columns] = value
+    for v in (kv[:, 1], w.v_suffix):
+        x = (np.abs(hh.orc.widen(v)) * factor).astype(np.float32)
+        v[...] = (x.view(np.uint32) >> 16).astype(np.uint16)
+    _, got = hh.run_hip(w)
+    _, want = hh.run_oracle(w)
+    g = hh.orc.widen(got)
+    tmx, tmean = hh.TOL["bf16"]
+    d = np.abs(g / factor - want / factor)
+    assert np.isfinite(g).all() and d.max() <= tmx and d.mean() <= tmean, (d.max(), d.mean())
+
+
 def long_one_token(seed, P=8192):
     s = wl.Shape(1, 8, 2, 128, "bf16", P // 16 + 9)
     w = wl.make_custom(s, [(P, 1)], seed=seed)
