@@ -88,7 +88,7 @@ int plan_piece_len(int n_sub, int n_max, int want, const PlanParams& p) {
   const int n = std::max(1, std::min(want, p.force_splits ? n_sub : n_sub / floor));
   int len = (n_sub + n - 1) / n;
   if (p.step_cost) return (len + 3) / 4 * 4;       // packed rows: the same number of wave steps on each of the four SIMDs
-  if (n > 1 && !p.force_splits) len = p.long_pieces ? (len + 5) / 8 * 8 + 2 : (len + 1) / 2 * 2;
+  if (n > 1 && !p.force_splits) len = p.rounded ? (len + 5) / 8 * 8 + 2 : (len + 1) / 2 * 2;
   return len;
 }
 

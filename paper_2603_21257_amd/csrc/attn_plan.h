@@ -32,12 +32,11 @@ struct PlanParams {
   int split_min;      // shortest piece of a long tile, in sub-tiles (plan_piece_len scales it down for short ones)
   int split_fill;     // cost of a workgroup's pipeline fill and drain, in sub-tile steps
   int force_splits;   // > 0: cut every tile into this many pieces (test knob)
-  // Few partial results: pieces never below split_min, the same number of every tile, no counts between the coarse
-  // ones, lengths of the form 8k + 2.  What calvo_prefill_attn_noalloc accepts depends on this rule: a batch it fits into the fixed-size array
-  // has to fit for good.
+  // Few partial results: pieces never below split_min, the same number of every tile, no counts between the coarse ones.
   bool long_pieces = false;
   int step_cost = 0;  // packed-rows kernel: cost of a wave's 32-key step, in units of split_fill; else 0
   int alone = 0;      // > 0: up to this many workgroups have a CU each, which makes them faster (attn_plan.cpp)
+  bool rounded = false;   // piece lengths of the form 8k + 2 instead of even ones
 };
 
 // A work item is one workgroup's share of the attention of one request: a tile of suffix tokens

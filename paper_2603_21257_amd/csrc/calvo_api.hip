@@ -1120,11 +1120,22 @@ int kept_pieces(calvo_ctx* c, int variant, const calvo_request* reqs, int n_reqs
   return c->plan_want;
 }
 
+// Which plan.  What calvo_prefill_attn_noalloc accepts is what fits its fixed-size array by one of them, tried in this
+// order.  The three behind the best one do not depend on what is known of the kernels' speed (but for kLong's choice of
+// kernel): a batch that they fit is not refused when the best plan changes.  None of them stands for another: few pieces for
+// every tile of a ragged batch can be more than many for its longest.  Packed-rows launches know two plans: the best, and
+// one without work items (uncut tiles).
+enum class PlanRule {
+  kBest,
+  kRounded,       // the kernel that the suffix lengths alone ask for (attn_mfma_choose), pieces of 8k + 2 sub-tiles
+  kLong,          // few, long pieces (PlanParams::long_pieces)
+  kLongByRows,    // the same with the kernel of kRounded
+};
+bool by_rows(PlanRule rule) { return rule == PlanRule::kRounded || rule == PlanRule::kLongByRows; }
+
 // cb > 0: the layer was loaded in nck chunks of cb block indices and attention follows the chunks.
-// small: what needs the least room for descriptors and partial results - a packed-rows launch without work
-// items (uncut tiles), the long pieces only of the others.  by_rows: see attn_mfma_choose.
 void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const int32_t* cu_suffix, int total, int cb,
-                    int nck, AttnPlan& ap, bool small = false, bool by_rows = false) {
+                    int nck, AttnPlan& ap, PlanRule rule = PlanRule::kBest) {
   const calvo_config& cf = c->cfg;
   ap.n_reqs = n_reqs;
   ap.total = total;
@@ -1133,7 +1144,7 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
   ap.variant = 0;
   std::vector<int32_t> pblocks(n_reqs), slens(n_reqs);
   for (int r = 0; r < n_reqs; r++) { pblocks[r] = reqs[r].n_prefix_blocks; slens[r] = reqs[r].suffix_len; }
-  if (ap.mfma) ap.variant = attn_mfma_choose(pblocks.data(), slens.data(), n_reqs, ap.HW, cf.n_q_heads / ap.HW, c->n_cus, by_rows);
+  if (ap.mfma) ap.variant = attn_mfma_choose(pblocks.data(), slens.data(), n_reqs, ap.HW, cf.n_q_heads / ap.HW, c->n_cus, by_rows(rule));
   ap.tile_tokens = ap.mfma ? attn_mfma_tile_tokens(ap.variant, ap.HW) : 1;
   // Work items: tiles of suffix tokens, heaviest first, each possibly cut into split-KV pieces
   // (consecutive work items) that the merge kernel combines; see attn_plan.cpp.
@@ -1142,18 +1153,20 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
   ap.plan = PlanItems();
   if (ap.mfma) {
     const std::vector<PlanTile> tiles = plan_tiles(pblocks.data(), slens.data(), n_reqs, ap.tile_tokens);
-    const PlanParams pp{cf.n_q_heads / ap.HW, c->n_cus * (8 / attn_mfma_waves_per_wg(ap.variant)), c->split_min, c->split_fill,
-                        c->force_splits, small, 0, ap.variant == kAttnDuo && !small ? c->n_cus : 0};
+    PlanParams pp{cf.n_q_heads / ap.HW, c->n_cus * (8 / attn_mfma_waves_per_wg(ap.variant)), c->split_min, c->split_fill, c->force_splits};
+    pp.long_pieces = rule == PlanRule::kLong || rule == PlanRule::kLongByRows;
+    pp.rounded = rule != PlanRule::kBest;
+    pp.alone = rule == PlanRule::kBest && ap.variant == kAttnDuo ? c->n_cus : 0;
     if (ap.chunked) {
       ap.plan = plan_items_chunked(tiles, pblocks.data(), cb, nck);
     } else {
-      ap.plan = plan_items(tiles, kept_pieces(c, ap.variant + (small ? 16 : 0), reqs, n_reqs, tiles, pp, INT64_MAX), pp);
+      ap.plan = plan_items(tiles, kept_pieces(c, ap.variant + 16 * (int)rule, reqs, n_reqs, tiles, pp, INT64_MAX), pp);
     }
   } else {
     const RowsShape shape = attn_rows_shape(cf.dtype == CALVO_F32, cf.head_dim);
     const std::vector<PlanTile> tiles = plan_row_tiles(pblocks.data(), slens.data(), n_reqs, cf.n_q_heads / cf.n_kv_heads, shape.tile_rows);
     ap.row_tiles = (int)tiles.size();
-    if (!small) {
+    if (rule == PlanRule::kBest) {
       const PlanParams pp = rows_plan_params(shape, cf.n_kv_heads, c->n_cus, c->force_splits);
       ap.plan = plan_items(tiles, kept_pieces(c, ap.variant, reqs, n_reqs, tiles, pp, kStaticPartSlots), pp);
       if (ap.plan.items.size() * (size_t)cf.n_kv_heads > kStaticPartSlots && !ap.plan.split_tiles.empty())
@@ -1175,7 +1188,8 @@ struct KeptBatch {
   std::vector<Req> reqs;
   std::vector<int32_t> pblocks, slens, cu;
   int cb = 0, nck = 0;
-  bool small = false, by_rows = false, on_device = false;      // see make_attn_plan; ap.blob is what the context's device buffer holds
+  PlanRule rule = PlanRule::kBest;
+  bool on_device = false;                     // ap.blob is what the context's device buffer holds
   AttnPlan ap;                                // ap.blob has the block tables
 
   bool holds(const calvo_request* rq, int n_reqs, const int32_t* cu_suffix) const {
@@ -1208,7 +1222,7 @@ struct KeptBatch {
 // The kernel shape the plan was made for is still the one to take (an environment variable can force it per call).
 bool same_shape(const calvo_ctx* c, const KeptBatch& k) {
   return !k.ap.mfma || attn_mfma_choose(k.pblocks.data(), k.slens.data(), (int)k.slens.size(), k.ap.HW, c->cfg.n_q_heads / k.ap.HW, c->n_cus,
-                                        k.by_rows) == k.ap.variant;
+                                        by_rows(k.rule)) == k.ap.variant;
 }
 
 hipError_t launch_attn(int variant, const AttnParams& p, hipStream_t stream) {
@@ -1419,29 +1433,24 @@ int calvo::host::prefill_attn_impl(calvo_ctx* c, int layer, const void* q, const
   }
   auto fits = [](const AttnPlan& a) { return a.blob.size() <= kStaticBlobInts && a.part_need <= kStaticPartSlots; };
   // a plan made for the other entry point is taken over only if this one would make the same
-  if (!known || kept->cb != cb || kept->nck != nck || (use_static ? !kept->small && !fits(kept->ap) : kept->small) ||
-      !same_shape(c, *kept)) {
+  const bool best = kept && kept->rule == PlanRule::kBest;
+  if (!known || kept->cb != cb || kept->nck != nck || (use_static ? best && !fits(kept->ap) : !best) || !same_shape(c, *kept)) {
     if (!kept) {
       c->kept = std::make_shared<KeptBatch>();
       kept = (KeptBatch*)c->kept.get();
     }
     kept->reqs.clear();                       // holds nothing until the plan is made
-    kept->on_device = kept->small = kept->by_rows = false;
+    kept->on_device = false;
+    kept->rule = PlanRule::kBest;
     kept->ap = AttnPlan();
     kept->cb = cb;
     kept->nck = nck;
     make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, kept->ap);
-    if (use_static && !fits(kept->ap)) {
-      kept->small = true;
+    for (PlanRule rule : {PlanRule::kRounded, PlanRule::kLong, PlanRule::kLongByRows}) {
+      if (!use_static || fits(kept->ap) || (!kept->ap.mfma && kept->rule != PlanRule::kBest)) break;
+      kept->rule = rule;
       kept->ap = AttnPlan();
-      make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, kept->ap, true);
-      // What this entry point accepts depends on the kernel that the suffix lengths alone ask for: a batch that fits
-      // with it fits for good.
-      if (!fits(kept->ap) && kept->ap.mfma) {
-        kept->by_rows = true;
-        kept->ap = AttnPlan();
-        make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, kept->ap, true, true);
-      }
+      make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, kept->ap, rule);
     }
     kept->take(reqs, n_reqs, cu_suffix);
   }

@@ -75,3 +75,36 @@ def test_noalloc_rejects_what_does_not_fit(monkeypatch):
         assert bool((out == 7.0).all())          # nothing was queued
     finally:
         cb.calvo_destroy(ctx)
+
+
+# (head layout, lengths): ragged batches whose best plan and whose plan with few, long pieces both need more partial
+# results than the array holds on 256 CUs
+RAGGED = [(32, 8, [(560, 3), (23936, 7), (5600, 33), (22976, 1486)]), (64, 8, [(7968, 434), (54432, 10), (9408, 41)]),
+          (40, 8, [(9392, 2), (78240, 35)]), (48, 8, [(6608, 584), (5312, 8)]), (32, 8, [(0, 10), (43328, 105), (864, 115)])]
+
+
+@pytest.mark.parametrize("hq,hkv,lens", RAGGED)
+def test_noalloc_takes_ragged_batches(hq, hkv, lens):
+    import torch
+    shape = wl.Shape(1, hq, hkv, 128, "bf16", sum(-(-(p + s) // 16) for p, s in lens) + 9)
+    w = wl.make_custom(shape, lens, seed=75, with_payload=False)
+    gen = torch.Generator(device="cuda:0").manual_seed(75)
+    normal = lambda *n: torch.randn(n, generator=gen, dtype=torch.float32, device="cuda:0").to(torch.bfloat16)
+    pool = normal(shape.pool_blocks, 2, 16, hkv, 128)
+    q, ks, vs = normal(w.total_suffix, hq, 128), normal(w.total_suffix, hkv, 128), normal(w.total_suffix, hkv, 128)
+    out = torch.full_like(q, float("nan"))
+    torch.cuda.synchronize()
+    ctx = cb.calvo_create(1, hq, hkv, 128, cb.CALVO_BF16, shape.pool_blocks, pool)
+    try:
+        reqs = [cb.make_request(None, 0, r.table, r.n_prefix_blocks, r.suffix_len, r.n_prefix_blocks) for r in w.requests]
+        cb.calvo_prefill_attn_noalloc(ctx, 0, q, ks, vs, out, reqs, w.cu_suffix)
+    finally:
+        cb.calvo_destroy(ctx)
+    view = hh.to_numpy_stored(pool, shape)                  # with the suffix rows
+    got, qn = hh.to_numpy_stored(out, shape), hh.to_numpy_stored(q, shape)
+    assert np.isfinite(hh.orc.widen(got)).all()
+    for i, r in enumerate(w.requests):
+        a, b = int(w.cu_suffix[i]), int(w.cu_suffix[i + 1])
+        rows = sorted({0, (b - a) // 2, b - a - 1})
+        want = hh.orc.prefill_attn_sampled(view, qn[a:b], r.table, r.prefix_len, r.suffix_len, 16, rows)
+        hh.assert_attn_close(got[a:b][rows], want, "bf16")
