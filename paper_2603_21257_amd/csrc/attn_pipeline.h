@@ -143,15 +143,20 @@ __device__ inline void mfma_next(f32x4& s, const bf16x8& a, const bf16x8& b) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(s) : "v"(a), "v"(b));
 }
 // The compiler knows nothing of the waits that these need where vector instructions write an operand or touch a result
-// before or after them.
+// before or after them.  A value pinned on both sides of this keeps its vector instructions out of the way on either.
 __device__ inline void mfma_settle() { asm volatile("s_nop 15"); }
 template <bool ACC, int QB>
-__device__ inline void acc_ready(f32x4 (&o)[8][QB]) {
-  mfma_settle();
+__device__ inline void pin_all(f32x4 (&o)[8][QB]) {
 #pragma unroll
   for (int db = 0; db < 8; db++)
 #pragma unroll
     for (int qb = 0; qb < QB; qb++) pin_acc<ACC>(o[db][qb]);
+}
+template <bool ACC, int QB>
+__device__ inline void acc_ready(f32x4 (&o)[8][QB]) {
+  pin_all<ACC>(o);
+  mfma_settle();
+  pin_all<ACC>(o);
 }
 
 // largest of the numbers (a NaN counts as nothing)
@@ -355,9 +360,13 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
     for (int q = 0; q < N; q++) asm volatile("" : "+v"(s[0][q]), "+v"(s[1][q]));
   };
   // O of N query blocks from QB0 on
-  auto pv = [&](int slot, auto qb0, auto n, const bf16x8* pw) {
+  auto pv = [&](int slot, auto qb0, auto n, bf16x8* pw) {
     constexpr int QB0 = decltype(qb0)::value, N = decltype(n)::value;
+#pragma unroll
+    for (int q = 0; q < N; q++) pin(pw[q]);
     acc_ready<ACC>(o);
+#pragma unroll
+    for (int q = 0; q < N; q++) pin(pw[q]);
 #pragma unroll
     for (int db = 0; db < 8; db++) {
       const bf16x8 a = read_vt(va_addr[db] + slot * kSlot);
@@ -367,7 +376,7 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
   };
   auto qk_all = [&](int slot, f32x4 (&s)[2][QB]) { qk(slot, Tag<0>{}, s); };
   auto softmax_all = [&](const f32x4 (&s)[2][QB], bf16x8 (&pw)[QB]) { softmax(Tag<0>{}, s, pw); };
-  auto pv_all = [&](int slot, const bf16x8 (&pw)[QB]) { pv(slot, Tag<0>{}, Tag<QB>{}, pw); };
+  auto pv_all = [&](int slot, bf16x8 (&pw)[QB]) { pv(slot, Tag<0>{}, Tag<QB>{}, pw); };
 
   // operand i of a step: K operand (key block i%2, d slice i/2) for i < 8, V^T operand of d block i - 8 beyond
   auto load_opnd = [&](auto idx, auto ks, auto vs) -> bf16x8 {
