@@ -94,7 +94,9 @@ int plan_piece_len(int n_sub, int n_max, int want, const PlanParams& p) {
 
 // kAttnDuo: what a step of a workgroup costs that has its CU to itself, of a step of one that shares it (0.69 us against
 // 0.95 at 65536+100 tokens).  What this decides: 61440+28 tokens in 30 pieces (240 workgroups) 51 us a call, in 39 (312) 66;
-// 8192+100 in 8 pieces (256) 31.9, in 16 (512) 36.3.
+// 8192+100 in 8 pieces (256) 31.9, in 16 (512) 36.3.  An uncut launch that is alone saves a merge at the cost of such steps, not
+// at its full price: 1648+7 tokens (16Q/8KV, 8 workgroups uncut) take 14.5 us a call in 6 pieces, 27.2 uncut, and 1712+428
+// (64Q/8KV, 224 uncut) 38.9 uncut, 49.1 in two.
 constexpr double kAlone = 0.7;
 
 int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots) {
@@ -121,7 +123,9 @@ int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t
     }
     if (n > 1 && slots > max_slots) break;
     // no order of the pieces beats the average load: most candidates need no replay
-    if (n > 1 && (slots <= p.alone ? kAlone : 1.) * (double)(work / p.wg_slots) + (cut ? p.split_fill : 0) >= best * 0.98) {
+    const double step = slots <= p.alone ? kAlone : 1.;
+    const double merge = (cut ? 1. : 1. - step) * p.split_fill;
+    if (n > 1 && step * (double)(work / p.wg_slots) + merge >= best * 0.98) {
       if (!cut) break;
       continue;
     }
@@ -140,7 +144,7 @@ int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t
         }
       }
     }
-    const double span = (slots <= p.alone ? kAlone * (double)end : (double)end) + (cut ? p.split_fill : 0);
+    const double span = step * (double)end + merge;
     if (n == 1 || span < best * 0.98) {            // a cut has to win by 2 % over what is chosen so far
       best = span;
       want = n;

@@ -43,3 +43,11 @@ def test_piece_lengths_are_alike_over_a_mixed_batch(seed):
     assert all(len(p) <= len(longest) for p in tiles.values())
     step = max(e - b for b, e, _ in longest)
     assert all(e - b <= 2 * step + 8 for p in tiles.values() for b, e, _ in p)
+
+
+@pytest.mark.parametrize("hq,hkv,lens", [(16, 8, [(1648, 7)]), (64, 8, [(1488, 27)]), (64, 8, [(128, 1), (1680, 10)]),
+                                         (32, 8, [(1616, 2), (160, 3), (0, 212), (240, 53)])])
+def test_contexts_between_1k_and_2k_are_cut(hq, hkv, lens):
+    """8 to 32 workgroups that walk some 50 sub-tiles each take twice the time of six times as many."""
+    tiles = pieces_by_tile(hq, hkv, lens)
+    assert max(len(p) for p in tiles.values()) >= 4
