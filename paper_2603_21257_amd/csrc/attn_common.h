@@ -31,7 +31,6 @@ __device__ inline void static_for(F&& f) {
     static_for<B + 1, E>(f);
   }
 }
-constexpr int kPD = 4;   // LDS operand reads run this many operands ahead
 constexpr float kRefShift = 16.f;       // the softmax reference is this far above the maximum it was taken from (exponent units)
 constexpr float kLazyBound = 1.f;       // a lane's partial row sum of a sub-tile may reach this before the reference is raised
 

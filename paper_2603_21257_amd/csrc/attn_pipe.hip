@@ -36,14 +36,15 @@ constexpr unsigned kMergeSingleRows = 8192;      // 256 CUs x 32 waves
 
 template <int ROWS>
 __global__ void __launch_bounds__(256) merge_splits_kernel(AttnParams p, const int32_t* split_tiles) {
-  const int NW = p.waves_per_wg;
+  const int NW = p.row_blocks_per_wg;
   const int HW = p.heads_per_wg, NHG = p.n_q_heads / HW, TPW = NW / HW;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   constexpr int kLanes = 64 / ROWS, kPieces = kMergeLoads / ROWS;
   constexpr int kWgs = 8 / ROWS;                                 // workgroups per 32-row slot
   // a head group is merged on the XCD whose L2 its pieces were written through (the workgroup order of
-  // attn_pipeline.h): 2048+209 tokens 35.7 -> 31.8 us a call, 4096+28 20.4 -> 18.1
+  // attn_pipeline.h): 2048+209 tokens 33.8 -> 28.3 us a call of one caller, 21.5 -> 20.7 with three in turn, 4096+28 20.2 -> 17.8
+  // and 14.1 -> 13.3
   int hg, rest = blockIdx.x;
   if ((NHG & 7) == 0) {
     const int per = NHG >> 3;
@@ -143,7 +144,7 @@ hipError_t launch_attn_pipe(const AttnParams& p, hipStream_t stream) {
 
 hipError_t launch_merge_splits(const AttnParams& p, const int32_t* split_tiles, int n_split_tiles, hipStream_t stream) {
   if (n_split_tiles <= 0) return hipSuccess;
-  const unsigned slots = (unsigned)n_split_tiles * (unsigned)(p.n_q_heads / p.heads_per_wg) * (unsigned)p.waves_per_wg;
+  const unsigned slots = (unsigned)n_split_tiles * (unsigned)(p.n_q_heads / p.heads_per_wg) * (unsigned)p.row_blocks_per_wg;
   if (slots * 32u <= pipe::kMergeSingleRows)
     hipLaunchKernelGGL(pipe::merge_splits_kernel<1>, dim3(slots * 8u), dim3(256), 0, stream, p, split_tiles);
   else

@@ -466,7 +466,7 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
 #pragma unroll
     for (int qb = 0; qb < QB; qb++) l_run[qb] += ps[qb];
     // What the next steps read and prefetch has landed; their requests go into slots that nobody reads until the next
-    // barrier.  One barrier for two steps: at the end of an even step t K up to t + 4 and V up to t + 1, i.e. everything
+    // barrier.  One barrier for two steps: at the end of an even step t K up to t + 4 and V up to t + 2, i.e. everything
     // but the requests of the last three steps.  One for each: K up to t + 3 and V up to t, i.e. everything but the requests
     // of the last two steps and those for V before them.
     if constexpr (!Cfg_::BAR2) {

@@ -30,12 +30,19 @@ int attn_duo_tile_tokens(int heads_per_wg);
 // heads: half the K/V traffic into LDS and out of it per query row) and kAttnDuo (32 rows per wave, two
 // 4-wave workgroups per CU, 32-token tiles).  The smaller tiles win where half of a 64-token tile would be empty (the short
 // queries of the paper's Table 1), and where the whole batch is little work: they spread it over twice as many workgroups,
-// which fill and drain faster.  Measured, us a call, kAttnPipe / kAttnDuo: 0+1024 tokens (8.5 steps of 32 keys per CU)
-// 34.6 / 29.1, 1024+1000 (25) 51.9 / 45.3, 2048+1000 (41) 59.4 / 60.2, 4096+1000 (73) 82.5 / 87.3, 0+4096 (130)
-// 122 / 134, 61440+4096 2961 / 3362.  One request whose suffix is a single tile of kAttnPipe only takes its append along
-// (launch_layer): there the line lies lower, 2048+64 (2) 22.6 / 19.4, 8192+64 (8) 29.6 / 30.3, 16384+64 (16) 35.6 / 37.7,
-// 65536+64 78 / 87.  The environment variable CALVO_ATTN_VARIANT (3 or 4, read per call: tests switch it
-// inside one process) forces one.
+// which fill and drain faster.  Measured, us a call of one caller, kAttnPipe / kAttnDuo (in brackets the 32-key steps of
+// kAttnPipe per CU):
+//   32Q/8KV  0+1024 tokens (8.5) 34.8 / 25.6, 1024+1000 (25) 52.0 / 38.7, 8192+256 (33) 49.0 / 50.2, 2048+1000 (41) 59.6 / 50.9,
+//            16384+256 (65) 72.1 / 75.9, 4096+1000 (73) 82.8 / 79.1, 61440+4096 2961 / 3362
+//   64Q/8KV  1024+1000 (49) 57.2 / 55.2, 4096+512 (68) 79.5 / 72.4, 2048+1000 (80) 80.9 / 82.2
+//   40Q/8KV  (tiles of 256 / 128) 4096+512 (44) 61.9 / 60.9, 2048+1000 (52) 76.7 / 67.1, 4096+1000 (92) 114.6 / 107.8
+//   16Q/8KV  (128 / 64) 4096+1000 (36) 54.4 / 55.9        8Q/8KV  (256 / 128) 4096+1000 (18) 43.6 / 40.8
+// The sides cross between 30 steps (long contexts, few tiles) and 90 (short ones, one head per workgroup); the line lies
+// where the larger tiles have begun to win.  One request whose suffix is a single tile of kAttnPipe has no more tiles to gain
+// from, and takes its append along where launch_layer allows it: 2048+64 (2) 23.1 / 20.7, 8192+64 (8) 29.6 / 26.2, 16384+64 (16)
+// 35.7 / 33.6, 64Q/8KV 16384+64 (32) 45.9 / 49.6, 40Q/8KV 8192+256 (41) 56.9 / 57.9, 8Q/8KV 16384+256 (16) 38.9 / 33.9; without suffix
+// arrays 16384+64 35.4 / 31.3, 64Q/8KV 16384+64 45.2 / 47.4.  The sides cross between 16 and 32 there, above the line.  The environment
+// variable CALVO_ATTN_VARIANT (3 or 4, read per call: tests switch it inside one process) forces one.
 constexpr int kPipeStepsPerCu = 40, kPipeStepsPerCuOneTile = 12;
 
 int attn_mfma_choose(const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int heads_per_wg, int n_head_groups, int n_cus,
@@ -57,7 +64,7 @@ int attn_mfma_choose(const int32_t* prefix_blocks, const int32_t* suffix_lens, i
 }
 
 // blocks of 32 query rows in a workgroup: a wave each, but two per wave in kAttnPipe
-int attn_mfma_waves_per_wg(int variant) { return variant == kAttnPipe ? 8 : 4; }
+int attn_mfma_row_blocks(int variant) { return variant == kAttnPipe ? 8 : 4; }
 
 int attn_mfma_tile_tokens(int variant, int heads_per_wg) {
   return variant == kAttnDuo ? attn_duo_tile_tokens(heads_per_wg) : attn_pipe_tile_tokens(heads_per_wg);
@@ -78,9 +85,9 @@ std::vector<PlanTile> plan_tiles(const int32_t* prefix_blocks, const int32_t* su
 
 // The kernels run a piece of n sub-tiles as a fill step, pairs of steady steps and one (n even) or two drain steps.
 // The shortest piece is a 32nd of the tile, between 8 and split_min (48): a piece of 8 sub-tiles is mostly
-// fill, but with one or two tiles the alternative is an idle chip.  Measured (8B shape, us a call with three
-// callers in turn, floor 48 -> this): 2048+1 tokens 29.2 -> 13.7, 8192+1 31.0 -> 14.1, 16384+28 34.2 -> 23.0,
-// 2048+209 34.3 -> 23.8; from 28K cached tokens on the two differ by less than 4 %.
+// fill, but with one or two tiles the alternative is an idle chip.  Measured with the kernels before the present ones (8B
+// shape, us a call with three callers in turn, floor 48 -> this): 2048+1 tokens 29.2 -> 13.7, 8192+1 31.0 -> 14.1, 16384+28
+// 34.2 -> 23.0, 2048+209 34.3 -> 23.8; from 28K cached tokens on the two differ by less than 4 %.
 int plan_piece_len(int n_sub, int n_max, int want, const PlanParams& p) {
   const int floor = p.step_cost ? 1 : p.long_pieces ? p.split_min : std::min(p.split_min, std::max(8, n_sub / 32));
   // a shorter tile gets as many pieces as it has of the longest tile's piece lengths (a quarter over is let go)
@@ -92,8 +99,8 @@ int plan_piece_len(int n_sub, int n_max, int want, const PlanParams& p) {
   return len;
 }
 
-// kAttnDuo: what a step of a workgroup costs that has its CU to itself, of a step of one that shares it (0.69 us against
-// 0.95 at 65536+100 tokens).  What this decides: 61440+28 tokens in 30 pieces (240 workgroups) 51 us a call, in 39 (312) 66;
+// kAttnDuo: what a step of a workgroup costs that has its CU to itself, of a step of one that shares it (32Q/8KV, 0.69 us
+// against 0.95 at 65536+100 tokens).  What this decides: 61440+28 tokens in 30 pieces (240 workgroups) 51 us a call, in 39 (312) 66;
 // 8192+100 in 8 pieces (256) 31.9, in 16 (512) 36.3.  An uncut launch that is alone saves a merge at the cost of such steps, not
 // at its full price: 1648+7 tokens (16Q/8KV, 8 workgroups uncut) take 14.5 us a call in 6 pieces, 27.2 uncut, and 1712+428
 // (64Q/8KV, 224 uncut) 38.9 uncut, 49.1 in two.
@@ -227,7 +234,7 @@ extern "C" int calvo_attn_plan_items(int32_t n_q_heads, int32_t n_kv_heads, int3
   const int hw = attn_heads_per_wg(n_q_heads, n_kv_heads);
   const int variant = attn_mfma_choose(prefix_blocks, suffix_lens, n_reqs, hw, n_q_heads / hw, n_cus);
   const std::vector<PlanTile> tiles = plan_tiles(prefix_blocks, suffix_lens, n_reqs, attn_mfma_tile_tokens(variant, hw));
-  const PlanParams p{n_q_heads / hw, n_cus * (8 / attn_mfma_waves_per_wg(variant)), 48, 30, 0, false, 0, variant == kAttnDuo ? n_cus : 0};
+  const PlanParams p{n_q_heads / hw, n_cus * (8 / attn_mfma_row_blocks(variant)), 48, 30, 0, false, 0, variant == kAttnDuo ? n_cus : 0};
   PlanItems pi;
   if (chunk_blocks > 0) {
     pi = plan_items_chunked(tiles, prefix_blocks, chunk_blocks, (max_blocks + chunk_blocks - 1) / chunk_blocks);
@@ -259,7 +266,7 @@ extern "C" int calvo_attn_plan(int32_t n_q_heads, int32_t n_kv_heads, int32_t n_
   const int variant = attn_mfma_choose(prefix_blocks, suffix_lens, n_reqs, hw, n_q_heads / hw, n_cus);
   const int tt = attn_mfma_tile_tokens(variant, hw);
   const std::vector<PlanTile> tiles = plan_tiles(prefix_blocks, suffix_lens, n_reqs, tt);
-  PlanParams p{n_q_heads / hw, n_cus * (8 / attn_mfma_waves_per_wg(variant)), 48, 30, 0, false, 0, variant == kAttnDuo ? n_cus : 0};
+  PlanParams p{n_q_heads / hw, n_cus * (8 / attn_mfma_row_blocks(variant)), 48, 30, 0, false, 0, variant == kAttnDuo ? n_cus : 0};
   const int want = plan_pieces(tiles, p);
   int64_t items = 0;
   for (const PlanTile& t : tiles) {

@@ -13,7 +13,7 @@ constexpr int kAttnDuo = 4;    // 32 query rows per wave, two workgroups per CU,
 int attn_mfma_choose(const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int heads_per_wg, int n_head_groups, int n_cus,
                      bool by_rows = false);      // by_rows: by the empty rows of the tiles alone
 int attn_mfma_tile_tokens(int variant, int heads_per_wg);
-int attn_mfma_waves_per_wg(int variant);
+int attn_mfma_row_blocks(int variant);           // blocks of 32 query rows in a workgroup
 
 // query heads of one KV group that share a workgroup: 4, 2 or 1 (the largest that divides the group)
 inline int attn_heads_per_wg(int n_q_heads, int n_kv_heads) {

@@ -33,8 +33,8 @@
 // The suffix's K and V are read from the caller's arrays where the launch is given them, and stored
 // to the pool on the side; the append launch and its dependency go away.
 //
-// Softmax reference raised lazily as in attn_pipeline.h: weights are taken against the maximum of an
-// earlier step and the reference moves only when a score passes it by 2^16.
+// Softmax reference raised lazily: weights are taken against the maximum of an earlier step and the reference
+// moves only when a score passes it by 2^16 (attn_pipeline.h, where it lies 16 above that maximum instead).
 //
 // What bounds it: fp32 the matrix pipes (a large fp32 product reaches 153 TFLOP/s on this part, a
 // sixteenth of bf16; 2.3 us per 32 keys of a wave's 32 rows at D = 64 against 1.8 us of MFMA), bf16 the

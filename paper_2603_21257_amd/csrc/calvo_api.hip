@@ -55,7 +55,7 @@ namespace {
 // process ends; host code only ever uses the address obtained per device from
 // hipGetSymbolAddress (the array's name is not a device address on the host side).
 constexpr size_t kStaticBlobInts = (size_t)262144;                  // 1 MiB of descriptors: about 80000 table entries
-constexpr size_t kStaticPartSlots = 2048;                           // (work item, head group, wave) slots
+constexpr size_t kStaticPartSlots = 2048;                           // (work item, head group, block of 32 rows) slots
 constexpr size_t kStaticBlobBytes = kStaticBlobInts * 4;
 constexpr size_t kStaticPartOBytes = kStaticPartSlots * 32 * 128 * sizeof(float);   // 32 MiB
 constexpr size_t kStaticPartMlBytes = kStaticPartSlots * 32 * 2 * sizeof(float);    // 512 KiB
@@ -242,7 +242,7 @@ int ensure_att_blob(calvo_ctx* c, size_t n) {
 }
 
 
-// Room for the split-KV partial results of `slots` (work item, head group, wave) triples.  Growing
+// Room for the split-KV partial results of `slots` (work item, head group, block of 32 rows) triples.  Growing
 // frees the old buffers, hence waits for the compute stream; contexts for bf16 / head-dim-128
 // pools start with room for the short-query batches (kPartialSlots0) - large batches that are cut to fill the last
 // round and long chunk-granular layers grow it; the others start with all that a packed-rows launch may use
@@ -715,8 +715,8 @@ int prepare_ingest(calvo_ctx* c, const calvo_request* reqs, int n_reqs, int laye
 // What the attention kernels read besides Q and the pool, as one array of int32 (offsets in int32):
 // request descriptors (ReqDesc x n), work items, first items of the cut tiles, per-launch work item
 // lists, block tables, block byte offsets.  Each request's table is followed by copies of its last
-// entry (kTablePad of them, one more if that makes the count even) so that a kernel may look
-// kTablePad blocks past the end without clamping.  The offsets are slot * block_bytes (the byte
+// entry (kTablePad of them, one more if that makes the count even: the last 32-key sub-tile has two blocks as well).
+// The offsets are slot * block_bytes (the byte
 // offset of the block inside a layer of the pool) for the same blocks, split by parity: first those
 // of blocks 0, 2, 4, ... then those of blocks 1, 3, 5, ... - a wave that always fetches the same
 // half of a 32-key sub-tile reads its offsets from consecutive addresses.
@@ -1153,7 +1153,7 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
   ap.plan = PlanItems();
   if (ap.mfma) {
     const std::vector<PlanTile> tiles = plan_tiles(pblocks.data(), slens.data(), n_reqs, ap.tile_tokens);
-    PlanParams pp{cf.n_q_heads / ap.HW, c->n_cus * (8 / attn_mfma_waves_per_wg(ap.variant)), c->split_min, c->split_fill, c->force_splits};
+    PlanParams pp{cf.n_q_heads / ap.HW, c->n_cus * (8 / attn_mfma_row_blocks(ap.variant)), c->split_min, c->split_fill, c->force_splits};
     pp.long_pieces = rule == PlanRule::kLong || rule == PlanRule::kLongByRows;
     pp.rounded = rule != PlanRule::kBest;
     pp.alone = rule == PlanRule::kBest && ap.variant == kAttnDuo ? c->n_cus : 0;
@@ -1176,7 +1176,7 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
   ap.lay = build_descriptor_blob(c, reqs, n_reqs, cu_suffix, ap.plan, ap.mfma, ap.blob);
   ap.part_need = ap.plan.split_tiles.empty()
                      ? 0
-                     : ap.mfma ? ap.plan.items.size() * (size_t)(cf.n_q_heads / ap.HW) * (size_t)attn_mfma_waves_per_wg(ap.variant)
+                     : ap.mfma ? ap.plan.items.size() * (size_t)(cf.n_q_heads / ap.HW) * (size_t)attn_mfma_row_blocks(ap.variant)
                                : ap.plan.items.size() * (size_t)cf.n_kv_heads;
 }
 
@@ -1273,7 +1273,7 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
   p.blk_offs = (const int64_t*)(d_att + ap.lay.offs_off);
   p.n_q_heads = cf.n_q_heads; p.n_kv_heads = cf.n_kv_heads; p.head_dim = cf.head_dim;
   p.heads_per_wg = ap.HW; p.tile_tokens = ap.tile_tokens;
-  p.waves_per_wg = attn_mfma_waves_per_wg(ap.variant);
+  p.row_blocks_per_wg = attn_mfma_row_blocks(ap.variant);
   p.scale = scale > 0.f ? scale : 1.0f / sqrtf((float)cf.head_dim);
   p.clock = {c->d_clock + kClockWords * (size_t)layer, 1};
   if (ap.mfma) {

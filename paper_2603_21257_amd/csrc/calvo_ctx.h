@@ -74,7 +74,7 @@ struct calvo_ctx {
   int plan_want = 1;
   float* part_o = nullptr;        // split-KV partial results (compute stream only)
   float* part_ml = nullptr;
-  size_t part_slots = 0;          // capacity in (work item, head group, wave) slots
+  size_t part_slots = 0;          // capacity in (work item, head group, block of 32 rows) slots
   int device = 0;
   // test hooks (environment, read by calvo_create): the host sleeps this long before it queues each
   // transfer of the L2 -> L1 stage (makes the loading stage the slow one without touching the

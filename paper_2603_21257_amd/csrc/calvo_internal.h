@@ -53,10 +53,10 @@ struct AttnParams {
   int32_t n_q_heads, n_kv_heads, head_dim;
   int32_t heads_per_wg;     // MFMA kernel: 1, 2 or 4 query heads of one KV group per workgroup
   int32_t tile_tokens;      // suffix tokens per work item
-  int32_t waves_per_wg;     // blocks of 32 query rows in an attention workgroup (8 or 4): layout of the split-KV partials
+  int32_t row_blocks_per_wg;     // blocks of 32 query rows in an attention workgroup (8 or 4): layout of the split-KV partials
   float scale;              // softmax scale (natural-exponent units)
-  // split-KV partial results, used by work items with n_splits > 1: per work item, head group, wave
-  // (head of the group x 32-token half of the tile): part_o [32 rows][D] fp32 unnormalised,
+  // split-KV partial results, used by work items with n_splits > 1: per work item, head group, block of 32 rows
+  // (head of the group x 32-token block of the tile): part_o [32 rows][D] fp32 unnormalised,
   // part_ml [32 rows][2] = (softmax reference in exponent units, i.e. score * scale * log2 e, row sum)
   float* part_o;
   float* part_ml;
@@ -126,8 +126,9 @@ hipError_t launch_merge_splits(const AttnParams& p, const int32_t* split_tiles, 
 int attn_pipe_tile_tokens(int heads_per_wg);
 
 constexpr int kBlockTokens = 16;
-// Entries appended to every request's device-side block table (copies of its last entry): the last sub-tile may be half
-// a block pair, the rest is slack.
+// Entries appended to every request's device-side block table (copies of its last entry).  No kernel needs more than the one
+// that makes the count even; the rest keeps the two halves of the block offsets (even and odd blocks, calvo_api.hip), which the waves
+// of a workgroup read side by side, from lying a power of two apart: with 4096 or 8192 blocks and no padding they do, and
+// 61440+4096 tokens take 3083 -> 3160 us a call, 122880+8192 (64Q/8KV) 24500 -> 24860.
 constexpr int kTablePad = 32;
-
 }  // namespace calvo
