@@ -267,9 +267,10 @@ int calvo_prefill_attn_batch(calvo_ctx* ctx, calvo_batch* batch, int layer, cons
  * (35.5 MiB per GPU, held until the process ends; its address is looked up once per device by
  * calvo_create).  Limits: 262144 descriptor words (about 80000 table entries over the batch) and
  * 2048 partial-result slots (pieces x head groups x blocks of 32 query rows in a workgroup, 8 or 4).  A batch whose best
- * plan is beyond either is planned again with longer, then few long pieces (slower); if none of that fits it gets
- * CALVO_ENOMEM with nothing queued - use calvo_prefill_attn for it (long layers loaded in chunks are
- * the usual case).  The array is shared by every call on the GPU, whatever the context: calls are
+ * plan is beyond either is planned again with longer, fewer, in the end only as many pieces as there is room for (slower).
+ * What does not fit even so - too many table entries, or a long layer loaded in chunks, which is cut by its chunks - gets
+ * CALVO_ENOMEM with nothing queued: use calvo_prefill_attn for it.
+ * The array is shared by every call on the GPU, whatever the context: calls are
  * ordered by the compute stream they are queued on, and calls that overlap on one GPU from different
  * streams or contexts race.  Nothing in it needs to start at zero (every word a kernel reads was
  * written by the same call). */

@@ -68,7 +68,7 @@ std::vector<PlanTile> plan_tiles(const int32_t* prefix_blocks, const int32_t* su
 // longest tile, which has n_max
 int plan_piece_len(int n_sub, int n_max, int want, const PlanParams& p);
 
-// pieces of the longest tile to ask for (1 = no cut), from a replay of the launch; packed rows: at most max_slots
+// pieces of the longest tile to ask for (1 = no cut), from a replay of the launch; a cut makes at most max_slots
 // (piece, head group) pairs (partial results there is room for)
 int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots = INT64_MAX);
 

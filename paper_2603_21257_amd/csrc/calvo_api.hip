@@ -1120,18 +1120,19 @@ int kept_pieces(calvo_ctx* c, int variant, const calvo_request* reqs, int n_reqs
   return c->plan_want;
 }
 
-// Which plan.  What calvo_prefill_attn_noalloc accepts is what fits its fixed-size array by one of them, tried in this
-// order.  The three behind the best one do not depend on what is known of the kernels' speed (but for kLong's choice of
-// kernel): a batch that they fit is not refused when the best plan changes.  None of them stands for another: few pieces for
-// every tile of a ragged batch can be more than many for its longest.  Packed-rows launches know two plans: the best, and
-// one without work items (uncut tiles).
+// Which plan.  calvo_prefill_attn_noalloc takes the first of them, in this order, that fits its fixed-size array.  None of
+// the first four stands for another: few pieces for every tile of a ragged batch can be more than many for its longest.  The
+// last one fits if the descriptors of uncut tiles do, whatever is known of the kernels' speed: a batch that is accepted is not
+// refused when the plans in front of it change.  Packed-rows launches know two plans: the best, and one without work items
+// (uncut tiles).
 enum class PlanRule {
   kBest,
   kRounded,       // the kernel that the suffix lengths alone ask for (attn_mfma_choose), pieces of 8k + 2 sub-tiles
   kLong,          // few, long pieces (PlanParams::long_pieces)
   kLongByRows,    // the same with the kernel of kRounded
+  kFitted,        // the kernel of kRounded, as many pieces as there is room for
 };
-bool by_rows(PlanRule rule) { return rule == PlanRule::kRounded || rule == PlanRule::kLongByRows; }
+bool by_rows(PlanRule rule) { return rule != PlanRule::kBest && rule != PlanRule::kLong; }
 
 // cb > 0: the layer was loaded in nck chunks of cb block indices and attention follows the chunks.
 void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const int32_t* cu_suffix, int total, int cb,
@@ -1160,7 +1161,8 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
     if (ap.chunked) {
       ap.plan = plan_items_chunked(tiles, pblocks.data(), cb, nck);
     } else {
-      ap.plan = plan_items(tiles, kept_pieces(c, ap.variant + 16 * (int)rule, reqs, n_reqs, tiles, pp, INT64_MAX), pp);
+      const int64_t max_slots = rule == PlanRule::kFitted ? (int64_t)kStaticPartSlots / attn_mfma_row_blocks(ap.variant) : INT64_MAX;
+      ap.plan = plan_items(tiles, kept_pieces(c, ap.variant + 16 * (int)rule, reqs, n_reqs, tiles, pp, max_slots), pp);
     }
   } else {
     const RowsShape shape = attn_rows_shape(cf.dtype == CALVO_F32, cf.head_dim);
@@ -1174,6 +1176,12 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
     }
   }
   ap.lay = build_descriptor_blob(c, reqs, n_reqs, cu_suffix, ap.plan, ap.mfma, ap.blob);
+  if (rule == PlanRule::kFitted && ap.blob.size() > kStaticBlobInts && !ap.plan.split_tiles.empty() && !ap.chunked && !c->force_splits) {
+    // no room for the pieces' work items
+    ap.plan = plan_items(plan_tiles(pblocks.data(), slens.data(), n_reqs, ap.tile_tokens), 1,
+                         PlanParams{cf.n_q_heads / ap.HW, c->n_cus, c->split_min, c->split_fill, 0});
+    ap.lay = build_descriptor_blob(c, reqs, n_reqs, cu_suffix, ap.plan, ap.mfma, ap.blob);
+  }
   ap.part_need = ap.plan.split_tiles.empty()
                      ? 0
                      : ap.mfma ? ap.plan.items.size() * (size_t)(cf.n_q_heads / ap.HW) * (size_t)attn_mfma_row_blocks(ap.variant)
@@ -1446,7 +1454,7 @@ int calvo::host::prefill_attn_impl(calvo_ctx* c, int layer, const void* q, const
     kept->cb = cb;
     kept->nck = nck;
     make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, kept->ap);
-    for (PlanRule rule : {PlanRule::kRounded, PlanRule::kLong, PlanRule::kLongByRows}) {
+    for (PlanRule rule : {PlanRule::kRounded, PlanRule::kLong, PlanRule::kLongByRows, PlanRule::kFitted}) {
       if (!use_static || fits(kept->ap) || (!kept->ap.mfma && kept->rule != PlanRule::kBest)) break;
       kept->rule = rule;
       kept->ap = AttnPlan();

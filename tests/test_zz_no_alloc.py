@@ -80,7 +80,8 @@ def test_noalloc_rejects_what_does_not_fit(monkeypatch):
 # (head layout, lengths): ragged batches whose best plan and whose plan with few, long pieces both need more partial
 # results than the array holds on 256 CUs
 RAGGED = [(32, 8, [(560, 3), (23936, 7), (5600, 33), (22976, 1486)]), (64, 8, [(7968, 434), (54432, 10), (9408, 41)]),
-          (40, 8, [(9392, 2), (78240, 35)]), (48, 8, [(6608, 584), (5312, 8)]), (32, 8, [(0, 10), (43328, 105), (864, 115)])]
+          (40, 8, [(9392, 2), (78240, 35)]), (48, 8, [(6608, 584), (5312, 8)]), (32, 8, [(0, 10), (43328, 105), (864, 115)]),
+          (16, 2, [(9232, 711), (80, 706)]), (16, 8, [(0, 749), (4592, 1273), (448, 6)])]
 
 
 @pytest.mark.parametrize("hq,hkv,lens", RAGGED)
