@@ -37,13 +37,16 @@ int attn_duo_tile_tokens(int heads_per_wg);
 //   64Q/8KV  1024+1000 (49) 57.2 / 55.2, 4096+512 (68) 79.5 / 72.4, 2048+1000 (80) 80.9 / 82.2
 //   40Q/8KV  (tiles of 256 / 128) 4096+512 (44) 61.9 / 60.9, 2048+1000 (52) 76.7 / 67.1, 4096+1000 (92) 114.6 / 107.8
 //   16Q/8KV  (128 / 64) 4096+1000 (36) 54.4 / 55.9        8Q/8KV  (256 / 128) 4096+1000 (18) 43.6 / 40.8
-// The sides cross between 30 steps (long contexts, few tiles) and 90 (short ones, one head per workgroup); the line lies
-// where the larger tiles have begun to win.  One request whose suffix is a single tile of kAttnPipe has no more tiles to gain
-// from, and takes its append along where launch_layer allows it: 2048+64 (2) 23.1 / 20.7, 8192+64 (8) 29.6 / 26.2, 16384+64 (16)
+// Over 1009 random batches of six layouts the sides cross at 100 steps and more where tiles are short; where they have 250
+// steps and more (8K tokens of context), fill, drain and diagonal of the larger tiles matter less and the sides cross from 40
+// on.  Between 40 and 60 steps the smaller tiles take 0.91 of the time on average (0.76 to 1.04): 2048+1000 as above, 40Q/8KV
+// 688+412,480+924,1008+438,736+233 78.4 / 61.9, 16Q/8KV 80+446,8752+647 79.9 / 67.3.  One request whose suffix is a single
+// tile of kAttnPipe has no more tiles to gain from, and takes its append along where launch_layer allows it: 2048+64 (2) 23.1 / 20.7,
+// 8192+64 (8) 29.6 / 26.2, 16384+64 (16)
 // 35.7 / 33.6, 64Q/8KV 16384+64 (32) 45.9 / 49.6, 40Q/8KV 8192+256 (41) 56.9 / 57.9, 8Q/8KV 16384+256 (16) 38.9 / 33.9; without suffix
 // arrays 16384+64 35.4 / 31.3, 64Q/8KV 16384+64 45.2 / 47.4.  The sides cross between 16 and 32 there, above the line.  The environment
 // variable CALVO_ATTN_VARIANT (3 or 4, read per call: tests switch it inside one process) forces one.
-constexpr int kPipeStepsPerCu = 40, kPipeStepsPerCuOneTile = 12;
+constexpr int kPipeStepsPerCu = 60, kPipeStepsPerCuLong = 40, kLongTile = 250, kPipeStepsPerCuOneTile = 12;
 
 int attn_mfma_choose(const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int heads_per_wg, int n_head_groups, int n_cus,
                      bool by_rows) {
@@ -51,15 +54,18 @@ int attn_mfma_choose(const int32_t* prefix_blocks, const int32_t* suffix_lens, i
   if (e && (e[0] == '3' || e[0] == '4') && e[1] == 0) return e[0] - '0';
   // query rows the tiles of each kernel would hold, empty ones included, and the steps of kAttnPipe
   const int t3 = attn_pipe_tile_tokens(heads_per_wg), t4 = attn_duo_tile_tokens(heads_per_wg);
-  int64_t rows3 = 0, rows4 = 0, steps = 0;
+  int64_t rows3 = 0, rows4 = 0, steps = 0, n_tiles = 0;
   for (int r = 0; r < n_reqs; r++) {
     const int64_t tiles = (suffix_lens[r] + t3 - 1) / t3;
     rows3 += tiles * t3;
+    n_tiles += tiles;
     rows4 += (int64_t)((suffix_lens[r] + t4 - 1) / t4) * t4;
     steps += tiles * (16 * (int64_t)prefix_blocks[r] + (suffix_lens[r] + t3) / 2) / 32;
   }
   if (rows3 * 9 > rows4 * 10) return kAttnDuo;                // the larger tiles would carry over 10 % more rows
-  const int line = n_reqs == 1 && suffix_lens[0] <= t3 ? kPipeStepsPerCuOneTile : kPipeStepsPerCu;
+  const int line = n_reqs == 1 && suffix_lens[0] <= t3 ? kPipeStepsPerCuOneTile
+                   : steps >= kLongTile * n_tiles     ? kPipeStepsPerCuLong
+                                                      : kPipeStepsPerCu;
   return !by_rows && steps * n_head_groups < (int64_t)line * n_cus ? kAttnDuo : kAttnPipe;
 }
 
