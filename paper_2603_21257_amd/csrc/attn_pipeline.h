@@ -34,6 +34,10 @@
 // instructions or one exponential, which fill the 16 cycles.  A step of HB = 2 (64 MFMAs, 32 exponentials, 83 other vector
 // instructions, 24 LDS reads) takes 1220 cycles that way, 1320 with the same instructions in the order of the dependences;
 // 1380 in the kernel, with the requests and the barrier.
+// The query blocks of an operand are walked there and back: from one MFMA to the next either A or B stays the same.
+// At the power limit operands that change cost clock: MFMAs alone on N(0,1) data sustain 1915 TFLOP/s where both change every
+// time, 1975 where A is held for four and then both change, 2025 there and back.  In the kernel 61440+4096 tokens 2936 -> 2904 us a
+// call, 16384+2048 412.7 -> 410.0, 38304+209 (40Q/8KV) 157.3 -> 156.1, the same bits (each sum keeps its order).
 // The step is written in this order, with scheduling barriers in between.  MFMAs are inline assembly so that their results
 // stay in place, O of HB = 2 in accumulation registers: left to the compiler, every value that vector instructions
 // touch as well is moved back and forth (45 to 250 moves a step).  What the compiler then does not know are the wait states
@@ -414,9 +418,10 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
         constexpr int qb = decltype(qtag)::value, kb = k & 1, ks = k >> 1;
         // four MFMAs per pair of weights: query block, key block and row of the pair
         constexpr int n = i * QB + qb, pair = n >> 2, part = n & 3, wq = pair >> 2, wkb = (pair >> 1) & 1, wr = 2 * (pair & 1);
-        if constexpr (i >= 8) mfma_acc<ACC>(o[k][qb], op[i], pp[qb]);
-        else if constexpr (ks == 0) mfma_first(sn[kb][qb], op[i], qB[qb][ks]);
-        else mfma_next(sn[kb][qb], op[i], qB[qb][ks]);
+        constexpr int qm = i & 1 ? QB - 1 - qb : qb;                  // there and back: either A or B stays from one MFMA to the next
+        if constexpr (i >= 8) mfma_acc<ACC>(o[k][qm], op[i], pp[qm]);
+        else if constexpr (ks == 0) mfma_first(sn[kb][qm], op[i], qB[qm][ks]);
+        else mfma_next(sn[kb][qm], op[i], qB[qm][ks]);
         __builtin_amdgcn_sched_barrier(0);
         // what is free behind an MFMA
         if constexpr (qb == 0) {
