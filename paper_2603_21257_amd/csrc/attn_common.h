@@ -91,20 +91,20 @@ __device__ inline void store_piece(float* po, int g, const f32x4 (&o)[8][QB], in
   for (int db = 0; db < 8; db++) *(f32x4*)(po + 16 * db + 4 * g) = o[db][qb];
 }
 
-// The suffix rows of request rd and KV head kv from the caller's arrays to the pool, by THREADS threads: four chunks of K and
-// of V in flight per thread while there are that many.
+// The suffix rows of n_tok tokens of request rd from token tok0 on and of KV head kv, from the caller's arrays to the pool, by
+// THREADS threads: four chunks of K and of V in flight per thread while there are that many.
 template <int THREADS>
 __device__ inline void append_rows(const unsigned char* ks, const unsigned char* vs, unsigned char* pool, const int32_t* table,
-                                   const ReqDesc& rd, int n_kv_heads, int kv, int tid) {
+                                   const ReqDesc& rd, int n_kv_heads, int kv, int tok0, int n_tok, int tid) {
   const int64_t rs = (int64_t)n_kv_heads * kRow, half_b = kBlockTokens * rs;
-  const int n = rd.suffix_len * (kRow / 16);
+  const int n = n_tok * (kRow / 16);
   auto move = [&](int i0, auto count) {
     constexpr int N = decltype(count)::value;
     u32x4 k[N], v[N];
     int64_t dst[N];
 #pragma unroll
     for (int u = 0; u < N; u++) {
-      const int i = i0 + u * THREADS, tok = i / (kRow / 16), pos = rd.prefix_len + tok;
+      const int i = i0 + u * THREADS, tok = tok0 + i / (kRow / 16), pos = rd.prefix_len + tok;
       const int64_t in_row = kv * kRow + (i % (kRow / 16)) * 16;
       const int64_t src = (int64_t)(rd.q_off + tok) * rs + in_row;
       dst[u] = (int64_t)table[pos / kBlockTokens] * (2 * half_b) + (int64_t)(pos % kBlockTokens) * rs + in_row;

@@ -1073,6 +1073,8 @@ struct AttnPlan {
   bool chunked = false;
   int nck = 0;
   int row_tiles = 0;                    // packed-rows kernel: tiles over all requests
+  int longest = 0;                      // suffix tokens of the longest one
+  bool apart = true;                    // no request's table names a slot that another one appends to
   PlanItems plan;
   std::vector<int32_t> blob;
   BlobLayout lay;
@@ -1102,6 +1104,24 @@ int check_pointer_args(const void* q, const void* k_suffix, const void* v_suffix
       return fail(CALVO_EINVAL, "q, out, k_suffix and v_suffix must be 16-byte aligned");
   }
   return CALVO_OK;
+}
+
+// Whether no slot that a request appends to is in another one's table: only then may a launch read one request's cached prefix
+// while it stores another one's suffix.
+bool appends_apart(const calvo_ctx* c, const calvo_request* reqs, int n_reqs) {
+  if (n_reqs <= 1) return true;
+  std::vector<char> mine((size_t)c->cfg.pool_blocks, 0);
+  auto n_sfx = [&](int r) { return (reqs[r].suffix_len + kBlockTokens - 1) / kBlockTokens; };
+  for (int r = 0; r < n_reqs; r++)
+    for (int j = 0; j < n_sfx(r); j++) {
+      char& m = mine[(size_t)reqs[r].block_table[reqs[r].n_prefix_blocks + j]];
+      if (m) return false;
+      m = 1;
+    }
+  for (int r = 0; r < n_reqs; r++)
+    for (int j = 0; j < reqs[r].n_prefix_blocks; j++)
+      if (mine[(size_t)reqs[r].block_table[j]]) return false;
+  return true;
 }
 
 // Pieces per tile.  The decision (a replay of the launch, attn_plan.cpp) depends only on the batch's
@@ -1145,6 +1165,8 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
   ap.variant = 0;
   std::vector<int32_t> pblocks(n_reqs), slens(n_reqs);
   for (int r = 0; r < n_reqs; r++) { pblocks[r] = reqs[r].n_prefix_blocks; slens[r] = reqs[r].suffix_len; }
+  ap.longest = n_reqs > 0 ? *std::max_element(slens.begin(), slens.end()) : 0;
+  ap.apart = appends_apart(c, reqs, n_reqs);
   if (ap.mfma) ap.variant = attn_mfma_choose(pblocks.data(), slens.data(), n_reqs, ap.HW, cf.n_q_heads / ap.HW, c->n_cus, by_rows(rule));
   ap.tile_tokens = ap.mfma ? attn_mfma_tile_tokens(ap.variant, ap.HW) : 1;
   // Work items: tiles of suffix tokens, heaviest first, each possibly cut into split-KV pieces
@@ -1233,10 +1255,16 @@ bool same_shape(const calvo_ctx* c, const KeptBatch& k) {
                                         by_rows(k.rule)) == k.ap.variant;
 }
 
-hipError_t launch_attn(int variant, const AttnParams& p, hipStream_t stream) {
-  return variant == kAttnDuo ? launch_attn_duo(p, stream) : launch_attn_pipe(p, stream);
+hipError_t launch_attn(const AttnPlan& ap, const AttnParams& p, hipStream_t stream) {
+  return ap.variant == kAttnDuo ? launch_attn_duo(p, ap.longest <= ap.tile_tokens, stream) : launch_attn_pipe(p, stream);
 }
 
+// Longest suffix whose rows a launch of small tiles takes along.  The append launch costs 2.4 us of host time and 2 to 4 us of
+// device time in front of the attention; against it, sub-tiles of the suffix run in the loop with run-time ring slots.  us a
+// call, append launch / along, three callers (one caller): 448+66 tokens 11.2 / 8.2 (17.3 / 17.1), 2048+209 22.9 / 21.9
+// (28.1 / 27.7), 1024+350 20.5 / 20.2 (28.2 / 28.4), 2048+400 28.1 / 27.5 (34.9 / 34.6), 2048+512 31.0 / 31.1 (37.4 / 38.9),
+// 1024+769,1360+200 29.7 / 30.9; 16Q/2KV 1024+512 22.6 / 19.9; 0+666,0+125 16.1 / 14.4, 0+1024 20.4 / 19.6, 0+2000 39.0 / 41.8.
+constexpr int kAlongTokens = 400;
 // Queues the suffix append and the attention of one layer on the compute stream.  d_att: the device
 // copy of ap.blob.  ready: NULL = the layer's own loading state decides what the stream waits for.
 int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, const void* v_suffix, void* out, float scale,
@@ -1256,17 +1284,18 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
   const ReqDesc* d_reqs = (const ReqDesc*)d_att;
   const int32_t* d_tables = d_att + ap.lay.tables_off;
 
-  // A packed-rows launch of one request takes the suffix rows along.  With several requests a cached
-  // prefix may be slots that another request of the call appends to: all rows are stored first.  So they are where
-  // the output goes over the suffix rows: a workgroup that is done would overwrite what others still read.
+  // The launch takes the suffix rows along: it reads them from the caller's arrays and stores them on the side.  Not where a
+  // cached prefix has slots that another request of the call appends to: all rows are stored first there.  So they are where
+  // the output goes over the suffix rows (a workgroup that is done would overwrite what others still read) and where
+  // they lie in the pool.
   const size_t row_b = (size_t)ap.total * cf.head_dim * c->elt;
-  auto in_out = [&](const void* sfx) {
-    return (uintptr_t)sfx < (uintptr_t)out + row_b * cf.n_q_heads && (uintptr_t)out < (uintptr_t)sfx + row_b * cf.n_kv_heads;
+  auto in = [&](const void* sfx, const void* at, size_t bytes) {
+    return (uintptr_t)sfx < (uintptr_t)at + bytes && (uintptr_t)at < (uintptr_t)sfx + row_b * cf.n_kv_heads;
   };
-  const bool append_along = ap.n_reqs == 1 && k_suffix && !in_out(k_suffix) && !in_out(v_suffix);
-  const bool rows_append = !ap.mfma && append_along;
-  // The same for a suffix of one tile in the pipelined kernels: no other tile reads its rows.
-  const bool tile_append = ap.mfma && append_along && !ap.chunked && ap.total <= ap.tile_tokens;
+  auto in_the_way = [&](const void* sfx) { return in(sfx, out, row_b * cf.n_q_heads) || in(sfx, pool_layer, (size_t)c->layer_bytes); };
+  const bool along = k_suffix && ap.apart && !in_the_way(k_suffix) && !in_the_way(v_suffix);
+  const bool rows_append = !ap.mfma && along;
+  const bool tile_append = ap.mfma && along && !ap.chunked && ap.longest <= (ap.variant == kAttnDuo ? kAlongTokens : ap.tile_tokens);
   if (k_suffix && !rows_append && !tile_append) {
     AppendParams app{};
     app.k_suffix = k_suffix; app.v_suffix = v_suffix; app.pool_layer = pool_layer;
@@ -1302,13 +1331,13 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
         if (groups[g].empty()) continue;
         p.n_items = (int32_t)groups[g].size();
         p.item_index = d_att + ap.lay.group_off[g];
-        HIP_TRY(launch_attn(ap.variant, p, c->s_compute));
+        HIP_TRY(launch_attn(ap, p, c->s_compute));
         p.clock.starts = 0;
       }
       p.item_index = nullptr;
     } else {
       p.n_items = (int32_t)ap.plan.items.size();
-      HIP_TRY(launch_attn(ap.variant, p, c->s_compute));
+      HIP_TRY(launch_attn(ap, p, c->s_compute));
     }
     HIP_TRY(launch_merge_splits(p, d_att + ap.lay.split_off, (int)ap.plan.split_tiles.size(), c->s_compute));
   } else {

@@ -60,8 +60,8 @@ struct AttnParams {
   // part_ml [32 rows][2] = (softmax reference in exponent units, i.e. score * scale * log2 e, row sum)
   float* part_o;
   float* part_ml;
-  // Suffix K / V of a batch of one request whose suffix is one tile, or NULL: the keys past the prefix are then
-  // read from here and stored to the pool by the launch itself (tables), no append launch in front of it.
+  // Suffix K / V, or NULL: the keys past the prefixes are then read from here and stored to the pool by the launch itself
+  // (tables), no append launch in front of it.
   const void* k_suffix;
   const void* v_suffix;
   LaunchClock clock;
@@ -118,7 +118,7 @@ hipError_t launch_attn_rows(const RowsParams& p, int dtype, int n_items, const i
 hipError_t attn_pipe_prepare();
 hipError_t attn_duo_prepare();
 hipError_t launch_attn_pipe(const AttnParams& p, hipStream_t stream);
-hipError_t launch_attn_duo(const AttnParams& p, hipStream_t stream);
+hipError_t launch_attn_duo(const AttnParams& p, bool one_tile, hipStream_t stream);
 int attn_duo_tile_tokens(int heads_per_wg);
 // combines the pieces of every split tile into out (bf16); n_split_tiles entries in split_tiles =
 // indices of the first work item of each split tile

@@ -108,7 +108,8 @@ def compiled(source, kernel, tmp_path):
 
 
 @pytest.mark.parametrize("source,kernel,mfmas,exps,turns", [("attn_pipe.hip", "attn_pipe_kernel", 64, 32, 8),
-                                                            ("attn_duo.hip", "attn_duo_kernel", 32, 16, 10)])
+                                                            ("attn_duo.hip", "attn_duo_kernel", 32, 16, 10),
+                                                            ("attn_duo.hip", "attn_duo_suffix_kernel", 32, 16, 10)])
 def test_no_register_is_spilled(source, kernel, mfmas, exps, turns, tmp_path):
     usage, asm = compiled(source, kernel, tmp_path)
     assert re.search(r"VGPRs Spill: 0\b", usage) and re.search(r"ScratchSize \[bytes/lane\]: 0\b", usage), usage

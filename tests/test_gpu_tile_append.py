@@ -1,7 +1,7 @@
-"""A suffix of one tile: the pipelined kernels read its rows from the caller's arrays and store them to the pool
-themselves.  Lengths around a block, a 32-key sub-tile and the tile; odd and even prefix block counts (the first suffix
-block shares a sub-tile with the prefix or not); groups with one, two and several head groups per KV head; cut contexts;
-both workgroup shapes; without suffix arrays the pool's rows are used."""
+"""Suffixes whose rows the pipelined kernels read from the caller's arrays and store to the pool themselves: one tile, and in
+small tiles up to 400 tokens, also of several requests.  Lengths around a block, a 32-key sub-tile, the tile and that line; odd
+and even prefix block counts (the first suffix block shares a sub-tile with the prefix or not); groups with one, two and several
+head groups per KV head; cut contexts; both workgroup shapes; without suffix arrays the pool's rows are used."""
 import pytest
 import torch
 
@@ -37,6 +37,55 @@ def test_head_groups_and_pieces(hq, hkv, S, pieces, monkeypatch):
         monkeypatch.setenv("CALVO_ATTN_SPLITS", str(pieces))
     P = 2064
     check(wl.Shape(2, hq, hkv, 128, "bf16", (P + S) // 16 + 9), [(P, S)], seed=hq + S)
+
+
+@pytest.mark.parametrize("heads", [(8, 2), (5, 1), (32, 8)])
+@pytest.mark.parametrize("P,S", [(0, 200), (16, 97), (48, 161), (336, 399), (320, 400), (336, 401), (1040, 260)])
+@pytest.mark.parametrize("pieces", [0, 2, 5])
+def test_several_tiles(heads, P, S, pieces, monkeypatch):
+    monkeypatch.setenv("CALVO_ATTN_VARIANT", "4")
+    if pieces:
+        monkeypatch.setenv("CALVO_ATTN_SPLITS", str(pieces))
+    check(wl.Shape(1, *heads, 128, "bf16", (P + S) // 16 + 9), [(P, S)], seed=P + S + pieces)
+
+
+@pytest.mark.parametrize("lens,shared", [([(64, 1), (0, 90), (272, 33), (16, 0)], 0), ([(160, 70), (112, 400), (96, 17)], 5), ([(48, 401), (48, 2)], 0)])
+@pytest.mark.parametrize("prepared", [False, True])
+def test_several_requests(lens, shared, prepared, monkeypatch):
+    monkeypatch.setenv("CALVO_ATTN_VARIANT", "4")
+    w = wl.make_custom(wl.Shape(2, 16, 2, 128, "bf16", 80), lens, seed=len(lens) + shared, shared_blocks=shared)
+    print(f"[case] lens={lens} shared={shared}", flush=True)
+    pool_g, out_g = hh.run_hip(w, prepared=prepared)
+    pool_o, out_o = hh.run_oracle(w)
+    hh.assert_pool_bit_exact(pool_g, pool_o)
+    hh.assert_attn_close(out_g, out_o, "bf16")
+
+
+@pytest.mark.parametrize("variant", ["3", "4"])
+def test_prefix_that_another_request_of_the_call_appends(variant, monkeypatch):
+    """One sequence as two requests: what the second one has cached is what the first one appends, so all rows are stored first."""
+    monkeypatch.setenv("CALVO_ATTN_VARIANT", variant)
+    s = wl.Shape(1, 8, 2, 128, "bf16", 64)
+    w = wl.make_custom(s, [(0, 64), (64, 30)], seed=43)
+    first, second = w.requests
+    table = second.table.copy()
+    table[:4] = first.table[:4]
+    dev = torch.device("cuda:0")
+    pool = hh.to_torch(hh.sentinel_pool_np(s), s, dev)
+    q, ks, vs = (hh.to_torch(a, s, dev) for a in (w.q, w.k_suffix, w.v_suffix))
+    out = torch.empty((1, w.total_suffix, s.n_q_heads, s.head_dim), dtype=torch.bfloat16, device=dev)
+    torch.cuda.synchronize()
+    ctx = cb.calvo_create(1, s.n_q_heads, s.n_kv_heads, s.head_dim, cb.CALVO_BF16, s.pool_blocks, pool)
+    try:
+        reqs = [cb.make_request(None, 0, first.table, 0, 64), cb.make_request(None, 0, table, 4, 30, 4)]
+        cb.calvo_prefill_attn(ctx, 0, q[0], ks[0], vs[0], out[0], reqs, w.cu_suffix)
+    finally:
+        cb.calvo_destroy(ctx)
+    torch.cuda.synchronize()
+    one = wl.make_custom(s, [(0, 94)], seed=44)          # the oracle sees the same as one request of 94 tokens
+    one.q, one.k_suffix, one.v_suffix = w.q, w.k_suffix, w.v_suffix
+    _, want = hh.run_oracle(one)
+    hh.assert_attn_close(hh.to_numpy_stored(out, s), want, "bf16")
 
 
 @pytest.mark.parametrize("kw", [dict(prepared=True), dict(attn_fn=cb.calvo_prefill_attn_noalloc), dict(chunk_blocks=[20]), dict(staging_bytes=1 << 20)])
