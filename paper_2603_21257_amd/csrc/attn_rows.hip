@@ -69,6 +69,9 @@ struct RowsCfg {
   static constexpr int LDS_BYTES = LDS_O + NW * ROWS * 8;
 };
 
+// Buffer resources: no stride, 32-bit data; an offset that lies in none
+constexpr unsigned kPastEnd = 0xfffff000u, kBufferWord3 = 0x00020000u;
+
 // by value: __builtin_bit_cast applied to an element of a vector reads element 0 with this compiler
 __device__ inline float as_float(unsigned x) { return __builtin_bit_cast(float, x); }
 __device__ inline unsigned bf16_rne(float x) {
@@ -155,20 +158,29 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
   const bool from_suffix = ks != nullptr;
   const unsigned head_b = (unsigned)(kv * D * E);
   bool k_ok[KJ];                                               // operand chunk j of this lane lies inside the head
-  unsigned k_off[KJ];
+  unsigned q_off[KJ];
 #pragma unroll
   for (int j = 0; j < KJ; j++) {
     const int d = F32 ? 16 * j + 4 * g : 32 * j + 8 * g;
     k_ok[j] = C::FULL || d < D;
-    k_off[j] = (unsigned)((k_ok[j] ? d : 0) * E);
+    q_off[j] = (unsigned)((k_ok[j] ? d : 0) * E);
   }
-  unsigned v_off[VQ];
-#pragma unroll
-  for (int q = 0; q < VQ; q++) {
-    const int d = VW * (16 * q + c);
-    v_off[q] = (unsigned)((C::FULL || d < D ? d : 0) * E);     // past the head: output rows that are not stored
-  }
-  const unsigned k_row = head_b + c * rs, v_row = head_b + 4 * g * rs;
+  // A block's K or V half is a buffer of the token rows that the context has there: a base that a step computes on the scalar
+  // unit, 32-bit offsets that stay.  What lies outside reads zeros, without an instruction that waits for the data: rows past
+  // the end of the context (their scores are masked), K past the head (in place of Q's zeros there) and V past the head (output rows
+  // that are not stored).
+  auto buffer = [&](const unsigned char* base, int b) {
+    const int rows = min(kBlockTokens, ctx_len - kBlockTokens * b);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(base), 0, (unsigned)rows * rs, kBufferWord3);
+  };
+  auto k_at = [&](int j) {
+    const unsigned at = head_b + c * rs + 16 * g;
+    return k_ok[j] ? at + (F32 ? 16 * j : 32 * j) * E : kPastEnd;
+  };
+  auto v_at = [&](int r, int q) {
+    const unsigned at = head_b + (4 * g + r) * rs + VW * E * c;
+    return C::FULL || VW * (16 * q + c) < D ? at + VW * E * 16 * q : kPastEnd;
+  };
   typedef typename std::conditional<(VW * E == 16), u32x4, u32x2>::type vreg;
 
   u32x4 kreg[KB][KJ];
@@ -179,7 +191,6 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
 #pragma unroll
     for (int kb = 0; kb < KB; kb++) slot[kb] = table[min(st * KB + kb, last_blk)];
   };
-  // Rows past the end of the context are not read: the last row again (their scores are masked).
   auto load_k = [&](int st) {
 #pragma unroll
     for (int kb = 0; kb < KB; kb++) {
@@ -188,32 +199,22 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
       const int64_t off = sfx ? s_base + (int64_t)(b - p_blk) * half : (int64_t)slot[kb] * (2 * half);
       const unsigned char* kp = (sfx ? ks : pool) + off;
       vp[kb] = sfx ? vs + off : kp + half;
-      const int rest = ctx_len - kBlockTokens * b;             // token rows the block holds
-      const unsigned row = rest >= kBlockTokens ? k_row : head_b + (unsigned)min(c, rest - 1) * rs;
+      const auto buf = buffer(kp, b);
 #pragma unroll
-      for (int j = 0; j < KJ; j++) {
-        kreg[kb][j] = *(const u32x4*)(kp + (row + k_off[j]));
-        if (!C::FULL && !k_ok[j]) kreg[kb][j] = (u32x4){0u, 0u, 0u, 0u};
-      }
+      for (int j = 0; j < KJ; j++) kreg[kb][j] = __builtin_amdgcn_raw_buffer_load_b128(buf, k_at(j), 0, 0);
     }
   };
   auto load_v = [&](int st) {
 #pragma unroll
     for (int kb = 0; kb < KB; kb++) {
-      const int rest = ctx_len - kBlockTokens * min(st * KB + kb, last_blk);
-      if (rest >= kBlockTokens) {
+      const auto buf = buffer(vp[kb], min(st * KB + kb, last_blk));
 #pragma unroll
-        for (int r = 0; r < 4; r++)
+      for (int r = 0; r < 4; r++)
 #pragma unroll
-          for (int q = 0; q < VQ; q++) vr[kb][r][q] = *(const vreg*)(vp[kb] + r * rs + (v_row + v_off[q]));
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-          const unsigned row = head_b + (unsigned)min(4 * g + r, rest - 1) * rs;
-#pragma unroll
-          for (int q = 0; q < VQ; q++) vr[kb][r][q] = *(const vreg*)(vp[kb] + (row + v_off[q]));
+        for (int q = 0; q < VQ; q++) {
+          if constexpr (VW * E == 16) vr[kb][r][q] = __builtin_amdgcn_raw_buffer_load_b128(buf, v_at(r, q), 0, 0);
+          else vr[kb][r][q] = __builtin_amdgcn_raw_buffer_load_b64(buf, v_at(r, q), 0, 0);
         }
-      }
     }
   };
 
@@ -222,21 +223,7 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
   const int st_begin = sub_begin * SPS + wave;
   int st = st_begin;
   const int st_end = min(sub_end * SPS, pos_max / (kBlockTokens * KB) + 1);
-  if (st < st_end) look_up(st);
-  u32x4 qreg[NQB][KJ];                                         // requested before K, so that waiting for K does not wait for V
-#pragma unroll
-  for (int qb = 0; qb < NQB; qb++)
-#pragma unroll
-    for (int j = 0; j < KJ; j++) {
-      qreg[qb][j] = *(const u32x4*)((const unsigned char*)p.q + qrow[qb] * (D * E) + k_off[j]);
-      if (!C::FULL && !k_ok[j]) qreg[qb][j] = (u32x4){0u, 0u, 0u, 0u};
-    }
-  if (st < st_end) {
-    load_k(st);
-    look_up(st + NW);
-    load_v(st);
-  }
-
+  u32x4 qreg[NQB][KJ];
   const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
   f32x4 o[NQB][C::NACC];                                       // tile (q, e): d = VW * (16q + 4g + r) + e of query row c
 #pragma unroll
@@ -313,9 +300,9 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
     }
   };
 
-  // One step.  DIAG: some row does not see all of its keys.
-  auto step = [&](auto diag_tag) {
-    constexpr bool DIAG = decltype(diag_tag)::value != 0;
+  // One step.  DIAG: some row does not see all of its keys.  MORE: the wave has another step, which this one asks for.
+  auto step = [&](auto diag_tag, auto more_tag) {
+    constexpr bool DIAG = decltype(diag_tag)::value != 0, MORE = decltype(more_tag)::value != 0;
     const int k0 = st * (kBlockTokens * KB);
     f32x4 s[KB][NQB];
 #pragma unroll
@@ -342,8 +329,7 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
                                                                 __builtin_bit_cast(bf16x8, qreg[qb][j]), s[kb][qb], 0, 0, 0);
       }
     }
-    const bool more = st + NW < st_end;
-    if (more) {
+    if constexpr (MORE) {
       load_k(st + NW);
       look_up(st + 2 * NW);                                    // clamped to the last block
     }
@@ -393,12 +379,35 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
       l[qb] += sum;
     }
     pv(w);
-    if (more) load_v(st + NW);
+    if constexpr (MORE) load_v(st + NW);
   };
-  // Two loops: the steps that every row sees in full spend nothing on masks.
-  const int st_full = min(st_end, (pos_min + 1) / (kBlockTokens * KB));
-  for (; st < st_full; st += NW) step(Tag<0>{});
-  for (; st < st_end; st += NW) step(Tag<1>{});
+  if (st < st_end) {
+    // Requested Q, K, V, as in the loop, and Q waited for before it: a wait for K is then a wait for all but the V requests behind
+    // it.  (Left to the scheduler, or with a test around the requests of a step, every step waited for the V it had just asked for.)
+    look_up(st);
+#pragma unroll
+    for (int qb = 0; qb < NQB; qb++)
+#pragma unroll
+      for (int j = 0; j < KJ; j++) qreg[qb][j] = *(const u32x4*)((const unsigned char*)p.q + qrow[qb] * (D * E) + q_off[j]);
+    __builtin_amdgcn_sched_barrier(0);
+    load_k(st);
+    look_up(st + NW);
+    __builtin_amdgcn_sched_barrier(0);
+    load_v(st);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int qb = 0; qb < NQB; qb++)
+#pragma unroll
+      for (int j = 0; j < KJ; j++) {
+        if (!C::FULL && !k_ok[j]) qreg[qb][j] = (u32x4){0u, 0u, 0u, 0u};
+        asm volatile("" : "+v"(qreg[qb][j]));
+      }
+    // Two loops: the steps that every row sees in full spend nothing on masks.  The last step has nothing to ask for.
+    const int st_last = st_end - NW, st_full = min(st_last, (pos_min + 1) / (kBlockTokens * KB));
+    for (; st < st_full; st += NW) step(Tag<0>{}, Tag<1>{});
+    for (; st < st_last; st += NW) step(Tag<1>{}, Tag<1>{});
+    step(Tag<1>{}, Tag<0>{});
+  }
 
   // The same keys for the rows of one block, a key at a time: a row adds weight times V of the keys that it sees and
   // touches no other.  Weights are taken against the running maximum: sums stay within those of a textbook loop.
