@@ -15,14 +15,6 @@
 
 namespace calvo {
 
-// Packed-rows kernel, in tenths of a microsecond: start and end of a workgroup (and a merge launch), and 32
-// keys for one wave's rows with both waves of its SIMD at work (measured per element type and padded head width).
-constexpr int kRowsFill = 60;
-static int rows_step_cost(bool f32, int head_dim) {
-  if (f32) return head_dim <= 64 ? 23 : head_dim <= 128 ? 48 : 64;
-  return head_dim <= 64 ? 7 : head_dim <= 128 ? 12 : 25;
-}
-
 int attn_pipe_tile_tokens(int heads_per_wg);
 int attn_duo_tile_tokens(int heads_per_wg);
 
@@ -112,10 +104,17 @@ int plan_piece_len(int n_sub, int n_max, int want, const PlanParams& p) {
 // (64Q/8KV, 224 uncut) 38.9 uncut, 49.1 in two.
 constexpr double kAlone = 0.7;
 
-int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots) {
+int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots, double* time) {
+  if (time) *time = 0.;
   if (p.force_splits) return p.force_splits;
   const int64_t wgs = (int64_t)tiles.size() * p.n_head_groups;
-  if (wgs <= 0 || wgs > 16 * (int64_t)p.wg_slots) return 1;     // many rounds: the last one hardly matters
+  if (wgs <= 0) return 1;
+  auto cost_of = [&](int64_t subs) { return (p.step_cost ? (subs + 3) / 4 * p.step_cost : subs) + p.split_fill; };
+  if (wgs > 16 * (int64_t)p.wg_slots) {                         // many rounds: the last one hardly matters
+    if (time)
+      for (const PlanTile& t : tiles) *time += 3. * (double)(cost_of(t.n_sub) * p.n_head_groups) / p.wg_slots;
+    return 1;
+  }
   static const std::vector<int> all = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 20, 24, 32, 48, 64};
   static const std::vector<int> coarse = {1, 2, 3, 4, 5, 6, 8, 12, 16, 24, 32, 48, 64};
   const int n_max = tiles.front().n_sub;           // heaviest first
@@ -124,7 +123,6 @@ int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t
   std::vector<int64_t> heap;
   for (int n : p.long_pieces ? coarse : all) {
     if (n > 1 && wgs * n > (p.step_cost ? 4 : 16) * (int64_t)p.wg_slots) break;
-    auto cost_of = [&](int64_t subs) { return (p.step_cost ? (subs + 3) / 4 * p.step_cost : subs) + p.split_fill; };
     bool cut = false;
     int64_t end = 0, slots = 0, work = 0;
     for (const PlanTile& t : tiles) {
@@ -161,6 +159,7 @@ int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t
     if (n == 1 || span < best * 0.98) {            // a cut has to win by 2 % over what is chosen so far
       best = span;
       want = n;
+      if (time) *time = 2. * span + (double)work / p.wg_slots + (cut ? p.split_fill : 0);
     }
     if (!cut && n > 1) break;                       // longer cuts are refused by split_min: nothing changes
   }
@@ -179,10 +178,6 @@ PlanItems plan_items(const std::vector<PlanTile>& tiles, int want, const PlanPar
   return out;
 }
 
-RowsShape attn_rows_shape(bool f32, int head_dim) {
-  return {head_dim <= 128 ? 32 : 16, rows_step_cost(f32, head_dim)};
-}
-
 std::vector<PlanTile> plan_row_tiles(const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int group, int tile_rows) {
   std::vector<PlanTile> tiles;
   for (int r = 0; r < n_reqs; r++) {
@@ -196,8 +191,47 @@ std::vector<PlanTile> plan_row_tiles(const int32_t* prefix_blocks, const int32_t
   return tiles;
 }
 
+// Packed-rows kernel, in tenths of a microsecond: start and end of a workgroup (a merge launch costs as much), and 32 keys for one wave's
+// rows while the other waves of its SIMD are at work (measured per element type and padded head width).
+// bf16 has a tiling of twice the rows, which reads K and V half as often: with the other one a workgroup waits for them (D = 64,
+// 8192+512 tokens, 32Q/8KV: 96 us a call, 74 without the requests for K, 95 with a third of the products for the weights; 72 with twice
+// the rows).  A step of twice the rows costs 1.0 (D = 256: one wave of a SIMD either way) to 1.8 as much.  The replay of both
+// launches decides.  us a call, three callers, 32Q/8KV, smaller / larger tiling, D = 64, 96, 256:
+//   2048+64    11.5 / 13.7   16.1 / 16.8   26.8 / 22.2          2048+256   16.6 / 19.8   22.8 / 25.6   83.9 / 46.5
+//   8192+128   28.5 / 25.6   41.4 / 38.4   147.4 / 83.2         0+512      12.0 / 10.5   16.2 / 12.7   37.2 / 25.9
+//   5008+300   46.4 / 41.3   71.4 / 59.5   241.2 / 148.3        512+400 (8Q/8KV)   7.7 / 10.1   10.1 / 16.4   16.9 / 17.3
+bool attn_rows_has_large(bool f32) { return !f32; }
+
+RowsShape attn_rows_shape(bool f32, int head_dim, bool large) {
+  if (f32) return {head_dim <= 128 ? 32 : 16, head_dim <= 64 ? 23 : head_dim <= 128 ? 48 : 64, 60, 1};
+  if (head_dim <= 64) return large ? RowsShape{64, 10, 65, 2} : RowsShape{32, 6, 60, 1};
+  if (head_dim <= 128) return large ? RowsShape{64, 16, 65, 2} : RowsShape{32, 9, 60, 1};
+  return large ? RowsShape{32, 22, 90, 2} : RowsShape{16, 21, 60, 1};
+}
+
 PlanParams rows_plan_params(RowsShape shape, int n_kv_heads, int n_cus, int force_splits) {
-  return {n_kv_heads, n_cus, 1, kRowsFill, force_splits, false, shape.step_cost};
+  return {n_kv_heads, n_cus, 1, shape.fill, force_splits, false, shape.step_cost};
+}
+
+RowsPlan plan_rows(bool f32, int head_dim, const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int group,
+                   int n_kv_heads, int n_cus, int force_splits, int64_t max_slots) {
+  const char* e = getenv("CALVO_ROWS_TILE");                    // test hook: 1 or 2 forces a tiling
+  RowsPlan best;
+  double best_time = 0.;
+  for (const bool large : {false, true}) {
+    if (large && (!attn_rows_has_large(f32) || (e && e[0] == '1'))) break;
+    RowsPlan p;
+    p.large = large;
+    p.shape = attn_rows_shape(f32, head_dim, large);
+    p.tiles = plan_row_tiles(prefix_blocks, suffix_lens, n_reqs, group, p.shape.tile_rows);
+    double time;
+    p.want = plan_pieces(p.tiles, rows_plan_params(p.shape, n_kv_heads, n_cus, force_splits), max_slots / p.shape.slots, &time);
+    if (!large || time < 0.97 * best_time || (e && e[0] == '2')) {
+      best = std::move(p);
+      best_time = time;
+    }
+  }
+  return best;
 }
 
 PlanItems plan_items_chunked(const std::vector<PlanTile>& tiles, const int32_t* prefix_blocks, int chunk_blocks, int n_chunks) {

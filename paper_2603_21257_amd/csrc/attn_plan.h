@@ -70,17 +70,30 @@ int plan_piece_len(int n_sub, int n_max, int want, const PlanParams& p);
 
 // pieces of the longest tile to ask for (1 = no cut), from a replay of the launch; a cut makes at most max_slots
 // (piece, head group) pairs (partial results there is room for)
-int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots = INT64_MAX);
+// time, if asked for: twice the length of the launch and once what it keeps the whole chip busy for, in units of split_fill
+int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots = INT64_MAX, double* time = nullptr);
 
 // work items of a whole-layer launch: every tile cut into pieces of plan_piece_len
 PlanItems plan_items(const std::vector<PlanTile>& tiles, int want, const PlanParams& p);
 
-// Tiling of the packed-rows kernel (attn_rows.hip): (token, head) rows of one KV head per work item, and what a
-// wave's step of 32 keys costs.
+// Tilings of the packed-rows kernel (attn_rows.hip): (token, head) rows of one KV head per work item, what a wave's step of
+// 32 keys costs and what the start and end of a workgroup do.
 struct RowsShape {
-  int tile_rows, step_cost;
+  int tile_rows, step_cost, fill;
+  int slots;          // partial-result slots (32 rows of 128 floats) of a work item and KV head
 };
-RowsShape attn_rows_shape(bool f32, int head_dim);
+bool attn_rows_has_large(bool f32);
+RowsShape attn_rows_shape(bool f32, int head_dim, bool large);
+
+// The tiling of a batch, its tiles and the pieces that the longest is asked to be cut into. 
+struct RowsPlan {
+  RowsShape shape;
+  std::vector<PlanTile> tiles;
+  int want;
+  bool large;
+};
+RowsPlan plan_rows(bool f32, int head_dim, const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int group,
+                   int n_kv_heads, int n_cus, int force_splits, int64_t max_slots);
 
 // the batch's tiles of tile_rows rows, heaviest first (group: query heads per KV head)
 std::vector<PlanTile> plan_row_tiles(const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int group, int tile_rows);

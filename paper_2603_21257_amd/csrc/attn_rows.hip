@@ -15,9 +15,9 @@
 //         bytes of a V row (d = 64q + 4c ..); output row m of instruction e is then d = 64q + 4m + e.
 //   bf16: v_mfma_f32_16x16x32_bf16.  V rows are read 8 or 16 bytes per lane in the same way and the four
 //         keys of a lane are brought together with v_perm_b32.  The weights stay fp32: each is split into
-//         three bf16 terms (24 significant bits), three products with the exact bf16 V.
+//         three bf16 terms (24 significant bits), three products with the exact bf16 V.  Two tilings (attn_rows_shape).
 // Neither product tells an infinite or NaN V of a key that a row does not see from one that it does (0 times
-// infinity), and the lower terms of a weight are negative or 0.  Such V leave sums that are not finite; a wave
+// infinity), and the lower terms of a weight may be 0.  Such V leave sums that are not finite; a wave
 // that finds one, or sums so large that weights above 1 (see the softmax reference) could be the reason, walks
 // its keys again with every row adding its own keys' fp32 products, weights at most 1 (walk_by_row).
 //
@@ -38,7 +38,8 @@
 //
 // What bounds it: fp32 the matrix pipes (a large fp32 product reaches 153 TFLOP/s on this part, a
 // sixteenth of bf16; 2.3 us per 32 keys of a wave's 32 rows at D = 64 against 1.8 us of MFMA), bf16 the
-// vector ALU (exponentials, weight split, V permutes; 0.7 us per step against 0.2 us of MFMA).
+// vector ALU (exponentials, weight split; at D = 64 in the larger tiling 0.9 us per step against 0.45 us of MFMA) and, in the
+// smaller tiling, K and V on their way from L2.
 // Measured against the kernel it replaces (one wave per token and head on the vector ALU), us a call:
 // fp32 8Q/2KV D = 64, 1024+128 tokens 193 -> 12.5; bf16 16Q/4KV D = 64, 4096+300 tokens 1168 -> 22.7.
 #include "attn_common.h"
@@ -63,6 +64,7 @@ struct RowsCfg {
   static constexpr int VW = F32 ? 4 : (DP % 128 == 0 ? 8 : 4);   // consecutive d a lane reads of a V row
   static constexpr int VQ = DP / (16 * VW);                  // such reads per row
   static constexpr int NACC = VQ * VW;                       // 16 x 16 output tiles per 16-row block
+  static constexpr bool V_FIRST = NACC <= (NW == 4 ? 8 : 4);      // V operands of a step in registers at a time
   static constexpr int ROWS = 16 * NQB;                      // rows of a tile
   static constexpr int UNITS = NQB * VQ * 4;                 // (row block, q, r): VW consecutive d of a lane's row
   static constexpr int LDS_O = NW * UNITS * VW * 64 * 4;     // all waves' accumulators
@@ -149,7 +151,7 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
   // ---- addressing: block b of the request; 16-byte offsets inside it
   const unsigned char* pool = (const unsigned char*)p.pool_layer;
   const unsigned rs = (unsigned)(Hkv * D * E);                 // bytes between token rows
-  const int64_t half = (int64_t)kBlockTokens * rs;
+  const unsigned half = kBlockTokens * rs;
   const const_i32p table = (const_i32p)(uintptr_t)(p.tables + rd.table_off);
   const int p_blk = P / kBlockTokens, last_blk = (ctx_len + kBlockTokens - 1) / kBlockTokens - 1;
   const unsigned char* ks = (const unsigned char*)p.k_suffix;
@@ -191,15 +193,16 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
 #pragma unroll
     for (int kb = 0; kb < KB; kb++) slot[kb] = table[min(st * KB + kb, last_blk)];
   };
+  const unsigned char *v_pool = pool + half, *k_sfx = ks + s_base, *v_sfx = vs + s_base;
+  const int sfx_blk = from_suffix ? p_blk : last_blk + 1;      // from this block on the caller's arrays
   auto load_k = [&](int st) {
 #pragma unroll
     for (int kb = 0; kb < KB; kb++) {
       const int b = min(st * KB + kb, last_blk);
-      const bool sfx = from_suffix && b >= p_blk;
-      const int64_t off = sfx ? s_base + (int64_t)(b - p_blk) * half : (int64_t)slot[kb] * (2 * half);
-      const unsigned char* kp = (sfx ? ks : pool) + off;
-      vp[kb] = sfx ? vs + off : kp + half;
-      const auto buf = buffer(kp, b);
+      const bool sfx = b >= sfx_blk;
+      const uint64_t off = (uint64_t)(unsigned)(sfx ? b - p_blk : 2 * slot[kb]) * half;
+      const auto buf = buffer((sfx ? k_sfx : pool) + off, b);
+      vp[kb] = (sfx ? v_sfx : v_pool) + off;
 #pragma unroll
       for (int j = 0; j < KJ; j++) kreg[kb][j] = __builtin_amdgcn_raw_buffer_load_b128(buf, k_at(j), 0, 0);
     }
@@ -230,30 +233,31 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
   for (int qb = 0; qb < NQB; qb++)
 #pragma unroll
     for (int a = 0; a < C::NACC; a++) o[qb][a] = zero4;
-  float m[NQB], l[NQB];                                        // reference (exponent units; -inf: no key seen), row sum of this lane
+  // Softmax reference (exponent units), negated and 0 while no key has been seen; the score above which it moves, -inf until
+  // then; row sum of this lane.
+  float nref[NQB], bound[NQB], l[NQB];
 #pragma unroll
-  for (int qb = 0; qb < NQB; qb++) { m[qb] = -INFINITY; l[qb] = 0.f; }
-  const float c2 = p.scale * 1.4426950408889634f;
+  for (int qb = 0; qb < NQB; qb++) { nref[qb] = 0.f; bound[qb] = -INFINITY; l[qb] = 0.f; }
+  const float c2 = p.scale * 1.4426950408889634f, inv_c2 = 1.f / c2;
+  auto reference = [&](int qb) { return bound[qb] == -INFINITY ? -INFINITY : -nref[qb]; };
 
-  // Second product: o += V^T * w for the keys in vr.
-  auto weights_bf16 = [&](const float (&w)[NQB][KB][4], bf16x8 (&pb)[NQB][3]) {
+  // Weights of a row block as three bf16 terms: the upper half cut off, which leaves an exact rest, twice.  (Of a pair one
+  // instruction packs them, two each clear and subtract; rounding the terms takes two more.)
+  auto weights_bf16 = [&](const float (&w)[KB][4], bf16x8 (&pb)[3]) {
+    u32x4 x[3];
 #pragma unroll
-    for (int qb = 0; qb < NQB; qb++) {
-      u32x4 x[3];
+    for (int i = 0; i < 4; i++) {
+      float v[2] = {w[(KB - 1) & (i >> 1)][2 * (i & 1)], w[(KB - 1) & (i >> 1)][2 * (i & 1) + 1]};
 #pragma unroll
-      for (int i = 0; i < 4; i++) {
-        float v[2] = {w[qb][i >> 1][2 * (i & 1)], w[qb][i >> 1][2 * (i & 1) + 1]};
-#pragma unroll
-        for (int t = 0; t < 3; t++) {
-          const bf16x2 top = {(__bf16)v[0], (__bf16)v[1]};
-          x[t][i] = __builtin_bit_cast(unsigned, top);
-          v[0] -= bf16_widen(x[t][i] & 0xffffu);
-          v[1] -= __builtin_bit_cast(float, x[t][i] & 0xffff0000u);
-        }
+      for (int t = 0; t < 3; t++) {
+        const unsigned b0 = __builtin_bit_cast(unsigned, v[0]), b1 = __builtin_bit_cast(unsigned, v[1]);
+        x[t][i] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+        v[0] -= as_float(b0 & 0xffff0000u);
+        v[1] -= as_float(b1 & 0xffff0000u);
       }
-#pragma unroll
-      for (int t = 0; t < 3; t++) pb[qb][t] = __builtin_bit_cast(bf16x8, x[t]);
     }
+#pragma unroll
+    for (int t = 0; t < 3; t++) pb[t] = __builtin_bit_cast(bf16x8, x[t]);
   };
   // V^T operand of tile (q, e): the lane's keys in k-slot order (kb, r)
   auto v_bf16 = [&](int q, int e) {
@@ -264,40 +268,17 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
                                    vr[(KB - 1) & (i >> 1)][2 * (i & 1)][q][e >> 1], e & 1 ? 0x07060302u : 0x05040100u);
     return __builtin_bit_cast(bf16x8, x);
   };
-  auto pv = [&](const float (&w)[NQB][KB][4]) {
-    if constexpr (F32) {
+  // Weights of row block qb, from its scores
+  auto weigh = [&](const f32x4 (&s)[KB][NQB], int qb, float (&w)[KB][4]) {
+    float sum = 0.f;
 #pragma unroll
-      for (int kb = 0; kb < KB; kb++)
+    for (int kb = 0; kb < KB; kb++)
 #pragma unroll
-        for (int r = 0; r < 4; r++)
-#pragma unroll
-          for (int q = 0; q < VQ; q++)
-#pragma unroll
-            for (int e = 0; e < VW; e++)
-#pragma unroll
-              for (int qb = 0; qb < NQB; qb++)
-                o[qb][q * VW + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(as_float(vr[kb][r][q][e]), w[qb][kb][r],
-                                                                         o[qb][q * VW + e], 0, 0, 0);
-    } else {
-      bf16x8 pb[NQB][3];
-      weights_bf16(w, pb);
-#pragma unroll
-      for (int q = 0; q < VQ; q++)
-#pragma unroll
-        for (int e0 = 0; e0 < VW; e0 += 4) {
-          bf16x8 a[4];
-#pragma unroll
-          for (int e = 0; e < 4; e++) a[e] = v_bf16(q, e0 + e);
-#pragma unroll
-          for (int t = 0; t < 3; t++)
-#pragma unroll
-            for (int e = 0; e < 4; e++)
-#pragma unroll
-              for (int qb = 0; qb < NQB; qb++)
-                o[qb][q * VW + e0 + e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[e], pb[qb][t], o[qb][q * VW + e0 + e], 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);                   // one group's operands at a time in registers
-        }
-    }
+      for (int r = 0; r < 4; r++) {
+        w[kb][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][qb][r], c2, nref[qb]));
+        sum += w[kb][r];
+      }
+    l[qb] += sum;
   };
 
   // One step.  DIAG: some row does not see all of its keys.  MORE: the wave has another step, which this one asks for.
@@ -351,36 +332,86 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
       for (int kb = 0; kb < KB; kb++)
 #pragma unroll
         for (int r = 0; r < 4; r++) mx[qb] = fmaxf(mx[qb], s[kb][qb][r]);
-      raise |= mx[qb] * c2 > m[qb] + 16.f;
+      raise |= mx[qb] > bound[qb];
     }
     if (__builtin_amdgcn_ballot_w64(raise) != 0) {
 #pragma unroll
       for (int qb = 0; qb < NQB; qb++) {
-        const float mn = fmaxf(m[qb], quad_max(mx[qb]) * c2);
-        const float a = __builtin_amdgcn_exp2f(m[qb] - (mn == -INFINITY ? 0.f : mn));
-        m[qb] = mn;
+        const float old = reference(qb), mn = fmaxf(old, quad_max(mx[qb]) * c2);
+        nref[qb] = mn == -INFINITY ? 0.f : -mn;                // a row that has seen no key yet: all its weights are 0
+        bound[qb] = (mn + 16.f) * inv_c2;
+        const float a = __builtin_amdgcn_exp2f(old + nref[qb]);
         l[qb] *= a;
 #pragma unroll
         for (int i = 0; i < C::NACC; i++) o[qb][i] *= a;
       }
     }
-    float w[NQB][KB][4];
+    // Second product: o += V^T * w
+    if constexpr (F32) {
+      float w[NQB][KB][4];
 #pragma unroll
-    for (int qb = 0; qb < NQB; qb++) {
-      const float ref = m[qb] == -INFINITY ? 0.f : m[qb];      // a row that has seen no key yet: all its weights are 0
-      float sum = 0.f;
+      for (int qb = 0; qb < NQB; qb++) weigh(s, qb, w[qb]);
 #pragma unroll
       for (int kb = 0; kb < KB; kb++)
 #pragma unroll
-        for (int r = 0; r < 4; r++) {
-          w[qb][kb][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][qb][r], c2, -ref));
-          sum += w[qb][kb][r];
+        for (int r = 0; r < 4; r++)
+#pragma unroll
+          for (int q = 0; q < VQ; q++)
+#pragma unroll
+            for (int e = 0; e < VW; e++)
+#pragma unroll
+              for (int qb = 0; qb < NQB; qb++)
+                o[qb][q * VW + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(as_float(vr[kb][r][q][e]), w[qb][kb][r],
+                                                                         o[qb][q * VW + e], 0, 0, 0);
+      if constexpr (MORE) load_v(st + NW);
+    } else if constexpr (C::V_FIRST) {
+      // V into operand order, which frees its registers for the next step's, then one row block after the other
+      bf16x8 a[C::NACC];
+#pragma unroll
+      for (int i = 0; i < C::NACC; i++) a[i] = v_bf16(i / VW, i % VW);
+      if constexpr (MORE) {
+        __builtin_amdgcn_sched_barrier(0);
+        load_v(st + NW);
+      }
+#pragma unroll
+      for (int qb = 0; qb < NQB; qb++) {
+        float w[KB][4];
+        bf16x8 pb[3];
+        weigh(s, qb, w);
+        weights_bf16(w, pb);
+#pragma unroll
+        for (int t = 0; t < 3; t++)
+#pragma unroll
+          for (int i = 0; i < C::NACC; i++) o[qb][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], pb[t], o[qb][i], 0, 0, 0);
+      }
+    } else {
+      bf16x8 pb[NQB][3];
+#pragma unroll
+      for (int qb = 0; qb < NQB; qb++) {
+        float w[KB][4];
+        weigh(s, qb, w);
+        weights_bf16(w, pb[qb]);
+      }
+#pragma unroll
+      for (int q = 0; q < VQ; q++)
+#pragma unroll
+        for (int e0 = 0; e0 < VW; e0 += 4) {
+          bf16x8 a[4];
+#pragma unroll
+          for (int e = 0; e < 4; e++) a[e] = v_bf16(q, e0 + e);
+#pragma unroll
+          for (int t = 0; t < 3; t++)
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+#pragma unroll
+              for (int qb = 0; qb < NQB; qb++)
+                o[qb][q * VW + e0 + e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[e], pb[qb][t], o[qb][q * VW + e0 + e], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);                   // one group's operands at a time in registers
         }
-      l[qb] += sum;
+      if constexpr (MORE) load_v(st + NW);
     }
-    pv(w);
-    if constexpr (MORE) load_v(st + NW);
   };
+
   if (st < st_end) {
     // Requested Q, K, V, as in the loop, and Q waited for before it: a wait for K is then a wait for all but the V requests behind
     // it.  (Left to the scheduler, or with a test around the requests of a step, every step waited for the V it had just asked for.)
@@ -408,6 +439,10 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
     for (; st < st_last; st += NW) step(Tag<1>{}, Tag<1>{});
     step(Tag<1>{}, Tag<0>{});
   }
+
+  float m[NQB];
+#pragma unroll
+  for (int qb = 0; qb < NQB; qb++) m[qb] = reference(qb);
 
   // The same keys for the rows of one block, a key at a time: a row adds weight times V of the keys that it sees and
   // touches no other.  Weights are taken against the running maximum: sums stay within those of a textbook loop.
@@ -527,7 +562,8 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
   float* lds_o = (float*)smem + (size_t)wave * (C::UNITS * VW * 64) + lane;
   float* lds_ml = (float*)(smem + C::LDS_O);
 #pragma unroll
-  for (int qb = 0; qb < NQB; qb++) l[qb] = quad_sum(l[qb]);
+  for (int qb = 0; qb < NQB; qb++)
+    l[qb] = quad_sum(l[qb]);
 #pragma unroll
   for (int qb = 0; qb < NQB; qb++)
     if (g == 0) *(f32x2*)(lds_ml + (wave * C::ROWS + 16 * qb + c) * 2) = (f32x2){m[qb], l[qb]};
@@ -690,9 +726,9 @@ hipError_t launch(const RowsParams& p, unsigned grid, const int32_t* split_tiles
   return hipGetLastError();
 }
 
-// f(configuration) for an element type and head width
+// f(configuration) for an element type, head width and tiling (attn_rows_shape)
 template <typename F>
-auto with_cfg(int dtype, int head_dim, F&& f) {
+auto with_cfg(int dtype, int head_dim, int tile_rows, F&& f) {
   typedef uint16_t B16;
   if (dtype == CALVO_F32) {
     if (head_dim == 64) return f(RowsCfg<float, 64, 2, 2, 8, true>{});
@@ -702,27 +738,28 @@ auto with_cfg(int dtype, int head_dim, F&& f) {
     if (head_dim == 256) return f(RowsCfg<float, 256, 1, 1, 4, true>{});
     return f(RowsCfg<float, 256, 1, 1, 4, false>{});
   }
-  if (head_dim == 64) return f(RowsCfg<B16, 64, 2, 2, 8, true>{});
-  if (head_dim < 64) return f(RowsCfg<B16, 64, 2, 2, 8, false>{});
-  if (head_dim <= 128) return f(RowsCfg<B16, 128, 2, 2, 8, false>{});     // 128 itself: attn_pipeline.h
-  if (head_dim == 256) return f(RowsCfg<B16, 256, 1, 2, 4, true>{});
-  return f(RowsCfg<B16, 256, 1, 2, 4, false>{});
+  if (head_dim == 64) return tile_rows == 64 ? f(RowsCfg<B16, 64, 4, 2, 8, true>{}) : f(RowsCfg<B16, 64, 2, 2, 8, true>{});
+  if (head_dim < 64) return tile_rows == 64 ? f(RowsCfg<B16, 64, 4, 2, 8, false>{}) : f(RowsCfg<B16, 64, 2, 2, 8, false>{});
+  if (head_dim <= 128)                                          // 128 itself: attn_pipeline.h
+    return tile_rows == 64 ? f(RowsCfg<B16, 128, 4, 2, 4, false>{}) : f(RowsCfg<B16, 128, 2, 2, 8, false>{});
+  if (head_dim == 256) return tile_rows == 32 ? f(RowsCfg<B16, 256, 2, 2, 4, true>{}) : f(RowsCfg<B16, 256, 1, 2, 4, true>{});
+  return tile_rows == 32 ? f(RowsCfg<B16, 256, 2, 2, 4, false>{}) : f(RowsCfg<B16, 256, 1, 2, 4, false>{});
 }
 
 }  // namespace rows
 
-hipError_t attn_rows_prepare(int dtype, int head_dim) {
-  return rows::with_cfg(dtype, head_dim, [](auto cfg) {
+hipError_t attn_rows_prepare(int dtype, int head_dim, int tile_rows) {
+  return rows::with_cfg(dtype, head_dim, tile_rows, [](auto cfg) {
     typedef decltype(cfg) C;
     return hipFuncSetAttribute((const void*)rows::attn_rows_kernel<C>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
   });
 }
 
-hipError_t launch_attn_rows(const RowsParams& p, int dtype, int n_items, const int32_t* split_tiles, int n_split_tiles,
+hipError_t launch_attn_rows(const RowsParams& p, int dtype, int tile_rows, int n_items, const int32_t* split_tiles, int n_split_tiles,
                             hipStream_t stream) {
   if (n_items <= 0) return hipSuccess;
   const unsigned grid = (unsigned)n_items * (unsigned)p.n_kv_heads;
-  return rows::with_cfg(dtype, p.head_dim, [&](auto cfg) {
+  return rows::with_cfg(dtype, p.head_dim, tile_rows, [&](auto cfg) {
     return rows::launch<decltype(cfg)>(p, grid, split_tiles, n_split_tiles, stream);
   });
 }

@@ -589,7 +589,10 @@ int calvo_create(const calvo_config* cfg, calvo_ctx** out) {
     if (e != hipSuccess) { const int prc = fail_hip(e, "hipFuncSetAttribute(dynamic LDS)"); destroy_partial(c); return prc; }
   }
   if (!(cfg->dtype == CALVO_BF16 && cfg->head_dim == 128)) {
-    hipError_t e = attn_rows_prepare(cfg->dtype, cfg->head_dim);
+    const bool f32 = cfg->dtype == CALVO_F32;
+    hipError_t e = attn_rows_prepare(cfg->dtype, cfg->head_dim, attn_rows_shape(f32, cfg->head_dim, false).tile_rows);
+    if (e == hipSuccess && attn_rows_has_large(f32))
+      e = attn_rows_prepare(cfg->dtype, cfg->head_dim, attn_rows_shape(f32, cfg->head_dim, true).tile_rows);
     if (e != hipSuccess) { const int prc = fail_hip(e, "hipFuncSetAttribute(dynamic LDS)"); destroy_partial(c); return prc; }
   }
   {
@@ -1072,7 +1075,8 @@ struct AttnPlan {
   int n_reqs = 0, total = 0;            // requests, suffix tokens over all of them
   bool chunked = false;
   int nck = 0;
-  int row_tiles = 0;                    // packed-rows kernel: tiles over all requests
+  int row_tiles = 0;                    // packed-rows kernel: tiles over all requests, rows of one, partial-result slots
+  int tile_rows = 0, item_slots = 1;
   int longest = 0;                      // suffix tokens of the longest one
   bool apart = true;                    // no request's table names a slot that another one appends to
   PlanItems plan;
@@ -1124,20 +1128,39 @@ bool appends_apart(const calvo_ctx* c, const calvo_request* reqs, int n_reqs) {
   return true;
 }
 
-// Pieces per tile.  The decision (a replay of the launch, attn_plan.cpp) depends only on the batch's
-// lengths and is kept for the following layers.
-int kept_pieces(calvo_ctx* c, int variant, const calvo_request* reqs, int n_reqs, const std::vector<PlanTile>& tiles,
-                const PlanParams& pp, int64_t max_slots) {
-  if (c->force_splits) return plan_pieces(tiles, pp);
+// The decision about tiles and pieces (a replay of the launch, attn_plan.cpp) depends only on the batch's lengths and is kept for the
+// following layers.
+bool plan_is_kept(calvo_ctx* c, int variant, const calvo_request* reqs, int n_reqs) {
   std::vector<int64_t> key;
   key.reserve(2 * n_reqs + 1);
   key.push_back(variant);
   for (int r = 0; r < n_reqs; r++) { key.push_back(reqs[r].n_prefix_blocks); key.push_back(reqs[r].suffix_len); }
-  if (key != c->plan_key) {
-    c->plan_want = plan_pieces(tiles, pp, max_slots);
-    c->plan_key = key;
-  }
+  if (key == c->plan_key) return true;
+  c->plan_key = std::move(key);
+  return false;
+}
+
+// Pieces per tile
+int kept_pieces(calvo_ctx* c, int variant, const calvo_request* reqs, int n_reqs, const std::vector<PlanTile>& tiles,
+                const PlanParams& pp, int64_t max_slots) {
+  if (c->force_splits) return plan_pieces(tiles, pp);
+  if (!plan_is_kept(c, variant, reqs, n_reqs)) c->plan_want = plan_pieces(tiles, pp, max_slots);
   return c->plan_want;
+}
+
+// The packed-rows kernel's tiles and their pieces
+RowsPlan kept_rows(calvo_ctx* c, const calvo_request* reqs, const int32_t* pblocks, const int32_t* slens, int n_reqs) {
+  const bool f32 = c->cfg.dtype == CALVO_F32;
+  const int hkv = c->cfg.n_kv_heads, group = c->cfg.n_q_heads / hkv, dim = c->cfg.head_dim;
+  if (!c->force_splits && plan_is_kept(c, 0, reqs, n_reqs)) {
+    RowsPlan p{attn_rows_shape(f32, dim, c->plan_large), {}, c->plan_want, c->plan_large};
+    p.tiles = plan_row_tiles(pblocks, slens, n_reqs, group, p.shape.tile_rows);
+    return p;
+  }
+  RowsPlan p = plan_rows(f32, dim, pblocks, slens, n_reqs, group, hkv, c->n_cus, c->force_splits, kStaticPartSlots);
+  c->plan_want = p.want;
+  c->plan_large = p.large;
+  return p;
 }
 
 // Which plan.  calvo_prefill_attn_noalloc takes the first of them, in this order, that fits its fixed-size array.  None of
@@ -1187,15 +1210,20 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
       ap.plan = plan_items(tiles, kept_pieces(c, ap.variant + 16 * (int)rule, reqs, n_reqs, tiles, pp, max_slots), pp);
     }
   } else {
-    const RowsShape shape = attn_rows_shape(cf.dtype == CALVO_F32, cf.head_dim);
-    const std::vector<PlanTile> tiles = plan_row_tiles(pblocks.data(), slens.data(), n_reqs, cf.n_q_heads / cf.n_kv_heads, shape.tile_rows);
-    ap.row_tiles = (int)tiles.size();
+    RowsPlan rows;
     if (rule == PlanRule::kBest) {
-      const PlanParams pp = rows_plan_params(shape, cf.n_kv_heads, c->n_cus, c->force_splits);
-      ap.plan = plan_items(tiles, kept_pieces(c, ap.variant, reqs, n_reqs, tiles, pp, kStaticPartSlots), pp);
-      if (ap.plan.items.size() * (size_t)cf.n_kv_heads > kStaticPartSlots && !ap.plan.split_tiles.empty())
-        ap.plan = plan_items(tiles, 1, pp);                // forced pieces beyond the room for partial results
+      rows = kept_rows(c, reqs, pblocks.data(), slens.data(), n_reqs);
+      const PlanParams pp = rows_plan_params(rows.shape, cf.n_kv_heads, c->n_cus, c->force_splits);
+      ap.plan = plan_items(rows.tiles, rows.want, pp);
+      if (ap.plan.items.size() * (size_t)cf.n_kv_heads * (size_t)rows.shape.slots > kStaticPartSlots && !ap.plan.split_tiles.empty())
+        ap.plan = plan_items(rows.tiles, 1, pp);                // forced pieces beyond the room for partial results
+    } else {
+      rows.shape = attn_rows_shape(cf.dtype == CALVO_F32, cf.head_dim, false);
+      rows.tiles = plan_row_tiles(pblocks.data(), slens.data(), n_reqs, cf.n_q_heads / cf.n_kv_heads, rows.shape.tile_rows);
     }
+    ap.row_tiles = (int)rows.tiles.size();
+    ap.tile_rows = rows.shape.tile_rows;
+    ap.item_slots = rows.shape.slots;
   }
   ap.lay = build_descriptor_blob(c, reqs, n_reqs, cu_suffix, ap.plan, ap.mfma, ap.blob);
   if (rule == PlanRule::kFitted && ap.blob.size() > kStaticBlobInts && !ap.plan.split_tiles.empty() && !ap.chunked && !c->force_splits) {
@@ -1207,7 +1235,7 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
   ap.part_need = ap.plan.split_tiles.empty()
                      ? 0
                      : ap.mfma ? ap.plan.items.size() * (size_t)(cf.n_q_heads / ap.HW) * (size_t)attn_mfma_row_blocks(ap.variant)
-                               : ap.plan.items.size() * (size_t)cf.n_kv_heads;
+                               : ap.plan.items.size() * (size_t)cf.n_kv_heads * (size_t)ap.item_slots;
 }
 
 // What calvo_prefill_attn works out for a batch - checks, plan, descriptor words - kept for the next call: a
@@ -1353,7 +1381,7 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
     rp.scale = p.scale;
     rp.part_o = part_o; rp.part_ml = part_ml;
     rp.clock = p.clock;
-    HIP_TRY(launch_attn_rows(rp, cf.dtype, listed ? (int)ap.plan.items.size() : ap.row_tiles,
+    HIP_TRY(launch_attn_rows(rp, cf.dtype, ap.tile_rows, listed ? (int)ap.plan.items.size() : ap.row_tiles,
                              d_att + ap.lay.split_off, (int)ap.plan.split_tiles.size(), c->s_compute));
   }
   const bool mark = c->mark_ends.load(std::memory_order_acquire);

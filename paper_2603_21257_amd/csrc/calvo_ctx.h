@@ -72,6 +72,7 @@ struct calvo_ctx {
   std::shared_ptr<void> kept;     // checked and planned batch of the latest calvo_prefill_attn (KeptBatch, calvo_api.hip)
   std::vector<int64_t> plan_key;  // lengths of the batch the cached decision belongs to
   int plan_want = 1;
+  bool plan_large = false;         // packed rows: the tiling that went with it
   float* part_o = nullptr;        // split-KV partial results (compute stream only)
   float* part_ml = nullptr;
   size_t part_slots = 0;          // capacity in (work item, head group, block of 32 rows) slots

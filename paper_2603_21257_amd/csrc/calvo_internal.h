@@ -110,8 +110,8 @@ struct RowsParams {
   LaunchClock clock;
 };
 // raises the kernel's dynamic LDS limit; once per device and shape, before the first launch
-hipError_t attn_rows_prepare(int dtype, int head_dim);
-hipError_t launch_attn_rows(const RowsParams& p, int dtype, int n_items, const int32_t* split_tiles, int n_split_tiles,
+hipError_t attn_rows_prepare(int dtype, int head_dim, int tile_rows);
+hipError_t launch_attn_rows(const RowsParams& p, int dtype, int tile_rows, int n_items, const int32_t* split_tiles, int n_split_tiles,
                             hipStream_t stream);
 // The pipelined bf16 / head-dim-128 kernels (attn_pipeline.h).  The *_prepare calls raise the
 // kernels' dynamic LDS limit; once per device, before the first launch.
