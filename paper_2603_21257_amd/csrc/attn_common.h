@@ -16,6 +16,12 @@ typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((address_space(3))) unsigned char lds_u8;
+// descriptor words, which no kernel writes: read on the scalar unit
+typedef const __attribute__((address_space(4))) int32_t* const_i32p;
+__device__ inline WorkItem load_item(const WorkItem* items, int i) {
+  const const_i32p w = (const_i32p)(uintptr_t)(items + i);
+  return {w[0], w[1], w[2], w[3], w[4], w[5], w[6], w[7]};
+}
 
 constexpr int kD = 128;
 constexpr int kSK = 32;                        // keys per sub-tile / ring slot

@@ -52,7 +52,8 @@ struct WorkItem {
   int32_t sub_end;    // one past its last sub-tile (the last piece ends at the tile's causal limit)
   int32_t n_splits;   // pieces the tile is cut into; 1 = the kernel writes the final output itself
   int32_t first_item; // index of the tile's first piece
-  int32_t pad0, pad1;
+  // of the request, so that the merge reads them from here (build_descriptor_blob)
+  int32_t q_off, suffix_len;
 };
 
 struct PlanItems {

@@ -744,7 +744,9 @@ BlobLayout build_descriptor_blob(const calvo_ctx* c, const calvo_request* reqs, 
     n_tab += (size_t)nt + kTablePad + (nt & 1);
   }
   lay.items_off = blob.size();
-  for (const WorkItem& it : plan.items) {
+  for (WorkItem it : plan.items) {
+    it.q_off = cu_suffix[it.req];
+    it.suffix_len = reqs[it.req].suffix_len;
     const int32_t* w = (const int32_t*)&it;
     blob.insert(blob.end(), w, w + sizeof(WorkItem) / 4);
   }
