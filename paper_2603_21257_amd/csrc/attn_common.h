@@ -97,35 +97,60 @@ __device__ inline void store_piece(float* po, int g, const f32x4 (&o)[8][QB], in
   for (int db = 0; db < 8; db++) *(f32x4*)(po + 16 * db + 4 * g) = o[db][qb];
 }
 
-// The suffix rows of n_tok tokens of request rd from token tok0 on and of KV head kv, from the caller's arrays to the pool, by
-// THREADS threads: four chunks of K and of V in flight per thread while there are that many.
-template <int THREADS>
-__device__ inline void append_rows(const unsigned char* ks, const unsigned char* vs, unsigned char* pool, const int32_t* table,
-                                   const ReqDesc& rd, int n_kv_heads, int kv, int tok0, int n_tok, int tid) {
-  const int64_t rs = (int64_t)n_kv_heads * kRow, half_b = kBlockTokens * rs;
-  const int n = n_tok * (kRow / 16);
-  auto move = [&](int i0, auto count) {
+// Suffix token i of request r sits at absolute position P_r + i: slot table_r[pos / 16], row pos % 16 of the K half and of the
+// V half.  One thread per 16-byte chunk of a row, four chunks of K and of V in flight: this is workgroup wg of n_wgs with 256 threads.
+__device__ inline void append_suffix(const AppendParams& p, int wg, int n_wgs, int tid) {
+  const int64_t n = (int64_t)p.total_tokens * p.row_chunks, stride = (int64_t)n_wgs * 256;
+  const int64_t half_chunks = (int64_t)kBlockTokens * p.row_chunks;   // one K (or V) half of a block
+  const u32x4* ks = (const u32x4*)p.k_suffix;
+  const u32x4* vs = (const u32x4*)p.v_suffix;
+  u32x4* pool = (u32x4*)p.pool_layer;
+  auto move = [&](int64_t i0, auto count) {
     constexpr int N = decltype(count)::value;
     u32x4 k[N], v[N];
     int64_t dst[N];
 #pragma unroll
     for (int u = 0; u < N; u++) {
-      const int i = i0 + u * THREADS, tok = tok0 + i / (kRow / 16), pos = rd.prefix_len + tok;
-      const int64_t in_row = kv * kRow + (i % (kRow / 16)) * 16;
-      const int64_t src = (int64_t)(rd.q_off + tok) * rs + in_row;
-      dst[u] = (int64_t)table[pos / kBlockTokens] * (2 * half_b) + (int64_t)(pos % kBlockTokens) * rs + in_row;
-      k[u] = *(const u32x4*)(ks + src);
-      v[u] = *(const u32x4*)(vs + src);
+      const int64_t i = i0 + u * stride;
+      k[u] = ks[i];
+      v[u] = vs[i];
     }
 #pragma unroll
     for (int u = 0; u < N; u++) {
-      *(u32x4*)(pool + dst[u]) = k[u];
-      *(u32x4*)(pool + dst[u] + half_b) = v[u];
+      const int64_t i = i0 + u * stride;
+      const int32_t tok = (int32_t)(i / p.row_chunks);
+      const int32_t c = (int32_t)(i - (int64_t)tok * p.row_chunks);
+      int r = 0;
+      while (r + 1 < p.n_reqs && tok >= p.reqs[r + 1].q_off) r++;
+      const ReqDesc rd = p.reqs[r];
+      const int32_t pos = rd.prefix_len + (tok - rd.q_off);
+      const int64_t slot = p.tables[rd.table_off + pos / kBlockTokens];
+      dst[u] = slot * 2 * half_chunks + (int64_t)(pos % kBlockTokens) * p.row_chunks + c;
+    }
+#pragma unroll
+    for (int u = 0; u < N; u++) {
+      pool[dst[u]] = k[u];
+      pool[dst[u] + half_chunks] = v[u];
     }
   };
-  int i = tid;
-  for (; i + 3 * THREADS < n; i += 4 * THREADS) move(i, Tag<4>{});
-  for (; i < n; i += THREADS) move(i, Tag<1>{});
+  int64_t i = (int64_t)wg * 256 + tid;
+  for (; i + 3 * stride < n; i += 4 * stride) move(i, Tag<4>{});
+  for (; i < n; i += stride) move(i, Tag<1>{});
+}
+
+// Workgroups behind those of the tiles in a launch that takes the suffix rows along: four chunks per thread.  They run beside the
+// tiles; at the end of a tile's workgroup the rows were in the way of its results (us a call of one caller, there / here: 3072+40
+// tokens, 8Q/8KV, 15.6 / 14.4, 512+1 13.3 / 12.9, 448+155 18.2 / 17.7).
+inline unsigned append_wgs(const AttnParams& p) {
+  return p.k_suffix ? (unsigned)(((int64_t)p.total_tokens * p.n_kv_heads * (kRow / 16) + 1023) / 1024) : 0;
+}
+__device__ inline bool append_wg(const AttnParams& p) {
+  if ((int)blockIdx.x < p.attn_wgs) return false;
+  AppendParams app{p.k_suffix, p.v_suffix, const_cast<void*>(p.pool_layer), p.reqs, p.tables, p.n_reqs, p.total_tokens,
+                   p.n_kv_heads * (kRow / 16)};
+  append_suffix(app, blockIdx.x - p.attn_wgs, gridDim.x - p.attn_wgs, threadIdx.x);
+  if (threadIdx.x == 0) clock_end(p.clock.words);
+  return true;
 }
 
 // 64 lanes x 16 bytes from global memory (uniform base + per-lane byte offset) to 1 KiB of LDS

@@ -16,6 +16,7 @@ using CfgSuffix = PipeCfg<4, 5, 1, true>;
 __global__ void __launch_bounds__(256, 2) __attribute__((amdgpu_num_vgpr(120))) attn_duo_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   clock_begin(p.clock);
+  if (append_wg(p)) return;
   attn_pipeline<Cfg>(p, smem);
 }
 
@@ -23,6 +24,7 @@ __global__ void __launch_bounds__(256, 2) __attribute__((amdgpu_num_vgpr(120))) 
 __global__ void __launch_bounds__(256, 2) __attribute__((amdgpu_num_vgpr(120))) attn_duo_suffix_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   clock_begin(p.clock);
+  if (append_wg(p)) return;
   attn_pipeline<CfgSuffix>(p, smem);
 }
 
@@ -42,7 +44,7 @@ hipError_t attn_duo_prepare() {
 hipError_t launch_attn_duo(const AttnParams& p, bool one_tile, hipStream_t stream) {
   if (p.n_items <= 0) return hipSuccess;
   const unsigned grid = (unsigned)p.n_items * (unsigned)(p.n_q_heads / p.heads_per_wg);
-  hipLaunchKernelGGL(p.k_suffix && !one_tile ? duo::attn_duo_suffix_kernel : duo::attn_duo_kernel, dim3(grid), dim3(256), duo::Cfg::LDS_BYTES, stream, p);
+  hipLaunchKernelGGL(p.k_suffix && !one_tile ? duo::attn_duo_suffix_kernel : duo::attn_duo_kernel, dim3(grid + attn::append_wgs(p)), dim3(256), duo::Cfg::LDS_BYTES, stream, p);
   return hipGetLastError();
 }
 

@@ -16,6 +16,7 @@ using Cfg = PipeCfg<4, 8, 2>;
 __global__ void __launch_bounds__(256, 1) __attribute__((amdgpu_num_vgpr(240))) attn_pipe_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   clock_begin(p.clock);
+  if (append_wg(p)) return;
   attn_pipeline<Cfg>(p, smem);
 }
 
@@ -143,7 +144,7 @@ hipError_t attn_pipe_prepare() {
 hipError_t launch_attn_pipe(const AttnParams& p, hipStream_t stream) {
   if (p.n_items <= 0) return hipSuccess;
   const unsigned grid = (unsigned)p.n_items * (unsigned)(p.n_q_heads / p.heads_per_wg);
-  hipLaunchKernelGGL(pipe::attn_pipe_kernel, dim3(grid), dim3(64 * pipe::Cfg::NW), pipe::Cfg::LDS_BYTES, stream, p);
+  hipLaunchKernelGGL(pipe::attn_pipe_kernel, dim3(grid + attn::append_wgs(p)), dim3(64 * pipe::Cfg::NW), pipe::Cfg::LDS_BYTES, stream, p);
   return hipGetLastError();
 }
 

@@ -252,11 +252,12 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
   auto fetch_off = [&](int j) -> int64_t { return boffs[jb + j]; };
   // Where the launch takes the suffix along, its rows are read from the caller's arrays: a 16-key block lies wholly in the
   // prefix or wholly in the suffix.  The first tile of a suffix meets such blocks on its diagonal only, later ones (SFX) in
-  // the pipelined part as well; their loop with ring slots known at compile time stays within the prefix.
+  // the pipelined part as well.  There the turns within the prefix come first, those that choose an address after them: 4096+700
+  // tokens 55.0 us a call, with the choice in every turn 58.5; 448+400 13.8, with run-time ring slots outside the prefix 15.6.
   constexpr bool SFX = Cfg_::SFX;
   typedef const __attribute__((address_space(4))) AttnParams* const_paramsp;
   const int p_blk = P / kBlockTokens;
-  const int n_pool = SFX ? max(0, min(n_pipe, p_blk / 2 - jb)) : n_pipe;
+  const int n_pool = SFX ? max(0, min(n_pipe, p_blk / 2 - jb)) : n_pipe;     // pipelined sub-tiles that lie in the prefix
   // Addresses of the request's suffix block 0 in the caller's arrays, as bases for voff_k and voff_v
   struct SuffixBases {
     const unsigned char *k, *v;
@@ -265,13 +266,14 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
     const int64_t off = (int64_t)rd.q_off * row_b;
     return {(const unsigned char*)k + off, (const unsigned char*)v + off - half_b};
   };
-  // K (V) of pipelined sub-tile j: base for voff_k (voff_v)
-  auto kv_base = [&](int j, const unsigned char* sfx) -> const unsigned char* {
+  // K (V) of pipelined sub-tile j, at offset off of the pool: base for voff_k (voff_v)
+  auto kv_base = [&](int j, int64_t off, const unsigned char* sfx) -> const unsigned char* {
     if constexpr (SFX) {
       const int sfx_blk = 2 * (jb + j) + wblk - p_blk;
-      if (sfx_blk >= 0) return sfx + (int64_t)sfx_blk * half_b;
+      const bool in_sfx = sfx_blk >= 0;
+      return (in_sfx ? sfx : pool) + (in_sfx ? (int64_t)sfx_blk * half_b : off);
     }
-    return pool + fetch_off(j);
+    return pool + off;
   };
   // request I of a step: the NI of a K sub-tile, then the NI of a V sub-tile, into their ring slots
   auto request_m0 = [&](auto kslot, auto vslot, auto idx) {
@@ -512,7 +514,8 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
   const SuffixBases sfx0 = suffix_bases(p.k_suffix, p.v_suffix);
   auto request_k = [&](auto j) {
     constexpr int J = decltype(j)::value;
-    const unsigned char* base = kv_base(min(J, n_pipe - 1), sfx0.k);
+    const int sub = min(J, n_pipe - 1);
+    const unsigned char* base = kv_base(sub, fetch_off(sub), sfx0.k);
     static_for<0, NI>([&](auto idx) {
       request_m0(Tag<J % RING>{}, Tag<0>{}, idx);
       asm volatile("s_nop 0");
@@ -521,7 +524,8 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
   };
   auto request_v = [&](auto j) {
     constexpr int J = decltype(j)::value;
-    const unsigned char* base = kv_base(min(J, n_pipe - 1), sfx0.v);
+    const int sub = min(J, n_pipe - 1);
+    const unsigned char* base = kv_base(sub, fetch_off(sub), sfx0.v);
     static_for<NI, 2 * NI>([&](auto idx) {
       request_m0(Tag<0>{}, Tag<J % RING>{}, idx);
       asm volatile("s_nop 0");
@@ -574,33 +578,40 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
       if (t + 2 < n_pipe) {
         static_for<0, PD>([&](auto idx) { pre[decltype(idx)::value] = load_opnd(idx, Tag<2>{}, Tag<0>{}); });
         constexpr int U = Cfg_::UNROLL;
-        // a turn asks for sub-tiles up to t + KA + U - 1, past the last one for that one again
-        const int n_turns = !SFX || n_pool == n_pipe ? n_pipe - 1 : min(n_pipe - 1, n_pool - KA);
-        if (t + U <= n_turns) {
+        const_paramsp ps = (const_paramsp)__builtin_amdgcn_kernarg_segment_ptr();
+        const SuffixBases sfx = suffix_bases(ps->k_suffix, ps->v_suffix);
+        if (t + U < n_pipe) {
           // offsets of sub-tiles t + VA .. t + KA + RING - 1
           int64_t off_cur[U + DV], off_nxt[U];
 #pragma unroll
           for (int i = 0; i < U + DV; i++) off_cur[i] = fetch_off(min(t + VA + i, n_pipe - 1));
-          for (; t + U <= n_turns; t += U) {
+          auto turns = [&](auto sfx_tag, int end) {
+            for (; t + U <= end; t += U) {
 #pragma unroll
-            for (int i = 0; i < U; i++) off_nxt[i] = fetch_off(min(t + KA + U + i, n_pipe - 1));
-            static_for<0, U>([&](auto h) {
-              constexpr int H = decltype(h)::value;
-              step(Tag<(H + 1) & 1>{}, [](auto d) { return Tag<(H + 1 + decltype(d)::value + RING) % RING>{}; }, pool + off_cur[H + DV], pool + off_cur[H]);
-            });
+              for (int i = 0; i < U; i++) off_nxt[i] = fetch_off(min(t + KA + U + i, n_pipe - 1));
+              static_for<0, U>([&](auto h) {
+                constexpr int H = decltype(h)::value;
+                auto base = [&](int j, int64_t off, const unsigned char* s) {
+                  if constexpr (decltype(sfx_tag)::value != 0) return kv_base(min(j, n_pipe - 1), off, s);
+                  else return pool + off;
+                };
+                step(Tag<(H + 1) & 1>{}, [](auto d) { return Tag<(H + 1 + decltype(d)::value + RING) % RING>{}; },
+                     base(t + H + KA, off_cur[H + DV], sfx.k), base(t + H + VA, off_cur[H], sfx.v));
+              });
 #pragma unroll
-            for (int i = 0; i < DV; i++) off_cur[i] = off_cur[U + i];
+              for (int i = 0; i < DV; i++) off_cur[i] = off_cur[U + i];
 #pragma unroll
-            for (int i = 0; i < U; i++) off_cur[DV + i] = off_nxt[i];
-          }
+              for (int i = 0; i < U; i++) off_cur[DV + i] = off_nxt[i];
+            }
+          };
+          // a turn asks for sub-tiles up to t + KA + U - 1, past the last one for that one again
+          turns(Tag<0>{}, !SFX || n_pool == n_pipe ? n_pipe - 1 : min(n_pipe - 1, n_pool - KA));
+          if constexpr (SFX) turns(Tag<1>{}, n_pipe - 1);
         }
         // pairs of steps, ring slots at run time
-        const_paramsp ps = (const_paramsp)__builtin_amdgcn_kernarg_segment_ptr();
-        if constexpr (SFX) asm volatile("" : "+s"(ps));   // loaded again: no scalar registers hold them through the loop above
-        const SuffixBases sfx = suffix_bases(ps->k_suffix, ps->v_suffix);
         for (; t + 2 < n_pipe; t += 2) {
-          const unsigned char *k0 = kv_base(min(t + KA, n_pipe - 1), sfx.k), *k1 = kv_base(min(t + 1 + KA, n_pipe - 1), sfx.k);
-          const unsigned char *v0 = kv_base(min(t + VA, n_pipe - 1), sfx.v), *v1 = kv_base(min(t + 1 + VA, n_pipe - 1), sfx.v);
+          auto base = [&](int j, const unsigned char* s) { return kv_base(min(j, n_pipe - 1), fetch_off(min(j, n_pipe - 1)), s); };
+          const unsigned char *k0 = base(t + KA, sfx.k), *k1 = base(t + 1 + KA, sfx.k), *v0 = base(t + VA, sfx.v), *v1 = base(t + 1 + VA, sfx.v);
           step(Tag<1>{}, [&](auto d) -> int { return ring_slot(t + decltype(d)::value); }, k0, v0);
           step(Tag<0>{}, [&](auto d) -> int { return ring_slot(t + 1 + decltype(d)::value); }, k1, v1);
         }
@@ -686,12 +697,6 @@ __device__ __forceinline__ void attn_pipeline(const AttnParams& p, unsigned char
       });
     }
   }
-
-  // ---- suffix rows of the tile -> pool: once per KV head, by the workgroup of the tile's first piece (the last one has the
-  // diagonal, up to nine sub-tiles) or, for small tiles, of the last one (which is the shorter)
-  if (ks && (HB == 2 ? jb == 0 : wi.sub_end * kSK >= min(ctx_len, P + q_base + TQ)) && hg * HW % (Hq / Hkv) == 0)
-    append_rows<64 * NW>(ks, vs, (unsigned char*)const_cast<void*>(pe->pool_layer), pe->tables + rd.table_off, rd, Hkv, kv, q_base,
-                         min(TQ, S - q_base), tid);
 
   // ---- results: of a cut tile's piece the unnormalised O, the reference (exponent units) and the row sum, else the output
   acc_ready<ACC>(o);

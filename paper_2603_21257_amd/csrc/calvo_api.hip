@@ -1289,12 +1289,6 @@ hipError_t launch_attn(const AttnPlan& ap, const AttnParams& p, hipStream_t stre
   return ap.variant == kAttnDuo ? launch_attn_duo(p, ap.longest <= ap.tile_tokens, stream) : launch_attn_pipe(p, stream);
 }
 
-// Longest suffix whose rows a launch of small tiles takes along.  The append launch costs 2.4 us of host time and 2 to 4 us of
-// device time in front of the attention; against it, sub-tiles of the suffix run in the loop with run-time ring slots.  us a
-// call, append launch / along, three callers (one caller): 448+66 tokens 11.2 / 8.2 (17.3 / 17.1), 2048+209 22.9 / 21.9
-// (28.1 / 27.7), 1024+350 20.5 / 20.2 (28.2 / 28.4), 2048+400 28.1 / 27.5 (34.9 / 34.6), 2048+512 31.0 / 31.1 (37.4 / 38.9),
-// 1024+769,1360+200 29.7 / 30.9; 16Q/2KV 1024+512 22.6 / 19.9; 0+666,0+125 16.1 / 14.4, 0+1024 20.4 / 19.6, 0+2000 39.0 / 41.8.
-constexpr int kAlongTokens = 400;
 // Queues the suffix append and the attention of one layer on the compute stream.  d_att: the device
 // copy of ap.blob.  ready: NULL = the layer's own loading state decides what the stream waits for.
 int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, const void* v_suffix, void* out, float scale,
@@ -1318,6 +1312,11 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
   // cached prefix has slots that another request of the call appends to: all rows are stored first there.  So they are where
   // the output goes over the suffix rows (a workgroup that is done would overwrite what others still read) and where
   // they lie in the pool.
+  // Small tiles take suffixes of any length along, the 64-row kernel those of one tile.  The append launch costs 2.4 us of host time
+  // and 2 to 4 us of device time in front of the attention.  us a call, append launch / along, three callers (one caller): 448+40
+  // tokens 10.3 / 9.4 (15.6 / 13.6), 448+400 15.4 / 13.8 (20.6 / 19.4), 1024+1000 30.5 / 29.8 (37.8 / 35.5), 0+2000 37.4 / 37.0
+  // (46.3 / 42.4), 4096+700 56.2 / 54.9 (69.3 / 67.2); 64-row kernel, several tiles: 4096+1000 69.7 / 71.1 (82.1 / 80.1), 16384+2048
+  // 421.6 / 425.1 (438.8 / 435.3), 0+4000 114.4 / 119.7 (119.9 / 121.2).
   const size_t row_b = (size_t)ap.total * cf.head_dim * c->elt;
   auto in = [&](const void* sfx, const void* at, size_t bytes) {
     return (uintptr_t)sfx < (uintptr_t)at + bytes && (uintptr_t)at < (uintptr_t)sfx + row_b * cf.n_kv_heads;
@@ -1325,7 +1324,7 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
   auto in_the_way = [&](const void* sfx) { return in(sfx, out, row_b * cf.n_q_heads) || in(sfx, pool_layer, (size_t)c->layer_bytes); };
   const bool along = k_suffix && ap.apart && !in_the_way(k_suffix) && !in_the_way(v_suffix);
   const bool rows_append = !ap.mfma && along;
-  const bool tile_append = ap.mfma && along && !ap.chunked && ap.longest <= (ap.variant == kAttnDuo ? kAlongTokens : ap.tile_tokens);
+  const bool tile_append = ap.mfma && along && !ap.chunked && (ap.variant == kAttnDuo || ap.longest <= ap.tile_tokens);
   if (k_suffix && !rows_append && !tile_append) {
     AppendParams app{};
     app.k_suffix = k_suffix; app.v_suffix = v_suffix; app.pool_layer = pool_layer;
@@ -1343,6 +1342,7 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
   p.row_blocks_per_wg = attn_mfma_row_blocks(ap.variant);
   p.scale = scale > 0.f ? scale : 1.0f / sqrtf((float)cf.head_dim);
   p.clock = {c->d_clock + kClockWords * (size_t)layer, 1};
+  p.n_reqs = ap.n_reqs; p.total_tokens = ap.total;
   if (ap.mfma) {
     p.part_o = part_o;
     p.part_ml = part_ml;
@@ -1360,6 +1360,7 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
         }
         if (groups[g].empty()) continue;
         p.n_items = (int32_t)groups[g].size();
+        p.attn_wgs = p.n_items * (cf.n_q_heads / ap.HW);
         p.item_index = d_att + ap.lay.group_off[g];
         HIP_TRY(launch_attn(ap, p, c->s_compute));
         p.clock.starts = 0;
@@ -1367,6 +1368,7 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
       p.item_index = nullptr;
     } else {
       p.n_items = (int32_t)ap.plan.items.size();
+      p.attn_wgs = p.n_items * (cf.n_q_heads / ap.HW);
       HIP_TRY(launch_attn(ap, p, c->s_compute));
     }
     HIP_TRY(launch_merge_splits(p, d_att + ap.lay.split_off, (int)ap.plan.split_tiles.size(), c->s_compute));

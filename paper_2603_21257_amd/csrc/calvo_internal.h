@@ -65,6 +65,8 @@ struct AttnParams {
   const void* k_suffix;
   const void* v_suffix;
   LaunchClock clock;
+  int32_t n_reqs, total_tokens;
+  int32_t attn_wgs;         // workgroups of the grid that work on tiles; those behind them append the suffix rows
 };
 
 struct AppendParams {

@@ -7,7 +7,7 @@
 // PCIe / HBM read stream is sequential; every lane keeps four loads in flight.
 // A few workgroups saturate the host link, so the grid is kept small and the
 // remaining compute units stay free for attention.
-#include "calvo_internal.h"
+#include "attn_common.h"
 
 namespace calvo {
 
@@ -108,27 +108,7 @@ hipError_t launch_clock_out(const unsigned long long* words, unsigned long long*
   return hipGetLastError();
 }
 
-// Suffix token i of request r sits at absolute position P_r + i: slot table_r[pos / 16],
-// row pos % 16 of the K half and of the V half.  One lane per 16-byte chunk of a row.
-__global__ void __launch_bounds__(256) suffix_append_kernel(AppendParams p) {
-  const int64_t n = (int64_t)p.total_tokens * p.row_chunks;
-  const int64_t half_chunks = (int64_t)kBlockTokens * p.row_chunks;   // one K (or V) half of a block
-  const u32x4* ks = (const u32x4*)p.k_suffix;
-  const u32x4* vs = (const u32x4*)p.v_suffix;
-  u32x4* pool = (u32x4*)p.pool_layer;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const int32_t tok = (int32_t)(i / p.row_chunks);
-    const int32_t c = (int32_t)(i - (int64_t)tok * p.row_chunks);
-    int r = 0;
-    while (r + 1 < p.n_reqs && tok >= p.reqs[r + 1].q_off) r++;
-    const ReqDesc rd = p.reqs[r];
-    const int32_t pos = rd.prefix_len + (tok - rd.q_off);
-    const int64_t slot = p.tables[rd.table_off + pos / kBlockTokens];
-    const int64_t base = slot * 2 * half_chunks + (int64_t)(pos % kBlockTokens) * p.row_chunks + c;
-    pool[base] = ks[i];
-    pool[base + half_chunks] = vs[i];
-  }
-}
+__global__ void __launch_bounds__(256) suffix_append_kernel(AppendParams p) { attn::append_suffix(p, blockIdx.x, gridDim.x, threadIdx.x); }
 
 hipError_t launch_suffix_append(const AppendParams& p, hipStream_t stream) {
   const int64_t n = (int64_t)p.total_tokens * p.row_chunks;

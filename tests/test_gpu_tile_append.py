@@ -1,5 +1,5 @@
 """Suffixes whose rows the pipelined kernels read from the caller's arrays and store to the pool themselves: one tile, and in
-small tiles up to 400 tokens, also of several requests.  Lengths around a block, a 32-key sub-tile, the tile and that line; odd
+small tiles any length, also of several requests.  Lengths around a block, a 32-key sub-tile, the tile and 400 tokens; odd
 and even prefix block counts (the first suffix block shares a sub-tile with the prefix or not); groups with one, two and several
 head groups per KV head; cut contexts; both workgroup shapes; without suffix arrays the pool's rows are used."""
 import pytest
@@ -47,6 +47,17 @@ def test_several_tiles(heads, P, S, pieces, monkeypatch):
     if pieces:
         monkeypatch.setenv("CALVO_ATTN_SPLITS", str(pieces))
     check(wl.Shape(1, *heads, 128, "bf16", (P + S) // 16 + 9), [(P, S)], seed=P + S + pieces)
+
+
+@pytest.mark.parametrize("heads", [(8, 2), (5, 1), (16, 8)])
+@pytest.mark.parametrize("lens", [[(0, 1100)], [(448, 607)], [(1040, 700)], [(2064, 530)], [(0, 600), (528, 450), (64, 3)]])
+@pytest.mark.parametrize("pieces", [0, 3])
+def test_long_suffixes_in_small_tiles(heads, lens, pieces, monkeypatch):
+    """Turns of the loop within the prefix, across its end and within the suffix."""
+    monkeypatch.setenv("CALVO_ATTN_VARIANT", "4")
+    if pieces:
+        monkeypatch.setenv("CALVO_ATTN_SPLITS", str(pieces))
+    check(wl.Shape(1, *heads, 128, "bf16", sum((p + s) // 16 + 1 for p, s in lens) + 9), lens, seed=lens[0][1] + pieces)
 
 
 @pytest.mark.parametrize("lens,shared", [([(64, 1), (0, 90), (272, 33), (16, 0)], 0), ([(160, 70), (112, 400), (96, 17)], 5), ([(48, 401), (48, 2)], 0)])
