@@ -193,17 +193,20 @@ std::vector<PlanTile> plan_row_tiles(const int32_t* prefix_blocks, const int32_t
 
 // Packed-rows kernel, in tenths of a microsecond: start and end of a workgroup (a merge launch costs as much), and 32 keys for one wave's
 // rows while the other waves of its SIMD are at work (measured per element type and padded head width).
-// bf16 has a tiling of twice the rows, which reads K and V half as often: with the other one a workgroup waits for them (D = 64,
+// bf16, and fp32 above 128-wide heads, have a tiling of twice the rows, which reads K and V half as often: with the other one a workgroup waits for them (D = 64,
 // 8192+512 tokens, 32Q/8KV: 96 us a call, 74 without the requests for K, 95 with a third of the products for the weights; 72 with twice
 // the rows).  A step of twice the rows costs 1.0 (D = 256: one wave of a SIMD either way) to 1.8 as much.  The replay of both
 // launches decides.  us a call, three callers, 32Q/8KV, smaller / larger tiling, D = 64, 96, 256:
 //   2048+64    11.5 / 13.7   16.1 / 16.8   26.8 / 22.2          2048+256   16.6 / 19.8   22.8 / 25.6   83.9 / 46.5
 //   8192+128   28.5 / 25.6   41.4 / 38.4   147.4 / 83.2         0+512      12.0 / 10.5   16.2 / 12.7   37.2 / 25.9
 //   5008+300   46.4 / 41.3   71.4 / 59.5   241.2 / 148.3        512+400 (8Q/8KV)   7.7 / 10.1   10.1 / 16.4   16.9 / 17.3
-bool attn_rows_has_large(bool f32) { return !f32; }
+// fp32, D = 256 (one caller): 2048+256 165.5 / 149.9 (168.1 / 155.3), 4096+300 16Q/4KV 227.1 / 200.9 (232.2 / 208.5), 2048+64 62.8 / 53.9
+// (52.3 / 57.1), 1024+60 8Q/2KV 18.9 / 21.2; up to D = 128 twice the rows gain nothing (matrix pipes): 8192+256, D = 64 136 / 141.
+bool attn_rows_has_large(bool f32, int head_dim) { return !f32 || head_dim > 128; }
 
 RowsShape attn_rows_shape(bool f32, int head_dim, bool large) {
-  if (f32) return {head_dim <= 128 ? 32 : 16, head_dim <= 64 ? 23 : head_dim <= 128 ? 48 : 64, 60, 1};
+  if (f32 && head_dim <= 128) return {32, head_dim <= 64 ? 23 : 48, 60, 1};
+  if (f32) return large ? RowsShape{32, 78, 90, 2} : RowsShape{16, 43, 60, 1};
   if (head_dim <= 64) return large ? RowsShape{64, 10, 65, 2} : RowsShape{32, 6, 60, 1};
   if (head_dim <= 128) return large ? RowsShape{64, 16, 65, 2} : RowsShape{32, 9, 60, 1};
   return large ? RowsShape{32, 22, 90, 2} : RowsShape{16, 21, 60, 1};
@@ -219,7 +222,7 @@ RowsPlan plan_rows(bool f32, int head_dim, const int32_t* prefix_blocks, const i
   RowsPlan best;
   double best_time = 0.;
   for (const bool large : {false, true}) {
-    if (large && (!attn_rows_has_large(f32) || (e && e[0] == '1'))) break;
+    if (large && (!attn_rows_has_large(f32, head_dim) || (e && e[0] == '1'))) break;
     RowsPlan p;
     p.large = large;
     p.shape = attn_rows_shape(f32, head_dim, large);

@@ -83,7 +83,7 @@ struct RowsShape {
   int tile_rows, step_cost, fill;
   int slots;          // partial-result slots (32 rows of 128 floats) of a work item and KV head
 };
-bool attn_rows_has_large(bool f32);
+bool attn_rows_has_large(bool f32, int head_dim);
 RowsShape attn_rows_shape(bool f32, int head_dim, bool large);
 
 // The tiling of a batch, its tiles and the pieces that the longest is asked to be cut into. 

@@ -740,8 +740,8 @@ auto with_cfg(int dtype, int head_dim, int tile_rows, F&& f) {
     if (head_dim < 64) return f(RowsCfg<float, 64, 2, 2, 8, false>{});
     if (head_dim == 128) return f(RowsCfg<float, 128, 2, 1, 4, true>{});
     if (head_dim < 128) return f(RowsCfg<float, 128, 2, 1, 4, false>{});
-    if (head_dim == 256) return f(RowsCfg<float, 256, 1, 1, 4, true>{});
-    return f(RowsCfg<float, 256, 1, 1, 4, false>{});
+    if (head_dim == 256) return tile_rows == 32 ? f(RowsCfg<float, 256, 2, 1, 4, true>{}) : f(RowsCfg<float, 256, 1, 1, 4, true>{});
+    return tile_rows == 32 ? f(RowsCfg<float, 256, 2, 1, 4, false>{}) : f(RowsCfg<float, 256, 1, 1, 4, false>{});
   }
   if (head_dim == 64) return tile_rows == 64 ? f(RowsCfg<B16, 64, 4, 2, 8, true>{}) : f(RowsCfg<B16, 64, 2, 2, 8, true>{});
   if (head_dim < 64) return tile_rows == 64 ? f(RowsCfg<B16, 64, 4, 2, 8, false>{}) : f(RowsCfg<B16, 64, 2, 2, 8, false>{});

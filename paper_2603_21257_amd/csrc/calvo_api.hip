@@ -591,7 +591,7 @@ int calvo_create(const calvo_config* cfg, calvo_ctx** out) {
   if (!(cfg->dtype == CALVO_BF16 && cfg->head_dim == 128)) {
     const bool f32 = cfg->dtype == CALVO_F32;
     hipError_t e = attn_rows_prepare(cfg->dtype, cfg->head_dim, attn_rows_shape(f32, cfg->head_dim, false).tile_rows);
-    if (e == hipSuccess && attn_rows_has_large(f32))
+    if (e == hipSuccess && attn_rows_has_large(f32, cfg->head_dim))
       e = attn_rows_prepare(cfg->dtype, cfg->head_dim, attn_rows_shape(f32, cfg->head_dim, true).tile_rows);
     if (e != hipSuccess) { const int prc = fail_hip(e, "hipFuncSetAttribute(dynamic LDS)"); destroy_partial(c); return prc; }
   }

@@ -54,14 +54,15 @@ def test_cut_contexts(dtype, D, pieces, monkeypatch):
 
 
 @pytest.mark.parametrize("pieces", [0, 3])
-@pytest.mark.parametrize("D,hq,hkv", [(8, 1, 1), (40, 6, 2), (64, 8, 2), (64, 34, 2), (72, 5, 1), (120, 6, 2), (136, 6, 2), (256, 8, 8), (256, 10, 2)])
+@pytest.mark.parametrize("D,hq,hkv", [(-136, 6, 2), (-256, 10, 2), (8, 1, 1), (40, 6, 2), (64, 8, 2), (64, 34, 2), (72, 5, 1), (120, 6, 2), (136, 6, 2), (256, 8, 8), (256, 10, 2)])
 @pytest.mark.parametrize("lens", [[(0, 1)], [(16, 7)], [(32, 15), (496, 33)], [(2064, 130), (0, 64), (48, 1)]])
 def test_large_tiling(D, hq, hkv, lens, pieces, monkeypatch):
-    """The tiling of twice the rows, which short suffixes get in no other way: rows around a tile, one step and many per wave."""
+    """The tiling of twice the rows, which short suffixes get in no other way: rows around a tile, one step and many per wave.
+    Head widths below 0: fp32."""
     monkeypatch.setenv("CALVO_ROWS_TILE", "2")
     if pieces:
         monkeypatch.setenv("CALVO_ATTN_SPLITS", str(pieces))
-    check(wl.make_custom(wl.Shape(1, hq, hkv, D, "bf16", slots(lens)), lens, seed=D + hq + pieces))
+    check(wl.make_custom(wl.Shape(1, hq, hkv, abs(D), "f32" if D < 0 else "bf16", slots(lens)), lens, seed=abs(D) + hq + pieces))
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
