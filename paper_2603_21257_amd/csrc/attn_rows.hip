@@ -45,6 +45,8 @@
 #include "attn_common.h"
 #include "../../include/calvo.h"
 
+#include <cfloat>
+
 namespace calvo {
 namespace rows {
 
@@ -239,6 +241,12 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
   for (int qb = 0; qb < NQB; qb++) { nref[qb] = 0.f; bound[qb] = -INFINITY; l[qb] = 0.f; }
   const float c2 = p.scale * 1.4426950408889634f, inv_c2 = 1.f / c2;
   auto reference = [&](int qb) { return bound[qb] == -INFINITY ? -INFINITY : -nref[qb]; };
+  // The score 16 above a reference.  Product and 1 / c2 are rounded: a 2^21st is taken off, so that no score above it stays below
+  // the bound (at 2^30 exponent units its weight would not be finite), and a reference of finite scores keeps a finite bound.
+  auto score_above = [&](float ref) {
+    const float b = fminf((ref + 16.f) * inv_c2, FLT_MAX);
+    return fmaxf(b - 0x1p-21f * __builtin_fabsf(b), -FLT_MAX);
+  };
 
   // Weights of a row block as three bf16 terms: the upper half cut off, which leaves an exact rest, twice.  (Of a pair one
   // instruction packs them, two each clear and subtract; rounding the terms takes two more.)
@@ -338,7 +346,7 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
       for (int qb = 0; qb < NQB; qb++) {
         const float old = reference(qb), mn = fmaxf(old, quad_max(mx[qb]) * c2);
         nref[qb] = mn == -INFINITY ? 0.f : -mn;                // a row that has seen no key yet: all its weights are 0
-        bound[qb] = (mn + 16.f) * inv_c2;
+        bound[qb] = mn == -INFINITY ? -INFINITY : score_above(mn);
         const float a = __builtin_amdgcn_exp2f(old + nref[qb]);
         l[qb] *= a;
 #pragma unroll

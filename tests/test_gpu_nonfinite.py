@@ -81,6 +81,29 @@ def test_large_v_under_rising_scores(dtype, D, value, columns, pieces, monkeypat
     assert np.isfinite(g).all() and d.max() <= tmx and d.mean() <= tmean, (d.max(), d.mean())
 
 
+@pytest.mark.parametrize("pieces", [1, 3])
+def test_next_score_in_32_bits_far_below_zero(pieces, monkeypatch):
+    """The scores of later keys are the next value in 32 bits above the earlier ones and 131 powers of two higher.  The score at
+    which the softmax reference moves is a product that rounds: rounded up to theirs, the weights against the earlier
+    reference would be finite and their sum not (V is so small that the sums of it are)."""
+    monkeypatch.setenv("CALVO_ATTN_SPLITS", str(pieces))
+    P, S, D = 1024, 20, 128
+    w = wl.make_custom(wl.Shape(1, 4, 2, D, "f32", (P + S) // 16 + 9), [(P, S)], seed=905)
+    w.q[...] = 0.0
+    w.q[..., 0] = 1.0
+    first = w.requests[0].host_block_start
+    kv = w.host_kv.reshape(1, w.host_blocks, 2, 16, 2, D)[0, first:first + P // 16]
+    kv[:16, 0, :, :, 0] = -16660231168.0
+    kv[16:, 0, :, :, 0] = w.k_suffix[..., 0] = -16660230144.0
+    kv[:, 1] *= np.float32(2.0 ** -30)
+    w.v_suffix *= np.float32(2.0 ** -30)
+    _, got = hh.run_hip(w)
+    _, want = hh.run_oracle(w)
+    d = np.abs(got.astype(np.float64) - want) * 2.0 ** 30
+    tmx, tmean = hh.TOL["f32"]
+    assert np.isfinite(got).all() and d.max() <= tmx and d.mean() <= tmean, (d.max(), d.mean())
+
+
 @pytest.mark.parametrize("variant", ["3", "4"])
 @pytest.mark.parametrize("value,columns", [(1e35, slice(None)), (1e33, slice(0, 1))])
 @pytest.mark.parametrize("P,S,rise", [
