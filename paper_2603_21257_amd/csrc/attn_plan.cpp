@@ -104,15 +104,17 @@ int plan_piece_len(int n_sub, int n_max, int want, const PlanParams& p) {
 // (64Q/8KV, 224 uncut) 38.9 uncut, 49.1 in two.
 constexpr double kAlone = 0.7;
 
-int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots, double* time) {
-  if (time) *time = 0.;
+int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots, PlanCost* found) {
+  if (found) *found = {};
   if (p.force_splits) return p.force_splits;
   const int64_t wgs = (int64_t)tiles.size() * p.n_head_groups;
   if (wgs <= 0) return 1;
   auto cost_of = [&](int64_t subs) { return (p.step_cost ? (subs + 3) / 4 * p.step_cost : subs) + p.split_fill; };
   if (wgs > 16 * (int64_t)p.wg_slots) {                         // many rounds: the last one hardly matters
-    if (time)
-      for (const PlanTile& t : tiles) *time += 3. * (double)(cost_of(t.n_sub) * p.n_head_groups) / p.wg_slots;
+    if (found) {
+      for (const PlanTile& t : tiles) found->span += (double)(cost_of(t.n_sub) * p.n_head_groups) / p.wg_slots;
+      found->load = found->span;
+    }
     return 1;
   }
   static const std::vector<int> all = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 20, 24, 32, 48, 64};
@@ -159,7 +161,7 @@ int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t
     if (n == 1 || span < best * 0.98) {            // a cut has to win by 2 % over what is chosen so far
       best = span;
       want = n;
-      if (time) *time = 2. * span + (double)work / p.wg_slots + (cut ? p.split_fill : 0);
+      if (found) *found = {span, (double)work / p.wg_slots + (cut ? p.split_fill : 0)};
     }
     if (!cut && n > 1) break;                       // longer cuts are refused by split_min: nothing changes
   }
@@ -196,7 +198,12 @@ std::vector<PlanTile> plan_row_tiles(const int32_t* prefix_blocks, const int32_t
 // bf16, and fp32 above 128-wide heads, have a tiling of twice the rows, which reads K and V half as often: with the other one a workgroup waits for them (D = 64,
 // 8192+512 tokens, 32Q/8KV: 96 us a call, 74 without the requests for K, 95 with a third of the products for the weights; 72 with twice
 // the rows).  A step of twice the rows costs 1.0 (D = 256: one wave of a SIMD either way) to 1.8 as much.  The replay of both
-// launches decides.  us a call, three callers, 32Q/8KV, smaller / larger tiling, D = 64, 96, 256:
+// launches decides: the larger tiling where its launch is not the longer one, and twice that length and once what it keeps the chip
+// busy for come to 3 % less.  One caller waits for a longer launch, whatever it leaves free for others: D = 256, 256+150 (6Q/3KV)
+// 9.9 / 11.0 with three callers, 12.6 / 16.4 with one, D = 200, 432+31 (32Q/8KV) 10.0 / 11.1 and 13.2 / 16.7, D = 120, 0+515 (16Q/4KV)
+// 10.2 / 10.7 and 12.5 / 16.0.  Over 46 such batches the larger tiling takes 1.27 times as long with one caller and 1.02 with
+// three, over 48 whose launch it makes up to a fifth shorter 0.96 and 0.91.
+// us a call, three callers, 32Q/8KV, smaller / larger tiling, D = 64, 96, 256:
 //   2048+64    11.5 / 13.7   16.1 / 16.8   26.8 / 22.2          2048+256   16.6 / 19.8   22.8 / 25.6   83.9 / 46.5
 //   8192+128   28.5 / 25.6   41.4 / 38.4   147.4 / 83.2         0+512      12.0 / 10.5   16.2 / 12.7   37.2 / 25.9
 //   5008+300   46.4 / 41.3   71.4 / 59.5   241.2 / 148.3        512+400 (8Q/8KV)   7.7 / 10.1   10.1 / 16.4   16.9 / 17.3
@@ -220,18 +227,19 @@ RowsPlan plan_rows(bool f32, int head_dim, const int32_t* prefix_blocks, const i
                    int n_kv_heads, int n_cus, int force_splits, int64_t max_slots) {
   const char* e = getenv("CALVO_ROWS_TILE");                    // test hook: 1 or 2 forces a tiling
   RowsPlan best;
-  double best_time = 0.;
+  PlanCost best_cost;
   for (const bool large : {false, true}) {
     if (large && (!attn_rows_has_large(f32, head_dim) || (e && e[0] == '1'))) break;
     RowsPlan p;
     p.large = large;
     p.shape = attn_rows_shape(f32, head_dim, large);
     p.tiles = plan_row_tiles(prefix_blocks, suffix_lens, n_reqs, group, p.shape.tile_rows);
-    double time;
-    p.want = plan_pieces(p.tiles, rows_plan_params(p.shape, n_kv_heads, n_cus, force_splits), max_slots / p.shape.slots, &time);
-    if (!large || time < 0.97 * best_time || (e && e[0] == '2')) {
+    PlanCost cost;
+    p.want = plan_pieces(p.tiles, rows_plan_params(p.shape, n_kv_heads, n_cus, force_splits), max_slots / p.shape.slots, &cost);
+    const bool better = cost.span <= best_cost.span && 2. * cost.span + cost.load < 0.97 * (2. * best_cost.span + best_cost.load);
+    if (!large || better || (e && e[0] == '2')) {
       best = std::move(p);
-      best_time = time;
+      best_cost = cost;
     }
   }
   return best;

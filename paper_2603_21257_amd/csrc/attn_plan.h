@@ -70,9 +70,13 @@ std::vector<PlanTile> plan_tiles(const int32_t* prefix_blocks, const int32_t* su
 int plan_piece_len(int n_sub, int n_max, int want, const PlanParams& p);
 
 // pieces of the longest tile to ask for (1 = no cut), from a replay of the launch; a cut makes at most max_slots
-// (piece, head group) pairs (partial results there is room for)
-// time, if asked for: twice the length of the launch and once what it keeps the whole chip busy for, in units of split_fill
-int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots = INT64_MAX, double* time = nullptr);
+// (piece, head group) pairs (partial results there is room for).  found, if asked for: what the replay makes of them, in units
+// of split_fill; 0 where the number of pieces is forced
+struct PlanCost {
+  double span = 0.;   // length of the launch and its merge
+  double load = 0.;   // what they keep the whole chip busy for
+};
+int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots = INT64_MAX, PlanCost* found = nullptr);
 
 // work items of a whole-layer launch: every tile cut into pieces of plan_piece_len
 PlanItems plan_items(const std::vector<PlanTile>& tiles, int want, const PlanParams& p);
@@ -86,7 +90,7 @@ struct RowsShape {
 bool attn_rows_has_large(bool f32, int head_dim);
 RowsShape attn_rows_shape(bool f32, int head_dim, bool large);
 
-// The tiling of a batch, its tiles and the pieces that the longest is asked to be cut into. 
+// The tiling of a batch, its tiles and the pieces that the longest is asked to be cut into.
 struct RowsPlan {
   RowsShape shape;
   std::vector<PlanTile> tiles;
