@@ -659,8 +659,9 @@ __global__ void __launch_bounds__(64 * C::NW) attn_rows_kernel(RowsParams p) {
 }
 
 // Combines the pieces of cut tiles as merge_splits_kernel does, for this file's layout: one wave per row.
-// us a call of one caller, 8 loads behind the weights / 16 in front: fp32 1024+128, 8Q/2KV, D = 64 15.5 / 14.6, 8192+4 D = 128 26.9 / 24.4,
-// bf16 8192+20, 16Q/4KV, D = 64 17.1 / 13.0.
+// us a call of one caller, 8 loads behind the weights / in front of them, 16 at D = 64: fp32 1024+128, 8Q/2KV, D = 64 15.8 / 14.4,
+// bf16 8192+20, 16Q/4KV, D = 64 16.9 / 12.8; wider heads, where loads past the last piece are left out: fp32 8192+4, 8Q/2KV, D = 128 28.1 / 19.5,
+// bf16 8192+4, 8Q/2KV, D = 256 22.6 / 15.8 (four in front 21.1), fp32 3040+1, 16Q/4KV, D = 256 22.0 / 16.4 (20.8).
 // A row that saw no key in a piece has m = -inf, l = 0, O = 0 there and adds nothing.
 template <typename T, int DP, int ROWS>
 __global__ void __launch_bounds__(256) merge_rows_kernel(RowsParams p, const int32_t* split_tiles) {
@@ -682,11 +683,13 @@ __global__ void __launch_bounds__(256) merge_rows_kernel(RowsParams p, const int
   const float* po = p.part_o + base * DP + W * lane;
   // at most 64 pieces per tile (attn_plan.cpp): lane i holds piece i
   const f32x2 mine = lane < n ? ml[lane * step] : (f32x2){-INFINITY, 0.f};
-  constexpr int B = 16 / W;                                    // loads in flight: the first are on their way while the weights are found
+  constexpr int B = W > 2 ? 8 : 16 / W;                        // loads in flight: the first are on their way while the weights are found
   vec v[B];
+  // Past the end nothing, or (4 bytes a lane) the last piece again, which costs no more than the branch
   auto fetch = [&](int c0) {
 #pragma unroll
-    for (int i = 0; i < B; i++) v[i] = *(const vec*)(po + min(c0 + i, n - 1) * step * DP);
+    for (int i = 0; i < B; i++)
+      if (W == 1 || c0 + i < n) v[i] = *(const vec*)(po + min(c0 + i, n - 1) * step * DP);
   };
   fetch(0);
   __builtin_amdgcn_sched_barrier(0);
