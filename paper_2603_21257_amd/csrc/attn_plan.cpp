@@ -198,11 +198,12 @@ std::vector<PlanTile> plan_row_tiles(const int32_t* prefix_blocks, const int32_t
 // bf16, and fp32 above 128-wide heads, have a tiling of twice the rows, which reads K and V half as often: with the other one a workgroup waits for them (D = 64,
 // 8192+512 tokens, 32Q/8KV: 96 us a call, 74 without the requests for K, 95 with a third of the products for the weights; 72 with twice
 // the rows).  A step of twice the rows costs 1.0 (D = 256: one wave of a SIMD either way) to 1.8 as much.  The replay of both
-// launches decides: the larger tiling where its launch is not the longer one, and twice that length and once what it keeps the chip
-// busy for come to 3 % less.  One caller waits for a longer launch, whatever it leaves free for others: D = 256, 256+150 (6Q/3KV)
-// 9.9 / 11.0 with three callers, 12.6 / 16.4 with one, D = 200, 432+31 (32Q/8KV) 10.0 / 11.1 and 13.2 / 16.7, D = 120, 0+515 (16Q/4KV)
-// 10.2 / 10.7 and 12.5 / 16.0.  Over 46 such batches the larger tiling takes 1.27 times as long with one caller and 1.02 with
-// three, over 48 whose launch it makes up to a fifth shorter 0.96 and 0.91.
+// launches decides: the larger tiling where twice the length of its launch and once what it keeps the chip busy for come to 3 %
+// less - unless its launch is the longer one and the smaller tiling leaves some of the chip idle (kFull) or is a tenth shorter.  One caller waits for a
+// longer launch, whatever it leaves free for others: D = 256, 256+150 (6Q/3KV) 9.9 / 11.0 with three callers, 12.6 / 16.4 with one, D = 200,
+// 432+31 (32Q/8KV) 10.0 / 11.1 and 13.2 / 16.7, D = 120, 0+515 (16Q/4KV) 10.2 / 10.7 and 12.5 / 16.0.  Time of the larger tiling over that of
+// the smaller one with one caller and with three: over 46 such batches 1.27 and 1.02; longer launches of a full chip (46
+// batches) 1.07 and 0.90; over 48 whose launch it makes up to a fifth shorter 0.96 and 0.91.
 // us a call, three callers, 32Q/8KV, smaller / larger tiling, D = 64, 96, 256:
 //   2048+64    11.5 / 13.7   16.1 / 16.8   26.8 / 22.2          2048+256   16.6 / 19.8   22.8 / 25.6   83.9 / 46.5
 //   8192+128   28.5 / 25.6   41.4 / 38.4   147.4 / 83.2         0+512      12.0 / 10.5   16.2 / 12.7   37.2 / 25.9
@@ -223,6 +224,9 @@ PlanParams rows_plan_params(RowsShape shape, int n_kv_heads, int n_cus, int forc
   return {n_kv_heads, n_cus, 1, shape.fill, force_splits, false, shape.step_cost};
 }
 
+constexpr double kFull = 0.92;     // load of a launch that fills the chip, of its length
+constexpr double kLonger = 1.1;
+
 RowsPlan plan_rows(bool f32, int head_dim, const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int group,
                    int n_kv_heads, int n_cus, int force_splits, int64_t max_slots) {
   const char* e = getenv("CALVO_ROWS_TILE");                    // test hook: 1 or 2 forces a tiling
@@ -236,7 +240,8 @@ RowsPlan plan_rows(bool f32, int head_dim, const int32_t* prefix_blocks, const i
     p.tiles = plan_row_tiles(prefix_blocks, suffix_lens, n_reqs, group, p.shape.tile_rows);
     PlanCost cost;
     p.want = plan_pieces(p.tiles, rows_plan_params(p.shape, n_kv_heads, n_cus, force_splits), max_slots / p.shape.slots, &cost);
-    const bool better = cost.span <= best_cost.span && 2. * cost.span + cost.load < 0.97 * (2. * best_cost.span + best_cost.load);
+    const bool better = 2. * cost.span + cost.load < 0.97 * (2. * best_cost.span + best_cost.load) &&
+                        (cost.span <= best_cost.span || (best_cost.load >= kFull * best_cost.span && cost.span <= kLonger * best_cost.span));
     if (!large || better || (e && e[0] == '2')) {
       best = std::move(p);
       best_cost = cost;

@@ -64,3 +64,25 @@ SMALL = {("bf16", 64): 32, ("bf16", 120): 32, ("bf16", 200): 16, ("bf16", 256): 
 def test_a_longer_launch_is_not_taken_for_less_load(rows_plan, dtype, dim, hq, hkv, lens):
     """Few tiles over a short context: cut in the smaller tiling, or of it, the launch is a fifth shorter."""
     assert rows_plan(dtype, dim, hq, hkv, lens)["rows"] == SMALL[dtype, dim]
+
+
+@pytest.mark.parametrize("dtype,dim,hq,hkv,lens,rows", [
+    ("bf16", 64, 32, 8, [(2048, 256)], 32), ("bf16", 64, 32, 8, [(8192, 512)], 64), ("bf16", 64, 32, 8, [(0, 512)], 64),
+    ("bf16", 64, 16, 4, [(4096, 300)], 32), ("bf16", 96, 32, 8, [(8192, 128)], 64), ("bf16", 96, 8, 8, [(512, 400)], 32),
+    ("bf16", 256, 32, 8, [(2048, 256)], 32), ("bf16", 256, 8, 2, [(2048, 16)], 16), ("f32", 256, 32, 8, [(2048, 256)], 32),
+    ("f32", 256, 8, 2, [(1024, 60)], 16), ("f32", 128, 32, 8, [(8192, 512)], 32), ("f32", 64, 32, 8, [(8192, 512)], 32),
+    ("bf16", 200, 40, 8, [(240, 386), (8720, 63), (2224, 3)], 32)])            # a longer launch on a full chip
+def test_which_tiling(rows_plan, dtype, dim, hq, hkv, lens, rows):
+    assert rows_plan(dtype, dim, hq, hkv, lens)["rows"] == rows
+
+
+@pytest.mark.parametrize("dtype,dim", [("bf16", 40), ("bf16", 96), ("bf16", 256), ("f32", 64), ("f32", 256)])
+@pytest.mark.parametrize("room", [64, 512, 4096])
+def test_pieces_fit_the_room_for_partial_results(rows_plan, dtype, dim, room):
+    """A slot is 32 rows of 128 floats: 64 rows, or 32 of 256-wide heads, take two."""
+    for lens in [(512, 1)], [(8192, 20)], [(2048, 256)], [(32768, 64)], [(8192, 128), (4096, 3), (0, 70)]:
+        for hq, hkv in (8, 2), (32, 8):
+            p = rows_plan(dtype, dim, hq, hkv, lens, room=room)
+            assert p["slots"] <= room
+            rows = max(p["rows"] * (64 if dim <= 64 else 128 if dim <= 128 else 256) // 128, p["rows"]) / 32
+            assert p["slots"] % p["items"] == 0 and (p["slots"] == 0 or p["slots"] // p["items"] >= hkv * rows)
