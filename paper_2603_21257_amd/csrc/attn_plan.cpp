@@ -104,7 +104,7 @@ int plan_piece_len(int n_sub, int n_max, int want, const PlanParams& p) {
 // (64Q/8KV, 224 uncut) 38.9 uncut, 49.1 in two.
 constexpr double kAlone = 0.7;
 
-int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots, PlanCost* found) {
+int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots, PlanCost* found, double limit) {
   if (found) *found = {};
   if (p.force_splits) return p.force_splits;
   const int64_t wgs = (int64_t)tiles.size() * p.n_head_groups;
@@ -121,25 +121,27 @@ int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t
   static const std::vector<int> coarse = {1, 2, 3, 4, 5, 6, 8, 12, 16, 24, 32, 48, 64};
   const int n_max = tiles.front().n_sub;           // heaviest first
   int want = 1;
-  double best = 0;
+  double best = limit / 0.98;
+  if (found) found->span = HUGE_VAL;
   std::vector<int64_t> heap;
   for (int n : p.long_pieces ? coarse : all) {
     if (n > 1 && wgs * n > (p.step_cost ? 4 : 16) * (int64_t)p.wg_slots) break;
     bool cut = false;
-    int64_t end = 0, slots = 0, work = 0;
+    int64_t end = 0, slots = 0, work = 0, longest = 0;
     for (const PlanTile& t : tiles) {
       const int len = plan_piece_len(t.n_sub, n_max, n, p);
       const int np = (t.n_sub + len - 1) / len;
       cut |= np > 1;
       slots += (int64_t)np * p.n_head_groups;
       work += ((np - 1) * cost_of(len) + cost_of(t.n_sub - (np - 1) * len)) * p.n_head_groups;
+      longest = std::max(longest, cost_of(std::min(len, t.n_sub)));
     }
     if (n > 1 && slots > max_slots) break;
-    // no order of the pieces beats the average load: most candidates need no replay
+    // no order of the pieces beats the average load or the longest piece: most candidates need no replay
     const double step = slots <= p.alone ? kAlone : 1.;
     const double merge = (cut ? 1. : 1. - step) * p.split_fill;
-    if (n > 1 && step * (double)(work / p.wg_slots) + merge >= best * 0.98) {
-      if (!cut) break;
+    if (step * (double)std::max(work / p.wg_slots, longest) + merge >= best * 0.98) {
+      if (!cut && n > 1) break;
       continue;
     }
     heap.assign((size_t)p.wg_slots, 0);            // min-heap of the times at which workgroup slots become free
@@ -158,7 +160,7 @@ int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t
       }
     }
     const double span = step * (double)end + merge;
-    if (n == 1 || span < best * 0.98) {            // a cut has to win by 2 % over what is chosen so far
+    if (span < best * 0.98) {                      // a cut has to win by 2 % over what is chosen so far
       best = span;
       want = n;
       if (found) *found = {span, (double)work / p.wg_slots + (cut ? p.split_fill : 0)};
@@ -238,11 +240,11 @@ RowsPlan plan_rows(bool f32, int head_dim, const int32_t* prefix_blocks, const i
     p.large = large;
     p.shape = attn_rows_shape(f32, head_dim, large);
     p.tiles = plan_row_tiles(prefix_blocks, suffix_lens, n_reqs, group, p.shape.tile_rows);
+    const bool forced = !large || (e && e[0] == '2');
+    const double limit = forced ? HUGE_VAL : (best_cost.load >= kFull * best_cost.span ? kLonger : 1.) * best_cost.span + 0.5;
     PlanCost cost;
-    p.want = plan_pieces(p.tiles, rows_plan_params(p.shape, n_kv_heads, n_cus, force_splits), max_slots / p.shape.slots, &cost);
-    const bool better = 2. * cost.span + cost.load < 0.97 * (2. * best_cost.span + best_cost.load) &&
-                        (cost.span <= best_cost.span || (best_cost.load >= kFull * best_cost.span && cost.span <= kLonger * best_cost.span));
-    if (!large || better || (e && e[0] == '2')) {
+    p.want = plan_pieces(p.tiles, rows_plan_params(p.shape, n_kv_heads, n_cus, force_splits), max_slots / p.shape.slots, &cost, limit);
+    if (forced || 2. * cost.span + cost.load < 0.97 * (2. * best_cost.span + best_cost.load)) {
       best = std::move(p);
       best_cost = cost;
     }

@@ -1,6 +1,7 @@
 // Host-side planning of an attention launch: which kernel, which tiles, how many split-KV pieces.
 // No device types here: the file is shared by the HIP translation units and by plain C++.
 #pragma once
+#include <cmath>
 #include <cstdint>
 #include <vector>
 
@@ -71,12 +72,13 @@ int plan_piece_len(int n_sub, int n_max, int want, const PlanParams& p);
 
 // pieces of the longest tile to ask for (1 = no cut), from a replay of the launch; a cut makes at most max_slots
 // (piece, head group) pairs (partial results there is room for).  found, if asked for: what the replay makes of them, in units
-// of split_fill; 0 where the number of pieces is forced
+// of split_fill; 0 where the number of pieces is forced, infinite where no launch is shorter than limit
 struct PlanCost {
   double span = 0.;   // length of the launch and its merge
   double load = 0.;   // what they keep the whole chip busy for
 };
-int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots = INT64_MAX, PlanCost* found = nullptr);
+int plan_pieces(const std::vector<PlanTile>& tiles, const PlanParams& p, int64_t max_slots = INT64_MAX, PlanCost* found = nullptr,
+                double limit = HUGE_VAL);
 
 // work items of a whole-layer launch: every tile cut into pieces of plan_piece_len
 PlanItems plan_items(const std::vector<PlanTile>& tiles, int want, const PlanParams& p);
