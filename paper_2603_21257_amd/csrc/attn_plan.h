@@ -3,6 +3,7 @@
 #pragma once
 #include <cmath>
 #include <cstdint>
+#include <utility>
 #include <vector>
 
 namespace calvo {
@@ -101,6 +102,29 @@ struct RowsPlan {
 };
 RowsPlan plan_rows(bool f32, int head_dim, const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int group,
                    int n_kv_heads, int n_cus, int force_splits, int64_t max_slots);
+
+// A decision about tiling and pieces (a replay of the launch), which depends only on the batch's lengths, and the lengths that it
+// was made for: the following layers take it over.
+struct KeptPlan {
+  int want = 1;
+  bool large = false;      // packed rows: the tiling
+  // decide() sets them, unless they are those of these lengths already.  If it throws, no lengths are known.
+  template <typename F>
+  const KeptPlan& of(int variant, const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, F&& decide) {
+    std::vector<int64_t> mine;
+    mine.reserve(2 * (size_t)n_reqs + 1);
+    mine.push_back(variant);
+    for (int r = 0; r < n_reqs; r++) { mine.push_back(prefix_blocks[r]); mine.push_back(suffix_lens[r]); }
+    if (mine == key) return *this;
+    key.clear();
+    decide(*this);
+    key = std::move(mine);
+    return *this;
+  }
+
+ private:
+  std::vector<int64_t> key;
+};
 
 // the batch's tiles of tile_rows rows, heaviest first (group: query heads per KV head)
 std::vector<PlanTile> plan_row_tiles(const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int group, int tile_rows);

@@ -1130,38 +1130,28 @@ bool appends_apart(const calvo_ctx* c, const calvo_request* reqs, int n_reqs) {
   return true;
 }
 
-// The decision about tiles and pieces (a replay of the launch, attn_plan.cpp) depends only on the batch's lengths and is kept for the
-// following layers.
-bool plan_is_kept(calvo_ctx* c, int variant, const calvo_request* reqs, int n_reqs) {
-  std::vector<int64_t> key;
-  key.reserve(2 * n_reqs + 1);
-  key.push_back(variant);
-  for (int r = 0; r < n_reqs; r++) { key.push_back(reqs[r].n_prefix_blocks); key.push_back(reqs[r].suffix_len); }
-  if (key == c->plan_key) return true;
-  c->plan_key = std::move(key);
-  return false;
-}
-
 // Pieces per tile
-int kept_pieces(calvo_ctx* c, int variant, const calvo_request* reqs, int n_reqs, const std::vector<PlanTile>& tiles,
+int kept_pieces(calvo_ctx* c, int variant, const int32_t* pblocks, const int32_t* slens, int n_reqs, const std::vector<PlanTile>& tiles,
                 const PlanParams& pp, int64_t max_slots) {
   if (c->force_splits) return plan_pieces(tiles, pp);
-  if (!plan_is_kept(c, variant, reqs, n_reqs)) c->plan_want = plan_pieces(tiles, pp, max_slots);
-  return c->plan_want;
+  return c->plan.of(variant, pblocks, slens, n_reqs, [&](KeptPlan& k) { k.want = plan_pieces(tiles, pp, max_slots); }).want;
 }
 
 // The packed-rows kernel's tiles and their pieces
-RowsPlan kept_rows(calvo_ctx* c, const calvo_request* reqs, const int32_t* pblocks, const int32_t* slens, int n_reqs) {
+RowsPlan kept_rows(calvo_ctx* c, const int32_t* pblocks, const int32_t* slens, int n_reqs) {
   const bool f32 = c->cfg.dtype == CALVO_F32;
   const int hkv = c->cfg.n_kv_heads, group = c->cfg.n_q_heads / hkv, dim = c->cfg.head_dim;
-  if (!c->force_splits && plan_is_kept(c, 0, reqs, n_reqs)) {
-    RowsPlan p{attn_rows_shape(f32, dim, c->plan_large), {}, c->plan_want, c->plan_large};
+  RowsPlan p;
+  auto decide = [&](KeptPlan& k) {
+    p = plan_rows(f32, dim, pblocks, slens, n_reqs, group, hkv, c->n_cus, c->force_splits, kStaticPartSlots);
+    k.want = p.want;
+    k.large = p.large;
+  };
+  const KeptPlan& k = c->plan.of(0, pblocks, slens, n_reqs, decide);
+  if (p.tiles.empty()) {
+    p = {attn_rows_shape(f32, dim, k.large), {}, k.want, k.large};
     p.tiles = plan_row_tiles(pblocks, slens, n_reqs, group, p.shape.tile_rows);
-    return p;
   }
-  RowsPlan p = plan_rows(f32, dim, pblocks, slens, n_reqs, group, hkv, c->n_cus, c->force_splits, kStaticPartSlots);
-  c->plan_want = p.want;
-  c->plan_large = p.large;
   return p;
 }
 
@@ -1209,12 +1199,12 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
       ap.plan = plan_items_chunked(tiles, pblocks.data(), cb, nck);
     } else {
       const int64_t max_slots = rule == PlanRule::kFitted ? (int64_t)kStaticPartSlots / attn_mfma_row_blocks(ap.variant) : INT64_MAX;
-      ap.plan = plan_items(tiles, kept_pieces(c, ap.variant + 16 * (int)rule, reqs, n_reqs, tiles, pp, max_slots), pp);
+      ap.plan = plan_items(tiles, kept_pieces(c, ap.variant + 16 * (int)rule, pblocks.data(), slens.data(), n_reqs, tiles, pp, max_slots), pp);
     }
   } else {
     RowsPlan rows;
     if (rule == PlanRule::kBest) {
-      rows = kept_rows(c, reqs, pblocks.data(), slens.data(), n_reqs);
+      rows = kept_rows(c, pblocks.data(), slens.data(), n_reqs);
       const PlanParams pp = rows_plan_params(rows.shape, cf.n_kv_heads, c->n_cus, c->force_splits);
       ap.plan = plan_items(rows.tiles, rows.want, pp);
       if (ap.plan.items.size() * (size_t)cf.n_kv_heads * (size_t)rows.shape.slots > kStaticPartSlots && !ap.plan.split_tiles.empty())

@@ -70,9 +70,7 @@ struct calvo_ctx {
   int n_cus = 256;                // compute units of the device
   int clock_khz = 100000;         // rate of the counter behind d_clock
   std::shared_ptr<void> kept;     // checked and planned batch of the latest calvo_prefill_attn (KeptBatch, calvo_api.hip)
-  std::vector<int64_t> plan_key;  // lengths of the batch the cached decision belongs to
-  int plan_want = 1;
-  bool plan_large = false;         // packed rows: the tiling that went with it
+  calvo::KeptPlan plan;           // the latest decision about tiles and pieces
   float* part_o = nullptr;        // split-KV partial results (compute stream only)
   float* part_ml = nullptr;
   size_t part_slots = 0;          // capacity in (work item, head group, block of 32 rows) slots

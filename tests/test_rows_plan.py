@@ -86,3 +86,26 @@ def test_pieces_fit_the_room_for_partial_results(rows_plan, dtype, dim, room):
             assert p["slots"] <= room
             rows = max(p["rows"] * (64 if dim <= 64 else 128 if dim <= 128 else 256) // 128, p["rows"]) / 32
             assert p["slots"] % p["items"] == 0 and (p["slots"] == 0 or p["slots"] // p["items"] >= hkv * rows)
+
+
+def test_a_decision_that_fails_is_not_kept(tmp_path):
+    """Host memory that runs out while a batch is planned: the next call with its lengths decides again."""
+    exe = compiled(tmp_path, DRIVER.split("// a line")[0] + r"""
+#include <new>
+
+int main() {
+  KeptPlan k;
+  const int32_t a[] = {4, 2}, b[] = {8, 2};
+  int made = 0;
+  auto seven = [&](KeptPlan& p) { made++; p.want = 7; };
+  auto fails = [&](KeptPlan&) { throw std::bad_alloc(); };
+  if (k.of(3, a, a, 2, seven).want != 7 || k.of(3, a, a, 2, fails).want != 7 || made != 1) return 1;
+  try { k.of(3, b, a, 2, fails); return 2; } catch (const std::bad_alloc&) {}
+  k.of(3, b, a, 2, [&](KeptPlan& p) { made++; p.want = 9; });
+  if (made != 2 || k.want != 9) return 3;
+  k.of(4, b, a, 2, seven);          // another kernel
+  k.of(4, b, a, 1, seven);          // fewer requests
+  return made == 4 ? 0 : 4;
+}
+""")
+    assert subprocess.run([str(exe)]).returncode == 0
