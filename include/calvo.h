@@ -529,6 +529,10 @@ int calvo_attn_plan_items(int32_t n_q_heads, int32_t n_kv_heads, int32_t n_cus, 
  * output may be NULL.  CALVO_ENOTREADY if none was queued. */
 int calvo_attn_kernel_info(calvo_ctx* ctx, int layer, int* kernel, int* n_workgroups);
 
+/* Measurement helper: which tiling of the packed-rows kernel the most recent calvo_prefill_attn for `layer` ran in: *tile_rows =
+ * (token, query head) rows of one KV head in a tile, 0 for the other kernels.  CALVO_ENOTREADY if none was queued. */
+int calvo_attn_tile_rows(calvo_ctx* ctx, int layer, int* tile_rows);
+
 /* Measurement helper: the rate the matrix pipes of the current device sustain on bf16 MFMAs alone
  * (shape = CALVO_MFMA_16x16x32, the shape of the attention kernels, or CALVO_MFMA_32x32x16; two waves
  * per SIMD on every CU, operands in registers), for the operand data the caller supplies: operands =

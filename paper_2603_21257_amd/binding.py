@@ -23,7 +23,7 @@ CALVO_EV_QUERY, CALVO_EV_HOST_WAIT, CALVO_EV_STREAM_WAIT = 0, 1, 2
 # CALVO_LIB names another build of the library (A/B timing of two builds); default: the in-tree one
 LIB_PATH = os.environ.get("CALVO_LIB") or os.path.join(os.path.dirname(os.path.abspath(__file__)), "libcalvo.so")
 EXPORTS = ["calvo_create", "calvo_destroy", "calvo_kv_ingest", "calvo_kv_ingest_chunked", "calvo_chunk_count",
-           "calvo_chunk_event", "calvo_kv_ingest_l3", "calvo_l3_wait", "calvo_layer_event", "calvo_prefill_attn", "calvo_prefill_attn_noalloc", "calvo_batch_prepare", "calvo_batch_destroy", "calvo_prefill_attn_batch", "calvo_attn_kernel_ms", "calvo_mfma_peak", "calvo_attn_kernel_info", "calvo_attn_plan", "calvo_attn_plan_items", "calvo_ingest_plan", "calvo_cost_fit", "calvo_cost_estimate",
+           "calvo_chunk_event", "calvo_kv_ingest_l3", "calvo_l3_wait", "calvo_layer_event", "calvo_prefill_attn", "calvo_prefill_attn_noalloc", "calvo_batch_prepare", "calvo_batch_destroy", "calvo_prefill_attn_batch", "calvo_attn_kernel_ms", "calvo_mfma_peak", "calvo_attn_kernel_info", "calvo_attn_tile_rows", "calvo_attn_plan", "calvo_attn_plan_items", "calvo_ingest_plan", "calvo_cost_fit", "calvo_cost_estimate",
            "calvo_sched_pick", "calvo_sched_simulate", "calvo_pool_create", "calvo_pool_destroy", "calvo_pool_reserve",
            "calvo_pool_retain", "calvo_pool_release", "calvo_pool_counts", "calvo_pool_admit", "calvo_pool_retry",
            "calvo_pool_cancel", "calvo_dispatch_create", "calvo_dispatch_submit", "calvo_dispatch_wait", "calvo_dispatch_poll",
@@ -132,6 +132,7 @@ def lib() -> C.CDLL:
         L.calvo_ingest_plan.argtypes = [C.POINTER(calvo_request), C.c_int32, C.c_int32, C.c_int32, C.c_int64, C.c_int64,
                                         C.c_int64, C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
         L.calvo_attn_kernel_info.argtypes = [C.c_void_p, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]
+        L.calvo_attn_tile_rows.argtypes = [C.c_void_p, C.c_int, C.POINTER(C.c_int)]
         dp = C.POINTER(C.c_double)
         L.calvo_cost_fit.argtypes = [dp, dp, C.c_int, dp, dp]
         L.calvo_cost_estimate.argtypes = [C.POINTER(calvo_cost_model), C.POINTER(calvo_job), dp, dp]
@@ -432,6 +433,13 @@ def calvo_attn_kernel_info(ctx: int, layer: int):
     k, n = C.c_int(), C.c_int()
     _check(lib().calvo_attn_kernel_info(ctx, layer, C.byref(k), C.byref(n)))
     return k.value, n.value
+
+
+def calvo_attn_tile_rows(ctx: int, layer: int) -> int:
+    """Rows of a tile of the layer's most recent packed-rows launch, 0 for the other kernels."""
+    n = C.c_int()
+    _check(lib().calvo_attn_tile_rows(ctx, layer, C.byref(n)))
+    return n.value
 
 
 def calvo_attn_kernel_ms(ctx: int, layer: int) -> float:

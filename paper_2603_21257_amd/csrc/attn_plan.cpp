@@ -230,17 +230,16 @@ constexpr double kFull = 0.92;     // load of a launch that fills the chip, of i
 constexpr double kLonger = 1.1;
 
 RowsPlan plan_rows(bool f32, int head_dim, const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int group,
-                   int n_kv_heads, int n_cus, int force_splits, int64_t max_slots) {
-  const char* e = getenv("CALVO_ROWS_TILE");                    // test hook: 1 or 2 forces a tiling
+                   int n_kv_heads, int n_cus, int force_splits, int64_t max_slots, int force_tile) {
   RowsPlan best;
   PlanCost best_cost;
   for (const bool large : {false, true}) {
-    if (large && (!attn_rows_has_large(f32, head_dim) || (e && e[0] == '1'))) break;
+    if (large && (!attn_rows_has_large(f32, head_dim) || force_tile == 1)) break;
     RowsPlan p;
     p.large = large;
     p.shape = attn_rows_shape(f32, head_dim, large);
     p.tiles = plan_row_tiles(prefix_blocks, suffix_lens, n_reqs, group, p.shape.tile_rows);
-    const bool forced = !large || (e && e[0] == '2');
+    const bool forced = !large || force_tile == 2;
     const double limit = forced ? HUGE_VAL : (best_cost.load >= kFull * best_cost.span ? kLonger : 1.) * best_cost.span + 0.5;
     PlanCost cost;
     p.want = plan_pieces(p.tiles, rows_plan_params(p.shape, n_kv_heads, n_cus, force_splits), max_slots / p.shape.slots, &cost, limit);

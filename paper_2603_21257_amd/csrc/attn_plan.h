@@ -93,7 +93,8 @@ struct RowsShape {
 bool attn_rows_has_large(bool f32, int head_dim);
 RowsShape attn_rows_shape(bool f32, int head_dim, bool large);
 
-// The tiling of a batch, its tiles and the pieces that the longest is asked to be cut into.
+// The tiling of a batch, its tiles and the pieces that the longest is asked to be cut into.  force_tile: 1 takes the smaller
+// tiling, 2 the larger one where there is one.
 struct RowsPlan {
   RowsShape shape;
   std::vector<PlanTile> tiles;
@@ -101,7 +102,7 @@ struct RowsPlan {
   bool large;
 };
 RowsPlan plan_rows(bool f32, int head_dim, const int32_t* prefix_blocks, const int32_t* suffix_lens, int n_reqs, int group,
-                   int n_kv_heads, int n_cus, int force_splits, int64_t max_slots);
+                   int n_kv_heads, int n_cus, int force_splits, int64_t max_slots, int force_tile = 0);
 
 // A decision about tiling and pieces (a replay of the launch), which depends only on the batch's lengths, and the lengths that it
 // was made for: the following layers take it over.

@@ -523,6 +523,7 @@ int calvo_create(const calvo_config* cfg, calvo_ctx** out) {
     const int g = atoi(e);
     if (g >= 1 && g <= 64) c->force_splits = g;
   }
+  if (const char* e = getenv("CALVO_ROWS_TILE")) { const int g = atoi(e); if (g >= 1 && g <= 2) c->force_rows_tile = g; }
   if (const char* e = getenv("CALVO_INGEST_DELAY_US")) { const int g = atoi(e); if (g > 0 && g <= 1000000) c->test_ingest_delay_us = g; }
   if (const char* e = getenv("CALVO_TEST_SCATTER_DELAY_US")) { const int g = atoi(e); if (g > 0 && g <= 20000) c->test_scatter_delay_us = g; }
   if (const char* e = getenv("CALVO_TEST_L3_FAIL_CHUNK")) { const int g = atoi(e); if (g >= 0) c->test_l3_fail_chunk = g; }
@@ -568,6 +569,7 @@ int calvo_create(const calvo_config* cfg, calvo_ctx** out) {
   c->end_marked.assign(cfg->n_layers, 0);
   c->last_variant.assign(cfg->n_layers, -1);
   c->last_wgs.assign(cfg->n_layers, 0);
+  c->last_tile_rows.assign(cfg->n_layers, 0);
   for (int l = 0; l < cfg->n_layers; l++) {
     CREATE_TRY(hipEventCreateWithFlags(&c->ev_layer[l], hipEventDisableTiming));
   }
@@ -1143,7 +1145,7 @@ RowsPlan kept_rows(calvo_ctx* c, const int32_t* pblocks, const int32_t* slens, i
   const int hkv = c->cfg.n_kv_heads, group = c->cfg.n_q_heads / hkv, dim = c->cfg.head_dim;
   RowsPlan p;
   auto decide = [&](KeptPlan& k) {
-    p = plan_rows(f32, dim, pblocks, slens, n_reqs, group, hkv, c->n_cus, c->force_splits, kStaticPartSlots);
+    p = plan_rows(f32, dim, pblocks, slens, n_reqs, group, hkv, c->n_cus, c->force_splits, kStaticPartSlots, c->force_rows_tile);
     k.want = p.want;
     k.large = p.large;
   };
@@ -1387,6 +1389,7 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
   c->timed[layer] = 1;
   c->last_variant[layer] = ap.mfma ? ap.variant : -1;
   c->last_wgs[layer] = ap.mfma ? (int32_t)(ap.plan.items.size() * (size_t)(cf.n_q_heads / ap.HW)) : 0;
+  c->last_tile_rows[layer] = ap.mfma ? 0 : ap.tile_rows;
   return CALVO_OK;
 }
 
@@ -1683,6 +1686,14 @@ int calvo_attn_kernel_info(calvo_ctx* c, int layer, int* kernel, int* n_workgrou
   if (!c->timed[layer]) return fail(CALVO_ENOTREADY, "no attention kernel was queued for layer %d", layer);
   if (kernel) *kernel = c->last_variant[layer];
   if (n_workgroups) *n_workgroups = c->last_wgs[layer];
+  return CALVO_OK;
+}
+
+int calvo_attn_tile_rows(calvo_ctx* c, int layer, int* tile_rows) {
+  if (!c || !tile_rows) return fail(CALVO_EINVAL, "NULL argument");
+  if (layer < 0 || layer >= c->cfg.n_layers) return fail(CALVO_EINVAL, "layer %d outside [0, %d)", layer, c->cfg.n_layers);
+  if (!c->timed[layer]) return fail(CALVO_ENOTREADY, "no attention kernel was queued for layer %d", layer);
+  *tile_rows = c->last_tile_rows[layer];
   return CALVO_OK;
 }
 

@@ -62,9 +62,11 @@ struct calvo_ctx {
   std::vector<char> end_marked;                  // per layer: the most recent launch has its event
   std::vector<char> timed;
   std::vector<int32_t> last_variant, last_wgs;   // per layer: attention kernel chosen, workgroups launched
+  std::vector<int32_t> last_tile_rows;           // per layer: rows of a packed-rows tile, 0 for the other kernels
   int scatter_grid = 64;
   size_t merge_bytes = (size_t)256 << 20;   // consecutive small layers cross PCIe together up to this size (CALVO_MERGE_MIB)
   int force_splits = 0;           // CALVO_ATTN_SPLITS: pieces per tile (0 = automatic)
+  int force_rows_tile = 0;        // CALVO_ROWS_TILE: packed rows, 1 = the smaller tiling, 2 = the larger one where there is one (0 = automatic)
   int split_min = 48;             // shortest piece of a cut tile, in 32-key sub-tiles
   int split_fill = 30;            // cost of a workgroup's pipeline fill and drain, in sub-tile steps (launch replay)
   int n_cus = 256;                // compute units of the device

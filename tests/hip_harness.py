@@ -56,12 +56,13 @@ def make_requests(w: wl.Workload, host: torch.Tensor):
 
 
 def run_hip(w: wl.Workload, staging_bytes: int = 0, n_staging: int = 0, n_copy_streams: int = 0,
-            scale: float = 0.0, append_suffix: bool = True, chunk_blocks=None, attn_fn=None, prepared: bool = False):
+            scale: float = 0.0, append_suffix: bool = True, chunk_blocks=None, attn_fn=None, prepared: bool = False, look=None):
     """Whole path on cuda:0.  Returns (pool image as stored-dtype numpy [L][slots][elems],
     out as stored-dtype numpy [L][T][Hq][D]).  chunk_blocks: per-layer chunk sizes for the
     chunk-granular load (None: whole layers).  attn_fn: the binding function that runs the
     attention stage (default calvo_prefill_attn).  prepared: the batch is prepared once
-    (calvo_batch_prepare) and every layer goes through calvo_prefill_attn_batch."""
+    (calvo_batch_prepare) and every layer goes through calvo_prefill_attn_batch.  look: called with the context before it is
+    destroyed."""
     attn_fn = attn_fn or cb.calvo_prefill_attn
     s = w.shape
     dev = torch.device("cuda:0")
@@ -94,6 +95,8 @@ def run_hip(w: wl.Workload, staging_bytes: int = 0, n_staging: int = 0, n_copy_s
                     attn_fn(ctx, l, *args, reqs, w.cu_suffix, scale)
             for l in range(s.n_layers):
                 assert cb.calvo_layer_event(ctx, l, cb.CALVO_EV_HOST_WAIT)
+            if look:
+                look(ctx)
         finally:
             if batch:
                 cb.calvo_batch_destroy(batch)

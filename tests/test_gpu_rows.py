@@ -62,7 +62,10 @@ def test_large_tiling(D, hq, hkv, lens, pieces, monkeypatch):
     monkeypatch.setenv("CALVO_ROWS_TILE", "2")
     if pieces:
         monkeypatch.setenv("CALVO_ATTN_SPLITS", str(pieces))
-    check(wl.make_custom(wl.Shape(1, hq, hkv, abs(D), "f32" if D < 0 else "bf16", slots(lens)), lens, seed=abs(D) + hq + pieces))
+    rows = []
+    check(wl.make_custom(wl.Shape(1, hq, hkv, abs(D), "f32" if D < 0 else "bf16", slots(lens)), lens, seed=abs(D) + hq + pieces),
+          look=lambda ctx: rows.append(cb.calvo_attn_tile_rows(ctx, 0)))
+    assert rows == [64 if 0 < D <= 128 else 32]
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -83,9 +86,11 @@ def test_entry_points(dtype, fn):
 
 @pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 256), ("bf16", 64), ("bf16", 256)])
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
-def test_later_tokens_do_not_reach_earlier_rows(dtype, D, value):
+@pytest.mark.parametrize("tile", ["1", "2"])
+def test_later_tokens_do_not_reach_earlier_rows(dtype, D, value, tile, monkeypatch):
     """V of token 20 is not finite: rows 0..19 are what the oracle gives for finite values (their keys are walked again
     one by one, a different order of the same sums), rows from 20 on what it gives for this one."""
+    monkeypatch.setenv("CALVO_ROWS_TILE", tile)
     w = wl.make_custom(wl.Shape(1, 6, 2, D, dtype, 32), [(64, 40)], seed=31)
     _, want = hh.run_oracle(w)
     bad = np.float32(value).view(np.uint32)

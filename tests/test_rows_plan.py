@@ -18,16 +18,16 @@ int attn_duo_tile_tokens(int heads_per_wg) { return 32 * (4 / heads_per_wg); }
 }
 using namespace calvo;
 
-// a line "f32 head_dim q_heads kv_heads cus forced_pieces room n, n times prefix suffix" -> "rows pieces items slots"
+// a line "f32 head_dim q_heads kv_heads cus forced_pieces forced_tiling room n, n times prefix suffix" -> "rows pieces items slots"
 int main() {
-  int f32, dim, hq, hkv, cus, force, room, n;
-  while (scanf("%d %d %d %d %d %d %d %d", &f32, &dim, &hq, &hkv, &cus, &force, &room, &n) == 8) {
+  int f32, dim, hq, hkv, cus, force, tile, room, n;
+  while (scanf("%d %d %d %d %d %d %d %d %d", &f32, &dim, &hq, &hkv, &cus, &force, &tile, &room, &n) == 9) {
     std::vector<int32_t> blocks(n), suffix(n);
     for (int i = 0; i < n; i++) {
       if (scanf("%d %d", &blocks[i], &suffix[i]) != 2) return 1;
       blocks[i] /= 16;
     }
-    const RowsPlan p = plan_rows(f32, dim, blocks.data(), suffix.data(), n, hq / hkv, hkv, cus, force, room);
+    const RowsPlan p = plan_rows(f32, dim, blocks.data(), suffix.data(), n, hq / hkv, hkv, cus, force, room, tile);
     const PlanItems it = plan_items(p.tiles, p.want, rows_plan_params(p.shape, hkv, cus, force));
     printf("%d %d %zu %zu\n", p.shape.tile_rows, p.want, it.items.size(),
            it.split_tiles.empty() ? (size_t)0 : it.items.size() * hkv * p.shape.slots);
@@ -48,8 +48,8 @@ def compiled(tmp, source):
 def rows_plan(tmp_path_factory):
     exe = compiled(tmp_path_factory.mktemp("rows"), DRIVER)
 
-    def ask(dtype, dim, hq, hkv, lens, cus=256, force=0, room=4096):
-        line = [int(dtype == "f32"), dim, hq, hkv, cus, force, room, len(lens)] + [x for ps in lens for x in ps]
+    def ask(dtype, dim, hq, hkv, lens, cus=256, force=0, tile=0, room=4096):
+        line = [int(dtype == "f32"), dim, hq, hkv, cus, force, tile, room, len(lens)] + [x for ps in lens for x in ps]
         out = subprocess.run([str(exe)], input=" ".join(map(str, line)), check=True, capture_output=True, text=True).stdout.split()
         return dict(zip(("rows", "pieces", "items", "slots"), map(int, out)))
     return ask
@@ -109,3 +109,11 @@ int main() {
 }
 """)
     assert subprocess.run([str(exe)]).returncode == 0
+
+
+@pytest.mark.parametrize("force", [0, 3])
+@pytest.mark.parametrize("dtype,dim,sizes", [("bf16", 64, (32, 64)), ("bf16", 96, (32, 64)), ("bf16", 256, (16, 32)), ("f32", 64, (32, 32)),
+                                             ("f32", 128, (32, 32)), ("f32", 136, (16, 32))])
+def test_a_forced_tiling(rows_plan, dtype, dim, sizes, force):
+    for lens in [(64, 1)], [(8192, 512)], [(2064, 130), (0, 64), (48, 1)]:
+        assert tuple(rows_plan(dtype, dim, 8, 2, lens, tile=t, force=force)["rows"] for t in (1, 2)) == sizes
