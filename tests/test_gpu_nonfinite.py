@@ -39,12 +39,14 @@ def poisoned(shape, P, S, seed):
 @pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 96), ("f32", 128), ("f32", 256), ("bf16", 40), ("bf16", 64),
                                      ("bf16", 96), ("bf16", 200), ("bf16", 256)])
 @pytest.mark.parametrize("pieces", [1, 3])
-def test_v_of_packed_rows(dtype, D, pieces, monkeypatch):
+@pytest.mark.parametrize("tile", ["1", "2"])
+def test_v_of_packed_rows(dtype, D, pieces, tile, monkeypatch):
+    monkeypatch.setenv("CALVO_ROWS_TILE", tile)
     if pieces > 1:
         monkeypatch.setenv("CALVO_ATTN_SPLITS", str(pieces))
     s = wl.Shape(1, 6, 2, D, dtype, 40)
     w = poisoned(s, 400, 45, seed=800 + D)
-    print(f"[case] {dtype} D={D} pieces={pieces}", flush=True)
+    print(f"[case] {dtype} D={D} pieces={pieces} tile={tile}", flush=True)
     _, got = hh.run_hip(w)
     with np.errstate(invalid="ignore"):
         _, want = hh.run_oracle(w)
@@ -54,10 +56,12 @@ def test_v_of_packed_rows(dtype, D, pieces, monkeypatch):
 @pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("f32", 256), ("bf16", 64), ("bf16", 96), ("bf16", 256)])
 @pytest.mark.parametrize("value,columns", [(1e35, slice(None)), (1e32, slice(0, 1))])
 @pytest.mark.parametrize("pieces", [1, 2])
-def test_large_v_under_rising_scores(dtype, D, value, columns, pieces, monkeypatch):
+@pytest.mark.parametrize("tile", ["1", "2"])
+def test_large_v_under_rising_scores(dtype, D, value, columns, pieces, tile, monkeypatch):
     """All scores are 0 up to a token from which on they are 15 powers of two higher.  The softmax reference lags by up
     to 16 powers of two; sums of V taken with weights of 2^15 would leave the range where the result does not - in one
     wave, or (1e32 in one column) where the waves' sums are added."""
+    monkeypatch.setenv("CALVO_ROWS_TILE", tile)
     monkeypatch.setenv("CALVO_ATTN_SPLITS", str(pieces))
     P, S = 1024, 20
     s = wl.Shape(1, 4, 2, D, dtype, (P + S) // 16 + 9)

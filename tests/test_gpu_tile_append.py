@@ -128,3 +128,60 @@ def test_output_over_the_suffix_rows(dtype, D, heads, P, S, over):
     pool_o, want = hh.run_oracle(w)
     hh.assert_pool_bit_exact(hh.to_numpy_stored(pool, s), pool_o)
     hh.assert_attn_close(hh.to_numpy_stored(out, s), want, dtype)
+
+
+KERNELS = [("bf16", 64, ""), ("f32", 64, ""), ("bf16", 256, ""), ("bf16", 128, "3"), ("bf16", 128, "4")]
+
+
+@pytest.mark.parametrize("dtype,D,variant", KERNELS)
+@pytest.mark.parametrize("P,S,at_home", [(48, 16, True), (64, 5, True), (320, 11, False), (336, 401, False)])
+def test_suffix_rows_in_the_pool(dtype, D, variant, P, S, at_home, monkeypatch):
+    """k_suffix and v_suffix are rows of the layer's pool: of blocks that no table names, or the very rows they go to.  All
+    rows are stored first."""
+    monkeypatch.setenv("CALVO_ATTN_VARIANT", variant)
+    s = wl.Shape(1, 8, 2, D, dtype, (P + S) // 16 + 9)
+    w = wl.make_custom(s, [(P, S)], seed=970 + S)
+    dev = torch.device("cuda:0")
+    spare = -(-S // 16) + 1
+    pool = torch.zeros((s.pool_blocks + spare, 2, 16, 2, D), dtype=hh.torch_dtype(s), device=dev)
+    pool[:s.pool_blocks] = hh.to_torch(hh.sentinel_pool_np(s), s, dev).view(-1, 2, 16, 2, D)
+    host = hh.to_torch(w.host_kv, s, pin=True)
+    q, ks, vs = (hh.to_torch(a, s, dev) for a in (w.q, w.k_suffix, w.v_suffix))
+    if at_home:
+        home = pool[int(w.requests[0].table[P // 16])]
+        k_rows, v_rows = home[0, :S], home[1, :S]
+    else:
+        k_rows, v_rows = pool[s.pool_blocks:].view(2, -1, 2, D)[:, :S]
+    k_rows.copy_(ks[0])
+    v_rows.copy_(vs[0])
+    out = torch.empty((1, S, 8, D), dtype=pool.dtype, device=dev)
+    torch.cuda.synchronize()
+    ctx = cb.calvo_create(1, 8, 2, D, cb.CALVO_BF16 if dtype == "bf16" else cb.CALVO_F32, s.pool_blocks + spare, pool)
+    try:
+        reqs = hh.make_requests(w, host)
+        cb.calvo_kv_ingest(ctx, reqs, 0, 1)
+        cb.calvo_prefill_attn(ctx, 0, q[0], k_rows, v_rows, out[0], reqs, w.cu_suffix)
+    finally:
+        cb.calvo_destroy(ctx)
+    torch.cuda.synchronize()
+    pool_o, want = hh.run_oracle(w)
+    hh.assert_pool_bit_exact(hh.to_numpy_stored(pool[:s.pool_blocks].reshape(1, s.pool_blocks, -1), s), pool_o)
+    hh.assert_attn_close(hh.to_numpy_stored(out, s), want, dtype)
+
+
+@pytest.mark.parametrize("dtype,D,variant", KERNELS)
+@pytest.mark.parametrize("P,S", [(0, 5), (48, 40), (64, 130)])
+def test_two_requests_that_append_to_the_same_slots(dtype, D, variant, P, S, monkeypatch):
+    """One sequence twice, the same rows to the same slots, under other queries."""
+    monkeypatch.setenv("CALVO_ATTN_VARIANT", variant)
+    s = wl.Shape(1, 8, 2, D, dtype, 2 * ((P + S) // 16 + 9))
+    w = wl.make_custom(s, [(P, S), (P, S)], seed=990 + S)
+    first, second = w.requests
+    second.table[:] = first.table
+    second.host_block_start = first.host_block_start
+    w.k_suffix[:, S:] = w.k_suffix[:, :S]
+    w.v_suffix[:, S:] = w.v_suffix[:, :S]
+    pool_g, out_g = hh.run_hip(w)
+    pool_o, out_o = hh.run_oracle(w)
+    hh.assert_pool_bit_exact(pool_g, pool_o)
+    hh.assert_attn_close(out_g, out_o, dtype)
