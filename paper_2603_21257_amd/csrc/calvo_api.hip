@@ -1172,7 +1172,8 @@ enum class PlanRule {
 bool by_rows(PlanRule rule) { return rule != PlanRule::kBest && rule != PlanRule::kLong; }
 
 // cb > 0: the layer was loaded in nck chunks of cb block indices and attention follows the chunks.
-void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const int32_t* cu_suffix, int total, int cb,
+// apart: appends_apart, which the caller works out once per batch (it goes over all tables).
+void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const int32_t* cu_suffix, int total, bool apart, int cb,
                     int nck, AttnPlan& ap, PlanRule rule = PlanRule::kBest) {
   const calvo_config& cf = c->cfg;
   ap.n_reqs = n_reqs;
@@ -1183,7 +1184,7 @@ void make_attn_plan(calvo_ctx* c, const calvo_request* reqs, int n_reqs, const i
   std::vector<int32_t> pblocks(n_reqs), slens(n_reqs);
   for (int r = 0; r < n_reqs; r++) { pblocks[r] = reqs[r].n_prefix_blocks; slens[r] = reqs[r].suffix_len; }
   ap.longest = n_reqs > 0 ? *std::max_element(slens.begin(), slens.end()) : 0;
-  ap.apart = appends_apart(c, reqs, n_reqs);
+  ap.apart = apart;
   if (ap.mfma) ap.variant = attn_mfma_choose(pblocks.data(), slens.data(), n_reqs, ap.HW, cf.n_q_heads / ap.HW, c->n_cus, by_rows(rule));
   ap.tile_tokens = ap.mfma ? attn_mfma_tile_tokens(ap.variant, ap.HW) : 1;
   // Work items: tiles of suffix tokens, heaviest first, each possibly cut into split-KV pieces
@@ -1507,12 +1508,13 @@ int calvo::host::prefill_attn_impl(calvo_ctx* c, int layer, const void* q, const
     kept->ap = AttnPlan();
     kept->cb = cb;
     kept->nck = nck;
-    make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, kept->ap);
+    const bool apart = appends_apart(c, reqs, n_reqs);
+    make_attn_plan(c, reqs, n_reqs, cu_suffix, total, apart, cb, nck, kept->ap);
     for (PlanRule rule : {PlanRule::kRounded, PlanRule::kLong, PlanRule::kLongByRows, PlanRule::kFitted}) {
       if (!use_static || fits(kept->ap) || (!kept->ap.mfma && kept->rule != PlanRule::kBest)) break;
       kept->rule = rule;
       kept->ap = AttnPlan();
-      make_attn_plan(c, reqs, n_reqs, cu_suffix, total, cb, nck, kept->ap, rule);
+      make_attn_plan(c, reqs, n_reqs, cu_suffix, total, apart, cb, nck, kept->ap, rule);
     }
     kept->take(reqs, n_reqs, cu_suffix);
   }
@@ -1588,7 +1590,7 @@ int calvo::host::prefill_attn_prepared(calvo_batch* b, int layer, const void* q,
       if (!pp) {
         pp = new (std::nothrow) PreparedPlan();
         if (!pp) return fail(CALVO_ENOMEM, "out of host memory");
-        make_attn_plan(c, b->reqs.data(), (int)b->reqs.size(), b->cu.data(), b->whole.ap.total, cb, nck, pp->ap);
+        make_attn_plan(c, b->reqs.data(), (int)b->reqs.size(), b->cu.data(), b->whole.ap.total, b->whole.ap.apart, cb, nck, pp->ap);
         rc = upload_prepared(c, *pp);
         if (rc != CALVO_OK) { free_prepared(c, *pp); delete pp; return rc; }
         b->chunked.push_back({{cb, nck}, pp});
@@ -1644,7 +1646,7 @@ int calvo_batch_prepare(calvo_ctx* c, const calvo_request* reqs, int n_reqs, con
   }
   b->cu.assign(cu_suffix, cu_suffix + (n_reqs > 0 ? n_reqs + 1 : 0));
   if (n_reqs == 0) b->cu.assign(1, 0);
-  make_attn_plan(c, b->reqs.data(), n_reqs, b->cu.data(), total, 0, 0, b->whole.ap);
+  make_attn_plan(c, b->reqs.data(), n_reqs, b->cu.data(), total, appends_apart(c, reqs, n_reqs), 0, 0, b->whole.ap);
   rc = upload_prepared(c, b->whole);
   if (rc != CALVO_OK) {
     const std::string msg = calvo_last_error();
