@@ -16,7 +16,7 @@ typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((address_space(3))) unsigned char lds_u8;
-// descriptor words, which no kernel writes: read on the scalar unit
+// descriptor words, which a launch in front of these kernels wrote (launch_upload_words) and none of them does: read on the scalar unit
 typedef const __attribute__((address_space(4))) int32_t* const_i32p;
 __device__ inline WorkItem load_item(const WorkItem* items, int i) {
   const const_i32p w = (const_i32p)(uintptr_t)(items + i);

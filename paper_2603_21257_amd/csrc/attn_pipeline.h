@@ -36,8 +36,9 @@
 // 1380 in the kernel, with the requests and the barrier.
 // The query blocks of an operand are walked there and back: from one MFMA to the next either A or B stays the same.
 // At the power limit operands that change cost clock: MFMAs alone on N(0,1) data sustain 1915 TFLOP/s where both change every
-// time, 1975 where A is held for four and then both change, 2025 there and back.  In the kernel 61440+4096 tokens 2936 -> 2904 us a
-// call, 16384+2048 412.7 -> 410.0, 38304+209 (40Q/8KV) 157.3 -> 156.1, the same bits (each sum keeps its order).
+// time, 1975 where A is held for four and then both change, 2025 there and back.  In the kernel it is worth no more than what runs differ
+// by (three in turn, with one order / there and back: 61440+4096 tokens 3084 / 3073 us a call, 16384+2048 424.7 / 423.8, 38304+209
+// (40Q/8KV) 162.7 / 162.4; one caller 2943 / 2926, 432 / 429, 159 / 159) and costs nothing; the same bits, each sum keeps its order.
 // The step is written in this order, with scheduling barriers in between.  MFMAs are inline assembly so that their results
 // stay in place, O of HB = 2 in accumulation registers: left to the compiler, every value that vector instructions
 // touch as well is moved back and forth (45 to 250 moves a step).  What the compiler then does not know are the wait states

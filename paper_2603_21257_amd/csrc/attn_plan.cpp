@@ -207,11 +207,12 @@ std::vector<PlanTile> plan_row_tiles(const int32_t* prefix_blocks, const int32_t
 // the smaller one with one caller and with three: over 46 such batches 1.27 and 1.02; longer launches of a full chip (46
 // batches) 1.07 and 0.90; over 48 whose launch it makes up to a fifth shorter 0.96 and 0.91.
 // us a call, three callers, 32Q/8KV, smaller / larger tiling, D = 64, 96, 256:
-//   2048+64    11.5 / 13.7   16.1 / 16.8   26.8 / 22.2          2048+256   16.6 / 19.8   22.8 / 25.6   83.9 / 46.5
-//   8192+128   28.5 / 25.6   41.4 / 38.4   147.4 / 83.2         0+512      12.0 / 10.5   16.2 / 12.7   37.2 / 25.9
-//   5008+300   46.4 / 41.3   71.4 / 59.5   241.2 / 148.3        512+400 (8Q/8KV)   7.7 / 10.1   10.1 / 16.4   16.9 / 17.3
-// fp32, D = 256 (one caller): 2048+256 165.5 / 149.9 (168.1 / 155.3), 4096+300 16Q/4KV 227.1 / 200.9 (232.2 / 208.5), 2048+64 62.8 / 53.9
-// (52.3 / 57.1), 1024+60 8Q/2KV 18.9 / 21.2; up to D = 128 twice the rows gain nothing (matrix pipes): 8192+256, D = 64 136 / 141.
+//   2048+64    10.0 / 12.7   16.1 / 16.1   26.8 / 21.7          2048+256   16.7 / 21.1   23.0 / 25.4   84.7 / 46.8
+//   8192+128   29.3 / 27.3   41.6 / 39.3   148.2 / 83.7         0+512      11.8 / 10.7   16.3 / 12.8   37.4 / 25.9
+//   5008+300   46.9 / 43.2   71.4 / 62.4   242.3 / 148.3        512+400 (8Q/8KV)   7.7 / 10.1   10.3 / 16.2   17.0 / 17.3
+// fp32, D = 256, three callers (one): 2048+256 166.6 / 150.8 (169.5 / 156.9), 8192+512 1244 / 1073 (1220 / 1073), 4096+300 16Q/4KV 228.2 /
+// 203.2 (232.3 / 209.5); the smaller one stays for 2048+64 58.7 / 54.8 (52.6 / 58.2), D = 200 48.4 / 51.7 (47.9 / 55.7), 1024+60 8Q/2KV
+// 18.0 / 20.3 (20.4 / 25.4).  Up to D = 128 twice the rows gain nothing (matrix pipes): 8192+256, D = 64 136 / 141.
 bool attn_rows_has_large(bool f32, int head_dim) { return !f32 || head_dim > 128; }
 
 RowsShape attn_rows_shape(bool f32, int head_dim, bool large) {

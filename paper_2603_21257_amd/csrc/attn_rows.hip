@@ -23,7 +23,8 @@
 //
 // No LDS on the way in: 16 keys are exactly one pool block, so a block's address is one scalar table
 // lookup and the lanes' offsets inside it are constants; K and V go straight to registers, K(next) is
-// requested as soon as the scores have consumed K and V(next) after the second product.  All waves of a
+// requested as soon as the scores have consumed K and V(next) after the second product, or as soon as V is in
+// operand order where all of it fits the registers that way (V_FIRST).  All waves of a
 // workgroup work on the same rows: they take alternate steps of the keys and are combined through LDS at
 // the end, which keeps short queries from being one long serial walk.  (Waves with rows of their own,
 // which read the same K and V through the L1, were measured: the same within 3 % where there are rows
