@@ -144,12 +144,10 @@ __device__ inline void append_suffix(const AppendParams& p, int wg, int n_wgs, i
   for (; i < n; i += stride) move(i, Tag<1>{});
 }
 
-// Workgroups behind those of the tiles in a launch that takes the suffix rows along: four chunks per thread.  They run beside the
+// Workgroups behind those of the tiles in a launch that takes the suffix rows along (append_wgs).  They run beside the
 // tiles; at the end of a tile's workgroup the rows were in the way of its results (us a call of one caller, there / here: 3072+40
 // tokens, 8Q/8KV, 15.6 / 14.4, 512+1 13.3 / 12.9, 448+155 18.2 / 17.7).
-inline unsigned append_wgs(const AttnParams& p) {
-  return p.k_suffix ? (unsigned)(((int64_t)p.total_tokens * p.n_kv_heads * (kRow / 16) + 1023) / 1024) : 0;
-}
+inline unsigned append_wgs(const AttnParams& p) { return p.k_suffix ? calvo::append_wgs(p.total_tokens, p.n_kv_heads) : 0; }
 __device__ inline bool append_wg(const AttnParams& p) {
   if ((int)blockIdx.x < p.attn_wgs) return false;
   AppendParams app{p.k_suffix, p.v_suffix, const_cast<void*>(p.pool_layer), p.reqs, p.tables, p.n_reqs, p.total_tokens,

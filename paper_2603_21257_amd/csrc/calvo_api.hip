@@ -1310,6 +1310,12 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
   // tokens 10.3 / 9.4 (15.6 / 13.6), 448+400 15.4 / 13.8 (20.6 / 19.4), 1024+1000 30.5 / 29.8 (37.8 / 35.5), 0+2000 37.4 / 37.0
   // (46.3 / 42.4), 4096+700 56.2 / 54.9 (69.3 / 67.2); 64-row kernel, several tiles: 4096+1000 69.7 / 71.1 (82.1 / 80.1), 16384+2048
   // 421.6 / 425.1 (438.8 / 435.3), 0+4000 114.4 / 119.7 (119.9 / 121.2).
+  // A workgroup that appends takes the place of one that works on a tile, with its LDS, while the append launch has eight and more on a CU:
+  // beyond two per CU (512) the rows go first.  Workgroups that append, requests, us as above:
+  //   256   8 x 2048+256 (8Q/8KV) 32.7 / 31.6 (39.1 / 35.3)    32 x 4096+64 140.5 / 141.0 (142.4 / 140.3)    64 x 1024+32 67.1 / 64.0 (62.8 / 58.8)
+  //   512   16 x 2048+256 49.7 / 47.5 (54.2 / 46.8)            64 x 4096+64 270.0 / 275.4 (272.3 / 272.1)    128 x 1024+32 130.5 / 131.0 (139.0 / 135.1)
+  //   800   64 x 0+100 (8Q/8KV) 21.8 / 22.2 (25.8 / 26.8)      64 x 1024+100 174.4 / 173.5 (181.8 / 182.8)
+  //   2048 up   256 x 1024+64 361 / 380 (371 / 389)            128 x 1024+256 (8Q/8KV) 254 / 297 (276 / 315)
   const size_t row_b = (size_t)ap.total * cf.head_dim * c->elt;
   auto in = [&](const void* sfx, const void* at, size_t bytes) {
     return (uintptr_t)sfx < (uintptr_t)at + bytes && (uintptr_t)at < (uintptr_t)sfx + row_b * cf.n_kv_heads;
@@ -1317,7 +1323,8 @@ int launch_layer(calvo_ctx* c, int layer, const void* q, const void* k_suffix, c
   auto in_the_way = [&](const void* sfx) { return in(sfx, out, row_b * cf.n_q_heads) || in(sfx, pool_layer, (size_t)c->layer_bytes); };
   const bool along = k_suffix && ap.apart && !in_the_way(k_suffix) && !in_the_way(v_suffix);
   const bool rows_append = !ap.mfma && along;
-  const bool tile_append = ap.mfma && along && !ap.chunked && (ap.variant == kAttnDuo || ap.longest <= ap.tile_tokens);
+  const bool tile_append = ap.mfma && along && !ap.chunked && (ap.variant == kAttnDuo || ap.longest <= ap.tile_tokens) &&
+                           append_wgs(ap.total, cf.n_kv_heads) <= 2u * (unsigned)c->n_cus;
   if (k_suffix && !rows_append && !tile_append) {
     AppendParams app{};
     app.k_suffix = k_suffix; app.v_suffix = v_suffix; app.pool_layer = pool_layer;

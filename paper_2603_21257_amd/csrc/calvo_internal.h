@@ -69,6 +69,9 @@ struct AttnParams {
   int32_t attn_wgs;         // workgroups of the grid that work on tiles; those behind them append the suffix rows
 };
 
+// workgroups that append the suffix rows in a launch of the pipelined kernels: four 16-byte chunks of K and of V per thread
+inline unsigned append_wgs(int total_tokens, int n_kv_heads) { return (unsigned)(((int64_t)total_tokens * n_kv_heads * 16 + 1023) / 1024); }
+
 struct AppendParams {
   const void* k_suffix;
   const void* v_suffix;
