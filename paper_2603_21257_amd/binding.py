@@ -207,7 +207,11 @@ def _req_array(reqs: Sequence[calvo_request]):
 # 512+1 tokens through calvo_prefill_attn 9.8 -> 7.9 us a call.
 def _req_arg(reqs: Sequence[calvo_request]):
     """The requests of one call as ctypes takes them; one request goes as it is."""
-    return reqs[0] if len(reqs) == 1 else _req_array(reqs)
+    if len(reqs) == 1:
+        (r,) = reqs
+        if isinstance(r, calvo_request):
+            return r
+    return _req_array(reqs)
 
 
 def _cu_arg(cu_suffix) -> bytes:

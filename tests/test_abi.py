@@ -95,6 +95,27 @@ def test_null_context_is_an_error_not_a_crash():
     assert "NULL" in cb.calvo_last_error()
 
 
+@pytest.mark.parametrize("n", [1, 2])
+@pytest.mark.parametrize("kind", ["list", "tuple", "dict values", "ctypes array", "fields"])
+def test_requests_of_a_call_in_any_collection(n, kind):
+    """One request is marshalled another way than several; both take what iterates and has a length."""
+    reqs = [cb.make_request(None, 0, np.arange(3), 2, 7, 2) for _ in range(n)]
+    if kind == "tuple":
+        reqs = tuple(reqs)
+    elif kind == "dict values":
+        reqs = dict(enumerate(reqs)).values()
+    elif kind == "ctypes array":
+        reqs = (cb.calvo_request * n)(*reqs)
+    elif kind == "fields":
+        reqs = [tuple(getattr(r, f) for f, _ in cb.calvo_request._fields_) for r in reqs]
+    cu = [7 * i for i in range(n + 1)]
+    for call in (lambda: cb.calvo_prefill_attn(0, 0, None, None, None, None, reqs, cu), lambda: cb.calvo_batch_prepare(0, reqs, cu),
+                 lambda: cb.calvo_prefill_attn_noalloc(0, 0, None, None, None, None, reqs, cu)):
+        with pytest.raises(cb.CalvoError) as ei:
+            call()
+        assert ei.value.code == cb.CALVO_EINVAL and "ctx is NULL" in str(ei.value)
+
+
 def test_make_request_marshals_table():
     tab = np.array([5, 3, 9], np.int64)
     r = cb.make_request(4096, 1 << 20, tab, 2, 7, 1)
